@@ -1,0 +1,252 @@
+"""Timed cases of the EliteKV decode hot path, through the package's public entry points.
+
+Five kinds of pass, the calls a serving program makes per layer:
+  step     one decode step: the new tokens appended, attention over the cache (elitekv_decode_step, or
+           elitekv_slrd_decode_step for separated latents)
+  block    the same with the query and output projections around it (elitekv_block_step)
+  verify   a few drafted tokens per sequence: appended, then every one of them attends (elitekv_append +
+           elitekv_multiquery_attn)
+  prefill  a prompt or a chunk of one over an existing context: appended, then causal attention
+           (elitekv_append + elitekv_prefill_attn, or their slrd forms)
+  search   the choice of a layer's elite chunks from a sample of its queries and keys (elitekv_ropelite_search)
+
+Model shapes are those of elitekv_synth.CONFIGS: the 7B shape at 25 % and 12.5 % of the full cache, the 13B shape
+at 25 %, separated latents at the 7B shape.  bf16 is what is served; fp32 is what a result is checked in.
+Planes, weights and activations follow the recipe of elitekv_synth (unit variance everywhere).
+"""
+import random
+
+import numpy as np
+import torch
+
+import paper_2503_01586_amd as ekv
+
+DEV = "cuda:0"
+
+# name: (d_model, heads, head_dim, r, d_c, d_ck; 0 = joint latent)
+SHAPES = {
+    "7b_25": (4096, 32, 128, 8, 1536, 0),
+    "7b_12": (4096, 32, 128, 4, 768, 0),
+    "13b_25": (5120, 40, 128, 8, 1920, 0),
+    "7b_r16": (4096, 32, 128, 16, 1024, 0),          # twice the elite chunks at the same 25 % of the cache
+    "7b_25_slrd_576": (4096, 32, 128, 8, 1536, 576),
+    "7b_25_slrd_768": (4096, 32, 128, 8, 1536, 768),
+}
+JOINT = ("7b_25", "7b_12", "13b_25", "7b_r16")
+
+# The largest cache one step streams, and the largest other passes of each kind, as listed below.
+MAX_STEP_BYTES = 16 * 8192 * 5120
+MAX_FP32_TOKENS = 2000
+MAX_PREFILL_PAIRS = 2 * 1021 * 8000
+
+
+def listed():
+    return [
+        # a chat that has just begun: one sequence, a few hundred tokens; launches and latency are all there is
+        dict(name="step_7b25_b1_s256", kind="step", shape="7b_25", dtype="bf16", B=1, S=256, ragged=False),
+        # one sequence with a long document behind it
+        dict(name="step_7b25_b1_s32768", kind="step", shape="7b_25", dtype="bf16", B=1, S=32768, ragged=False),
+        # a small server batch, every sequence of another length
+        dict(name="step_7b25_b8_s4096_ragged", kind="step", shape="7b_25", dtype="bf16", B=8, S=4096, ragged=True),
+        # a full server batch of short chats at the smallest cache
+        dict(name="step_7b12_b64_s2048_ragged", kind="step", shape="7b_12", dtype="bf16", B=64, S=2048, ragged=True),
+        # the larger model, a long-context batch: the most cache bytes
+        dict(name="step_13b25_b16_s8192", kind="step", shape="13b_25", dtype="bf16", B=16, S=8192, ragged=False),
+        # separated latents, an odd number of sequences of odd lengths
+        dict(name="step_slrd_b3_s5001", kind="step", shape="7b_25_slrd_576", dtype="bf16", B=3, S=5001, ragged=True),
+        # a result checked in fp32
+        dict(name="step_fp32_b2_s1000", kind="step", shape="7b_25", dtype="fp32", B=2, S=1000, ragged=True),
+        # the whole attention block of a layer for one user
+        dict(name="block_7b25_b1_s4096", kind="block", shape="7b_25", dtype="bf16", B=1, S=4096, ragged=False),
+        # four sequences, five drafted tokens each
+        dict(name="verify_7b25_b4_t5_s4096", kind="verify", shape="7b_25", dtype="bf16", B=4, T=5, S=4096),
+        # one prompt of the usual length
+        dict(name="prefill_7b25_b1_t2048", kind="prefill", shape="7b_25", dtype="bf16", B=1, T=2048, S=2048),
+        # two prompts' chunks of an odd length over what is already cached
+        dict(name="prefill_13b25_b2_t1021_s8000", kind="prefill", shape="13b_25", dtype="bf16", B=2, T=1021, S=8000),
+        # the elite chunks of one layer from a thousand sampled tokens
+        dict(name="search_7b_t1000", kind="search", T=1000),
+    ]
+
+
+def _log(rng, lo, hi):
+    return max(lo, min(hi, int(round(lo * (hi / lo) ** rng.random()))))
+
+
+def draw(rng):
+    """Another case of the same kinds; in each kind no larger than the largest listed one."""
+    kind = rng.choice(("step", "step", "step", "step", "block", "block", "verify", "prefill", "prefill", "prefill",
+                       "search"))
+    if kind == "step":
+        dtype = "fp32" if rng.random() < 0.12 else "bf16"
+        shape = rng.choice(tuple(SHAPES) if dtype == "bf16" else ("7b_25", "7b_12"))
+        B = _log(rng, 1, 64) if dtype == "bf16" else rng.randint(1, 4)
+        most = min(32768, MAX_STEP_BYTES // (B * _row_elems(shape) * 2)) if dtype == "bf16" else MAX_FP32_TOKENS // B
+        return dict(kind=kind, shape=shape, dtype=dtype, B=B, S=_log(rng, 128, most), ragged=rng.random() < 0.6)
+    if kind == "block":
+        shape, B = rng.choice(JOINT), _log(rng, 1, 32)
+        most = min(16384, MAX_STEP_BYTES // (B * _row_elems(shape) * 2))
+        return dict(kind=kind, shape=shape, dtype="bf16", B=B, S=_log(rng, 128, most), ragged=rng.random() < 0.6)
+    if kind == "verify":
+        return dict(kind=kind, shape=rng.choice(JOINT), dtype="bf16", B=rng.randint(1, 8), T=rng.randint(2, 8),
+                    S=_log(rng, 200, 8192))
+    if kind == "prefill":
+        shape, B, T = rng.choice(("7b_25", "7b_12", "13b_25", "7b_25_slrd_576")), rng.randint(1, 2), _log(rng, 64, 2048)
+        S = T if rng.random() < 0.5 else min(8000, T + _log(rng, 100, 7000))
+        T = min(T, MAX_PREFILL_PAIRS // (B * S))
+        return dict(kind=kind, shape=shape, dtype="bf16", B=B, T=T, S=S)
+    return dict(kind=kind, T=_log(rng, 128, 1000))
+
+
+def _row_elems(shape):
+    _, n_h, _, r, d_c, _ = SHAPES[shape]
+    return 2 * r * n_h + d_c
+
+
+def _lengths(case):
+    """Cached tokens of every sequence, the new ones included: all S, or spread between S/4 and S."""
+    B, S = case["B"], case["S"]
+    if not case.get("ragged"):
+        return [S] * B
+    return [max(1, S - (S * 3 // 4) * ((37 * b) % 64) // 64) for b in range(B)]
+
+
+def prepare(case, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    host = random.Random(seed)
+
+    def normal(*size, std=1.0, dtype=torch.bfloat16):
+        return torch.randn(*size, generator=g, device=DEV, dtype=torch.float32).mul_(std).to(dtype)
+
+    if case["kind"] == "search":
+        # queries and keys whose chunks differ in strength from head to head, as a trained layer's do
+        n_h, d_h, r, T = 32, 128, 8, case["T"]
+        strength = torch.exp2(torch.randn(1, n_h, d_h // 2, generator=g, device=DEV)).repeat_interleave(2, dim=2)
+        st = dict(kind="search", q=normal(T, n_h, d_h, dtype=torch.float32) * strength.sqrt(),
+                  k=normal(T, n_h, d_h, dtype=torch.float32) * strength.sqrt(),
+                  pos=torch.arange(T, dtype=torch.int32, device=DEV), r=r,
+                  elite=torch.zeros(n_h, r, dtype=torch.int32, device=DEV),
+                  dist=torch.zeros(n_h, r, dtype=torch.float32, device=DEV))
+        st["ws"] = _workspace(ekv.elitekv_ropelite_search_workspace_bytes(T, n_h, d_h, r))
+        return st
+
+    d, n_h, d_h, r, d_c, d_ck = SHAPES[case["shape"]]
+    dt = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
+    dims = ekv.make_dims(d, n_h, d_h, r, d_c, case["dtype"])
+    kind, B, T = case["kind"], case["B"], case.get("T", 1)
+    lens = _lengths(case)
+    host.shuffle(lens)
+    S = max(lens)
+    stride = S + 16                                      # room for the tokens to come
+    idx = np.stack([np.array(host.sample(range(d_h // 2), r), dtype=np.int32) for _ in range(n_h)])
+    dk, dv = (d_ck, d_c - d_ck) if d_ck else (d_c, d_c)
+    st = dict(kind=kind, dims=dims, d_ck=d_ck, S=S, stride=stride, idx=torch.from_numpy(idx).to(DEV),
+              W_ke=normal(d, n_h, 2 * r, std=d ** -0.5, dtype=dt), W_d=normal(d, dk, std=d ** -0.5, dtype=dt),
+              W_uk=normal(dk, n_h, d_h - 2 * r, std=dk ** -0.5, dtype=dt),
+              W_uv=normal(dv, n_h, d_h, std=dv ** -0.5, dtype=dt),
+              ke=normal(B * stride, n_h, 2 * r, dtype=dt), c=normal(B * stride, d_c, dtype=dt),
+              x=normal(B * T, d, dtype=dt))
+    if d_ck:
+        st["W_d2"] = normal(d, dv, std=d ** -0.5, dtype=dt)
+    # the T new tokens of a sequence are its last ones
+    pos = np.array([[n - T + t for t in range(T)] for n in lens])
+    slot = pos + np.arange(B)[:, None] * stride
+    st["pos"] = torch.from_numpy(pos.astype(np.int32)).to(DEV)
+    st["slot"] = torch.from_numpy(slot.astype(np.int64).reshape(-1)).to(DEV)
+    st["len"] = torch.from_numpy((pos + 1).astype(np.int32)).to(DEV)
+    # the appended rows as views of the planes (of the first sequences where there are many)
+    first = [b * stride + n - T for b, n in enumerate(lens)][:24]
+    st["rows"] = [p[s:s + T] for s in first for p in (st["ke"], st["c"])]
+    if kind == "block":
+        st["W_q"] = normal(d, n_h, d_h, std=d ** -0.5, dtype=dt)
+        st["W_o"] = normal(n_h, d_h, d, std=(n_h * d_h) ** -0.5, dtype=dt)
+        st["out"] = torch.zeros(B, d, dtype=dt, device=DEV)
+        st["ws"] = _workspace(ekv.elitekv_block_step_workspace_bytes(dims, B, S))
+        return st
+    st["q"] = normal(B, T, n_h, d_h, dtype=dt) if kind != "step" else normal(B, n_h, d_h, dtype=dt)
+    st["out"] = torch.zeros_like(st["q"])
+    if kind == "step":
+        st["ws"] = _workspace(ekv.elitekv_slrd_decode_step_workspace_bytes(dims, d_ck, B, S) if d_ck
+                              else ekv.elitekv_decode_step_workspace_bytes(dims, B, S))
+    else:
+        st["ws_append"] = _workspace(ekv.elitekv_slrd_append_workspace_bytes(dims, d_ck, B * T) if d_ck
+                                     else ekv.elitekv_append_workspace_bytes(dims, B * T))
+        st["ws"] = _workspace(ekv.elitekv_multiquery_workspace_bytes(dims, B, T, S) if kind == "verify"
+                              else ekv.elitekv_slrd_prefill_attn_workspace_bytes(dims, d_ck, B, T, S) if d_ck
+                              else ekv.elitekv_prefill_attn_workspace_bytes(dims, B, T, S))
+    return st
+
+
+def _workspace(nbytes):
+    return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=DEV)
+
+
+def run(st):
+    if st["kind"] == "search":
+        ekv.elitekv_ropelite_search(st["q"], st["k"], st["pos"], st["r"], 10000.0, st["elite"], st["dist"], st["ws"])
+        return dict(elite=st["elite"], dist=st["dist"])
+    dims, d_ck, S, stride, kind = st["dims"], st["d_ck"], st["S"], st["stride"], st["kind"]
+    up = (st["W_uk"], st["W_uv"], st["idx"], st["ke"], st["c"], st["out"], st["ws"])
+    if kind == "step":
+        if d_ck:
+            ekv.elitekv_slrd_decode_step(dims, d_ck, st["x"], st["q"], st["pos"], st["slot"], st["len"], S, stride,
+                                         st["W_ke"], st["W_d"], st["W_d2"], *up)
+        else:
+            ekv.elitekv_decode_step(dims, st["x"], st["q"], st["pos"], st["slot"], st["len"], S, stride, st["W_ke"],
+                                    st["W_d"], *up)
+    elif kind == "block":
+        ekv.elitekv_block_step(dims, st["x"], st["pos"], st["slot"], st["len"], S, stride, st["W_q"], st["W_ke"],
+                               st["W_d"], st["W_uk"], st["W_uv"], st["W_o"], st["idx"], st["ke"], st["c"], st["out"],
+                               st["ws"])
+    else:
+        if d_ck:
+            ekv.elitekv_slrd_append(dims, d_ck, st["x"], st["pos"], st["slot"], st["W_ke"], st["W_d"], st["W_d2"],
+                                    st["idx"], st["ke"], st["c"], ws=st["ws_append"])
+        else:
+            ekv.elitekv_append(dims, st["x"], st["pos"], st["slot"], st["W_ke"], st["W_d"], st["idx"], st["ke"],
+                               st["c"], ws=st["ws_append"])
+        if kind == "verify":
+            ekv.elitekv_multiquery_attn(dims, st["q"], st["pos"], st["len"], S, stride, *up)
+        elif d_ck:
+            ekv.elitekv_slrd_prefill_attn(dims, d_ck, st["q"], st["pos"], st["len"], S, stride, *up)
+        else:
+            ekv.elitekv_prefill_attn(dims, st["q"], st["pos"], st["len"], S, stride, *up)
+    return dict(out=st["out"], rows=st["rows"], ke=st["ke"], c=st["c"])
+
+
+def work(case):
+    """Bytes: every input and every cached row read once, new rows and results written once.  Operations: the
+    projections, and the attention in the cheaper of its two orders (B^k, B^v absorbed, or keys and values rebuilt)."""
+    if case["kind"] == "search":
+        n_h, d_h, r, T = 32, 128, 8, case["T"]
+        # per round, causal pair and chunk: a 4-term product, a subtraction, an absolute value and a sum
+        return dict(bytes=2 * T * n_h * d_h * 4 + 2 * n_h * r * 4, flops=12.0 * r * (T * (T + 1) / 2) * n_h * (d_h // 2))
+    d, n_h, d_h, r, d_c, d_ck = SHAPES[case["shape"]]
+    e = 2 if case["dtype"] == "bf16" else 4
+    B, T = case["B"], case.get("T", 1)
+    lens = _lengths(case)
+    row = _row_elems(case["shape"])
+    dk, dv = (d_ck, d_c - d_ck) if d_ck else (d_c, d_c)
+    weights = d * row + n_h * (dk * (d_h - 2 * r) + dv * d_h)
+    token = d + row + 2 * n_h * d_h                      # x in, a row out, q in, out out
+    flops = 2.0 * B * T * d * row
+    if case["kind"] == "block":
+        weights += 2 * d * n_h * d_h
+        token = 2 * d + row
+        flops += 4.0 * B * d * n_h * d_h
+    pairs = sum(T * n - T * (T - 1) // 2 for n in lens)  # (query, visible row)
+    up = 2.0 * n_h * (dk * (d_h - 2 * r) + dv * d_h)
+    absorbed = pairs * n_h * 2.0 * (2 * r + dk + dv) + B * T * up
+    rebuilt = pairs * n_h * 4.0 * d_h + sum(lens) * up
+    flops += min(absorbed, rebuilt)
+    return dict(bytes=e * (weights + B * T * token + sum(n - T for n in lens) * row), flops=flops)
+
+
+def tolerance(case):
+    if case["kind"] == "search":
+        # fp32 sums of millions of terms; a near-tie may pick the other chunk of a round
+        return {"rel": 1e-4, "max": 1e-3, "differ": 0.01}
+    if case["dtype"] == "fp32":
+        return {"rel": 1e-5, "max": 5e-5}           # one pass against float64: 1.3e-6, 6.6e-6 at most
+    return {"rel": 1.2e-2, "max": 0.2}               # one pass against float64: 3.2e-3, 5.7e-2 at most
