@@ -250,3 +250,77 @@ def tolerance(case):
     if case["dtype"] == "fp32":
         return {"rel": 1e-5, "max": 5e-5}           # one pass against float64: 1.3e-6, 6.6e-6 at most
     return {"rel": 1.2e-2, "max": 0.2}               # one pass against float64: 3.2e-3, 5.7e-2 at most
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in 64 bits and without the package's kernels: the new rows, then every query's
+    softmax over its visible rows.  The planes themselves are inputs but for those rows, and have no value here."""
+    st = prepare(case, seed)
+    if case["kind"] == "search":
+        return _exact_search(st)
+    d, n_h, d_h, r, d_c, d_ck = SHAPES[case["shape"]]
+    kind, B, T = case["kind"], case["B"], case.get("T", 1)
+    dk = d_ck or d_c
+    f64 = lambda name: st[name].double()
+    idx, pos = st["idx"].long(), st["pos"].reshape(-1)
+    pairs = torch.stack((2 * idx, 2 * idx + 1), dim=2).reshape(n_h, 2 * r)     # elite dims in slot order, per head
+    others = torch.stack([torch.tensor([i for i in range(d_h) if i not in chosen], device=DEV)
+                          for chosen in map(set, pairs.tolist())])
+
+    x = f64("x")
+    new_ke = _rotate((x @ f64("W_ke").reshape(d, -1)).reshape(B * T, n_h, 2 * r), pos, idx, d_h)
+    new_c = torch.cat([x @ f64(w) for w in ("W_d", "W_d2") if w in st], dim=1)
+    q = (x @ f64("W_q").reshape(d, -1) if kind == "block" else f64("q")).reshape(B * T, n_h, d_h)
+    q_e = _rotate(q.gather(2, pairs.expand(B * T, -1, -1)), pos, idx, d_h)
+    q_n = q.gather(2, others.expand(B * T, -1, -1))
+    W_uk, W_uv = f64("W_uk"), f64("W_uv")
+
+    out = torch.zeros(B * T, n_h, d_h, dtype=torch.float64, device=DEV)
+    rows, stride, seen = [], st["stride"], st["len"].reshape(B, T)
+    for b in range(B):
+        new, n = slice(b * T, (b + 1) * T), int(seen[b, -1])
+        ke, c = (st[p][b * stride:b * stride + n].double() for p in ("ke", "c"))
+        ke[n - T:], c[n - T:] = new_ke[new], new_c[new]
+        if len(rows) < len(st["rows"]):
+            rows += [ke[n - T:].clone(), c[n - T:].clone()]
+        hidden = torch.arange(n, device=DEV)[None, :] >= seen[b][:, None]
+        ck, cv = c[:, :dk], c[:, d_ck:]
+        for h in range(n_h):
+            s = (q_n[new, h] @ W_uk[:, h].T) @ ck.T + q_e[new, h] @ ke[:, h].T
+            p = (s * d_h ** -0.5).masked_fill_(hidden, float("-inf")).softmax(dim=1)
+            out[new, h] = (p @ cv) @ W_uv[:, h]
+    if kind == "block":
+        out = out.reshape(B, -1) @ f64("W_o").reshape(-1, d)
+    return dict(out=out.reshape(st["out"].shape), rows=rows, ke=None, c=None)
+
+
+def _rotate(pairs, pos, idx, d_h):
+    """pairs [N, n_h, 2 r] in slot order, every pair turned by its position times its chunk's frequency."""
+    angle = pos.double()[:, None, None] * (10000.0 ** (-2.0 * idx.double() / d_h))[None]
+    u, v = pairs[..., 0::2], pairs[..., 1::2]
+    return torch.stack((u * angle.cos() - v * angle.sin(), u * angle.sin() + v * angle.cos()), dim=3).reshape(pairs.shape)
+
+
+def _exact_search(st):
+    q, k, r = st["q"].double(), st["k"].double(), st["r"]
+    T, n_h, d_h = q.shape
+    every = torch.arange(d_h // 2, device=DEV).expand(n_h, -1)
+    qr, kr = (_rotate(v, st["pos"], every, d_h) for v in (q, k))
+    causal = torch.ones(T, T, dtype=torch.bool, device=DEV).tril()
+    elite = torch.zeros(n_h, r, dtype=torch.int32, device=DEV)
+    dist = torch.zeros(n_h, r, dtype=torch.float64, device=DEV)
+    for h in range(n_h):
+        # what rotating one chunk adds to a pair's score, for every chunk
+        gain = torch.stack([(qr[:, h, c:c + 2] @ kr[:, h, c:c + 2].T - q[:, h, c:c + 2] @ k[:, h, c:c + 2].T)[causal]
+                            for c in range(0, d_h, 2)]) * d_h ** -0.5
+        left = gain.sum(dim=0)
+        away = torch.full((d_h // 2,), float("inf"), dtype=torch.float64, device=DEV)
+        chosen = []
+        for i in range(r):
+            for c in range(d_h // 2):
+                away[c] = (left - gain[c]).abs().sum() if c not in chosen else float("inf")
+            best = int(away.argmin())
+            chosen.append(best)
+            elite[h, i], dist[h, i] = best, away[best]
+            left = left - gain[best]
+    return dict(elite=elite, dist=dist)
