@@ -52,6 +52,26 @@ static int32_t auto_splits_generic(const elitekv_dims* d, int64_t B, int64_t max
   return (int32_t)want;
 }
 
+// Splits per batch row of the matrix-core path: `groups` (batch row, head group) pairs of up to `tiles` tiles each on a
+// chip that holds `slots` work-groups at once.  The launch takes as many rounds as its work-groups fill the chip, and a
+// round costs its longest work-group: a start (first tile from cold memory, about four tiles' time) and its tiles.
+// Rounding the split count UP to fill every slot started a second round for the last few work-groups: 260 of them for
+// 4 sequences x 5 drafted tokens (7B 25 %, 4096 tokens): 92.9 us, 240 (twelve splits): 55.9 us; 258 for three sequences of 5001
+// tokens, separated latents: 23.5 us, 237: 16.5 us.  Of equal counts the smallest (fewest partials to merge).
+static int64_t balanced_splits(int64_t groups, int64_t tiles, int64_t slots) {
+  int64_t best = 1, best_cost = INT64_MAX;
+  for (int64_t rounds = 1; rounds <= 2; ++rounds) {
+    int64_t ns = rounds == 1 ? slots / groups : (slots + groups - 1) / groups;
+    if (ns > tiles) ns = tiles;
+    if (ns > kMaxSplits) ns = kMaxSplits;
+    if (ns < 1) continue;
+    const int64_t per_split = (tiles + ns - 1) / ns;
+    const int64_t cost = (groups * ns + slots - 1) / slots * (4 + per_split);
+    if (cost < best_cost) { best = (tiles + per_split - 1) / per_split; best_cost = cost; }
+  }
+  return best;
+}
+
 // Decide the path and lay the workspace out.  Returns a status.
 // d_ck = 0: joint latent; d_ck > 0: separated latents, a cache row is [c^k (d_ck) | c^v (d_c - d_ck)]
 // want_fresh: plan the fused decode step (the newest token enters as one more split) if the kernels cover it
@@ -95,13 +115,9 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     if (ns == 0) {
       // the narrow-latent instantiations run two work-groups per compute unit; with many batch rows
       // it pays to give every compute unit two (more splits also mean more partials to merge)
-      const int64_t want = (decode_mfma_groups_per_cu(*d) == 2 && Bq * p->head_groups >= 16) ? 2 * kComputeUnits
-                                                                                            : kComputeUnits;
-      ns = (want + Bq * p->head_groups - 1) / (Bq * p->head_groups);
-      const int64_t cap = (seq + 15) / 16;
-      if (ns > cap) ns = cap;
-      if (ns > kMaxSplits) ns = kMaxSplits;
-      if (ns < 1) ns = 1;
+      const int64_t slots = (decode_mfma_groups_per_cu(*d) == 2 && Bq * p->head_groups >= 16) ? 2 * kComputeUnits
+                                                                                             : kComputeUnits;
+      ns = balanced_splits(Bq * p->head_groups, (seq + 15) / 16, slots);
     }
     p->n_splits = (int32_t)ns;
     p->n_part = (int32_t)ns;
