@@ -76,8 +76,9 @@ static int64_t balanced_splits(int64_t groups, int64_t tiles, int64_t slots) {
 // d_ck = 0: joint latent; d_ck > 0: separated latents, a cache row is [c^k (d_ck) | c^v (d_c - d_ck)]
 // want_fresh: plan the fused decode step (the newest token enters as one more split) if the kernels cover it
 // block: plan the whole-block step (EUNSUPPORTED unless the fused step's kernels cover the shape)
+// tiled: false leaves the tiled fp32 kernels out, whose automatic split counts can ask for more workspace
 static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t max_seq, int32_t n_splits,
-                       DecodePlan* p, bool want_fresh = false, bool block = false) {
+                       DecodePlan* p, bool want_fresh = false, bool block = false, bool tiled = true) {
   int st = check_dims(d);
   if (st) return st;
   if (B < 0 || max_seq < 0 || n_splits < 0) return ELITEKV_EINVAL;
@@ -151,7 +152,10 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     if (block) return ELITEKV_EUNSUPPORTED;
     p->mfma = 0;
     p->head_groups = 1;
-    p->n_splits = n_splits > 0 ? n_splits : auto_splits_generic(d, Bq, seq);
+    p->tiled = tiled && decode_tiled_supported(*d, d_ck);
+    p->n_splits = n_splits > 0 ? n_splits
+                  : p->tiled   ? (int32_t)balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits)
+                               : auto_splits_generic(d, Bq, seq);
     p->n_part = p->n_splits;
     int64_t chunk = (seq + p->n_splits - 1) / p->n_splits;
     if (chunk < 1) chunk = 1;
@@ -161,6 +165,8 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     p->off_m = off;  off = align_up(off + Bz * ns * nh * sizeof(float), 256);
     p->off_l = off;  off = align_up(off + Bz * ns * nh * sizeof(float), 256);
     p->off_u = off;  off = align_up(off + Bz * ns * nh * du * sizeof(float), 256);
+    p->off_opart = off;
+    if (p->tiled) off = align_up(off + Bz * nh * du * sizeof(float), 256);
   }
   p->total = off;
   return ELITEKV_OK;
@@ -282,11 +288,18 @@ static AppendArgs append_args(const elitekv_dims* dims, int32_t d_ck, const void
   return a;
 }
 
+static hipError_t decode_dispatch(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream) {
+  return p.mfma    ? launch_decode_mfma(a, p, stream)
+         : p.tiled ? launch_decode_tiled(a, p, stream)
+                   : launch_decode_generic(a, p, stream);
+}
+
 static hipError_t append_dispatch(const AppendArgs& a, hipStream_t stream) {
   const elitekv_dims* dims = &a.dims;
   return append_gemm_supported(*dims, a.T, a.d_ck)     ? launch_append_gemm(a, stream)
          : append_skinny_supported(*dims, a.T, a.d_ck) ? launch_append_skinny(a, stream)
          : append_small_supported(*dims, a.T, a.d_ck)  ? launch_append_small(a, stream)
+         : append_tiled_supported(*dims, a.T, a.d_ck)  ? launch_append_tiled(a, stream)
                                                        : launch_append_generic(a, stream);
 }
 
@@ -372,17 +385,16 @@ static int decode_impl(const elitekv_dims* dims, int32_t d_ck, const void* q, co
                        int64_t batch_stride_rows, const void* W_uk, const void* W_uv,
                        const int32_t* elite_idx, const void* ke_plane, const void* c_plane,
                        int64_t plane_rows, void* out, void* ws, size_t ws_bytes, int32_t n_splits,
-                       void* hip_stream, int32_t stages, int32_t q_per_seq = 1) {
+                       void* hip_stream, int32_t stages, int32_t q_per_seq = 1, bool tiled = true) {
   DecodePlan p;
-  int st = plan_decode(dims, d_ck, B, max_seq_len, n_splits, &p);
+  int st = plan_decode(dims, d_ck, B, max_seq_len, n_splits, &p, false, false, tiled);
   if (st) return st;
   st = decode_check(dims, p, q, q_pos, seq_len, B, batch_stride_rows, W_uk, W_uv, elite_idx, ke_plane, c_plane,
                     plane_rows, out, ws, ws_bytes);
   if (st || B == 0) return st;
   const DecodeArgs a = decode_args(dims, d_ck, q, q_pos, seq_len, B, max_seq_len, batch_stride_rows, W_uk, W_uv,
                                    elite_idx, ke_plane, c_plane, plane_rows, out, ws, stages, q_per_seq);
-  const hipError_t e = p.mfma ? launch_decode_mfma(a, p, (hipStream_t)hip_stream)
-                             : launch_decode_generic(a, p, (hipStream_t)hip_stream);
+  const hipError_t e = decode_dispatch(a, p, (hipStream_t)hip_stream);
   return e == hipSuccess ? ELITEKV_OK : ELITEKV_EHIP;
 }
 
@@ -433,7 +445,7 @@ static int step_impl(const elitekv_dims* dims, int32_t d_ck, const void* x, cons
     if (e == hipSuccess) e = launch_decode_mfma(a, p, stream);
   } else {
     e = append_dispatch(ap, stream);
-    if (e == hipSuccess) e = p.mfma ? launch_decode_mfma(a, p, stream) : launch_decode_generic(a, p, stream);
+    if (e == hipSuccess) e = decode_dispatch(a, p, stream);
   }
   return e == hipSuccess ? ELITEKV_OK : ELITEKV_EHIP;
 }
@@ -821,7 +833,11 @@ int elitekv_decode_attn_noalloc(const elitekv_dims* dims, const void* q, const i
                                 const int32_t* elite_idx, const void* ke_plane, const void* c_plane,
                                 int64_t plane_rows, void* out, int32_t n_splits, void* hip_stream) {
   DecodePlan p;
-  const int st = plan_decode(dims, 0, B, max_seq_len, n_splits, &p);
+  int st = plan_decode(dims, 0, B, max_seq_len, n_splits, &p);
+  if (st) return st;
+  // where the tiled fp32 kernels' plan is too large for the scratch buffer, the any-shape kernels' may still fit
+  const bool tiled = p.total <= (size_t)ELITEKV_NOALLOC_SCRATCH_BYTES;
+  if (!tiled && p.tiled) st = plan_decode(dims, 0, B, max_seq_len, n_splits, &p, false, false, false);
   if (st) return st;
   if (p.total > (size_t)ELITEKV_NOALLOC_SCRATCH_BYTES) return ELITEKV_ESCRATCH;
   void* ws = scratch_ptr();
@@ -829,7 +845,8 @@ int elitekv_decode_attn_noalloc(const elitekv_dims* dims, const void* q, const i
   // every kernel of the call writes the part of the scratch it later reads (empty splits included),
   // so nothing needs clearing between calls
   return decode_impl(dims, 0, q, q_pos, seq_len, B, max_seq_len, batch_stride_rows, W_uk, W_uv, elite_idx,
-                     ke_plane, c_plane, plane_rows, out, ws, ELITEKV_NOALLOC_SCRATCH_BYTES, n_splits, hip_stream, 7);
+                     ke_plane, c_plane, plane_rows, out, ws, ELITEKV_NOALLOC_SCRATCH_BYTES, n_splits, hip_stream, 7, 1,
+                     tiled);
 }
 
 int elitekv_decode_attn_stages(const elitekv_dims* dims, const void* q, const int32_t* q_pos,

@@ -34,7 +34,8 @@ inline hipError_t raise_lds_limit(LdsLimit& st, const void* kernel, size_t bytes
 struct DecodePlan {
   int32_t n_splits;     // sequence splits per batch row
   int32_t chunk;        // cached tokens per split
-  int32_t mfma;         // 1: bf16 MFMA kernels, 0: generic VALU kernels
+  int32_t mfma;         // 1: bf16 MFMA kernels, 0: kernels in fp32 arithmetic
+  int32_t tiled;        // mfma 0: 1: the tiled fp32 matrix-core kernels (tiled_f32.hip), 0: the any-shape kernels
   int32_t head_groups;  // MFMA path: groups of up to 32 heads
   int32_t up_cw;        // MFMA path: latent columns per merge/up-projection work-group
   int32_t merge_batch;  // MFMA path: 1 = the merge kernel that takes all batch rows per work-group
@@ -45,7 +46,7 @@ struct DecodePlan {
   size_t off_m;         // split maxima (log2 domain)       fp32 [B, n_splits, n_h_pad]
   size_t off_l;         // split sums                       fp32 [B, n_splits, n_h_pad]
   size_t off_u;         // split latent accumulators        fp32 [B, n_splits, ...]
-  size_t off_opart;     // up-projection partials           fp32
+  size_t off_opart;     // up-projection partials (MFMA path), merged latents (tiled path)   fp32
   size_t off_cnt;       // MFMA path: arrival counters of the merge kernels' chunk groups   int32 [B, n_h]
   // fused decode step (fresh != 0): the cache row of the newest token of every sequence is finished (summed,
   // rotated, stored) inside the attention kernel, by the work-group whose tiles include its position,
@@ -138,6 +139,10 @@ size_t append_skinny_workspace(const elitekv_dims& d, int64_t T);
 hipError_t launch_append_skinny(const AppendArgs& a, hipStream_t stream);
 bool append_gemm_supported(const elitekv_dims& d, int64_t T, int d_ck);
 hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream);
+bool append_tiled_supported(const elitekv_dims& d, int64_t T, int d_ck);
+hipError_t launch_append_tiled(const AppendArgs& a, hipStream_t stream);
+bool decode_tiled_supported(const elitekv_dims& d, int d_ck);
+hipError_t launch_decode_tiled(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 hipError_t launch_decode_generic(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 bool decode_mfma_supported(const elitekv_dims& d, int d_ck);
 int decode_mfma_groups_per_cu(const elitekv_dims& d);
