@@ -11,6 +11,8 @@
 // streamed once, split over column blocks and over the contraction dimension so that every
 // compute unit pulls a share.  fp32 partials go to the workspace; the finish kernel of the
 // small-batch path sums the contraction splits, rotates and stores.
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 #include "append_skinny.hpp"
@@ -86,6 +88,12 @@ constexpr int kGmStage = 64;                   // contraction rows per stage
 constexpr int kGmARow = kGmCols * 2 + 32;      // bytes of a staged weight row [k][128 n] (+ bank spread)
 constexpr int kGmBRow = kGmStage * 2 + 16;     // bytes of a staged token row [t][64 k] (+ bank spread)
 
+template <int NI>
+struct GemmStore {
+  static constexpr int kRow = NI * 32 + 4;    // floats of a token's columns in LDS
+  static constexpr int kWaveBytes = 32 * kRow * 4;
+};
+
 template <int WN>
 struct GemmLayout {
   static constexpr int BN = 64 * WN;                          // tokens per work-group
@@ -93,67 +101,90 @@ struct GemmLayout {
   static constexpr int B_BYTES = BN * kGmBRow;
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int LDS_BYTES = 2 * STAGE;
+  static_assert(4 * GemmStore<2>::kWaveBytes <= LDS_BYTES, "the epilogue reuses the staging buffers");
   static constexpr int NB = BN * 8 / 256;                     // 16-byte token pieces per thread per stage
 };
 
-// Epilogue of the GEMM kernels: lane <-> token; registers 4*g4 .. 4*g4+3 of accumulator tile (i, j)
-// are the output columns n0 + wm*64 + i*32 + 8*g4 + 4*hi + {0, 1, 2, 3} of token
-// t0 + wn*32*WN + j*32 + n32.  Elite pairs are rotated in registers; bf16 rows go to the planes.
-template <int WN>
-__device__ __forceinline__ void gemm_epilogue(am_f32x16 (&acc)[2][WN], int n0, int64_t t0, int wm, int wn, int n32,
-                                              int hi, int64_t T, const int32_t* __restrict__ pos,
-                                              const int64_t* __restrict__ slot, const int32_t* __restrict__ elite_idx,
-                                              bf16_t* __restrict__ ke_plane, bf16_t* __restrict__ c_plane,
-                                              int64_t plane_rows, int n_h, int d_h, int r, int d_c,
-                                              const RopeTable& rope) {
+// Epilogue of the GEMM kernels.  A wave holds 32 NI columns (from nw) x 32 NJ tokens (from tw): registers 4 g .. 4 g + 3 of
+// accumulator tile (i, j) are columns nw + 32 i + 8 g + 4 (lane / 32) + {0, 1, 2, 3} of token tw + 32 j + lane % 32.  The tile
+// leaves through the wave's own piece of LDS, 32 tokens at a time, so that a store instruction writes whole pieces of
+// rows (64 NI bytes; straight from the accumulators it would touch 32 rows with 16 bytes each), and so that the
+// rotation of the elite pairs is one short loop: unrolled over the accumulators it was 230 KB of code, which every work-group
+// fetched anew.  1536 x 7680 x 2048 tokens, 256 x 256 tiles: 80 -> 61 us a launch; 4096 x 2048 x 32768: 620 -> 534.
+template <int NI, int NJ, typename Acc>
+__device__ __forceinline__ void gemm_store(const Acc& acc, char* lds, int wave, int nw, int64_t tw, int lane, int64_t T,
+                                           const int32_t* __restrict__ pos, const int64_t* __restrict__ slot,
+                                           const int32_t* __restrict__ elite_idx, bf16_t* __restrict__ ke_plane,
+                                           bf16_t* __restrict__ c_plane, int64_t plane_rows, int n_h, int d_h, int r, int d_c,
+                                           const RopeTable& rope) {
+  using G = GemmStore<NI>;
+  constexpr int kLanes = NI * 4, kRows = 64 / kLanes;         // lanes per row of the tile, rows per instruction
+  float* buf = reinterpret_cast<float*>(lds + wave * G::kWaveBytes);
   const int NE = 2 * r * n_h;
+  const int n32 = lane & 31, hi = lane >> 5;
+  // this lane's eight columns on the way out
+  const int cl = (lane % kLanes) * 8, n = nw + cl, rl = lane / kLanes;
+  const bool elite = n < NE;
+  double theta[4] = {0.0, 0.0, 0.0, 0.0};
+  if (elite) {
 #pragma unroll
-  for (int j = 0; j < WN; ++j) {
-    const int64_t t = t0 + wn * 32 * WN + j * 32 + n32;
-    if (t >= T) continue;
-    const int64_t row = slot ? slot[t] : t;                  // no slot list: rows are written in place
-    if (row < 0 || row >= plane_rows) continue;
-    const int32_t p = pos ? pos[t] : 0;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int n = n0 + wm * 64 + i * 32 + 8 * g4 + 4 * hi;
-        const bool elite_block = n < NE;                       // uniform over the wave's 64-column half
-        float v0 = acc[i][j][4 * g4], v1 = acc[i][j][4 * g4 + 1], v2 = acc[i][j][4 * g4 + 2], v3 = acc[i][j][4 * g4 + 3];
-        bf16_t* dst;
-        if (elite_block) {
-          // two (even, odd) pairs: slots (n % 2r)/2 and the next one of the same head (2r is even and
-          // n is a multiple of 4, so a group of four never straddles a head when 2r % 4 == 0; with
-          // 2r % 4 == 2 the second pair may belong to the next head: both are looked up separately)
-          float sn, cs;
-          {
-            const int hh = n / (2 * r), jj = (n % (2 * r)) >> 1;
-            int ch = elite_idx[hh * r + jj];
-            ch = min(max(ch, 0), d_h / 2 - 1);
-            rope_sincos_poly(p, rope.theta[ch], &sn, &cs);
-            const float a0 = v0 * cs - v1 * sn, a1 = v0 * sn + v1 * cs;
-            v0 = a0; v1 = a1;
-          }
-          {
-            const int n2 = n + 2;
-            const int hh = n2 / (2 * r), jj = (n2 % (2 * r)) >> 1;
-            int ch = elite_idx[hh * r + jj];
-            ch = min(max(ch, 0), d_h / 2 - 1);
-            rope_sincos_poly(p, rope.theta[ch], &sn, &cs);
-            const float a2 = v2 * cs - v3 * sn, a3 = v2 * sn + v3 * cs;
-            v2 = a2; v3 = a3;
-          }
-          dst = ke_plane + row * NE + n;
-        } else {
-          dst = c_plane + row * d_c + (n - NE);
-        }
-        uint2 pk;
-        pk.x = (uint32_t)f32_to_bf16_bits(v0) | ((uint32_t)f32_to_bf16_bits(v1) << 16);
-        pk.y = (uint32_t)f32_to_bf16_bits(v2) | ((uint32_t)f32_to_bf16_bits(v3) << 16);
-        *reinterpret_cast<uint2*>(dst) = pk;
-      }
+    for (int e = 0; e < 4; ++e) {             // slots of the four pairs, which may belong to different heads
+      const int m = n + 2 * e;
+      int ch = elite_idx[(m / (2 * r)) * r + ((m % (2 * r)) >> 1)];
+      ch = min(max(ch, 0), d_h / 2 - 1);
+      theta[e] = rope.theta[ch];
     }
+  }
+  bf16_t* plane = elite ? ke_plane + n : c_plane + (n - NE);
+  const int64_t ld_out = elite ? NE : d_c;
+  // destination rows (-1: not stored) and positions of the tile's tokens, one token per lane and j, requested at once
+  int64_t rows[NJ];
+  int32_t posn[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int64_t t = min(tw + j * 32 + n32, T - 1);
+    rows[j] = slot ? slot[t] : t;                             // no slot list: rows are written in place
+    posn[j] = pos ? pos[t] : 0;
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+    if (tw + j * 32 + n32 >= T || rows[j] >= plane_rows || rows[j] < 0) rows[j] = -1;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const am_f32x16& a = acc(i, j);
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(buf + n32 * G::kRow + i * 32 + 8 * g + 4 * hi) =
+            make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // the wave's own pieces
+#pragma unroll 4
+    for (int it = 0; it < 32 / kRows; ++it) {
+      const int tl = it * kRows + rl;
+      const float4 lo = *reinterpret_cast<const float4*>(buf + tl * G::kRow + cl);
+      const float4 up = *reinterpret_cast<const float4*>(buf + tl * G::kRow + cl + 4);
+      float v[8] = {lo.x, lo.y, lo.z, lo.w, up.x, up.y, up.z, up.w};
+      const int64_t row = ((int64_t)__shfl((int)(rows[j] >> 32), tl, kWave) << 32) | (uint32_t)__shfl((int)rows[j], tl, kWave);
+      const int32_t p = __shfl(posn[j], tl, kWave);
+      if (row < 0) continue;
+      if (elite) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float sn, cs;
+          rope_sincos_poly(p, theta[e], &sn, &cs);
+          const float x0 = v[2 * e] * cs - v[2 * e + 1] * sn, x1 = v[2 * e] * sn + v[2 * e + 1] * cs;
+          v[2 * e] = x0; v[2 * e + 1] = x1;
+        }
+      }
+      ekv_u32x4 pk;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        pk[e] = (uint32_t)f32_to_bf16_bits(v[2 * e]) | ((uint32_t)f32_to_bf16_bits(v[2 * e + 1]) << 16);
+      __builtin_nontemporal_store(pk, reinterpret_cast<ekv_u32x4*>(plane + row * ld_out));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // read before the next tokens overwrite it
   }
 }
 
@@ -256,8 +287,9 @@ __global__ __launch_bounds__(256) void append_gemm_kernel(
     __syncthreads();
   }
 
-  gemm_epilogue<WN>(acc, n0, t0, wm, wn, n32, hi, T, pos, slot, elite_idx, ke_plane, c_plane, plane_rows, n_h, d_h,
-                    r, d_c, rope);
+  // (the last stage's barrier has passed: the staging buffers are free)
+  gemm_store<2, WN>([&](int i, int j) -> const am_f32x16& { return acc[i][j]; }, gsm, wave, n0 + wm * 64, t0 + wn * 32 * WN, lane,
+                    T, pos, slot, elite_idx, ke_plane, c_plane, plane_rows, n_h, d_h, r, d_c, rope);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -297,8 +329,22 @@ struct GemmDmaLayout {
   static constexpr int LPW = LOADS / NWAVES;                  // ... per wave
   static_assert(LOADS % NWAVES == 0, "the loads of a stage are divided evenly among the waves");
   static_assert(LDS_BYTES <= 160 * 1024, "exceeds the LDS of a compute unit");
+  static_assert(NWAVES * GemmStore<2>::kWaveBytes <= LDS_BYTES, "the epilogue reuses the ring");
   static_assert(NS >= 3 && NS <= 12 && (NS - 2) * LPW <= 63, "ring depth outside what the load counter can express");
 };
+
+struct GemmTileMap {              // which (column block, token block) a work-group takes; see gemm_tile_map
+  int xt, tb_x, cb_x, group, col_blocks;
+};
+__device__ __forceinline__ bool gemm_tile_of(const GemmTileMap& m, int wg, int* cb, int64_t* tb) {
+  const int xcd = wg & 7, seq = wg >> 3;
+  const int g = seq / (m.group * m.cb_x), rem = seq - g * m.group * m.cb_x;
+  const int in_group = min(m.group, m.tb_x - g * m.group);
+  *tb = (int64_t)(g * m.group + rem % in_group) * m.xt + xcd % m.xt;
+  const int c = rem / in_group;
+  *cb = (xcd / m.xt) * m.cb_x + c;
+  return c < m.cb_x && *cb < m.col_blocks;
+}
 
 // SPB = stages consumed per barrier (1 or 2).  With 2 the work-group synchronises once per 64 contraction rows:
 // half as many barriers and load waits, the operands of the second stage of a pair read while the first is
@@ -313,7 +359,8 @@ __global__ __launch_bounds__(64 * CM * WNW) void append_gemm_dma_kernel(
     const bf16_t* __restrict__ x, const int32_t* __restrict__ pos, const int64_t* __restrict__ slot, int64_t T,
     const bf16_t* __restrict__ W_ke, const bf16_t* __restrict__ W_dkv, const bf16_t* __restrict__ W_dkv2, int d_ck,
     const int32_t* __restrict__ elite_idx, bf16_t* __restrict__ ke_plane, bf16_t* __restrict__ c_plane,
-    int64_t plane_rows, int d, int n_h, int d_h, int r, int d_c, RopeTable rope, int64_t x_ld, int x_off2, int d2) {
+    int64_t plane_rows, int d, int n_h, int d_h, int r, int d_c, RopeTable rope, int64_t x_ld, int x_off2, int d2,
+    GemmTileMap map) {
   using L = GemmDmaLayout<WN, NS, WNW, CM>;
   extern __shared__ __attribute__((aligned(16))) char gsm[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -325,15 +372,13 @@ __global__ __launch_bounds__(64 * CM * WNW) void append_gemm_dma_kernel(
   const int wm = wv % CM, wn = wv / CM;
   const int n32 = lane & 31, hi = lane >> 5, i16 = lane & 15, q16 = lane >> 4;
   const int NE = 2 * r * n_h;
-  // Work-groups go to the eight XCDs round-robin by linear index.  All column blocks of one token
-  // block are given to the SAME XCD, one after the other, so the token tile is fetched into that
-  // XCD's L2 once and re-used by every column block instead of being fetched by eight L2s.
-  const int col_blocks = (NE + d_c) / L::COLS;
-  const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-  const int64_t tblock = (int64_t)(seq / col_blocks) * 8 + xcd;
-  const int n0 = (seq % col_blocks) * L::COLS;
+  int cb;
+  int64_t tblock;
+  if (!gemm_tile_of(map, blockIdx.x, &cb, &tblock)) return;
   const int64_t t0 = tblock * L::BN;
   if (t0 >= T) return;
+  // an odd last half block of columns is computed together with the half before it, which is then written twice
+  const int n0 = min(cb * L::COLS, NE + d_c - L::COLS);
   // a column block inside W_dkv2 may contract a different column slice of the input rows (d2 > 0; the host
   // makes sure that no block straddles the two matrices then)
   const bool second = d2 > 0 && n0 - NE >= d_ck;
@@ -507,12 +552,180 @@ __global__ __launch_bounds__(64 * CM * WNW) void append_gemm_dma_kernel(
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int v = 0; v < 16; ++v) fin[i][0][v] += xb[((partner * 2 + i) * 16 + v) * 64 + lane];
-    gemm_epilogue<1>(fin, n0, t0, wm, wn * 2 + kg, n32, hi, T, pos, slot, elite_idx, ke_plane, c_plane, plane_rows, n_h,
-                     d_h, r, d_c, rope);
+    __syncthreads();
+    gemm_store<2, 1>([&](int i, int j) -> const am_f32x16& { return fin[i][j]; }, gsm, wave, n0 + wm * 64,
+                     t0 + (wn * 2 + kg) * 32, lane, T, pos, slot, elite_idx, ke_plane, c_plane, plane_rows, n_h, d_h, r, d_c,
+                     rope);
   } else {
-    gemm_epilogue<WN>(acc, n0, t0, wm, wn, n32, hi, T, pos, slot, elite_idx, ke_plane, c_plane, plane_rows, n_h, d_h,
-                      r, d_c, rope);
+    __syncthreads();                          // every wave is done with the ring
+    gemm_store<2, WN>([&](int i, int j) -> const am_f32x16& { return acc[i][j]; }, gsm, wave, n0 + wm * 64,
+                      t0 + wn * 32 * WN, lane, T, pos, slot, elite_idx, ke_plane, c_plane, plane_rows, n_h, d_h, r, d_c, rope);
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// append_gemm_wide: 256 columns x 256 tokens per work-group by FOUR waves, one per SIMD, each 128 x 128 outputs.
+// At this tile the LDS is what eight waves of 64 x 128 keep busy: per 16 contraction rows they read 48 KB and the direct
+// loads write 16 KB, 512 cycles of 128 bytes, beside 512 cycles of matrix instructions.  Four waves read 32 KB.  With one
+// wave per SIMD nothing else hides a wave's waits, so the loop is skewed by one k-step of 16 rows and ordered by hand: while
+// the 16 products of a k-step run, the operands of the next one are read into a second register set, two reads per product;
+// the barrier that publishes the next stage sits between two products; the direct loads of the stage that takes the freed
+// buffer go out one per product.
+// 4096 x 2048 x 32768 tokens: 493 us = 1114 TFLOP/s (eight waves 521).
+// ---------------------------------------------------------------------------------------------
+template <int NS>
+struct GemmWideLayout {
+  static constexpr int A_BYTES = kGdStage * 256 * 2, STAGE = 2 * A_BYTES, LDS_BYTES = NS * STAGE, LPW = STAGE / 1024 / 4;
+  static_assert(LDS_BYTES <= 160 * 1024 && (NS - 1) * LPW <= 63, "ring depth");
+};
+
+template <int NS>
+__global__ __launch_bounds__(256, 1) void append_gemm_wide_kernel(
+    const bf16_t* __restrict__ x, const int32_t* __restrict__ pos, const int64_t* __restrict__ slot, int64_t T,
+    const bf16_t* __restrict__ W_ke, const bf16_t* __restrict__ W_dkv, const bf16_t* __restrict__ W_dkv2, int d_ck,
+    const int32_t* __restrict__ elite_idx, bf16_t* __restrict__ ke_plane, bf16_t* __restrict__ c_plane,
+    int64_t plane_rows, int d, int n_h, int d_h, int r, int d_c, RopeTable rope, int64_t x_ld, int x_off2, int d2,
+    GemmTileMap map) {
+  using L = GemmWideLayout<NS>;
+  extern __shared__ __attribute__((aligned(16))) char gsm[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int n32 = lane & 31, hi = lane >> 5, i16 = lane & 15, q16 = lane >> 4;
+  const int NE = 2 * r * n_h, N = NE + d_c;
+  int cb;
+  int64_t tb;
+  if (!gemm_tile_of(map, blockIdx.x, &cb, &tb)) return;
+  const int64_t t0 = tb * 256;
+  if (t0 >= T) return;
+  const int n0 = min(cb * 256, N - 256);      // an odd last half block is computed with the half before it, twice
+  const bool second = d2 > 0 && n0 - NE >= d_ck;
+  const bf16_t* xs = second ? x + x_off2 : x;
+  const int nstages = (second ? d2 : d) / kGdStage;
+
+  // ---- loader: waves 0, 1 bring the weights (16 blocks of 8 rows x 64 columns), waves 2, 3 the tokens (16 blocks of 16)
+  const char* gsrc[L::LPW];
+  int64_t gstep[L::LPW];
+#pragma unroll
+  for (int u = 0; u < L::LPW; ++u) {
+    const int idx = wave * L::LPW + u;
+    if (idx < 16) {
+      const int kb = idx >> 2, nb = idx & 3, row = lane >> 3, pc = (lane & 7) ^ gd_swz8(row);
+      const bf16_t* wb;
+      int64_t ws;
+      weight_column(n0 + nb * 64, NE, d_ck, d_c, W_ke, W_dkv, W_dkv2, &wb, &ws);
+      gsrc[u] = reinterpret_cast<const char*>(wb + (int64_t)(kb * 8 + row) * ws + pc * 8);
+      gstep[u] = (int64_t)kGdStage * ws * 2;
+    } else {
+      const int tbk = idx - 16, row = lane >> 2, pc = (lane & 3) ^ gd_swz4(row);
+      const int64_t t = min(t0 + tbk * 16 + row, T - 1);         // rows past the end repeat the last token
+      gsrc[u] = reinterpret_cast<const char*>(xs + t * x_ld + pc * 8);
+      gstep[u] = (int64_t)kGdStage * 2;
+    }
+  }
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)gsm);
+  int issue_slot = 0;
+  auto issue_one = [&](int u) {
+    const uint32_t base = __builtin_amdgcn_readfirstlane(lds0 + issue_slot * L::STAGE + wave * L::LPW * 1024);
+    gd_dma16(gsrc[u], base + u * 1024);
+    gsrc[u] += gstep[u];
+    if (u == L::LPW - 1) issue_slot = (issue_slot + 1 == NS) ? 0 : issue_slot + 1;
+  };
+
+  am_f32x16 acc[4][4];                        // [32-column tile][32-token tile]
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = (am_f32x16)(0.f);
+
+  int a_off[2][2];                            // [32-column tile of a 64-column block][rows 0-3 | 4-7 of a weight block]
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int r8 = 4 * e + (i16 >> 2);
+      const int piece = (i << 2) | ((q16 & 1) << 1) | ((i16 & 3) >> 1);
+      a_off[i][e] = ((q16 >> 1) * 4 + wm * 2) * 1024 + r8 * 128 + ((piece ^ gd_swz8(r8)) << 4) + ((i16 & 1) << 3);
+    }
+  int b_off[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int row = n32 & 15;
+    b_off[ks] = L::A_BYTES + (wn * 8 + (n32 >> 4)) * 1024 + row * 64 + (((2 * ks + hi) ^ gd_swz4(row)) << 4);
+  }
+
+  struct Ops {
+    am_s16x4 a[4][2];
+    am_bf16x8 b[4];
+  };
+  // operand read u (of 12) of k-step ks of the stage at st: the first products need tile 0 of both
+  auto read_one = [&](Ops& o, const char* st, int ks, int u) {
+    const int k = u / 3, w = u % 3;
+    if (w < 2) o.a[k][w] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                   (am_lds_s16x4_t*)(st + ks * 8192 + (k >> 1) * 1024 + a_off[k & 1][w]));
+    else o.b[k] = *reinterpret_cast<const am_bf16x8*>(st + b_off[ks] + k * 2048);
+  };
+  auto product = [&](const Ops& o, int m) {
+    const int i = m >> 2, j = m & 3;
+    const am_bf16x8 a = __builtin_bit_cast(am_bf16x8, __builtin_shufflevector(o.a[i][0], o.a[i][1], 0, 1, 2, 3, 4, 5, 6, 7));
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, o.b[j], acc[i][j], 0, 0, 0);
+  };
+  auto wait_loads = [&](int ahead) {
+    switch (ahead) {
+      case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+#define EKV_WAIT(K) case K: if constexpr (K <= NS - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(K * L::LPW) : "memory"); break;
+      EKV_WAIT(1) EKV_WAIT(2) EKV_WAIT(3) EKV_WAIT(4)
+#undef EKV_WAIT
+      default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+    }
+  };
+
+  for (int s = 0; s < NS && s < nstages; ++s) {
+#pragma unroll
+    for (int u = 0; u < L::LPW; ++u) issue_one(u);
+  }
+  Ops o0, o1;
+  wait_loads(min(nstages, NS) - 1);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int u = 0; u < 12; ++u) read_one(o0, gsm, 0, u);
+  int slot_s = 0;
+  // stage s: its first k-step is in o0.  STEADY: a stage s + NS exists.
+  auto stage = [&](int s, auto steady) {
+    constexpr bool STEADY = decltype(steady)::value;
+    const char* st = gsm + slot_s * L::STAGE;
+    slot_s = (slot_s + 1 == NS) ? 0 : slot_s + 1;
+    const char* st_next = gsm + slot_s * L::STAGE;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      if (m < 6) { read_one(o1, st, 1, 2 * m); read_one(o1, st, 1, 2 * m + 1); }
+      product(o0, m);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bool more = STEADY || s + 1 < nstages, refill = STEADY || s + NS < nstages;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      if (m == 2 && more) {
+        // this wave has the whole of stage s in registers, and its loads of stage s + 1 have landed
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (STEADY) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * L::LPW) : "memory");
+        else wait_loads(min(nstages - 2 - s, NS - 2));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      if (m >= 2 && m < 8 && more) { read_one(o0, st_next, 0, 2 * m - 4); read_one(o0, st_next, 0, 2 * m - 3); }
+      if (m >= 8 && refill) issue_one(m - 8);
+      product(o1, m);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  int s = 0;
+  for (; s + NS < nstages; ++s) stage(s, std::true_type{});
+  for (; s < nstages; ++s) stage(s, std::false_type{});
+
+  __syncthreads();                            // every wave is done with the ring
+  gemm_store<4, 4>([&](int i, int j) -> const am_f32x16& { return acc[i][j]; }, gsm, wave, n0 + wm * 128, t0 + wn * 128, lane,
+                   T, pos, slot, elite_idx, ke_plane, c_plane, plane_rows, n_h, d_h, r, d_c, rope);
 }
 
 bool append_gemm_supported(const elitekv_dims& d, int64_t T, int d_ck) {
@@ -538,6 +751,29 @@ static hipError_t launch_gemm_wn(const AppendArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The XCDs as a grid of xt token groups x 8 / xt column groups, every XCD's tiles in groups of `group` token blocks, all
+// columns of a group one after the other: the 32 compute units of an XCD then hold about group x (32 / group) tiles at any
+// moment and share their rows and weights through its L2 (with one token block after the other they asked for 32 different
+// weight blocks at once, which the Infinity Cache delivers to eight XCDs at 7.5 TB/s).  Fewest rounds first, then the
+// fewest distinct blocks.
+static GemmTileMap gemm_tile_map(int64_t tblocks, int cblocks) {
+  GemmTileMap best{};
+  int64_t best_cost = INT64_MAX;
+  for (int xt = 8; xt >= 1; xt /= 2) {
+    GemmTileMap m;
+    m.xt = xt;
+    m.tb_x = (int)((tblocks + xt - 1) / xt);
+    m.cb_x = (cblocks + 8 / xt - 1) / (8 / xt);
+    m.group = m.tb_x < 6 ? m.tb_x : 6;
+    m.col_blocks = cblocks;
+    const int64_t rounds = ((int64_t)m.tb_x * m.cb_x + 31) / 32;
+    const int at_once = (32 + m.group - 1) / m.group;
+    const int64_t cost = rounds * 1000 + m.group + (m.cb_x < at_once ? m.cb_x : at_once);
+    if (cost < best_cost) { best = m; best_cost = cost; }
+  }
+  return best;
+}
+
 template <int WN, int NS, int WNW, int CM, int SPB = 1, int KG = 1>
 static hipError_t launch_gemm_dma(const AppendArgs& a, hipStream_t stream) {
   using L = GemmDmaLayout<WN, NS, WNW, CM>;
@@ -547,20 +783,34 @@ static hipError_t launch_gemm_dma(const AppendArgs& a, hipStream_t stream) {
   const hipError_t le = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&append_gemm_dma_kernel<WN, NS, WNW, CM, SPB, KG>),
                                         L::LDS_BYTES);
   if (le != hipSuccess) return le;
-  const int64_t tblocks = (a.T + L::BN - 1) / L::BN;
-  const dim3 grid((unsigned)((tblocks + 7) / 8 * 8 * (N / L::COLS)));   // token blocks padded to whole rounds of 8 XCDs
-  append_gemm_dma_kernel<WN, NS, WNW, CM, SPB, KG><<<grid, 64 * CM * WNW, L::LDS_BYTES, stream>>>(
+  const GemmTileMap m = gemm_tile_map((a.T + L::BN - 1) / L::BN, (N + L::COLS - 1) / L::COLS);
+  append_gemm_dma_kernel<WN, NS, WNW, CM, SPB, KG><<<8u * m.tb_x * m.cb_x, 64 * CM * WNW, L::LDS_BYTES, stream>>>(
       (const bf16_t*)a.x, a.pos, a.slot, a.T, (const bf16_t*)a.W_ke, (const bf16_t*)a.W_dkv,
       (const bf16_t*)a.W_dkv2, a.d_ck, a.elite_idx, (bf16_t*)a.ke_plane, (bf16_t*)a.c_plane, a.plane_rows,
       d.d_model, d.n_heads, d.head_dim, d.r, d.d_c, rope_table(d.rope_base, d.head_dim),
-      a.x_ld ? a.x_ld : (int64_t)d.d_model, a.x_off2, a.d2);
+      a.x_ld ? a.x_ld : (int64_t)d.d_model, a.x_off2, a.d2, m);
+  return hipGetLastError();
+}
+
+static hipError_t launch_gemm_wide(const AppendArgs& a, hipStream_t stream) {
+  constexpr int NS = 5;
+  using L = GemmWideLayout<NS>;
+  const elitekv_dims& d = a.dims;
+  static LdsLimit lds_limit;
+  const hipError_t le = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&append_gemm_wide_kernel<NS>), L::LDS_BYTES);
+  if (le != hipSuccess) return le;
+  const GemmTileMap m = gemm_tile_map((a.T + 255) / 256, (2 * d.r * d.n_heads + d.d_c + 255) / 256);
+  append_gemm_wide_kernel<NS><<<8u * m.tb_x * m.cb_x, 256, L::LDS_BYTES, stream>>>(
+      (const bf16_t*)a.x, a.pos, a.slot, a.T, (const bf16_t*)a.W_ke, (const bf16_t*)a.W_dkv,
+      (const bf16_t*)a.W_dkv2, a.d_ck, a.elite_idx, (bf16_t*)a.ke_plane, (bf16_t*)a.c_plane, a.plane_rows,
+      d.d_model, d.n_heads, d.head_dim, d.r, d.d_c, rope_table(d.rope_base, d.head_dim),
+      a.x_ld ? a.x_ld : (int64_t)d.d_model, a.x_off2, a.d2, m);
   return hipGetLastError();
 }
 
 hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream) {
   const elitekv_dims& d = a.dims;
   const int64_t col_blocks = (2 * d.r * d.n_heads + d.d_c) / kGmCols;
-  // the widest token tile that still gives every compute unit work
   const int split = 2 * d.r * d.n_heads + a.d_ck;              // first column of W_dkv2
   if (a.d2 > 0 || a.x_ld > 0) {
     // column slices of wider rows: only the direct-load kernels take them, with whole stages in both slices
@@ -570,19 +820,31 @@ hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream) {
   }
   if (d.d_model % kGdStage == 0) {
     const int N = 2 * d.r * d.n_heads + d.d_c;
-    // 256 x 256 tiles, one work-group per compute unit: a third fewer operand bytes per flop, 13 % faster
-    // than 256 x 128 whenever its work-groups fill the 256 compute units evenly -- one full round, or
-    // enough rounds that the ragged last one costs less than that (measured: slower at 260-320
-    // work-groups and at 128, faster at 224-256 and from 360 on)
-    const int64_t wide = N % 256 == 0 && (a.d2 == 0 || split % 256 == 0) ? (N / 256) * ((a.T + 255) / 256) : 0;
-    if (wide >= 352 || (wide >= 224 && wide <= 256)) return launch_gemm_dma<4, 4, 2, 4>(a, stream);
-    if (col_blocks * ((a.T + 255) / 256) >= 512) return launch_gemm_dma<2, 6, 4, 2>(a, stream);
-    // 128 x 128 tiles: with about one work-group per compute unit eight waves (two per SIMD, 32 tokens x 64
-    // columns each) hide a little more of the stage latency than four (595 against 549 TFLOP/s at 2048 tokens
-    // x 2048 columns; two ring stages per barrier: 626; the waves as two contraction groups: 688); with more rounds the four-wave form and its larger share of the tile per wave is kept
-    const int64_t wgs128 = col_blocks * ((a.T + 127) / 128);
-    if (wgs128 >= 256 && wgs128 <= 384) return launch_gemm_dma<1, 6, 4, 2, 2, 2>(a, stream);
-    if (wgs128 >= 256) return launch_gemm_dma<2, 4, 2, 2>(a, stream);
+    const double K = a.d2 > d.d_model ? a.d2 : d.d_model;
+    // The tile whose rounds of work-groups cost least.  A round's cost in us, fixed part (first stages from cold memory,
+    // epilogue) + contraction rows, fitted to measurements from 1000 to 32768 tokens, 768 to 5120 rows, 1024 to 9600 columns:
+    //   tokens x columns     work-groups at once     a round        measured, 1536 x 7680 rows x columns, 1000 / 2048 / 8192 tokens
+    //   256 x 256, 4 waves   256                     20 + 0.021 K   51 / 62 / 208 us
+    //   256 x 256, 8 waves   256                     13 + 0.025 K   51 / 61 / 211
+    //   256 x 128            256                     10 + 0.0145 K  35 / 66 / 232
+    //   128 x 128            256                     1.5 + 0.0118 K 39 / 78 / 270
+    //    64 x 128            512                     3 + 0.0128 K   41 / 82 / 296
+    // (4096 x 2048: 99 / 115 / 73 / 50 / 56 at 2048 tokens, 493 / 521 / 620 / 727 / 815 at 32768.)
+    auto cost = [&](int tokens, int cols, int slots, double fixed, double per_row) {
+      const GemmTileMap m = gemm_tile_map((a.T + tokens - 1) / tokens, (N + cols - 1) / cols);
+      const int64_t per_xcd = (int64_t)m.tb_x * m.cb_x;
+      return (double)((per_xcd + slots / 8 - 1) / (slots / 8)) * (fixed + per_row * K);
+    };
+    const bool wide_ok = N >= 256 && (a.d2 == 0 || (N % 256 == 0 && split % 256 == 0));
+    const double c[5] = {wide_ok ? cost(256, 256, 256, 20., .021) : 1e30, wide_ok ? cost(256, 256, 256, 13., .025) : 1e30,
+                         cost(256, 128, 256, 10., .0145), cost(128, 128, 256, 1.5, .0118), cost(64, 128, 512, 3., .0128)};
+    int best = 4;                                              // of equal costs the smaller tile
+    for (int i = 3; i >= 0; --i)
+      if (c[i] < c[best]) best = i;
+    if (best == 0) return launch_gemm_wide(a, stream);
+    if (best == 1) return launch_gemm_dma<4, 4, 2, 4>(a, stream);
+    if (best == 2) return launch_gemm_dma<2, 6, 4, 2>(a, stream);
+    if (best == 3) return launch_gemm_dma<1, 6, 4, 2, 2, 2>(a, stream);
     return launch_gemm_dma<1, 6, 2, 2>(a, stream);
   }
   if (col_blocks * ((a.T + 255) / 256) >= 1024) return launch_gemm_wn<4>(a, stream);
