@@ -443,6 +443,10 @@ static int step_impl(const elitekv_dims* dims, int32_t d_ck, const void* x, cons
     e = launch_decode_front_mfma(ap, a, p, stream);
     a.stages = 6;
     if (e == hipSuccess) e = launch_decode_mfma(a, p, stream);
+  } else if (front_tiled_supported(ap, a, p)) {
+    e = launch_front_tiled(ap, a, p, stream);
+    a.stages = 6;
+    if (e == hipSuccess) e = launch_decode_tiled(a, p, stream);
   } else {
     e = append_dispatch(ap, stream);
     if (e == hipSuccess) e = decode_dispatch(a, p, stream);

@@ -143,6 +143,8 @@ bool append_tiled_supported(const elitekv_dims& d, int64_t T, int d_ck);
 hipError_t launch_append_tiled(const AppendArgs& a, hipStream_t stream);
 bool decode_tiled_supported(const elitekv_dims& d, int d_ck);
 hipError_t launch_decode_tiled(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
+bool front_tiled_supported(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p);
+hipError_t launch_front_tiled(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 hipError_t launch_decode_generic(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 bool decode_mfma_supported(const elitekv_dims& d, int d_ck);
 int decode_mfma_groups_per_cu(const elitekv_dims& d);

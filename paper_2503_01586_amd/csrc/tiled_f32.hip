@@ -29,19 +29,17 @@ __device__ __forceinline__ tf_f32x4 ld4(const bf16_t* p) {
 constexpr int kTaThreads = 1024, kTaCols = 16;
 
 template <typename T, int TT>
-__global__ __launch_bounds__(kTaThreads) void append_tiled_kernel(
-    const T* __restrict__ x, const int32_t* __restrict__ pos, const int64_t* __restrict__ slot, int64_t T_tokens,
-    const T* __restrict__ W_ke, const T* __restrict__ W_dkv, const T* __restrict__ W_dkv2, int d_ck,
-    const int32_t* __restrict__ elite_idx, T* __restrict__ ke_plane, T* __restrict__ c_plane, int64_t plane_rows,
-    int d, int n_h, int d_h, int r, int d_c, RopeTable rope) {
+__device__ __forceinline__ void append_tiled_body(
+    int slice, int n_slices, int64_t t0, const T* __restrict__ x, const int32_t* __restrict__ pos,
+    const int64_t* __restrict__ slot, int64_t T_tokens, const T* __restrict__ W_ke, const T* __restrict__ W_dkv,
+    const T* __restrict__ W_dkv2, int d_ck, const int32_t* __restrict__ elite_idx, T* __restrict__ ke_plane,
+    T* __restrict__ c_plane, int64_t plane_rows, int d, int n_h, int d_h, int r, int d_c, const RopeTable& rope) {
   __shared__ float red[kTaThreads / 64][TT][kTaCols];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int NE = 2 * r * n_h;
   // neighbouring slices share 128-byte lines of the weights: both on one XCD (linear index modulo 8) where they pair up
-  int slice = blockIdx.x;
-  if ((gridDim.x & 15) == 0) slice = 2 * (8 * (slice >> 4) + (slice & 7)) + ((slice >> 3) & 1);
+  if ((n_slices & 15) == 0) slice = 2 * (8 * (slice >> 4) + (slice & 7)) + ((slice >> 3) & 1);
   const int n0 = slice * kTaCols;
-  const int64_t t0 = (int64_t)blockIdx.y * TT;
   const T* w;
   int64_t wstride;
   weight_column(n0, NE, d_ck, d_c, W_ke, W_dkv, W_dkv2, &w, &wstride);
@@ -96,6 +94,16 @@ __global__ __launch_bounds__(kTaThreads) void append_tiled_kernel(
   }
 }
 
+template <typename T, int TT>
+__global__ __launch_bounds__(kTaThreads) void append_tiled_kernel(
+    const T* __restrict__ x, const int32_t* __restrict__ pos, const int64_t* __restrict__ slot, int64_t T_tokens,
+    const T* __restrict__ W_ke, const T* __restrict__ W_dkv, const T* __restrict__ W_dkv2, int d_ck,
+    const int32_t* __restrict__ elite_idx, T* __restrict__ ke_plane, T* __restrict__ c_plane, int64_t plane_rows,
+    int d, int n_h, int d_h, int r, int d_c, RopeTable rope) {
+  append_tiled_body<T, TT>(blockIdx.x, gridDim.x, (int64_t)blockIdx.y * TT, x, pos, slot, T_tokens, W_ke, W_dkv, W_dkv2, d_ck,
+                           elite_idx, ke_plane, c_plane, plane_rows, d, n_h, d_h, r, d_c, rope);
+}
+
 // Up to kTaMaxTokens tokens: every tile of eight tokens reads the weights again (from the Infinity Cache), which the
 // serial kernel does too, but more slowly.  Measured (7B 25 %, fp32, us, this kernel / append_generic_kernel): 
 // 8 tokens 18 / 560, 64: 64, 128: 124, 256: 244 / about 420, 512: about 490 / 418.
@@ -128,31 +136,29 @@ hipError_t launch_append_tiled(const AppendArgs& a, hipStream_t stream) {
 }
 
 // ---- query preparation ----
-// Work-group = (64 latent columns, head, up to BT query rows): eight lanes read one W_uk row of the head together
+// Work-group = (NT / 4 latent columns, head, up to BT query rows): eight lanes read one W_uk row of the head together
 // (16 bytes each), so W_uk is read once per BT rows; bound by its bytes.  
 // Two rows, 7B 25 %: 10.8 us for 22 MB (qprep_generic_kernel 44.5).
-constexpr int kTqRows = 64;
-
-template <typename T, int BT>
-__global__ __launch_bounds__(256) void qprep_tiled_kernel(const T* __restrict__ q, const int32_t* __restrict__ q_pos,
-                                                          const T* __restrict__ W_uk,
-                                                          const int32_t* __restrict__ elite_idx, float* __restrict__ qe,
-                                                          float* __restrict__ qt, int B, int n_h, int d_h, int r, int d_q,
-                                                          RopeTable rope, float scale_log2e) {
+template <typename T, int BT, int NT>
+__device__ __forceinline__ void qprep_tiled_body(int kb, int h, int b0, const T* __restrict__ q,
+                                                 const int32_t* __restrict__ q_pos, const T* __restrict__ W_uk,
+                                                 const int32_t* __restrict__ elite_idx, float* __restrict__ qe,
+                                                 float* __restrict__ qt, int B, int n_h, int d_h, int r, int d_q,
+                                                 const RopeTable& rope, float scale_log2e) {
   __shared__ __align__(16) float q_ne[BT][256];     // d_h <= 256 checked on the host
   __shared__ unsigned long long elite[2];
-  const int tid = threadIdx.x, h = blockIdx.y, b0 = blockIdx.z * BT;
+  const int tid = threadIdx.x;
   const int nd = d_h - 2 * r, half = d_h / 2;
   if (tid < 2) elite[tid] = 0ull;
-  for (int e = tid; e < BT * 256; e += 256) q_ne[e >> 8][e & 255] = 0.f;
+  for (int e = tid; e < BT * 256; e += NT) q_ne[e >> 8][e & 255] = 0.f;
   __syncthreads();
-  for (int j = tid; j < r; j += 256) {
+  for (int j = tid; j < r; j += NT) {
     const int i = elite_idx[h * r + j];
     if (i >= 0 && i < half) atomicOr(&elite[i >> 6], 1ull << (i & 63));
   }
   __syncthreads();
   const unsigned long long e0 = elite[0], e1 = elite[1];
-  for (int e = tid; e < BT * half; e += 256) {
+  for (int e = tid; e < BT * half; e += NT) {
     const int bt = e / half, i = e % half;
     if (((i < 64 ? e0 : e1) >> (i & 63)) & 1ull) continue;
     // non-elite chunks keep their order: the chunk's place is the number of non-elite ones before it
@@ -163,8 +169,8 @@ __global__ __launch_bounds__(256) void qprep_tiled_kernel(const T* __restrict__ 
     q_ne[bt][2 * before] = ld(qrow, 2 * i) * scale_log2e;
     q_ne[bt][2 * before + 1] = ld(qrow, 2 * i + 1) * scale_log2e;
   }
-  if (blockIdx.x == 0) {
-    for (int e = tid; e < BT * r; e += 256) {
+  if (kb == 0) {
+    for (int e = tid; e < BT * r; e += NT) {
       const int b = b0 + e / r, j = e % r;
       if (b >= B) continue;
       int i = elite_idx[h * r + j];
@@ -181,8 +187,8 @@ __global__ __launch_bounds__(256) void qprep_tiled_kernel(const T* __restrict__ 
   __syncthreads();
   const int sub = tid & 7;
 #pragma unroll
-  for (int p = 0; p < kTqRows / 32; ++p) {
-    const int k = blockIdx.x * kTqRows + p * 32 + (tid >> 3);
+  for (int p = 0; p < 2; ++p) {
+    const int k = kb * (NT / 4) + p * (NT / 8) + (tid >> 3);
     float acc[BT];
 #pragma unroll
     for (int b = 0; b < BT; ++b) acc[b] = 0.f;
@@ -205,6 +211,41 @@ __global__ __launch_bounds__(256) void qprep_tiled_kernel(const T* __restrict__ 
       a += __shfl_xor(a, 4, kWave);
       if (sub == 0 && k < d_q && b0 + b < B) qt[((int64_t)(b0 + b) * n_h + h) * d_q + k] = a;
     }
+  }
+}
+
+template <typename T, int BT>
+__global__ __launch_bounds__(256) void qprep_tiled_kernel(const T* __restrict__ q, const int32_t* __restrict__ q_pos,
+                                                          const T* __restrict__ W_uk,
+                                                          const int32_t* __restrict__ elite_idx, float* __restrict__ qe,
+                                                          float* __restrict__ qt, int B, int n_h, int d_h, int r, int d_q,
+                                                          RopeTable rope, float scale_log2e) {
+  qprep_tiled_body<T, BT, 256>(blockIdx.x, blockIdx.y, blockIdx.z * BT, q, q_pos, W_uk, elite_idx, qe, qt, B, n_h, d_h, r,
+                               d_q, rope, scale_log2e);
+}
+
+// The first launch of a decode step of up to eight sequences: append and query preparation do not depend on each other and
+// are one grid, the append's work-groups first (both kinds 1024 threads).
+// Two sequences, 7B 25 %, fp32: 19.8 us (one after the other 18.7 + 10.8 and a launch gap; the step 66.2 -> 55.9).
+struct TiledFrontArgs {
+  int64_t plane_rows;
+  int B, d, n_h, d_h, r, d_c, d_ck, d_q, n_slices, q_blocks;
+  float scale_log2e;
+};
+template <typename T, int BT>
+__global__ __launch_bounds__(kTaThreads) void front_tiled_kernel(
+    const T* __restrict__ x, const T* __restrict__ q, const int32_t* __restrict__ pos, const int64_t* __restrict__ slot,
+    const T* __restrict__ W_ke, const T* __restrict__ W_dkv, const T* __restrict__ W_dkv2, const T* __restrict__ W_uk,
+    const int32_t* __restrict__ elite_idx, T* __restrict__ ke_plane, T* __restrict__ c_plane, float* __restrict__ qe,
+    float* __restrict__ qt, TiledFrontArgs A, RopeTable rope) {
+  const int wg = blockIdx.x;
+  if (wg < A.n_slices) {
+    append_tiled_body<T, BT>(wg, A.n_slices, 0, x, pos, slot, A.B, W_ke, W_dkv, W_dkv2, A.d_ck, elite_idx, ke_plane, c_plane,
+                             A.plane_rows, A.d, A.n_h, A.d_h, A.r, A.d_c, rope);
+  } else {
+    const int i = wg - A.n_slices;
+    qprep_tiled_body<T, BT, kTaThreads>(i % A.q_blocks, i / A.q_blocks, 0, q, pos, W_uk, elite_idx, qe, qt, A.B, A.n_h,
+                                        A.d_h, A.r, A.d_q, rope, A.scale_log2e);
   }
 }
 
@@ -500,7 +541,7 @@ static hipError_t launch_decode_tiled_t(const DecodeArgs& a, const DecodePlan& p
   hipError_t e = hipSuccess;
   if (a.stages & 1) {
 #define EKV_QPREP(BT)                                                                                               \
-  qprep_tiled_kernel<T, BT><<<dim3((p.d_q + kTqRows - 1) / kTqRows, n_h, (B + BT - 1) / BT), 256, 0, stream>>>(      \
+  qprep_tiled_kernel<T, BT><<<dim3((p.d_q + 63) / 64, n_h, (B + BT - 1) / BT), 256, 0, stream>>>(      \
       (const T*)a.q, a.q_pos, (const T*)a.W_uk, a.elite_idx, qe, qt, B, n_h, d_h, d.r, p.d_q,                       \
       rope_table(d.rope_base, d_h), kLog2e / sqrtf((float)d_h))
     if (B == 1) EKV_QPREP(1);
@@ -537,6 +578,28 @@ static hipError_t launch_decode_tiled_t(const DecodeArgs& a, const DecodePlan& p
     else EKV_UP(4)
 #undef EKV_UP
   }
+  return hipGetLastError();
+}
+
+// (fp32 only: bf16 shapes of this path may have a faster append of their own)
+bool front_tiled_supported(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p) {
+  return p.tiled && a.dims.dtype == ELITEKV_FP32 && a.B <= 8 && append_tiled_supported(a.dims, a.B, ap.d_ck);
+}
+
+hipError_t launch_front_tiled(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p, hipStream_t stream) {
+  using T = float;
+  const elitekv_dims& d = a.dims;
+  TiledFrontArgs A;
+  A.plane_rows = ap.plane_rows; A.B = (int)a.B; A.d = d.d_model; A.n_h = d.n_heads; A.d_h = d.head_dim; A.r = d.r;
+  A.d_c = d.d_c; A.d_ck = ap.d_ck; A.d_q = p.d_q; A.n_slices = (2 * d.r * d.n_heads + d.d_c) / kTaCols;
+  A.q_blocks = (p.d_q + kTaThreads / 4 - 1) / (kTaThreads / 4);
+  A.scale_log2e = kLog2e / sqrtf((float)d.head_dim);
+#define EKV_FRONT(BT)                                                                                                       front_tiled_kernel<T, BT><<<A.n_slices + A.q_blocks * d.n_heads, kTaThreads, 0, stream>>>(                                   (const T*)ap.x, (const T*)a.q, a.q_pos, ap.slot, (const T*)ap.W_ke, (const T*)ap.W_dkv, (const T*)ap.W_dkv2,              (const T*)a.W_uk, a.elite_idx, (T*)ap.ke_plane, (T*)ap.c_plane, (float*)(a.ws + p.off_qe),                                (float*)(a.ws + p.off_qt), A, rope_table(d.rope_base, d.head_dim))
+  if (a.B == 1) EKV_FRONT(1);
+  else if (a.B == 2) EKV_FRONT(2);
+  else if (a.B <= 4) EKV_FRONT(4);
+  else EKV_FRONT(8);
+#undef EKV_FRONT
   return hipGetLastError();
 }
 

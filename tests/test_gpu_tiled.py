@@ -117,3 +117,30 @@ def test_scratch_limit_takes_the_plan_that_fits():
     ref = orc.decode_attn(host64(q), [S - 1], host64(ke)[None], host64(c)[None], [S], host64(W_uk), host64(W_uv), idx, 128,
                           10000.0)
     assert orc.max_abs_rel(host64(out), ref) <= TOL["fp32"]
+
+
+@pytest.mark.parametrize("B", [1, 2, 3, 5, 8, 9])           # front launches of 1, 2, 4 and 8 rows; two launches beyond 8
+@pytest.mark.parametrize("name", ["seventeen_blocks_17_heads", "all_elite", "7b"])
+def test_tiled_step_matches_oracle(name, B):
+    d, n_h, d_h, r, _, d_c, dt, _ = CASES[name]
+    dims = ekv.make_dims(d, n_h, d_h, r, d_c, dt)
+    rng, idx, _, t = _draw(name)
+    lens = [1 + (37 * b) % 50 for b in range(B)]
+    S, stride = max(lens), max(lens) + 2
+    n = lambda *s: dev(rng.standard_normal(s), dt)
+    x, q, ke, c = n(B, d), n(B, n_h, d_h), n(B * stride, n_h, 2 * r), n(B * stride, d_c)
+    pos, slot = np.array(lens) - 1, np.arange(B) * stride + np.array(lens) - 1
+    h = {k: host64(v) for k, v in t.items()}
+    ke_r, c_r = orc.append(host64(x), pos, h["W_ke"], h["W_d"], idx, d_h, 10000.0)
+    ke_all, c_all = host64(ke), host64(c)
+    ke_all[slot], c_all[slot] = ke_r, c_r
+    ref = orc.decode_attn(host64(q), pos, ke_all.reshape(B, stride, n_h, 2 * r), c_all.reshape(B, stride, d_c), lens, h["W_uk"],
+                          h["W_uv"], idx, d_h, 10000.0)
+    out = torch.full((B, n_h, d_h), float("nan"), dtype=x.dtype, device=DEV)
+    ws = torch.full((ekv.elitekv_decode_step_workspace_bytes(dims, B, S),), 0xFF, dtype=torch.uint8, device=DEV)
+    ke[i64(slot)], c[i64(slot)] = float("nan"), float("nan")        # the step writes the new rows before it reads them
+    ekv.elitekv_decode_step(dims, x, q, i32(pos), i64(slot), i32(lens), S, stride, t["W_ke"], t["W_d"], t["W_uk"], t["W_uv"],
+                            i32(idx), ke, c, out, ws)
+    torch.cuda.synchronize()
+    assert orc.max_abs_rel(host64(c), c_all) <= TOL[dt] and (r == 0 or orc.max_abs_rel(host64(ke), ke_all) <= TOL[dt])
+    assert orc.max_abs_rel(host64(out), ref) <= TOL[dt]
