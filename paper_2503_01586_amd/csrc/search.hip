@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void search_pack_kernel(const float* __restric
 
 // Key tiles per work-group (a power of two, at least one per wave) and the work-groups ("items") per head: 32-query block Q
 // has 2 Q + 2 key tiles, cut into pieces of that many.  A search's launches have about a thousand work-groups (two to four
-// rounds of the chip: 512 / 1024 / 2048 / 4096 wanted: 1103 / 1060 / 1145 / 1233 us at 1000 tokens of 32 heads, 205 / 235 /
+// rounds of the chip: 512 / 1024 / 2048 / 4096 wanted: 1103 / 1060 / 1145 / 1233 us (before the products were grouped) at 1000 tokens of 32 heads, 205 / 235 /
 // 235 / 235 at 300), and a head at most about a thousand, since one work-group adds up their distances.
 inline int sr_keys_per_item(int64_t n_q32, int64_t n_h) {
   int k = 4;
@@ -114,20 +114,23 @@ __device__ __forceinline__ void sr_distances(const sr_f32x4 (*A)[64], int lane, 
 #pragma unroll
   for (int c4 = 0; c4 <= kSrMaxChunks / 4; ++c4) {
     if (c4 + 1 < kSrMaxChunks / 4) a4_next = A[c4 + 1][lane];
+    if (c4 < kSrMaxChunks / 4) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (c4 < kSrMaxChunks / 4)
+      for (int u = 0; u < 4; ++u)
         D[c4 & 1][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[u], B[4 * c4 + u], FUSED ? R : (sr_f32x4)(0.f), 0, 0, 0);
-      // the order as written: the vector unit adds up one product while the matrix core makes another (left alone, the
-      // compiler groups them, and sinks the additions behind the next branch, with 64 products kept for them)
-      __builtin_amdgcn_sched_barrier(0);
-      if (c4 > 0) {
-        float& a = acc[4 * c4 - 4 + u];
+    }
+    // the order as written: left alone, the compiler sinks the additions behind the next branch, with 64 products kept
+    __builtin_amdgcn_sched_barrier(0);
+    if (c4 > 0) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) a = fmaf(w[v], fabsf(FUSED ? D[(c4 - 1) & 1][u][v] : R[v] + D[(c4 - 1) & 1][u][v]), a);
-        asm volatile("" : "+v"(a));
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float& a = acc[4 * c4 - 4 + u];
+          a = fmaf(w[v], fabsf(FUSED ? D[(c4 - 1) & 1][u][v] : R[v] + D[(c4 - 1) & 1][u][v]), a);
+          if (v == 3) asm volatile("" : "+v"(a));
+        }
+      __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (PREFETCH) {
       if (c4 < kSrMaxChunks / 4) {
@@ -147,7 +150,7 @@ __device__ __forceinline__ void sr_distances(const sr_f32x4 (*A)[64], int lane, 
 // (lane l of a result tile holds queries 4 (l / 16) + v, v < 4, against key l % 16).  Chunks in E are computed like the
 // others and ignored by the choice.  Bound by the fp32 matrix cores: 64 instructions of 32 cycles per tile of 256 pairs.
 // Before (the residual summed again in every round, subtraction and weights on the vector units, 16 queries per
-// work-group) a round of 1000 tokens, 32 heads took 302 us and a launch of 6 us for the choice; now 130.
+// work-group) a round of 1000 tokens, 32 heads took 302 us and a launch of 6 us for the choice; now 127.
 // The product and the additions of its four absolute values do not overlap on a SIMD (measured apart: 13.9 ns a product,
 // 2 ns an addition, 25 ns for one product and four additions), which leaves 60 % of the measured time for the instructions.
 template <bool LOAD, bool FUSED>
