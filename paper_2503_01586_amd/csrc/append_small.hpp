@@ -6,6 +6,7 @@
 // The body is a device function: it is the whole of append_small_kernel and one of the two roles of
 // the decode step's front kernel.
 #pragma once
+#include "chunk_sum.hpp"
 #include "common.hpp"
 
 namespace ekv {
@@ -30,6 +31,10 @@ struct AppendSmallParams {
   // up-projection, x[t, h d_h + j] = bf16(sum_c x_opart[t, h, c, j])  (what out_reduce would store)
   const float* x_opart;
   int x_heads, x_chunks, x_dh;
+  // XS = 1 only: the sum of the contraction splits, by the last work-group of a column block to arrive, as bf16 rows [T, N]
+  bf16_t* dense_out;
+  int* arrived;           // [column blocks], zero when the launch starts
+  int n_splits;
 };
 
 // Work-group (bx, by, bz) = (column block, contraction split, token tile); TT = tokens per pass,
@@ -164,7 +169,28 @@ __device__ __forceinline__ void append_small_body(const AppendSmallParams& P, in
     if (t < T) {
       const float v = red[0][c >> 3][tt][c & 7] + red[1][c >> 3][tt][c & 7] + red[2][c >> 3][tt][c & 7] +
                       red[3][c >> 3][tt][c & 7];
-      partial[((int64_t)by * T + t) * N + n0 + c] = v;
+      float* dst = partial + ((int64_t)by * T + t) * N + n0 + c;
+      if constexpr (XS == 1) store_partial_device_scope(dst, v);
+      else *dst = v;
+    }
+  }
+  if constexpr (XS == 1) {
+    // device-scope stores, acknowledged before the count; the splits are added in their order, whoever is last
+    __shared__ int last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0)
+      last = __hip_atomic_fetch_add(P.arrived + bx, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == P.n_splits - 1;
+    __syncthreads();
+    if (!last) return;
+    for (int e = tid; e < TT * kAsCols; e += kAsThreads) {
+      const int64_t t = t0 + e / kAsCols, o = t * N + n0 + e % kAsCols;
+      if (t >= T) continue;
+      float a = 0.f;
+#pragma unroll 8
+      for (int sp = 0; sp < P.n_splits; ++sp)
+        a += __hip_atomic_load(partial + (int64_t)sp * T * N + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      st(P.dense_out, o, a);
     }
   }
 }
