@@ -199,7 +199,7 @@ int elitekv_decode_attn_noalloc(const elitekv_dims* dims, const void* q, const i
  *   dist_out  [n_heads, r] float32, device, or NULL: the winning distance of every round
  * Arithmetic is fp32 (angles reduced in double); a near-tie between two chunks may resolve
  * differently from exact arithmetic.  head_dim <= 128.  Workspace: the _workspace_bytes function.
- * Enqueues 2 r + 2 kernels on hip_stream; no host synchronisation.
+ * Enqueues r + 1 kernels on hip_stream; no host synchronisation.
  * ------------------------------------------------------------------------------------------- */
 size_t elitekv_ropelite_search_workspace_bytes(int64_t T, int32_t n_heads, int32_t head_dim, int32_t r);
 int elitekv_ropelite_search(const float* q, const float* k, const int32_t* pos, int64_t T, int32_t n_heads,
@@ -372,11 +372,11 @@ int elitekv_decode_step(const elitekv_dims* dims, const void* x, const void* q, 
  *   W_o   [n_h, d_h, d_model]      dims->dtype
  *   y     [B, d_model]             written, dims->dtype
  *   the other arguments as in elitekv_decode_step; ws: elitekv_block_step_workspace_bytes bytes.
- * Fewer than eight sequences (bf16 shapes of the matrix-core path): seven launches -- the first pass of
+ * Fewer than eight sequences (bf16 shapes of the matrix-core path): six launches -- the first pass of
  * the append and of x W_q in one weight-streaming launch; the sum of the query's contraction splits; the
  * query preparation; the attention, which also finishes and stores the new rows; the merge with the
- * up-projection; out W_o read straight from the merge's column-chunk partials; the sum of its
- * contraction splits.  Eight to 64 sequences, and bf16 shapes outside the matrix-core path: the composed
+ * up-projection; out W_o read straight from the merge's column-chunk partials, its contraction splits
+ * added by the last work-group of a column block.  Eight to 64 sequences, and bf16 shapes outside the matrix-core path: the composed
  * form -- q = x W_q and y = out W_o as weight-streaming launches of their own around the kernels of
  * elitekv_decode_step, q and out (rounded to dims->dtype) staying in the workspace.
  * EUNSUPPORTED unless bf16, B <= 64 and d_model and n_h d_h are multiples of 64; other errors as

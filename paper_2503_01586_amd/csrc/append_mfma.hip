@@ -829,6 +829,7 @@ hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream) {
     //   256 x 128            256                     10 + 0.0145 K  35 / 66 / 232
     //   128 x 128            256                     1.5 + 0.0118 K 39 / 78 / 270
     //    64 x 128            512                     3 + 0.0128 K   41 / 82 / 296
+    //                        256 (alone on its unit) 3 + 0.0095 K   42 against 47 us of 128 x 128, 4096 x 1024, 2048 tokens
     // (4096 x 2048: 99 / 115 / 73 / 50 / 56 at 2048 tokens, 493 / 521 / 620 / 727 / 815 at 32768.)
     auto cost = [&](int tokens, int cols, int slots, double fixed, double per_row) {
       const GemmTileMap m = gemm_tile_map((a.T + tokens - 1) / tokens, (N + cols - 1) / cols);
@@ -837,7 +838,8 @@ hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream) {
     };
     const bool wide_ok = N >= 256 && (a.d2 == 0 || (N % 256 == 0 && split % 256 == 0));
     const double c[5] = {wide_ok ? cost(256, 256, 256, 20., .021) : 1e30, wide_ok ? cost(256, 256, 256, 13., .025) : 1e30,
-                         cost(256, 128, 256, 10., .0145), cost(128, 128, 256, 1.5, .0118), cost(64, 128, 512, 3., .0128)};
+                         cost(256, 128, 256, 10., .0145), cost(128, 128, 256, 1.5, .0118),
+                         col_blocks * ((a.T + 63) / 64) <= 256 ? cost(64, 128, 256, 3., .0095) : cost(64, 128, 512, 3., .0128)};
     int best = 4;                                              // of equal costs the smaller tile
     for (int i = 3; i >= 0; --i)
       if (c[i] < c[best]) best = i;
