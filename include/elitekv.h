@@ -120,7 +120,9 @@ int elitekv_decode_path(const elitekv_dims* dims, int32_t d_ck);
  * Returns <= 0 on bad dims. */
 int32_t elitekv_decode_auto_splits(const elitekv_dims* dims, int64_t B, int64_t max_seq_len);
 
-/* Workspace (device bytes) elitekv_decode_attn needs.  n_splits == 0 means "auto". 0 on bad dims. */
+/* Workspace (device bytes) for elitekv_decode_attn.  n_splits == 0 means "auto". 0 on bad dims.
+ * For a given B this size, and that of every decode entry point below, never falls as max_seq_len grows: a workspace
+ * allocated for the longest bound serves every shorter one. */
 size_t elitekv_decode_workspace_bytes(const elitekv_dims* dims, int64_t B, int64_t max_seq_len,
                                       int32_t n_splits);
 

@@ -58,7 +58,13 @@ static int32_t auto_splits_generic(const elitekv_dims* d, int64_t B, int64_t max
 // Rounding the split count UP to fill every slot started a second round for the last few work-groups: 260 of them for
 // 4 sequences x 5 drafted tokens (7B 25 %, 4096 tokens): 92.9 us, 240 (twelve splits): 55.9 us; 258 for three sequences of 5001
 // tokens, separated latents: 23.5 us, 237: 16.5 us.  Of equal counts the smallest (fewest partials to merge).
-static int64_t balanced_splits(int64_t groups, int64_t tiles, int64_t slots) {
+// *most: no count for as many tiles or fewer is larger.  The count itself falls wherever equal shares take fewer splits, so
+// the size functions answer with *most: a workspace sized for a longer bound serves every shorter one.
+static int64_t balanced_splits(int64_t groups, int64_t tiles, int64_t slots, int64_t* most) {
+  *most = slots / groups;
+  if (*most > tiles) *most = tiles;
+  if (*most > kMaxSplits) *most = kMaxSplits;
+  if (*most < 1) *most = 1;
   int64_t best = 1, best_cost = INT64_MAX;
   for (int64_t rounds = 1; rounds <= 2; ++rounds) {
     int64_t ns = rounds == 1 ? slots / groups : (slots + groups - 1) / groups;
@@ -92,6 +98,16 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
   p->d_q = d_ck > 0 ? d_ck : d->d_c;
   p->d_u = d_ck > 0 ? d->d_c - d_ck : d->d_c;
   const size_t dq = p->d_q, du = p->d_u;
+  // the split maxima, sums and accumulators of `rows` heads per batch row and split; spare: what `most` splits would add
+  size_t spare = 0;
+  auto lay_partials = [&](size_t at, int64_t splits, int64_t most, size_t rows, size_t row_bytes) {
+    auto bytes = [&](int64_t n, size_t each) { return align_up(Bz * (size_t)n * rows * each, 256); };
+    p->off_m = at;
+    p->off_l = p->off_m + bytes(splits, sizeof(float));
+    p->off_u = p->off_l + bytes(splits, sizeof(float));
+    spare = 2 * (bytes(most, sizeof(float)) - bytes(splits, sizeof(float))) + bytes(most, row_bytes) - bytes(splits, row_bytes);
+    return p->off_u + bytes(splits, row_bytes);
+  };
   size_t off = 0;
   p->off_qe = off; off = align_up(off + Bz * nh * 2 * d->r * sizeof(float), 256);
   if (decode_mfma_supported(*d, d_ck)) {
@@ -112,24 +128,21 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
       p->fr_ks = ks; p->fr_kc = kc; p->y_ks = yks; p->y_kc = ykc;
       p->fr_stride += d->n_heads * d->head_dim;            // x W_q is computed alongside the cache row
     }
-    int64_t ns = n_splits;
+    int64_t ns = n_splits, most = n_splits;
     if (ns == 0) {
       // the narrow-latent instantiations run two work-groups per compute unit; with many batch rows
       // it pays to give every compute unit two (more splits also mean more partials to merge)
       const int64_t slots = (decode_mfma_groups_per_cu(*d) == 2 && Bq * p->head_groups >= 16) ? 2 * kComputeUnits
                                                                                              : kComputeUnits;
-      ns = balanced_splits(Bq * p->head_groups, (seq + 15) / 16, slots);
+      ns = balanced_splits(Bq * p->head_groups, (seq + 15) / 16, slots, &most);
     }
     p->n_splits = (int32_t)ns;
     p->n_part = (int32_t)ns;
     int64_t chunk = (seq + ns - 1) / ns;
     chunk = (chunk + 31) / 32 * 32;
     p->chunk = (int32_t)chunk;
-    const size_t np = Bz * (size_t)p->n_part * p->head_groups;
     p->off_qt = off; off = align_up(off + Bz * (size_t)p->head_groups * 32 * dq * 2, 256);   // head groups padded to 32
-    p->off_m = off;  off = align_up(off + np * 32 * sizeof(float), 256);
-    p->off_l = off;  off = align_up(off + np * 32 * sizeof(float), 256);
-    p->off_u = off;  off = align_up(off + np * 32 * du * 2, 256);
+    off = lay_partials(off, ns, most, p->head_groups * 32, du * 2);
     p->merge_batch = merge_mfma_supported(*d, p->d_u, B, p->n_part) ? 1 : 0;
     p->up_cw = p->merge_batch ? 128 : (p->d_u % 192 == 0) ? 192 : 64;
     p->off_opart = off;
@@ -153,22 +166,21 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     p->mfma = 0;
     p->head_groups = 1;
     p->tiled = tiled && decode_tiled_supported(*d, d_ck);
-    p->n_splits = n_splits > 0 ? n_splits
-                  : p->tiled   ? (int32_t)balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits)
-                               : auto_splits_generic(d, Bq, seq);
+    int64_t ns = n_splits, most = n_splits;
+    if (ns == 0 && p->tiled) ns = balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits, &most);
+    else if (ns == 0) ns = most = auto_splits_generic(d, Bq, seq);
+    p->n_splits = (int32_t)ns;
     p->n_part = p->n_splits;
     int64_t chunk = (seq + p->n_splits - 1) / p->n_splits;
     if (chunk < 1) chunk = 1;
     p->chunk = (int32_t)chunk;
-    const size_t ns = p->n_splits;
     p->off_qt = off; off = align_up(off + Bz * nh * dq * sizeof(float), 256);
-    p->off_m = off;  off = align_up(off + Bz * ns * nh * sizeof(float), 256);
-    p->off_l = off;  off = align_up(off + Bz * ns * nh * sizeof(float), 256);
-    p->off_u = off;  off = align_up(off + Bz * ns * nh * du * sizeof(float), 256);
+    off = lay_partials(off, ns, most, nh, du * sizeof(float));
     p->off_opart = off;
     if (p->tiled) off = align_up(off + Bz * nh * du * sizeof(float), 256);
   }
   p->total = off;
+  p->reserve = off + spare;
   return ELITEKV_OK;
 }
 
@@ -345,7 +357,7 @@ size_t elitekv_decode_workspace_bytes(const elitekv_dims* dims, int64_t B, int64
                                       int32_t n_splits) {
   DecodePlan p;
   if (plan_decode(dims, 0, B, max_seq_len, n_splits, &p)) return 0;
-  return p.total;
+  return p.reserve;
 }
 
 static int decode_check(const elitekv_dims* dims, const DecodePlan& p, const void* q, const int32_t* q_pos,
@@ -401,10 +413,12 @@ static int decode_impl(const elitekv_dims* dims, int32_t d_ck, const void* q, co
 /* ---- fused decode step: append of the step's tokens + attention ---- */
 
 // workspace = [decode workspace (with the fused step's extra pieces) | append workspace of B tokens]
-static size_t step_ws_bytes(const elitekv_dims* dims, int32_t d_ck, int64_t B, int64_t max_seq_len, int32_t n_splits) {
+// (reserve: what the size functions answer; false: what a call needs)
+static size_t step_ws_bytes(const elitekv_dims* dims, int32_t d_ck, int64_t B, int64_t max_seq_len, int32_t n_splits,
+                            bool reserve = true) {
   DecodePlan p;
   if (plan_decode(dims, d_ck, B, max_seq_len, n_splits, &p, true)) return 0;
-  return p.total + (p.fresh ? 0 : append_ws_bytes(dims, d_ck > 0 ? d_ck : dims->d_c, B));
+  return (reserve ? p.reserve : p.total) + (p.fresh ? 0 : append_ws_bytes(dims, d_ck > 0 ? d_ck : dims->d_c, B));
 }
 
 static int step_impl(const elitekv_dims* dims, int32_t d_ck, const void* x, const void* q, const int32_t* pos,
@@ -500,11 +514,11 @@ static hipError_t launch_projection(const elitekv_dims* dims, const void* in, co
 // Workspace: [decode-step workspace | q bf16 [B, n_h d_h] | out bf16 [B, n_h d_h] | projection partial sums].
 struct BlockLayout { size_t step, off_q, off_o, off_proj, total; };
 static bool block_composed_layout(const elitekv_dims* dims, int32_t d_ck, int64_t B, int64_t max_seq_len,
-                                  int32_t n_splits, BlockLayout* L) {
+                                  int32_t n_splits, BlockLayout* L, bool reserve) {
   if (check_dims(dims) || dims->dtype != ELITEKV_BF16 || B < 1 || B > 64) return false;
   const int hd = dims->n_heads * dims->head_dim;
   if (!projection_supported(dims, B, dims->d_model, hd) || !projection_supported(dims, B, hd, dims->d_model)) return false;
-  L->step = step_ws_bytes(dims, d_ck, B, max_seq_len, n_splits);
+  L->step = step_ws_bytes(dims, d_ck, B, max_seq_len, n_splits, reserve);
   if (L->step == 0) return false;
   size_t off = align_up(L->step, 256);
   L->off_q = off; off = align_up(off + (size_t)B * hd * 2, 256);
@@ -522,7 +536,7 @@ static int block_composed_impl(const elitekv_dims* dims, int32_t d_ck, const voi
                                const int32_t* elite_idx, void* ke_plane, void* c_plane, int64_t plane_rows, void* y,
                                void* ws, size_t ws_bytes, int32_t n_splits, void* hip_stream) {
   BlockLayout L;
-  if (!block_composed_layout(dims, d_ck, B, max_seq_len, n_splits, &L)) return ELITEKV_EUNSUPPORTED;
+  if (!block_composed_layout(dims, d_ck, B, max_seq_len, n_splits, &L, false)) return ELITEKV_EUNSUPPORTED;
   if (!x || !W_q || !W_o || !y || !ws) return ELITEKV_ENULL;
   if (!aligned16(x) || !aligned16(W_q) || !aligned16(W_o) || !aligned16(y) || !aligned16(ws)) return ELITEKV_EALIGN;
   if (ws_bytes < L.total) return ELITEKV_EWORKSPACE;
@@ -555,9 +569,9 @@ static int block_composed_impl(const elitekv_dims* dims, int32_t d_ck, const voi
 
 size_t elitekv_block_step_workspace_bytes(const elitekv_dims* dims, int64_t B, int64_t max_seq_len, int32_t n_splits) {
   DecodePlan p;
-  if (plan_decode(dims, 0, B, max_seq_len, n_splits, &p, true, true) == ELITEKV_OK) return p.total;
+  if (plan_decode(dims, 0, B, max_seq_len, n_splits, &p, true, true) == ELITEKV_OK) return p.reserve;
   BlockLayout L;
-  return block_composed_layout(dims, 0, B, max_seq_len, n_splits, &L) ? L.total : 0;
+  return block_composed_layout(dims, 0, B, max_seq_len, n_splits, &L, true) ? L.total : 0;
 }
 
 int elitekv_block_step(const elitekv_dims* dims, const void* x, const int32_t* pos, const int64_t* slot,
@@ -604,7 +618,7 @@ size_t elitekv_slrd_block_step_workspace_bytes(const elitekv_dims* dims, int32_t
                                                int32_t n_splits) {
   BlockLayout L;
   if (!dims || d_ck <= 0 || d_ck >= dims->d_c) return 0;
-  return block_composed_layout(dims, d_ck, B, max_seq_len, n_splits, &L) ? L.total : 0;
+  return block_composed_layout(dims, d_ck, B, max_seq_len, n_splits, &L, true) ? L.total : 0;
 }
 
 int elitekv_slrd_block_step(const elitekv_dims* dims, int32_t d_ck, const void* x, const int32_t* pos,
@@ -674,7 +688,7 @@ size_t elitekv_multiquery_workspace_bytes(const elitekv_dims* dims, int64_t B, i
                                           int32_t n_splits) {
   DecodePlan p;
   if (B < 0 || T < 1 || B * T > 65535 || plan_decode(dims, 0, B * T, max_seq_len, n_splits, &p)) return 0;
-  return p.total;
+  return p.reserve;
 }
 
 int elitekv_multiquery_attn(const elitekv_dims* dims, const void* q, const int32_t* q_pos, const int32_t* kv_len,
@@ -786,7 +800,7 @@ size_t elitekv_slrd_decode_workspace_bytes(const elitekv_dims* dims, int32_t d_c
                                            int64_t max_seq_len, int32_t n_splits) {
   DecodePlan p;
   if (d_ck <= 0 || plan_decode(dims, d_ck, B, max_seq_len, n_splits, &p)) return 0;
-  return p.total;
+  return p.reserve;
 }
 
 int elitekv_slrd_decode_attn(const elitekv_dims* dims, int32_t d_ck, const void* q, const int32_t* q_pos,
@@ -805,7 +819,7 @@ size_t elitekv_slrd_multiquery_workspace_bytes(const elitekv_dims* dims, int32_t
   DecodePlan p;
   if (d_ck <= 0 || B < 0 || T < 1 || B * T > 65535 || plan_decode(dims, d_ck, B * T, max_seq_len, n_splits, &p))
     return 0;
-  return p.total;
+  return p.reserve;
 }
 
 int elitekv_slrd_multiquery_attn(const elitekv_dims* dims, int32_t d_ck, const void* q, const int32_t* q_pos,

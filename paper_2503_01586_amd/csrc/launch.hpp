@@ -62,7 +62,8 @@ struct DecodePlan {
   size_t off_ypart;     // whole-block step: split sums of the output projection  fp32 [y_ks, B, d_model]
   int32_t y_ks, y_kc;
   size_t off_sincos;    // (sin, cos) of the rotated chunks  fp32 [B, n_h r, 2]
-  size_t total;
+  size_t total;         // bytes the call needs
+  size_t reserve;       // ... and what a workspace for sequences up to max_seq_len is sized for (at least total)
 };
 
 struct DecodeArgs {

@@ -19,3 +19,36 @@ def test_one_round_of_work_groups(shape, slots_per_cu, B, S):
     # as many splits as one round holds, or as few as give the same tiles per split
     most = min(tiles, max(1, slots // groups))
     assert -(-tiles // ns) <= -(-tiles // most)
+
+
+# name: (d_model, n_heads, head_dim, r, d_c, dtype, d_ck of the separated forms)
+FORMS = {"7b_25": (4096, 32, 128, 8, 1536, "bf16", 576), "13b_25": (5120, 40, 128, 8, 1920, "bf16", 960),
+         "7b_12": (4096, 32, 128, 4, 768, "bf16", 384), "fp32": (4096, 32, 128, 8, 1536, "fp32", 576),
+         "bf16_320": (512, 8, 64, 4, 320, "bf16", 160), "any_shape": (36, 5, 36, 3, 17, "fp32", 5)}
+
+
+@pytest.mark.parametrize("name", list(FORMS))
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 7, 8, 16, 33, 43, 64])
+def test_workspace_of_a_longer_bound_covers_every_shorter_one(name, B):
+    """A serving loop allocates once for the longest sequence and passes the current bound: the automatic workspace never
+    falls as max_seq_len grows."""
+    *shape, dtype, d_ck = FORMS[name]
+    dims = ekv.make_dims(*shape, dtype)
+    sizes = {
+        "decode": lambda S: ekv.elitekv_decode_workspace_bytes(dims, B, S),
+        "step": lambda S: ekv.elitekv_decode_step_workspace_bytes(dims, B, S),
+        "block": lambda S: ekv.elitekv_block_step_workspace_bytes(dims, B, S),
+        "multiquery": lambda S: ekv.elitekv_multiquery_workspace_bytes(dims, B, 5, S),
+        "prefill": lambda S: ekv.elitekv_prefill_attn_workspace_bytes(dims, B, 5, S),
+        "slrd_decode": lambda S: ekv.elitekv_slrd_decode_workspace_bytes(dims, d_ck, B, S),
+        "slrd_step": lambda S: ekv.elitekv_slrd_decode_step_workspace_bytes(dims, d_ck, B, S),
+        "slrd_block": lambda S: ekv.elitekv_slrd_block_step_workspace_bytes(dims, d_ck, B, S),
+        "slrd_multiquery": lambda S: ekv.elitekv_slrd_multiquery_workspace_bytes(dims, d_ck, B, 5, S),
+    }
+    lengths = sorted(set(range(0, 8300, 16)) | set(range(1, 8300, 16)) | {5001, 16384, 32768, 32769, 131072, 131073})
+    for form, of in sizes.items():
+        before = 0
+        for S in lengths:
+            now = of(S)
+            assert now >= before, (form, S, before, now)
+            before = now
