@@ -93,10 +93,11 @@ __global__ __launch_bounds__(256) void search_pack_kernel(const float* __restric
 // Key tiles per work-group (a power of two, at least one per wave) and the work-groups ("items") per head: 32-query block Q
 // has 2 Q + 2 key tiles, cut into pieces of that many.  A search's launches have about a thousand work-groups (two to four
 // rounds of the chip: 512 / 1024 / 2048 / 4096 wanted: 1103 / 1060 / 1145 / 1233 us (before the products were grouped) at 1000 tokens of 32 heads, 205 / 235 /
-// 235 / 235 at 300), and a head at most about a thousand, since one work-group adds up their distances.
+// 235 / 235 at 300), and a head at most about a thousand or one per 32-query block, since one work-group adds up their
+// distances (a piece of 2 n_q32 tiles is a whole block: nothing is gained by longer ones).
 inline int sr_keys_per_item(int64_t n_q32, int64_t n_h) {
   int k = 4;
-  while (n_q32 * n_q32 / k > 1024 || n_h * n_q32 * n_q32 / k > 1024) k *= 2;
+  while (k < 2 * n_q32 && (n_q32 * n_q32 / k > 1024 || n_h * n_q32 * n_q32 / k > 1024)) k *= 2;
   return k;
 }
 inline int64_t sr_items_before(int q32, int keys) {      // items of the 32-query blocks below q32

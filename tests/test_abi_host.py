@@ -370,3 +370,11 @@ def test_decode_path_query_names_the_kernels_a_shape_runs():
     assert ekv.elitekv_decode_path(mk(8, 1536), 500) == GEN
     with pytest.raises(ekv.EliteKVError):
         ekv.elitekv_decode_path(mk(8, 1536, n_h=32, d_h=127))
+
+
+@pytest.mark.parametrize("T", [1, 4096, 4097, 1 << 17, 1 << 20])
+@pytest.mark.parametrize("n_h", [1, 32, 4096, 65535])
+def test_search_workspace_at_the_largest_samples(T, n_h):
+    """Many heads of a long sample: the plan ends, and grows with the packed copies (32 KiB per head and 16 tokens)."""
+    packed = 2 * 16 * 256 * 4 * n_h * ((T + 15) // 16)
+    assert ekv.elitekv_ropelite_search_workspace_bytes(T, n_h, 128, 8) > packed
