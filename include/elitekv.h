@@ -200,10 +200,16 @@ int elitekv_decode_attn_noalloc(const elitekv_dims* dims, const void* q, const i
  *   elite_out [n_heads, r] int32, device: chunk indices in selection order (usable as elite_idx)
  *   dist_out  [n_heads, r] float32, device, or NULL: the winning distance of every round
  * Arithmetic is fp32 (angles reduced in double); a near-tie between two chunks may resolve
- * differently from exact arithmetic.  head_dim <= 128.  Workspace: the _workspace_bytes function.
+ * differently from exact arithmetic.  head_dim <= 128.
+ * Workspace: elitekv_ropelite_search_min_workspace_bytes is what a search needs (about 32 KiB per head and 16 tokens: 66 MB
+ * for 32 heads, 1000 tokens; 270 MB for 4096); it never falls as T grows.  elitekv_ropelite_search_workspace_bytes adds
+ * room to keep every causal pair's residual score from round to round (4 bytes a pair and head, T <= 4096, up to 4 GiB:
+ * 66 MB and 1.1 GB there), with which 1000 tokens take 1.1 instead of 1.6 ms; with less room it sums them again in every
+ * round, to the same distances up to rounding.  EWORKSPACE below the smaller size.
  * Enqueues r + 1 kernels on hip_stream; no host synchronisation.
  * ------------------------------------------------------------------------------------------- */
 size_t elitekv_ropelite_search_workspace_bytes(int64_t T, int32_t n_heads, int32_t head_dim, int32_t r);
+size_t elitekv_ropelite_search_min_workspace_bytes(int64_t T, int32_t n_heads, int32_t head_dim, int32_t r);
 int elitekv_ropelite_search(const float* q, const float* k, const int32_t* pos, int64_t T, int32_t n_heads,
                             int32_t head_dim, int32_t r, double rope_base, int32_t* elite_out, float* dist_out,
                             void* ws, size_t ws_bytes, void* hip_stream);

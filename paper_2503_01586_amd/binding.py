@@ -54,6 +54,7 @@ def _load():
         "elitekv_decode_attn": (C.c_int, [DP, P, P, P, I64, I64, I64, P, P, P, P, P, I64, P, P, SZ, I32, P]),
         "elitekv_decode_attn_noalloc": (C.c_int, [DP, P, P, P, I64, I64, I64, P, P, P, P, P, I64, P, I32, P]),
         "elitekv_ropelite_search_workspace_bytes": (SZ, [I64, I32, I32, I32]),
+        "elitekv_ropelite_search_min_workspace_bytes": (SZ, [I64, I32, I32, I32]),
         "elitekv_ropelite_search": (C.c_int, [P, P, P, I64, I32, I32, I32, C.c_double, P, P, P, SZ, P]),
         "elitekv_multiquery_workspace_bytes": (SZ, [DP, I64, I64, I64, I32]),
         "elitekv_multiquery_attn": (C.c_int, [DP, P, P, P, I64, I64, I64, I64, P, P, P, P, P, I64, P, P, SZ, I32, P]),
@@ -214,6 +215,10 @@ def elitekv_decode_attn_noalloc(dims, q, q_pos, seq_len, max_seq_len, batch_stri
 
 def elitekv_ropelite_search_workspace_bytes(T, n_heads, head_dim, r) -> int:
     return _lib.elitekv_ropelite_search_workspace_bytes(int(T), int(n_heads), int(head_dim), int(r))
+
+
+def elitekv_ropelite_search_min_workspace_bytes(T, n_heads, head_dim, r) -> int:
+    return _lib.elitekv_ropelite_search_min_workspace_bytes(int(T), int(n_heads), int(head_dim), int(r))
 
 
 def elitekv_ropelite_search(q, k, pos, r, rope_base, elite_out, dist_out, ws, stream=None):

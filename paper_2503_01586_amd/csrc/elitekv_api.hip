@@ -666,7 +666,12 @@ static int check_search(int64_t T, int32_t n_h, int32_t head_dim, int32_t r, dou
 
 size_t elitekv_ropelite_search_workspace_bytes(int64_t T, int32_t n_heads, int32_t head_dim, int32_t r) {
   if (check_search(T, n_heads, head_dim, r, 10000.0)) return 0;
-  return search_workspace_bytes(T, n_heads, head_dim);
+  return search_workspace_bytes(T, n_heads);
+}
+
+size_t elitekv_ropelite_search_min_workspace_bytes(int64_t T, int32_t n_heads, int32_t head_dim, int32_t r) {
+  if (check_search(T, n_heads, head_dim, r, 10000.0)) return 0;
+  return search_min_workspace_bytes(T, n_heads);
 }
 
 int elitekv_ropelite_search(const float* q, const float* k, const int32_t* pos, int64_t T, int32_t n_heads,
@@ -676,9 +681,9 @@ int elitekv_ropelite_search(const float* q, const float* k, const int32_t* pos, 
   if (st) return st;
   if (!q || !k || !pos || !elite_out || !ws) return ELITEKV_ENULL;
   if (!aligned16(q) || !aligned16(k) || !aligned16(ws)) return ELITEKV_EALIGN;
-  if (ws_bytes < search_workspace_bytes(T, n_heads, head_dim)) return ELITEKV_EWORKSPACE;
+  if (ws_bytes < search_min_workspace_bytes(T, n_heads)) return ELITEKV_EWORKSPACE;
   const hipError_t e = launch_ropelite_search(q, k, pos, T, n_heads, head_dim, r, rope_base, elite_out, dist_out,
-                                              (char*)ws, (hipStream_t)hip_stream);
+                                              (char*)ws, ws_bytes, (hipStream_t)hip_stream);
   return e == hipSuccess ? ELITEKV_OK : ELITEKV_EHIP;
 }
 

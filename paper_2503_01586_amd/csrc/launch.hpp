@@ -179,10 +179,11 @@ bool prefill_flash_supported(const elitekv_dims& d, int d_ck, int64_t T, int64_t
 size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len);
 hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipStream_t stream);
 hipError_t launch_mha_decode(const MhaArgs& a, hipStream_t stream);
-size_t search_workspace_bytes(int64_t T, int n_h, int d_h);
+size_t search_workspace_bytes(int64_t T, int n_h);
+size_t search_min_workspace_bytes(int64_t T, int n_h);
 hipError_t launch_ropelite_search(const float* q, const float* k, const int32_t* pos, int64_t T, int n_h, int d_h,
                                   int r, double rope_base, int32_t* elite_out, float* dist_out, char* ws,
-                                  hipStream_t stream);
+                                  size_t ws_bytes, hipStream_t stream);
 hipError_t launch_stream_read(const void* src, size_t bytes, uint32_t* sink, int mode, size_t* bytes_read,
                               hipStream_t stream);
 

@@ -20,6 +20,8 @@
 //                   takes the arg-min.
 // All state (packed copies, residuals, partial distances, elite masks) lives in the caller's workspace; a search is
 // 1 + r launches on the caller's stream with no host synchronisation in between.
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -293,11 +295,16 @@ __global__ __launch_bounds__(256, 2) void search_round_kernel(
   }
 }
 
-// Samples of up to this many tokens keep the residuals (n_h (T / 16)^2 / 2 KiB: 66 MB for 1000 tokens of 32 heads, 1.1 GB
-// for 4096); longer ones sum them again in every round, at twice the matrix instructions.
+// Samples of up to this many tokens keep the residuals where the caller's workspace has room for them (n_h (T / 16)^2 / 2
+// KiB: 66 MB for 1000 tokens of 32 heads, 1.1 GB for 4096) and the size function asks for that room up to this many bytes.
+// The other searches sum the residuals again in every round, at twice the matrix instructions (32 heads, r = 8, 128 / 1000 / 4096
+// tokens: 0.128 / 1.56 / 20.9 ms instead of 0.108 / 1.07 / 14.3).
 constexpr int64_t kSrKeepTokens = 4096;
+constexpr size_t kSrKeepBytes = (size_t)4 << 30;
 
-struct SearchLayout { size_t kp, partial, emask, arrived, res, total; int n_tiles, keys, n_items; };
+// least: bytes a search needs, which never falls as T grows (the pieces per head do, wherever a piece gets longer: the
+// partial distances are laid out for the most that a shorter sample has); total: with the residuals, if they are kept
+struct SearchLayout { size_t kp, partial, emask, arrived, res, least, total; int n_tiles, keys, n_items; };
 static SearchLayout search_layout(int64_t T, int n_h) {
   SearchLayout L;
   L.n_tiles = (int)((T + kSrTile - 1) / kSrTile);
@@ -308,26 +315,29 @@ static SearchLayout search_layout(int64_t T, int n_h) {
   const size_t vec = up((size_t)L.n_tiles * kSrTile * n_h * kSrRow * sizeof(float));      // one packed operand (whole tiles)
   L.kp = vec;
   L.partial = L.kp + vec;
-  L.emask = L.partial + up((size_t)n_h * L.n_items * kSrMaxChunks * sizeof(float));
+  const int64_t most_items = std::min<int64_t>(sr_items_before(n_q32, 4), 1024 + n_q32);
+  L.emask = L.partial + up((size_t)n_h * most_items * kSrMaxChunks * sizeof(float));
   L.arrived = L.emask + up((size_t)n_h * sizeof(uint64_t));
   L.res = L.arrived + up((size_t)n_h * sizeof(int32_t));
-  L.total = L.res;
-  if (T <= kSrKeepTokens) L.total += (size_t)L.n_tiles * (L.n_tiles + 1) / 2 * n_h * 1024;
+  L.least = L.total = L.res;
+  const size_t kept = (size_t)L.n_tiles * (L.n_tiles + 1) / 2 * n_h * 1024;
+  if (T <= kSrKeepTokens && kept <= kSrKeepBytes) L.total += kept;
   return L;
 }
 
-size_t search_workspace_bytes(int64_t T, int n_h, int d_h) { return search_layout(T, n_h).total; }
+size_t search_workspace_bytes(int64_t T, int n_h) { return search_layout(T, n_h).total; }
+size_t search_min_workspace_bytes(int64_t T, int n_h) { return search_layout(T, n_h).least; }
 
 hipError_t launch_ropelite_search(const float* q, const float* k, const int32_t* pos, int64_t T, int n_h, int d_h,
                                   int r, double rope_base, int32_t* elite_out, float* dist_out, char* ws,
-                                  hipStream_t stream) {
+                                  size_t ws_bytes, hipStream_t stream) {
   const SearchLayout L = search_layout(T, n_h);
   float* qp = (float*)ws;
   float* kp = (float*)(ws + L.kp);
   float* partial = (float*)(ws + L.partial);
   uint64_t* emask = (uint64_t*)(ws + L.emask);
   int32_t* arrived = (int32_t*)(ws + L.arrived);
-  float* res = T <= kSrKeepTokens ? (float*)(ws + L.res) : nullptr;
+  float* res = L.total > L.least && ws_bytes >= L.total ? (float*)(ws + L.res) : nullptr;
   const int half = d_h / 2;
   const float scale = 1.f / sqrtf((float)d_h);
   search_pack_kernel<<<dim3(L.n_tiles, (n_h + kSrPackHeads - 1) / kSrPackHeads), 256, 0, stream>>>(

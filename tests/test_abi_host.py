@@ -378,3 +378,21 @@ def test_search_workspace_at_the_largest_samples(T, n_h):
     """Many heads of a long sample: the plan ends, and grows with the packed copies (32 KiB per head and 16 tokens)."""
     packed = 2 * 16 * 256 * 4 * n_h * ((T + 15) // 16)
     assert ekv.elitekv_ropelite_search_workspace_bytes(T, n_h, 128, 8) > packed
+
+
+@pytest.mark.parametrize("n_h", [1, 32, 64, 1024, 65535])
+def test_search_workspace_of_a_longer_sample_covers_every_shorter_one(n_h):
+    """What a search needs never falls as T grows; what the size function adds for speed is bounded."""
+    before = 0
+    for T in sorted(set(range(1, 1 << 20, 997)) | set(range(1, 8300, 16)) | {2048, 4096, 4097, 1 << 20}):
+        least = ekv.elitekv_ropelite_search_min_workspace_bytes(T, n_h, 128, 8)
+        most = ekv.elitekv_ropelite_search_workspace_bytes(T, n_h, 128, 8)
+        assert before <= least <= most <= least + (4 << 30), T
+        before = least
+    assert ekv.elitekv_ropelite_search_min_workspace_bytes(0, n_h, 128, 8) == 0
+
+
+def test_search_refuses_less_than_it_needs():
+    need = ekv.elitekv_ropelite_search_min_workspace_bytes(300, 8, 64, 4)
+    assert lib.elitekv_ropelite_search(FAKE, FAKE, FAKE, 300, 8, 64, 4, 10000.0, FAKE, None, FAKE, need - 1,
+                                       None) == ekv.EWORKSPACE

@@ -19,13 +19,13 @@ pytestmark = pytest.mark.gpu
 RTOL = 2e-4     # fp32 sums of up to ~10^5 terms against float64
 
 
-def gpu_search(q, k, pos, r, base):
+def gpu_search(q, k, pos, r, base, ws_bytes=None):
     T, n_h, d_h = q.shape
     qd = torch.from_numpy(q.astype(np.float32)).to(DEV)
     kd = torch.from_numpy(k.astype(np.float32)).to(DEV)
     elite = torch.full((n_h, r), -1, dtype=torch.int32, device=DEV)
     dist = torch.full((n_h, r), float("nan"), dtype=torch.float32, device=DEV)
-    nws = ekv.elitekv_ropelite_search_workspace_bytes(T, n_h, d_h, r)
+    nws = ekv.elitekv_ropelite_search_workspace_bytes(T, n_h, d_h, r) if ws_bytes is None else ws_bytes
     assert nws > 0
     ws = torch.full((nws,), 0xFF, dtype=torch.uint8, device=DEV)
     ekv.elitekv_ropelite_search(qd, kd, i32(pos), r, base, elite, dist, ws)

@@ -4,6 +4,7 @@ GPU's own earlier choices, every reported distance the oracle's, to 2e-4 (fp32 s
 import numpy as np
 import pytest
 
+import paper_2503_01586_amd as ekv
 from oracle import elitekv_oracle as orc
 from test_gpu_search import RTOL, gpu_search
 
@@ -27,3 +28,18 @@ def test_search_at_tile_edges(T, n_h, d_h, r):
             floor = 1e-6 * float(np.max(ref[np.isfinite(ref)])) + 1e-6
             assert ref[c] <= float(np.min(ref)) * (1 + RTOL) + floor * T, (h, i)
             assert abs(dist[h, i] - ref[c]) <= RTOL * ref[c] + floor * T, (h, i)
+
+
+@pytest.mark.parametrize("T,n_h,d_h,r", [(16, 5, 8, 4), (129, 1, 64, 32), (300, 8, 128, 8), (2048, 1, 16, 2)])
+def test_search_in_the_least_workspace(T, n_h, d_h, r):
+    """Without room for the residuals (here: the room of a longer sample that keeps none) they are summed again in every
+    round: the same choices, the same distances to rounding."""
+    rng = np.random.default_rng(T + d_h)
+    mag = np.exp(rng.normal(0.0, 0.7, size=(1, n_h, d_h // 2))).repeat(2, axis=2)
+    q, k, pos = (rng.standard_normal((T, n_h, d_h)) * mag, rng.standard_normal((T, n_h, d_h)) * mag, np.arange(T))
+    _, _, elite, dist = gpu_search(q, k, pos, r, 10000.0)
+    least = ekv.elitekv_ropelite_search_min_workspace_bytes(T, n_h, d_h, r)
+    assert least < ekv.elitekv_ropelite_search_workspace_bytes(T, n_h, d_h, r)
+    _, _, elite_least, dist_least = gpu_search(q, k, pos, r, 10000.0, ws_bytes=least)
+    assert np.array_equal(elite, elite_least)
+    assert np.max(np.abs(dist - dist_least)) <= RTOL * np.max(dist)
