@@ -170,12 +170,13 @@ int elitekv_decode_attn(const elitekv_dims* dims, const void* q, const int32_t* 
 /*
  * elitekv_decode_attn for callers that cannot allocate device memory or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments
- * (without ws / ws_bytes), same kernels and bit-for-bit the same result as elitekv_decode_attn; the
- * intermediates live in a buffer of ELITEKV_NOALLOC_SCRATCH_BYTES that is part of the library's device
+ * (without ws / ws_bytes), same kernels and, with the same number of splits, bit-for-bit the same result as
+ * elitekv_decode_attn; the intermediates live in a buffer of ELITEKV_NOALLOC_SCRATCH_BYTES that is part of the library's device
  * image (one copy per GPU, held until the process ends).  The call allocates and frees nothing.
- *   - ESCRATCH (nothing enqueued) when elitekv_decode_workspace_bytes(dims, B, max_seq_len, n_splits)
- *     exceeds ELITEKV_NOALLOC_SCRATCH_BYTES; 32 MiB covers the 7B shape at 25 % cache, one sequence,
- *     32768 cached tokens with the automatic split count.
+ *   - ESCRATCH (nothing enqueued) when the call needs more than ELITEKV_NOALLOC_SCRATCH_BYTES, never where
+ *     elitekv_decode_workspace_bytes(dims, B, max_seq_len, n_splits) does not exceed them; 32 MiB covers the 7B shape at 25 % cache, one sequence,
+ *     32768 cached tokens with the automatic split count.  Calls in fp32 arithmetic (ELITEKV_PATH_GENERIC) with
+ *     the automatic count take as many of its splits as the buffer holds, where it does not hold them all.
  *   - All calls on one GPU share that GPU's buffer: two calls whose kernels may overlap (different
  *     streams, no ordering between them) race.  Calls on one stream are ordered and safe.  Nothing in
  *     the buffer has to be cleared between calls.

@@ -82,9 +82,10 @@ static int64_t balanced_splits(int64_t groups, int64_t tiles, int64_t slots, int
 // d_ck = 0: joint latent; d_ck > 0: separated latents, a cache row is [c^k (d_ck) | c^v (d_c - d_ck)]
 // want_fresh: plan the fused decode step (the newest token enters as one more split) if the kernels cover it
 // block: plan the whole-block step (EUNSUPPORTED unless the fused step's kernels cover the shape)
-// tiled: false leaves the tiled fp32 kernels out, whose automatic split counts can ask for more workspace
+// tight: the tiled fp32 kernels leave the merged latents in the place of every row's first split instead of a piece of
+// their own (the same results; the partials are used up, where otherwise the merge can be repeated)
 static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t max_seq, int32_t n_splits,
-                       DecodePlan* p, bool want_fresh = false, bool block = false, bool tiled = true) {
+                       DecodePlan* p, bool want_fresh = false, bool block = false, bool tight = false) {
   int st = check_dims(d);
   if (st) return st;
   if (B < 0 || max_seq < 0 || n_splits < 0) return ELITEKV_EINVAL;
@@ -165,7 +166,7 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     if (block) return ELITEKV_EUNSUPPORTED;
     p->mfma = 0;
     p->head_groups = 1;
-    p->tiled = tiled && decode_tiled_supported(*d, d_ck);
+    p->tiled = decode_tiled_supported(*d, d_ck);
     int64_t ns = n_splits, most = n_splits;
     if (ns == 0 && p->tiled) ns = balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits, &most);
     else if (ns == 0) ns = most = auto_splits_generic(d, Bq, seq);
@@ -176,8 +177,9 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     p->chunk = (int32_t)chunk;
     p->off_qt = off; off = align_up(off + Bz * nh * dq * sizeof(float), 256);
     off = lay_partials(off, ns, most, nh, du * sizeof(float));
-    p->off_opart = off;
-    if (p->tiled) off = align_up(off + Bz * nh * du * sizeof(float), 256);
+    p->ubar_rows = tight ? p->n_part : 1;
+    p->off_opart = tight ? p->off_u : off;
+    if (p->tiled && !tight) off = align_up(off + Bz * nh * du * sizeof(float), 256);
   }
   p->total = off;
   p->reserve = off + spare;
@@ -397,9 +399,9 @@ static int decode_impl(const elitekv_dims* dims, int32_t d_ck, const void* q, co
                        int64_t batch_stride_rows, const void* W_uk, const void* W_uv,
                        const int32_t* elite_idx, const void* ke_plane, const void* c_plane,
                        int64_t plane_rows, void* out, void* ws, size_t ws_bytes, int32_t n_splits,
-                       void* hip_stream, int32_t stages, int32_t q_per_seq = 1, bool tiled = true) {
+                       void* hip_stream, int32_t stages, int32_t q_per_seq = 1, bool tight = false) {
   DecodePlan p;
-  int st = plan_decode(dims, d_ck, B, max_seq_len, n_splits, &p, false, false, tiled);
+  int st = plan_decode(dims, d_ck, B, max_seq_len, n_splits, &p, false, false, tight);
   if (st) return st;
   st = decode_check(dims, p, q, q_pos, seq_len, B, batch_stride_rows, W_uk, W_uv, elite_idx, ke_plane, c_plane,
                     plane_rows, out, ws, ws_bytes);
@@ -858,18 +860,24 @@ int elitekv_decode_attn_noalloc(const elitekv_dims* dims, const void* q, const i
   DecodePlan p;
   int st = plan_decode(dims, 0, B, max_seq_len, n_splits, &p);
   if (st) return st;
-  // where the tiled fp32 kernels' plan is too large for the scratch buffer, the any-shape kernels' may still fit
-  const bool tiled = p.total <= (size_t)ELITEKV_NOALLOC_SCRATCH_BYTES;
-  if (!tiled && p.tiled) st = plan_decode(dims, 0, B, max_seq_len, n_splits, &p, false, false, false);
-  if (st) return st;
-  if (p.total > (size_t)ELITEKV_NOALLOC_SCRATCH_BYTES) return ELITEKV_ESCRATCH;
+  const size_t room = ELITEKV_NOALLOC_SCRATCH_BYTES;
+  const bool tight = p.tiled && p.total > room;
+  if (tight) {
+    // The tiled fp32 kernels: without a piece for the merged latents, and of an automatic split count as much as fits, if
+    // the buffer holds the partials of auto_splits_generic()'s count.
+    auto fits = [&](int32_t n) { return plan_decode(dims, 0, B, max_seq_len, n, &p, false, false, true) == ELITEKV_OK && p.total <= room; };
+    if (n_splits == 0 && fits(auto_splits_generic(dims, B, max_seq_len)))
+      for (n_splits = elitekv_decode_auto_splits(dims, B, max_seq_len); n_splits > 1 && !fits(n_splits);) --n_splits;
+    if (!fits(n_splits)) return ELITEKV_ESCRATCH;
+  }
+  if (p.total > room) return ELITEKV_ESCRATCH;
   void* ws = scratch_ptr();
   if (!ws) return ELITEKV_EHIP;
   // every kernel of the call writes the part of the scratch it later reads (empty splits included),
   // so nothing needs clearing between calls
   return decode_impl(dims, 0, q, q_pos, seq_len, B, max_seq_len, batch_stride_rows, W_uk, W_uv, elite_idx,
                      ke_plane, c_plane, plane_rows, out, ws, ELITEKV_NOALLOC_SCRATCH_BYTES, n_splits, hip_stream, 7, 1,
-                     tiled);
+                     tight);
 }
 
 int elitekv_decode_attn_stages(const elitekv_dims* dims, const void* q, const int32_t* q_pos,

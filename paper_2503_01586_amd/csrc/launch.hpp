@@ -47,6 +47,7 @@ struct DecodePlan {
   size_t off_l;         // split sums                       fp32 [B, n_splits, n_h_pad]
   size_t off_u;         // split latent accumulators        fp32 [B, n_splits, ...]
   size_t off_opart;     // up-projection partials (MFMA path), merged latents (tiled path)   fp32
+  int32_t ubar_rows;    // tiled path: [n_h, d_u] pieces from one row's merged latents to the next row's
   size_t off_cnt;       // MFMA path: arrival counters of the merge kernels' chunk groups   int32 [B, n_h]
   // fused decode step (fresh != 0): the cache row of the newest token of every sequence is finished (summed,
   // rotated, stored) inside the attention kernel, by the work-group whose tiles include its position,

@@ -406,9 +406,8 @@ __global__ __launch_bounds__(kTtWaves * 64) void attn_tiled_kernel(
 // Bound by the split accumulators' bytes.  
 // 63 splits of two rows, 7B 25 %: 9.3 us for 25 MB; with the up-projection below 18.5 (merge_upproj_generic_kernel 291).
 __global__ __launch_bounds__(256) void merge_tiled_kernel(const float* __restrict__ part_m,
-                                                          const float* __restrict__ part_l,
-                                                          const float* __restrict__ part_u, float* __restrict__ ubar,
-                                                          int n_h, int d_u, int n_splits) {
+                                                          const float* __restrict__ part_l, const float* part_u,
+                                                          float* ubar, int ubar_rows, int n_h, int d_u, int n_splits) {
   extern __shared__ __align__(16) float smem[];
   tf_f32x4* sums = reinterpret_cast<tf_f32x4*>(smem);      // [4][64]
   float* red = smem + 1024;                                // [8]
@@ -452,7 +451,9 @@ __global__ __launch_bounds__(256) void merge_tiled_kernel(const float* __restric
   a = (sums[lane] + sums[64 + lane]) + (sums[128 + lane] + sums[192 + lane]);
 #pragma unroll
   for (int e = 0; e < 4; ++e) a[e] *= inv;
-  *reinterpret_cast<tf_f32x4*>(ubar + ((int64_t)b * n_h + h) * d_u + k) = a;
+  // (ubar may be the first split's accumulators: this work-group alone reads and writes these columns of the head, and
+  // every wave's sums have passed the barrier)
+  *reinterpret_cast<tf_f32x4*>(ubar + ((int64_t)b * ubar_rows * n_h + h) * d_u + k) = a;
 }
 
 // ---- up-projection o = ubar W_uv ----
@@ -462,8 +463,9 @@ __global__ __launch_bounds__(256) void merge_tiled_kernel(const float* __restric
 constexpr int kTuCols = 32;
 
 template <typename T, int BT>
-__global__ __launch_bounds__(1024) void upproj_tiled_kernel(const float* __restrict__ ubar, const T* __restrict__ W_uv,
-                                                            T* __restrict__ out, int B, int n_h, int d_h, int d_u) {
+__global__ __launch_bounds__(1024) void upproj_tiled_kernel(const float* __restrict__ ubar, int ubar_rows,
+                                                            const T* __restrict__ W_uv, T* __restrict__ out, int B,
+                                                            int n_h, int d_h, int d_u) {
   extern __shared__ __align__(16) float smem[];
   float* us = smem;                                        // [BT][d_u]
   float* red = smem + BT * d_u;                            // [16 waves][BT][kTuCols]
@@ -471,7 +473,7 @@ __global__ __launch_bounds__(1024) void upproj_tiled_kernel(const float* __restr
   const int h = blockIdx.y, j0 = blockIdx.x * kTuCols, b0 = blockIdx.z * BT;
   for (int e = tid; e < BT * d_u / 4; e += 1024) {
     const int bt = e / (d_u / 4), k4 = e % (d_u / 4);
-    reinterpret_cast<tf_f32x4*>(us)[e] = ld4(ubar + ((int64_t)min(b0 + bt, B - 1) * n_h + h) * d_u + 4 * k4);
+    reinterpret_cast<tf_f32x4*>(us)[e] = ld4(ubar + ((int64_t)min(b0 + bt, B - 1) * ubar_rows * n_h + h) * d_u + 4 * k4);
   }
   __syncthreads();
   tf_f32x4 acc[BT];
@@ -563,7 +565,7 @@ static hipError_t launch_decode_tiled_t(const DecodeArgs& a, const DecodePlan& p
   }
   if (a.stages & 4) {
     merge_tiled_kernel<<<dim3((p.d_u + 255) / 256, n_h, B), 256, sizeof(float) * (size_t)(1024 + 8 + p.n_splits), stream>>>(
-        pm, pl, pu, ubar, n_h, p.d_u, p.n_splits);
+        pm, pl, pu, ubar, p.ubar_rows, n_h, p.d_u, p.n_splits);
 #define EKV_UP(BT)                                                                                              \
   {                                                                                                             \
     static LdsLimit limit;                                                                                      \
@@ -571,7 +573,7 @@ static hipError_t launch_decode_tiled_t(const DecodeArgs& a, const DecodePlan& p
     e = raise_lds_limit(limit, (const void*)upproj_tiled_kernel<T, BT>, lds);                                   \
     if (e != hipSuccess) return e;                                                                              \
     upproj_tiled_kernel<T, BT><<<dim3(d_h / kTuCols, n_h, (B + BT - 1) / BT), 1024, lds, stream>>>(             \
-        ubar, (const T*)a.W_uv, (T*)a.out, B, n_h, d_h, p.d_u);                                                 \
+        ubar, p.ubar_rows, (const T*)a.W_uv, (T*)a.out, B, n_h, d_h, p.d_u);                                    \
   }
     if (B == 1) EKV_UP(1)
     else if (B == 2) EKV_UP(2)

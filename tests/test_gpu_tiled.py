@@ -144,3 +144,24 @@ def test_tiled_step_matches_oracle(name, B):
     torch.cuda.synchronize()
     assert orc.max_abs_rel(host64(c), c_all) <= TOL[dt] and (r == 0 or orc.max_abs_rel(host64(ke), ke_all) <= TOL[dt])
     assert orc.max_abs_rel(host64(out), ref) <= TOL[dt]
+
+
+@pytest.mark.parametrize("n_splits", [0, 126])
+def test_scratch_limit_keeps_the_kernels(n_splits):
+    """... and with the same number of splits its result is elitekv_decode_attn's bit for bit.  126 is the largest count whose
+    partials the scratch holds (qe 512 + q~ 262144 + 126 x 262400 bytes), without room for the merged latents; at
+    2048 tokens the automatic count is 128."""
+    dims = ekv.make_dims(64, 32, 128, 2, 2048, "fp32")
+    B, S, stride = 1, 2048, 2049
+    assert ekv.elitekv_decode_workspace_bytes(dims, B, S, n_splits) > ekv.NOALLOC_SCRATCH_BYTES
+    rng = np.random.default_rng(4)
+    idx = synth.draw_elite_idx(rng, 32, 128, 2)
+    n = lambda *s, std=1.0: dev(rng.standard_normal(s) * std, "fp32")
+    q, W_uk, W_uv = n(B, 32, 128), n(2048, 32, 124, std=2048 ** -0.5), n(2048, 32, 128, std=2048 ** -0.5)
+    ke, c = n(stride, 32, 4), n(stride, 2048)
+    out = torch.full((B, 32, 128), float("nan"), device=DEV)
+    ekv.elitekv_decode_attn_noalloc(dims, q, i32([S - 1]), i32([S]), S, stride, W_uk, W_uv, i32(idx), ke, c, out,
+                                    n_splits=n_splits)
+    torch.cuda.synchronize()
+    same = gpu_decode(dims, q, i32([S - 1]), i32([S]), S, stride, W_uk, W_uv, i32(idx), ke, c, n_splits=126)
+    assert torch.equal(out, same)
