@@ -364,10 +364,11 @@ __global__ __launch_bounds__(kTtWaves * 64) void attn_tiled_kernel(
     mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
     mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
     const float m_new = fmaxf(m, mx);
-    const float alpha = exp2f(m - m_new);                  // m = -inf on the first tile gives 0
+    const float m_sub = m_new == -INFINITY ? 0.f : m_new;  // nothing visible yet (keys of -inf): weights and sum stay 0
+    const float alpha = exp2f(m - m_sub);                  // m = -inf on the first tile gives 0
     tf_f32x4 p;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) p[v] = exp2f(s[v] - m_new);
+    for (int v = 0; v < 4; ++v) p[v] = exp2f(s[v] - m_sub);
     float ps = (p[0] + p[1]) + (p[2] + p[3]);
     ps += __shfl_xor(ps, 16, kWave);
     ps += __shfl_xor(ps, 32, kWave);

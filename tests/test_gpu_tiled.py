@@ -165,3 +165,23 @@ def test_scratch_limit_keeps_the_kernels(n_splits):
     torch.cuda.synchronize()
     same = gpu_decode(dims, q, i32([S - 1]), i32([S]), S, stride, W_uk, W_uv, i32(idx), ke, c, n_splits=126)
     assert torch.equal(out, same)
+
+
+@pytest.mark.parametrize("n_splits", [1, 3])
+def test_a_tile_of_keys_at_minus_infinity(n_splits):
+    """Elite keys of -inf hide their tokens: whole tiles of them (16 tokens, the first of every split) leave the others'
+    softmax as it is."""
+    d_h, n_h, d_c, S, hidden = 32, 16, 48, 150, 60
+    dims = ekv.make_dims(64, n_h, d_h, 2, d_c, "fp32")
+    rng = np.random.default_rng(6)
+    idx = synth.draw_elite_idx(rng, n_h, d_h, 2)
+    n = lambda *s, std=1.0: dev(rng.standard_normal(s) * std, "fp32")
+    q, W_uk, W_uv = n(1, n_h, d_h), n(d_c, n_h, d_h - 4, std=d_c ** -0.5), n(d_c, n_h, d_h, std=d_c ** -0.5)
+    ke, c = n(S, n_h, 4), n(S, d_c)
+    for h in range(n_h):                                     # at position 0 the query enters as it is: make it positive
+        q[0, h, 2 * int(idx[h, 0])] = 1.0
+    ke[:hidden, :, 0] = float("-inf")
+    out = gpu_decode(dims, q, i32([0]), i32([S]), S, S, W_uk, W_uv, i32(idx), ke, c, n_splits=n_splits)
+    ref = orc.decode_attn(host64(q), [0], host64(ke)[None, hidden:], host64(c)[None, hidden:], [S - hidden], host64(W_uk),
+                          host64(W_uv), idx, d_h, 10000.0)
+    assert orc.max_abs_rel(host64(out), ref) <= TOL["fp32"]
