@@ -3,6 +3,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "launch.hpp"
 
 // Built-in scratch of elitekv_decode_attn_noalloc: device memory that belongs to the library's code
@@ -52,27 +54,39 @@ static int32_t auto_splits_generic(const elitekv_dims* d, int64_t B, int64_t max
   return (int32_t)want;
 }
 
-// Splits per batch row of the matrix-core path: `groups` (batch row, head group) pairs of up to `tiles` tiles each on a
-// chip that holds `slots` work-groups at once.  The launch takes as many rounds as its work-groups fill the chip, and a
-// round costs its longest work-group: a start (first tile from cold memory, about four tiles' time) and its tiles.
-// Rounding the split count UP to fill every slot started a second round for the last few work-groups: 260 of them for
-// 4 sequences x 5 drafted tokens (7B 25 %, 4096 tokens): 92.9 us, 240 (twelve splits): 55.9 us; 258 for three sequences of 5001
-// tokens, separated latents: 23.5 us, 237: 16.5 us.  Of equal counts the smallest (fewest partials to merge).
+// Splits per batch row: `groups` (batch row, head group) pairs of up to `tiles` tiles each on a chip that holds `slots`
+// work-groups at once, as many as make one, two or three whole rounds of work-groups, whichever is shortest: a round costs
+// its longest work-group, a start and a write of its partials (about seven tiles' time) and its tiles.
+// Rounding the count UP to fill every slot starts another round for the last few work-groups: 260 of them for 4 sequences
+// x 5 drafted tokens (7B 25 %, 4096 tokens): 92.9 us, 240 (twelve splits): 55.9 us; 258 for three sequences of 5001
+// tokens, separated latents: 23.5 us, 237: 16.5 us.  One round alone leaves up to half of the chip idle from about 64
+// groups on.  Steps, us, all lengths equal / between a quarter of the longest and all of it (whose work-groups end at
+// different times, so that more and shorter ones, and even a few too many, cost less):
+//                                     rounded up     one round     this rule
+//   13B 25 %, 33 sequences of 4096    370 / 217 (4)  265 / 257 (3) 260 / 233 (7)
+//   13B 25 %, 43 sequences of 4096    459 / 267 (3)  357 / 349 (2) 332 / 275 (8)
+//   13B 25 %, 43 sequences of 800     157 / 117 (3)  131 / 128 (2) the same
+//   7B 25 %, 52 sequences of 4096     268 / 163 (5)  181 / 176 (4) the same
+//   7B 25 %, 60 sequences of 4096     274 / 217 (5)  196 / 186 (4) the same
+//   7B 25 %, 129 sequences of 2000    366 / 242 (2)  341 / 335 (1) 294 / 258 (5)
+// (the host knows the longest length only).  A start of ten tiles fits equal lengths best; seven leans to shorter rounds.
+// Several rounds are taken where they hold at least a twentieth more work-groups than one round does in their time, which
+// pays for their partials in memory, and `holds` says that elitekv_decode_attn_noalloc keeps every call it takes with one.
+// Of equal counts the smallest (fewest partials to merge).
 // *most: no count for as many tiles or fewer is larger.  The count itself falls wherever equal shares take fewer splits, so
 // the size functions answer with *most: a workspace sized for a longer bound serves every shorter one.
-static int64_t balanced_splits(int64_t groups, int64_t tiles, int64_t slots, int64_t* most) {
-  *most = slots / groups;
-  if (*most > tiles) *most = tiles;
-  if (*most > kMaxSplits) *most = kMaxSplits;
-  if (*most < 1) *most = 1;
+template <typename Holds>
+static int64_t balanced_splits(int64_t groups, int64_t tiles, int64_t slots, Holds holds, int64_t* most) {
+  const int64_t one = std::max<int64_t>(1, std::min<int64_t>(slots / groups, kMaxSplits));
   int64_t best = 1, best_cost = INT64_MAX;
-  for (int64_t rounds = 1; rounds <= 2; ++rounds) {
-    int64_t ns = rounds == 1 ? slots / groups : (slots + groups - 1) / groups;
-    if (ns > tiles) ns = tiles;
-    if (ns > kMaxSplits) ns = kMaxSplits;
-    if (ns < 1) continue;
+  *most = 1;
+  for (int64_t rounds = 1; rounds <= 3; ++rounds) {
+    int64_t ns = std::max<int64_t>(1, std::min<int64_t>(rounds * slots / groups, kMaxSplits));
+    if (rounds > 1 && (20 * ns < 21 * rounds * one || (holds(one) && !holds(ns)))) continue;
+    ns = std::min(ns, tiles);
+    *most = std::max(*most, ns);
     const int64_t per_split = (tiles + ns - 1) / ns;
-    const int64_t cost = (groups * ns + slots - 1) / slots * (4 + per_split);
+    const int64_t cost = (groups * ns + slots - 1) / slots * (7 + per_split);
     if (cost < best_cost) { best = (tiles + per_split - 1) / per_split; best_cost = cost; }
   }
   return best;
@@ -99,6 +113,11 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
   p->d_q = d_ck > 0 ? d_ck : d->d_c;
   p->d_u = d_ck > 0 ? d->d_c - d_ck : d->d_c;
   const size_t dq = p->d_q, du = p->d_u;
+  // does the built-in scratch hold a decode call of this many splits?
+  auto scratch_holds = [&](int64_t n) {
+    DecodePlan t;
+    return plan_decode(d, d_ck, B, max_seq, (int32_t)n, &t) == ELITEKV_OK && t.total <= (size_t)ELITEKV_NOALLOC_SCRATCH_BYTES;
+  };
   // the split maxima, sums and accumulators of `rows` heads per batch row and split; spare: what `most` splits would add
   size_t spare = 0;
   auto lay_partials = [&](size_t at, int64_t splits, int64_t most, size_t rows, size_t row_bytes) {
@@ -135,7 +154,7 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
       // it pays to give every compute unit two (more splits also mean more partials to merge)
       const int64_t slots = (decode_mfma_groups_per_cu(*d) == 2 && Bq * p->head_groups >= 16) ? 2 * kComputeUnits
                                                                                              : kComputeUnits;
-      ns = balanced_splits(Bq * p->head_groups, (seq + 15) / 16, slots, &most);
+      ns = balanced_splits(Bq * p->head_groups, (seq + 15) / 16, slots, scratch_holds, &most);
     }
     p->n_splits = (int32_t)ns;
     p->n_part = (int32_t)ns;
@@ -168,7 +187,8 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     p->head_groups = 1;
     p->tiled = decode_tiled_supported(*d, d_ck);
     int64_t ns = n_splits, most = n_splits;
-    if (ns == 0 && p->tiled) ns = balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits, &most);
+    if (ns == 0 && p->tiled) ns = balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits,
+                                                  scratch_holds, &most);
     else if (ns == 0) ns = most = auto_splits_generic(d, Bq, seq);
     p->n_splits = (int32_t)ns;
     p->n_part = p->n_splits;

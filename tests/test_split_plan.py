@@ -1,5 +1,5 @@
-"""The automatic split count of the matrix-core decode path: no second round of work-groups for a few of them, no
-more splits than tiles, never zero."""
+"""The automatic split count of the matrix-core decode path: whole rounds of work-groups, no more splits than tiles, never
+zero; the workspace it asks for."""
 import pytest
 
 import paper_2503_01586_amd as ekv
@@ -7,18 +7,20 @@ import paper_2503_01586_amd as ekv
 
 @pytest.mark.parametrize("shape,slots_per_cu", [((4096, 32, 128, 8, 1536), 1), ((5120, 40, 128, 8, 1920), 1),
                                                 ((4096, 32, 128, 4, 768), 2)])
-@pytest.mark.parametrize("B", [1, 2, 3, 5, 16, 20, 33, 64, 127, 128, 129, 255, 256, 257, 700])
+@pytest.mark.parametrize("B", [1, 2, 3, 5, 16, 20, 33, 43, 64, 86, 127, 128, 129, 150, 180, 255, 256, 257, 700])
 @pytest.mark.parametrize("S", [1, 16, 17, 256, 5001, 32768])
-def test_one_round_of_work_groups(shape, slots_per_cu, B, S):
+def test_whole_rounds_of_work_groups(shape, slots_per_cu, B, S):
     dims = ekv.make_dims(*shape, "bf16")
     ns = ekv.elitekv_decode_auto_splits(dims, B, S)
     groups, tiles = B * ((shape[1] + 31) // 32), (S + 15) // 16
     slots = 256 * (slots_per_cu if groups >= 16 else 1)
     assert 1 <= ns <= tiles
-    assert ns == 1 or groups * ns <= slots or groups > slots // 2
-    # as many splits as one round holds, or as few as give the same tiles per split
-    most = min(tiles, max(1, slots // groups))
-    assert -(-tiles // ns) <= -(-tiles // most)
+    # as many splits as one, two or three rounds hold, or as few as give the same tiles per split
+    rounds = [min(tiles, max(1, k * slots // groups)) for k in (1, 2, 3)]
+    assert -(-tiles // ns) in [-(-tiles // most) for most in rounds]
+    if groups <= slots and S == 32768:
+        # long sequences leave at most a quarter of the chip idle
+        assert groups * ns >= 0.74 * slots * -(-groups * ns // slots)
 
 
 # name: (d_model, n_heads, head_dim, r, d_c, dtype, d_ck of the separated forms)
@@ -52,3 +54,18 @@ def test_workspace_of_a_longer_bound_covers_every_shorter_one(name, B):
             now = of(S)
             assert now >= before, (form, S, before, now)
             before = now
+
+
+@pytest.mark.parametrize("d_c", [128, 512, 1024, 1536])
+@pytest.mark.parametrize("n_h", [16, 32, 40])
+def test_several_rounds_stay_inside_the_built_in_scratch(d_c, n_h):
+    """Where the scratch of elitekv_decode_attn_noalloc holds the partials of one round, it holds those of the count taken."""
+    dims = ekv.make_dims(4096, n_h, 128, 8, d_c, "bf16")
+    need = lambda B, S, ns: ekv.elitekv_decode_workspace_bytes(dims, B, S, ns)
+    for B in range(1, 260):
+        groups = B * ((n_h + 31) // 32)
+        for S in (40, 800, 32768):
+            slots = 512 if d_c <= 768 and groups >= 16 else 256  # narrow latents: up to two work-groups per compute unit
+            one = min(-(-slots // groups), (S + 15) // 16)       # one round, rounded up
+            if need(B, S, one) <= ekv.NOALLOC_SCRATCH_BYTES:
+                assert need(B, S, ekv.elitekv_decode_auto_splits(dims, B, S)) <= ekv.NOALLOC_SCRATCH_BYTES, (B, S)
