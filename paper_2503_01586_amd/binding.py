@@ -48,6 +48,8 @@ def _load():
         "elitekv_validate_elite_idx": (C.c_int, [DP, P]),
         "elitekv_append_workspace_bytes": (SZ, [DP, I64]),
         "elitekv_append": (C.c_int, [DP, P, P, P, I64, P, P, P, P, P, I64, P, SZ, P]),
+        "elitekv_append_gemm_tile": (I32, [DP, I32, I64]),
+        "elitekv_prefill_gemm_tile": (I32, [DP, I32, I64, I64]),
         "elitekv_decode_path": (C.c_int, [DP, I32]),
         "elitekv_decode_auto_splits": (I32, [DP, I64, I64]),
         "elitekv_decode_workspace_bytes": (SZ, [DP, I64, I64, I32]),
@@ -171,7 +173,23 @@ def elitekv_append(dims, x, pos, slot, W_ke, W_dkv, elite_idx, ke_plane, c_plane
     _check(st, "elitekv_append")
 
 
+(TILE_NONE, TILE_64_128, TILE_128_128, TILE_256_128, TILE_256_256, TILE_256_256_WIDE, TILE_STAGED_64_128,
+ TILE_STAGED_256_128) = range(8)
 PATH_GENERIC, PATH_MATRIX_CORE = 0, 1
+
+
+def elitekv_append_gemm_tile(dims, T, d_ck=0) -> int:
+    st = _lib.elitekv_append_gemm_tile(C.byref(dims), int(d_ck), int(T))
+    if st < 0:
+        raise EliteKVError(st, "elitekv_append_gemm_tile")
+    return st
+
+
+def elitekv_prefill_gemm_tile(dims, T, max_seq_len, d_ck=0) -> int:
+    st = _lib.elitekv_prefill_gemm_tile(C.byref(dims), int(d_ck), int(T), int(max_seq_len))
+    if st < 0:
+        raise EliteKVError(st, "elitekv_prefill_gemm_tile")
+    return st
 
 
 def elitekv_decode_path(dims, d_ck=0) -> int:

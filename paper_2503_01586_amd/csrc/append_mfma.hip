@@ -79,9 +79,8 @@ hipError_t launch_append_skinny(const AppendArgs& a, hipStream_t stream) {
 // Work-group tile: 128 output columns x (64 * WN) tokens, 2 x 2 waves, each wave 64 columns x
 // (32 * WN) tokens = 2 x WN accumulator tiles of 32 x 32.  Both operands go through LDS in
 // double-buffered stages of 64 contraction rows (global -> registers -> LDS, the loads of stage
-// s+1 in flight while stage s is multiplied).  The epilogue rotates the elite pairs in registers
-// (a lane holds one token and four consecutive columns per group) and stores bf16 rows straight
-// into the cache planes.
+// s+1 in flight while stage s is multiplied).  The epilogue (gemm_store, shared by all the GEMM kernels) takes the tile
+// through LDS, rotates the elite pairs there and stores whole pieces of bf16 rows.
 // ---------------------------------------------------------------------------------------------
 constexpr int kGmCols = 128;                   // output columns per work-group
 constexpr int kGmStage = 64;                   // contraction rows per stage
@@ -808,49 +807,59 @@ static hipError_t launch_gemm_wide(const AppendArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream) {
+int append_gemm_tile(const AppendArgs& a) {
   const elitekv_dims& d = a.dims;
   const int64_t col_blocks = (2 * d.r * d.n_heads + d.d_c) / kGmCols;
+  if (d.d_model % kGdStage)
+    return col_blocks * ((a.T + 255) / 256) >= 1024 ? ELITEKV_TILE_STAGED_256_128 : ELITEKV_TILE_STAGED_64_128;
   const int split = 2 * d.r * d.n_heads + a.d_ck;              // first column of W_dkv2
+  const int N = 2 * d.r * d.n_heads + d.d_c;
+  const double K = a.d2 > d.d_model ? a.d2 : d.d_model;
+  // The tile whose rounds of work-groups cost least.  A round's cost in us, fixed part (first stages from cold memory,
+  // epilogue) + contraction rows, fitted to measurements from 1000 to 32768 tokens, 768 to 5120 rows, 1024 to 9600 columns:
+  //   tokens x columns     work-groups at once     a round        measured, 1536 x 7680 rows x columns, 1000 / 2048 / 8192 tokens
+  //   256 x 256, 4 waves   256                     20 + 0.021 K   51 / 62 / 208 us
+  //   256 x 256, 8 waves   256                     13 + 0.025 K   51 / 61 / 211
+  //   256 x 128            256                     10 + 0.0145 K  35 / 66 / 232
+  //   128 x 128            256                     1.5 + 0.0118 K 39 / 78 / 270
+  //    64 x 128            512                     3 + 0.0128 K   41 / 82 / 296
+  //                        256 (alone on its unit) 3 + 0.0095 K   42 against 47 us of 128 x 128, 4096 x 1024, 2048 tokens
+  // (4096 x 2048: 99 / 115 / 73 / 50 / 56 at 2048 tokens, 493 / 521 / 620 / 727 / 815 at 32768.)
+  auto cost = [&](int tokens, int cols, int slots, double fixed, double per_row) {
+    const GemmTileMap m = gemm_tile_map((a.T + tokens - 1) / tokens, (N + cols - 1) / cols);
+    const int64_t per_xcd = (int64_t)m.tb_x * m.cb_x;
+    return (double)((per_xcd + slots / 8 - 1) / (slots / 8)) * (fixed + per_row * K);
+  };
+  const bool wide_ok = N >= 256 && (a.d2 == 0 || (N % 256 == 0 && split % 256 == 0));
+  const double c[5] = {wide_ok ? cost(256, 256, 256, 20., .021) : 1e30, wide_ok ? cost(256, 256, 256, 13., .025) : 1e30,
+                       cost(256, 128, 256, 10., .0145), cost(128, 128, 256, 1.5, .0118),
+                       col_blocks * ((a.T + 63) / 64) <= 256 ? cost(64, 128, 256, 3., .0095) : cost(64, 128, 512, 3., .0128)};
+  constexpr int tile[5] = {ELITEKV_TILE_256_256_WIDE, ELITEKV_TILE_256_256, ELITEKV_TILE_256_128, ELITEKV_TILE_128_128,
+                           ELITEKV_TILE_64_128};
+  int best = 4;                                                // of equal costs the smaller tile
+  for (int i = 3; i >= 0; --i)
+    if (c[i] < c[best]) best = i;
+  return tile[best];
+}
+
+hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream) {
+  const elitekv_dims& d = a.dims;
   if (a.d2 > 0 || a.x_ld > 0) {
     // column slices of wider rows: only the direct-load kernels take them, with whole stages in both slices
     // and no 128-column block across the two matrices
+    const int split = 2 * d.r * d.n_heads + a.d_ck;
     if (d.d_model % kGdStage || a.d2 % kGdStage || a.x_off2 % 8 || a.x_ld % 8 || (a.d2 > 0 && split % kGmCols))
       return hipErrorInvalidValue;
   }
-  if (d.d_model % kGdStage == 0) {
-    const int N = 2 * d.r * d.n_heads + d.d_c;
-    const double K = a.d2 > d.d_model ? a.d2 : d.d_model;
-    // The tile whose rounds of work-groups cost least.  A round's cost in us, fixed part (first stages from cold memory,
-    // epilogue) + contraction rows, fitted to measurements from 1000 to 32768 tokens, 768 to 5120 rows, 1024 to 9600 columns:
-    //   tokens x columns     work-groups at once     a round        measured, 1536 x 7680 rows x columns, 1000 / 2048 / 8192 tokens
-    //   256 x 256, 4 waves   256                     20 + 0.021 K   51 / 62 / 208 us
-    //   256 x 256, 8 waves   256                     13 + 0.025 K   51 / 61 / 211
-    //   256 x 128            256                     10 + 0.0145 K  35 / 66 / 232
-    //   128 x 128            256                     1.5 + 0.0118 K 39 / 78 / 270
-    //    64 x 128            512                     3 + 0.0128 K   41 / 82 / 296
-    //                        256 (alone on its unit) 3 + 0.0095 K   42 against 47 us of 128 x 128, 4096 x 1024, 2048 tokens
-    // (4096 x 2048: 99 / 115 / 73 / 50 / 56 at 2048 tokens, 493 / 521 / 620 / 727 / 815 at 32768.)
-    auto cost = [&](int tokens, int cols, int slots, double fixed, double per_row) {
-      const GemmTileMap m = gemm_tile_map((a.T + tokens - 1) / tokens, (N + cols - 1) / cols);
-      const int64_t per_xcd = (int64_t)m.tb_x * m.cb_x;
-      return (double)((per_xcd + slots / 8 - 1) / (slots / 8)) * (fixed + per_row * K);
-    };
-    const bool wide_ok = N >= 256 && (a.d2 == 0 || (N % 256 == 0 && split % 256 == 0));
-    const double c[5] = {wide_ok ? cost(256, 256, 256, 20., .021) : 1e30, wide_ok ? cost(256, 256, 256, 13., .025) : 1e30,
-                         cost(256, 128, 256, 10., .0145), cost(128, 128, 256, 1.5, .0118),
-                         col_blocks * ((a.T + 63) / 64) <= 256 ? cost(64, 128, 256, 3., .0095) : cost(64, 128, 512, 3., .0128)};
-    int best = 4;                                              // of equal costs the smaller tile
-    for (int i = 3; i >= 0; --i)
-      if (c[i] < c[best]) best = i;
-    if (best == 0) return launch_gemm_wide(a, stream);
-    if (best == 1) return launch_gemm_dma<4, 4, 2, 4>(a, stream);
-    if (best == 2) return launch_gemm_dma<2, 6, 4, 2>(a, stream);
-    if (best == 3) return launch_gemm_dma<1, 6, 4, 2, 2, 2>(a, stream);
-    return launch_gemm_dma<1, 6, 2, 2>(a, stream);
+  switch (append_gemm_tile(a)) {
+    case ELITEKV_TILE_256_256_WIDE: return launch_gemm_wide(a, stream);
+    case ELITEKV_TILE_256_256: return launch_gemm_dma<4, 4, 2, 4>(a, stream);
+    case ELITEKV_TILE_256_128: return launch_gemm_dma<2, 6, 4, 2>(a, stream);
+    case ELITEKV_TILE_128_128: return launch_gemm_dma<1, 6, 4, 2, 2, 2>(a, stream);
+    case ELITEKV_TILE_64_128: return launch_gemm_dma<1, 6, 2, 2>(a, stream);
+    case ELITEKV_TILE_STAGED_256_128: return launch_gemm_wn<4>(a, stream);
+    default: return launch_gemm_wn<1>(a, stream);
   }
-  if (col_blocks * ((a.T + 255) / 256) >= 1024) return launch_gemm_wn<4>(a, stream);
-  return launch_gemm_wn<1>(a, stream);
 }
 
 }  // namespace ekv

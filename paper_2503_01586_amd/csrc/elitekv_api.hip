@@ -362,6 +362,23 @@ int elitekv_append(const elitekv_dims* dims, const void* x, const int32_t* pos, 
                      plane_rows, ws, ws_bytes, hip_stream);
 }
 
+int32_t elitekv_append_gemm_tile(const elitekv_dims* dims, int32_t d_ck, int64_t T) {
+  const int st = check_dims(dims);
+  if (st) return st;
+  if (T < 0 || d_ck < 0 || d_ck >= dims->d_c) return ELITEKV_EINVAL;
+  AppendArgs a{};
+  a.dims = *dims; a.d_ck = d_ck > 0 ? d_ck : dims->d_c; a.T = T;
+  return append_gemm_supported(*dims, T, a.d_ck) ? append_gemm_tile(a) : ELITEKV_TILE_NONE;
+}
+
+int32_t elitekv_prefill_gemm_tile(const elitekv_dims* dims, int32_t d_ck, int64_t T, int64_t max_seq_len) {
+  const int st = check_dims(dims);
+  if (st) return st;
+  if (T < 1 || max_seq_len < 0 || d_ck < 0 || d_ck >= dims->d_c) return ELITEKV_EINVAL;
+  if (!prefill_flash_supported(*dims, d_ck, T, max_seq_len)) return ELITEKV_TILE_NONE;
+  return append_gemm_tile(prefill_rebuild_args(*dims, d_ck, max_seq_len));
+}
+
 int elitekv_decode_path(const elitekv_dims* dims, int32_t d_ck) {
   DecodePlan p;
   const int st = plan_decode(dims, d_ck, 1, 16, 0, &p);

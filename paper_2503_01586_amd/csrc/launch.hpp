@@ -141,6 +141,7 @@ size_t append_skinny_workspace(const elitekv_dims& d, int64_t T);
 hipError_t launch_append_skinny(const AppendArgs& a, hipStream_t stream);
 bool append_gemm_supported(const elitekv_dims& d, int64_t T, int d_ck);
 hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream);
+int append_gemm_tile(const AppendArgs& a);      // the elitekv_gemm_tile that launch_append_gemm takes
 bool append_tiled_supported(const elitekv_dims& d, int64_t T, int d_ck);
 hipError_t launch_append_tiled(const AppendArgs& a, hipStream_t stream);
 bool decode_tiled_supported(const elitekv_dims& d, int d_ck);
@@ -177,6 +178,7 @@ hipError_t launch_decode_mfma(const DecodeArgs& a, const DecodePlan& p, hipStrea
 // many queries per sequence: keys and values rebuilt from the latent once per cached row (with the append's
 // matrix-core GEMM), then flash attention; a.B = B * T query rows, a.seq_len = the visible rows of each
 bool prefill_flash_supported(const elitekv_dims& d, int d_ck, int64_t T, int64_t max_seq_len);
+AppendArgs prefill_rebuild_args(const elitekv_dims& d, int d_ck, int64_t rows);   // the rebuild's GEMM, without its pointers
 size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len);
 hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipStream_t stream);
 hipError_t launch_mha_decode(const MhaArgs& a, hipStream_t stream);

@@ -389,6 +389,15 @@ bool prefill_flash_supported(const elitekv_dims& d, int d_ck, int64_t T, int64_t
   return append_gemm_supported(g, max_seq_len, d.n_heads * (d.head_dim - 2 * d.r));
 }
 
+AppendArgs prefill_rebuild_args(const elitekv_dims& d, int d_ck, int64_t rows) {
+  AppendArgs g{};
+  g.dims = rebuild_dims(d); g.d_ck = d.n_heads * (d.head_dim - 2 * d.r); g.T = rows;
+  if (d_ck > 0) {                                              // [c^k | c^v] rows: keys from c^k, values from c^v
+    g.dims.d_model = d_ck; g.x_ld = d.d_c; g.x_off2 = d_ck; g.d2 = d.d_c - d_ck;
+  }
+  return g;
+}
+
 static size_t pf_align(size_t v) { return (v + 255) / 256 * 256; }
 
 // workspace: the rebuilt K/V rows of all sequences
@@ -433,13 +442,10 @@ hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipSt
     const int64_t want = packed ? B * S : S;
     const int64_t rows = want < a.plane_rows - row0 ? want : a.plane_rows - row0;
     if (rows <= 0) continue;
-    AppendArgs g;
-    g.dims = gd; g.d_ck = (int32_t)NK; g.W_dkv = a.W_uk; g.W_dkv2 = a.W_uv; g.W_ke = nullptr;
-    if (a.d_ck > 0) {                                          // [c^k | c^v] rows: keys from c^k, values from c^v
-      g.dims.d_model = a.d_ck; g.x_ld = d.d_c; g.x_off2 = a.d_ck; g.d2 = d.d_c - a.d_ck;
-    }
-    g.x = (const bf16_t*)a.c_plane + row0 * d.d_c; g.pos = nullptr; g.slot = nullptr; g.T = rows;   // rows written in place
-    g.elite_idx = nullptr; g.ke_plane = nullptr; g.c_plane = kv + b * S * NKV; g.plane_rows = want; g.ws = nullptr;
+    AppendArgs g = prefill_rebuild_args(d, a.d_ck, rows);
+    g.W_dkv = a.W_uk; g.W_dkv2 = a.W_uv;
+    g.x = (const bf16_t*)a.c_plane + row0 * d.d_c;             // (no slots: rows written in place)
+    g.c_plane = kv + b * S * NKV; g.plane_rows = want;
     e = launch_append_gemm(g, stream);
     if (e != hipSuccess) return e;
   }

@@ -396,3 +396,16 @@ def test_search_refuses_less_than_it_needs():
     need = ekv.elitekv_ropelite_search_min_workspace_bytes(300, 8, 64, 4)
     assert lib.elitekv_ropelite_search(FAKE, FAKE, FAKE, 300, 8, 64, 4, 10000.0, FAKE, None, FAKE, need - 1,
                                        None) == ekv.EWORKSPACE
+
+
+def test_gemm_tile_query():
+    mk = lambda d, d_c, dtype="bf16": ekv.make_dims(d, 32, 128, 8, d_c, dtype)
+    assert ekv.elitekv_append_gemm_tile(mk(4096, 1536), 64) == ekv.TILE_NONE             # the small-batch append
+    assert ekv.elitekv_append_gemm_tile(mk(4096, 1536, "fp32"), 2048) == ekv.TILE_NONE
+    assert ekv.elitekv_append_gemm_tile(mk(4096, 1536), 32768) == ekv.TILE_256_256_WIDE
+    assert ekv.elitekv_append_gemm_tile(mk(4096, 1536), 32768, 768) == ekv.TILE_256_256_WIDE
+    assert ekv.elitekv_prefill_gemm_tile(mk(4096, 1536), 47, 2048) == ekv.TILE_NONE      # few queries: the absorbed form
+    assert ekv.elitekv_prefill_gemm_tile(mk(4096, 1536), 2048, 8192) != ekv.TILE_NONE
+    for bad in (dict(T=-1), dict(T=100, d_ck=1536), dict(T=100, d_ck=-1)):
+        with pytest.raises(ekv.EliteKVError):
+            ekv.elitekv_append_gemm_tile(mk(4096, 1536), **bad)
