@@ -1,6 +1,7 @@
 """The search's round kernel at the edges of its tiles (16 tokens, blocks of 32 queries, pieces of key tiles), and samples
 too long for the kept residuals, against the float64 oracle: every choice an arg-min of the oracle's distances for the
-GPU's own earlier choices, every reported distance the oracle's, to 2e-4 (fp32 sums of up to 10^7 terms)."""
+GPU's own earlier choices, every reported distance the oracle's, to 2e-4 (fp32 sums of up to 10^7 terms) and the rounding of
+the residuals."""
 import numpy as np
 import pytest
 
@@ -11,23 +12,37 @@ from test_gpu_search import RTOL, gpu_search
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,n_h,d_h,r", [(1, 3, 16, 2), (16, 5, 8, 4), (17, 1, 128, 3), (33, 2, 66, 5), (48, 7, 16, 8),
-                                         (129, 1, 64, 32), (530, 1, 16, 3), (4097, 1, 4, 2)])
+def residual_rounding(q, k, h):
+    """What rounding can make of a distance that vanishes (the last chunk leaves nothing): a pair's residual is a sum of d_h / 2
+    chunks of two scores each, the vectors rotated and rounded before, every operation to 2^-24 of the terms so far."""
+    T, _, d_h = q.shape
+    size = lambda v: np.linalg.norm(v[:, h].reshape(T, d_h // 2, 2), axis=2)     # [T, chunks]
+    terms = 2.0 * d_h ** -0.5 * float(np.sum(size(q) * np.cumsum(size(k), axis=0)))
+    return (d_h // 2 + 16) * 2.0 ** -24 * terms
+
+
+@pytest.mark.parametrize("T,n_h,d_h,r", [
+    (1, 3, 16, 2), (16, 5, 8, 4), (17, 1, 128, 3), (33, 2, 66, 5), (48, 7, 16, 8), (129, 1, 64, 32), (530, 1, 16, 3),
+    (395, 64, 16, 3),        # pieces of sixteen key tiles, residuals kept over three rounds
+    (4097, 1, 4, 2),         # longer than what keeps the residuals; one token in the last tile
+])
 def test_search_at_tile_edges(T, n_h, d_h, r):
     rng = np.random.default_rng(T + d_h)
     mag = np.exp(rng.normal(0.0, 0.7, size=(1, n_h, d_h // 2))).repeat(2, axis=2)
     pos = np.sort(rng.choice(3 * T, size=T, replace=False))
-    q64, k64, elite, dist = gpu_search(rng.standard_normal((T, n_h, d_h)) * mag, rng.standard_normal((T, n_h, d_h)) * mag,
-                                       pos, r, 10000.0)
+    q, k = rng.standard_normal((T, n_h, d_h)) * mag, rng.standard_normal((T, n_h, d_h)) * mag
+    last = (T - 1) // 16 * 16                    # a lost last tile would show in every distance
+    q[last:] *= 8.0
+    k[last:] *= 8.0
+    q64, k64, elite, dist = gpu_search(q, k, pos, r, 10000.0)
     for h in range(n_h):
         assert len(set(elite[h].tolist())) == r and elite[h].min() >= 0 and elite[h].max() < d_h // 2
+        floor = residual_rounding(q64, k64, h)
         for i in range(r):
             ref = orc.ropelite_distances(q64, k64, pos, elite[h, :i], h, d_h, 10000.0)
             c = int(elite[h, i])
-            # a distance can vanish (the last chunk leaves nothing): the bound's floor is the scale of the largest one
-            floor = 1e-6 * float(np.max(ref[np.isfinite(ref)])) + 1e-6
-            assert ref[c] <= float(np.min(ref)) * (1 + RTOL) + floor * T, (h, i)
-            assert abs(dist[h, i] - ref[c]) <= RTOL * ref[c] + floor * T, (h, i)
+            assert ref[c] <= float(np.min(ref)) * (1 + RTOL) + floor, (h, i)
+            assert abs(dist[h, i] - ref[c]) <= RTOL * ref[c] + floor, (h, i)
 
 
 @pytest.mark.parametrize("T,n_h,d_h,r", [(16, 5, 8, 4), (129, 1, 64, 32), (300, 8, 128, 8), (2048, 1, 16, 2)])
