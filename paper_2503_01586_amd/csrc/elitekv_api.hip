@@ -368,7 +368,10 @@ int32_t elitekv_append_gemm_tile(const elitekv_dims* dims, int32_t d_ck, int64_t
   if (T < 0 || d_ck < 0 || d_ck >= dims->d_c) return ELITEKV_EINVAL;
   AppendArgs a{};
   a.dims = *dims; a.d_ck = d_ck > 0 ? d_ck : dims->d_c; a.T = T;
-  return append_gemm_supported(*dims, T, a.d_ck) ? append_gemm_tile(a) : ELITEKV_TILE_NONE;
+  if (T == 0) return ELITEKV_TILE_NONE;
+  if (append_gemm_supported(*dims, T, a.d_ck)) return append_gemm_tile(a);
+  if (append_skinny_supported(*dims, T, a.d_ck) || append_small_supported(*dims, T, a.d_ck)) return ELITEKV_TILE_NONE;
+  return append_tiled_supported(*dims, T, a.d_ck) ? ELITEKV_TILE_FP32 : ELITEKV_TILE_NONE;
 }
 
 int32_t elitekv_prefill_gemm_tile(const elitekv_dims* dims, int32_t d_ck, int64_t T, int64_t max_seq_len) {

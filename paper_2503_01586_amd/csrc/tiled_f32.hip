@@ -104,13 +104,27 @@ __global__ __launch_bounds__(kTaThreads) void append_tiled_kernel(
                            elite_idx, ke_plane, c_plane, plane_rows, d, n_h, d_h, r, d_c, rope);
 }
 
-// Up to kTaMaxTokens tokens: every tile of eight tokens reads the weights again (from the Infinity Cache), which the
-// serial kernel does too, but more slowly.  Measured (7B 25 %, fp32, us, this kernel / append_generic_kernel): 
-// 8 tokens 18 / 560, 64: 64, 128: 124, 256: 244 / about 420, 512: about 490 / 418.
+// Up to kTaMaxTokens tokens, and where it costs less than append_generic_kernel.  Every tile of eight tokens reads the
+// weights again and a work-group has a start of its own, so the cost goes with the work-groups; the serial kernel's goes
+// with the contraction rows, and doubles where the token tiles read more weights than the L2s hold.  Fitted, us, to 32 to
+// 4096 rows x 32 to 4144 columns x 1 to 256 tokens in both types: never more than a tenth or two us behind the faster one.
+// This kernel / append_generic_kernel, fp32:
+//   rows x columns    1 token     8 tokens    64 tokens    256 tokens
+//     64 x 2512       8.3 / 8.8   10 / 10      41 / 10     150 / 10
+//    512 x 1520       8 / 30      10 / 33      26 / 34      96 / 34
+//   1024 x 2512       8 / 56      12 / 60      56 / 111    198 / 109
+//   4096 x 2048       14 / 400    18 / 430     64 / 425    244 / 420
 constexpr int64_t kTaMaxTokens = 256;
+static bool append_tiled_pays(const elitekv_dims& d, int64_t T) {
+  const double rows = d.d_model;
+  const int64_t N = 2 * (int64_t)d.r * d.n_heads + d.d_c, groups = N / kTaCols * ((T + 7) / 8);
+  const int64_t at_once = T <= 4 ? 512 : 256;
+  const int64_t bytes = N * d.d_model * (d.dtype == ELITEKV_FP32 ? 4 : 2), tiles8 = T < 64 ? T : 64;
+  return (groups + at_once - 1) / at_once * (7. + .003 * rows) <= 3. + (bytes * tiles8 > 64LL * (4 << 20) ? .105 : .06) * rows;
+}
 bool append_tiled_supported(const elitekv_dims& d, int64_t T, int d_ck) {
   return T <= kTaMaxTokens && d.d_model % 4 == 0 && (2 * d.r * d.n_heads) % kTaCols == 0 && d_ck % kTaCols == 0 &&
-         (d.d_c - d_ck) % kTaCols == 0;
+         (d.d_c - d_ck) % kTaCols == 0 && append_tiled_pays(d, T);
 }
 
 template <typename T>

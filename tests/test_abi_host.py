@@ -402,6 +402,7 @@ def test_gemm_tile_query():
     mk = lambda d, d_c, dtype="bf16": ekv.make_dims(d, 32, 128, 8, d_c, dtype)
     assert ekv.elitekv_append_gemm_tile(mk(4096, 1536), 64) == ekv.TILE_NONE             # the small-batch append
     assert ekv.elitekv_append_gemm_tile(mk(4096, 1536, "fp32"), 2048) == ekv.TILE_NONE
+    assert ekv.elitekv_append_gemm_tile(mk(4096, 1536, "fp32"), 0) == ekv.TILE_NONE
     assert ekv.elitekv_append_gemm_tile(mk(4096, 1536), 32768) == ekv.TILE_256_256_WIDE
     assert ekv.elitekv_append_gemm_tile(mk(4096, 1536), 32768, 768) == ekv.TILE_256_256_WIDE
     assert ekv.elitekv_prefill_gemm_tile(mk(4096, 1536), 47, 2048) == ekv.TILE_NONE      # few queries: the absorbed form
@@ -409,3 +410,16 @@ def test_gemm_tile_query():
     for bad in (dict(T=-1), dict(T=100, d_ck=1536), dict(T=100, d_ck=-1)):
         with pytest.raises(ekv.EliteKVError):
             ekv.elitekv_append_gemm_tile(mk(4096, 1536), **bad)
+
+
+def test_short_contractions_of_many_tokens_take_the_serial_append():
+    """The tiled fp32 append pays by its work-groups, the serial one by its contraction rows."""
+    tile = lambda d, n_h, r, d_c, T, dtype="fp32": ekv.elitekv_append_gemm_tile(ekv.make_dims(d, n_h, 64, r, d_c, dtype), T)
+    for dtype in ("fp32", "bf16"):
+        assert tile(64, 32, 8, 2000, 256, dtype) == ekv.TILE_NONE          # 10 us against 150
+        assert tile(512, 32, 8, 2000, 128, dtype) == ekv.TILE_NONE         # 57 against 82 (fp32), 35 against 79
+        assert tile(512, 32, 8, 2000, 8, dtype) == ekv.TILE_FP32           # 33 against 10
+        assert tile(4096, 32, 8, 2000, 128, dtype) == ekv.TILE_FP32        # 423 against 210
+    assert tile(1024, 3, 8, 1200, 256, "bf16") == ekv.TILE_NONE            # 65 against 92
+    assert tile(4096, 32, 8, 1536, 256) == ekv.TILE_FP32                   # 420 against 244
+    assert tile(4096, 32, 8, 1536, 257) == ekv.TILE_NONE

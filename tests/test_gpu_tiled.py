@@ -16,13 +16,13 @@ pytestmark = pytest.mark.gpu
 # and many 16-byte pieces; sequences at the edges of a tile of 16; more splits than tiles
 CASES = {
     "one_block": (64, 3, 32, 2, 0, 16, "fp32", [1, 15, 16, 17, 0]),
-    "seventeen_blocks_17_heads": (36, 17, 64, 0, 0, 272, "fp32", [33, 5]),
+    "seventeen_blocks_17_heads": (100, 17, 64, 0, 0, 272, "fp32", [33, 5]),
     "widest_r64": (32, 16, 256, 64, 0, 2048, "fp32", [40]),
-    "all_elite": (64, 8, 32, 16, 0, 48, "fp32", [50, 7, 129]),
+    "all_elite": (92, 8, 32, 16, 0, 48, "fp32", [50, 7, 129]),
     "7b": (128, 32, 128, 8, 0, 1536, "fp32", [100, 1]),
     "13b": (128, 40, 128, 8, 0, 1920, "fp32", [70]),
     "separated": (64, 5, 64, 4, 16, 144, "fp32", [0, 64, 65, 3, 100]),
-    "separated_wide_values": (64, 32, 128, 8, 1024, 1536, "fp32", [37]),
+    "separated_wide_values": (84, 32, 128, 8, 1024, 1536, "fp32", [37]),
     "bf16_320": (64, 8, 64, 4, 0, 320, "bf16", [33, 50, 200]),
     "bf16_13b_separated": (64, 40, 128, 8, 960, 1920, "bf16", [49]),
 }
@@ -72,11 +72,14 @@ def test_tiled_decode_matches_oracle(name):
         assert orc.max_abs_rel(host64(out), ref) <= TOL[dt], ns
 
 
-@pytest.mark.parametrize("name", ["one_block", "seventeen_blocks_17_heads", "all_elite", "7b", "separated"])
+@pytest.mark.parametrize("name", ["one_block", "seventeen_blocks_17_heads", "all_elite", "7b", "separated",
+                                  "separated_wide_values"])
 @pytest.mark.parametrize("T", [1, 2, 3, 5, 9, 257])     # token tiles of 1, 2, 4 and 8; the serial kernel beyond 256
 def test_tiled_append_matches_oracle(name, T):
     d, n_h, d_h, r, d_ck, d_c, dt, _ = CASES[name]
     dims = ekv.make_dims(d, n_h, d_h, r, d_c, dt)
+    tiled = T <= 256 and 2 * r * n_h % 16 == 0          # whole slices of 16 columns; the others take the serial kernel
+    assert ekv.elitekv_append_gemm_tile(dims, T, d_ck) == (ekv.TILE_FP32 if tiled else ekv.TILE_NONE)
     rng, idx, _, t = _draw(name)
     x, pos = dev(rng.standard_normal((T, d)), dt), rng.integers(0, 5000, T)
     slot = rng.permutation(T + 4)[:T]
