@@ -185,11 +185,13 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     if (block) return ELITEKV_EUNSUPPORTED;
     p->mfma = 0;
     p->head_groups = 1;
-    p->tiled = decode_tiled_supported(*d, d_ck);
+    p->tiled = decode_tiled_supported(*d, d_ck, Bq, seq);
+    const bool shorter_tiled = p->tiled || decode_tiled_supported(*d, d_ck, Bq, 1);     // with a shorter bound, at least
     int64_t ns = n_splits, most = n_splits;
-    if (ns == 0 && p->tiled) ns = balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits,
-                                                  scratch_holds, &most);
-    else if (ns == 0) ns = most = auto_splits_generic(d, Bq, seq);
+    if (ns == 0 && shorter_tiled) ns = balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits,
+                                                       scratch_holds, &most);
+    if (n_splits == 0 && !p->tiled) ns = auto_splits_generic(d, Bq, seq);
+    most = std::max(most, ns);
     p->n_splits = (int32_t)ns;
     p->n_part = p->n_splits;
     int64_t chunk = (seq + p->n_splits - 1) / p->n_splits;
@@ -199,7 +201,9 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     off = lay_partials(off, ns, most, nh, du * sizeof(float));
     p->ubar_rows = tight ? p->n_part : 1;
     p->off_opart = tight ? p->off_u : off;
-    if (p->tiled && !tight) off = align_up(off + Bz * nh * du * sizeof(float), 256);
+    const size_t merged = align_up(Bz * nh * du * sizeof(float), 256);
+    if (p->tiled && !tight) off += merged;
+    else if (shorter_tiled && !tight) spare += merged;
   }
   p->total = off;
   p->reserve = off + spare;

@@ -144,7 +144,7 @@ hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream);
 int append_gemm_tile(const AppendArgs& a);      // the elitekv_gemm_tile that launch_append_gemm takes
 bool append_tiled_supported(const elitekv_dims& d, int64_t T, int d_ck);
 hipError_t launch_append_tiled(const AppendArgs& a, hipStream_t stream);
-bool decode_tiled_supported(const elitekv_dims& d, int d_ck);
+bool decode_tiled_supported(const elitekv_dims& d, int d_ck, int64_t rows, int64_t max_seq);
 hipError_t launch_decode_tiled(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 bool front_tiled_supported(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p);
 hipError_t launch_front_tiled(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);

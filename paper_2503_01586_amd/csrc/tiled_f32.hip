@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kTaThreads) void front_tiled_kernel(
 // whose keys differ from head to head, is added by vector instructions, two tokens per wave.  Bound by the fp32 matrix
 // cores (d_c / 2 instructions of 32 cycles per tile and 16 heads) and, at a few tiles per work-group, by the start.
 // Two sequences of 1000 tokens, 7B 25 %: 18 us (attn_generic_kernel 190).
-constexpr int kTtTok = 16, kTtWaves = 8, kTtKeRegs = 4;
+constexpr int kTtTok = 16, kTtWaves = 8, kTtKeRegs = 4, kTtComputeUnits = 256;
 
 template <typename T, int CPW>
 __global__ __launch_bounds__(kTtWaves * 64) void attn_tiled_kernel(
@@ -526,7 +526,13 @@ __global__ __launch_bounds__(1024) void upproj_tiled_kernel(const float* __restr
 
 // Widths in whole blocks of 16 columns (a block is a score block, a value block or both), rows of W_uk and elite rows in
 // whole 16-byte (fp32) / 8-byte (bf16) pieces, output columns in whole slices; at d_c = 2048 a tile fills the LDS.
-bool decode_tiled_supported(const elitekv_dims& d, int d_ck) {
+// One or two heads of a latent of four blocks leave 14 of the 16 lanes' heads and four of the eight waves without work:
+// with long shares of a sequence per work-group, or more rows than compute units, the any-shape kernels are faster.  One
+// head, 64 columns, us, this / any-shape: 60 rows of 700 tokens 32.8 / 30.6, 128 of 700 (bf16) 53.5 / 40.3, 300 of 100
+// 30.6 / 27.5; 32 of 700 25.8 / 29.8; two heads, 300 of 100 34.6 / 30.2, 128 of 700 52.6 / 61.9; 144 columns: always faster.
+bool decode_tiled_supported(const elitekv_dims& d, int d_ck, int64_t rows, int64_t max_seq) {
+  const bool narrow = d.d_c <= 64 && d.n_heads <= 2;
+  if (narrow && (rows > kTtComputeUnits || (d.n_heads == 1 && rows * ((max_seq + 15) / 16) >= 10 * kTtComputeUnits))) return false;
   return d.d_c % 16 == 0 && d_ck % 16 == 0 && d.d_c <= 2048 && (d.head_dim - 2 * d.r) % 4 == 0 && (2 * d.r) % 4 == 0 &&
          2 * d.r <= 128 && d.head_dim % kTuCols == 0 && d.head_dim <= 256;
 }

@@ -26,7 +26,7 @@ def test_whole_rounds_of_work_groups(shape, slots_per_cu, B, S):
 # name: (d_model, n_heads, head_dim, r, d_c, dtype, d_ck of the separated forms)
 FORMS = {"7b_25": (4096, 32, 128, 8, 1536, "bf16", 576), "13b_25": (5120, 40, 128, 8, 1920, "bf16", 960),
          "7b_12": (4096, 32, 128, 4, 768, "bf16", 384), "fp32": (4096, 32, 128, 8, 1536, "fp32", 576),
-         "bf16_320": (512, 8, 64, 4, 320, "bf16", 160), "any_shape": (36, 5, 36, 3, 17, "fp32", 5)}
+         "bf16_320": (512, 8, 64, 4, 320, "bf16", 160), "any_shape": (36, 5, 36, 3, 17, "fp32", 5), "one_head": (64, 1, 64, 4, 64, "fp32", 16)}
 
 
 @pytest.mark.parametrize("name", list(FORMS))
@@ -69,3 +69,13 @@ def test_several_rounds_stay_inside_the_built_in_scratch(d_c, n_h):
             one = min(-(-slots // groups), (S + 15) // 16)       # one round, rounded up
             if need(B, S, one) <= ekv.NOALLOC_SCRATCH_BYTES:
                 assert need(B, S, ekv.elitekv_decode_auto_splits(dims, B, S)) <= ekv.NOALLOC_SCRATCH_BYTES, (B, S)
+
+
+@pytest.mark.parametrize("n_h,d_c,B,S,splits", [
+    (1, 64, 128, 700, 8), (1, 16, 32, 3000, 32), (2, 64, 300, 100, 2),     # any-shape kernels: about 1024 work-groups
+    (1, 64, 32, 700, 8), (2, 64, 128, 700, 2), (1, 144, 128, 700, 2),      # tiled: one round of 256
+])
+def test_one_or_two_narrow_heads(n_h, d_c, B, S, splits):
+    """Long shares of one narrow head keep the any-shape fp32 kernels, which take more and shorter splits."""
+    for dtype in ("fp32", "bf16"):
+        assert ekv.elitekv_decode_auto_splits(ekv.make_dims(64, n_h, 64, 4, d_c, dtype), B, S) == splits
