@@ -188,8 +188,8 @@ int elitekv_decode_attn(const elitekv_dims* dims, const void* q, const int32_t* 
  * image (one copy per GPU, held until the process ends).  The call allocates and frees nothing.
  *   - ESCRATCH (nothing enqueued) when the call needs more than ELITEKV_NOALLOC_SCRATCH_BYTES, never where
  *     elitekv_decode_workspace_bytes(dims, B, max_seq_len, n_splits) does not exceed them; 32 MiB covers the 7B shape at 25 % cache, one sequence,
- *     32768 cached tokens with the automatic split count.  Calls in fp32 arithmetic (ELITEKV_PATH_GENERIC) with
- *     the automatic count take as many of its splits as the buffer holds, where it does not hold them all.
+ *     32768 cached tokens with the automatic split count.  A call with the automatic count takes as many of its
+ *     splits as the buffer holds, where it does not hold them all but those of one round of work-groups.
  *   - All calls on one GPU share that GPU's buffer: two calls whose kernels may overlap (different
  *     streams, no ordering between them) race.  Calls on one stream are ordered and safe.  Nothing in
  *     the buffer has to be cleared between calls.

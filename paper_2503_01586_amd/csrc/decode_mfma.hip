@@ -731,7 +731,8 @@ static void shape_of(int d_c, int* nw, int* dcw) {
 static int slice_width(int d_c) { int nw, w; shape_of(d_c, &nw, &w); return w; }
 int decode_mfma_slice_width(int d_c) { return slice_width(d_c); }
 
-// work-groups of the attention kernel that fit one compute unit (see the launch bounds of the kernel)
+// work-groups of the attention kernel that run side by side on a compute unit: as many as its launch bounds ask for, and
+// two where a work-group has two waves for its four SIMDs
 int decode_mfma_groups_per_cu(const elitekv_dims& d) {
   int g = 1;
   const int two_r = 2 * d.r;
@@ -743,7 +744,9 @@ int decode_mfma_groups_per_cu(const elitekv_dims& d) {
       : two_r == 64 ? AttnMfmaLayout<NWV, DCW, 64>::kGroupsPerCu : 1;
   EKV_ATTN_SHAPES(X)
 #undef X
-  return g;
+  int nw, w;
+  shape_of(d.d_c, &nw, &w);
+  return nw == 2 ? 2 : g;
 }
 
 bool decode_mfma_supported(const elitekv_dims& d, int d_ck) {

@@ -71,25 +71,25 @@ static int32_t auto_splits_generic(const elitekv_dims* d, int64_t B, int64_t max
 //   7B 25 %, 129 sequences of 2000    366 / 242 (2)  341 / 335 (1) 294 / 258 (5)
 // (the host knows the longest length only).  A start of ten tiles fits equal lengths best; seven leans to shorter rounds.
 // Several rounds are taken where they hold at least a twentieth more work-groups than one round does in their time, which
-// pays for their partials in memory, and `holds` says that elitekv_decode_attn_noalloc keeps every call it takes with one.
-// Of equal counts the smallest (fewest partials to merge).
-// *most: no count for as many tiles or fewer is larger.  The count itself falls wherever equal shares take fewer splits, so
-// the size functions answer with *most: a workspace sized for a longer bound serves every shorter one.
-template <typename Holds>
-static int64_t balanced_splits(int64_t groups, int64_t tiles, int64_t slots, Holds holds, int64_t* most) {
+// pays for their partials in memory.  Of equal counts the smallest (fewest partials to merge).
+// most: no count for as many tiles or fewer is larger.  The count itself falls wherever equal shares take fewer splits, so
+// the size functions answer with `most`: a workspace sized for a longer bound serves every shorter one.
+struct AutoSplits { int64_t count, one_round, most; };
+static AutoSplits balanced_splits(int64_t groups, int64_t tiles, int64_t slots) {
   const int64_t one = std::max<int64_t>(1, std::min<int64_t>(slots / groups, kMaxSplits));
-  int64_t best = 1, best_cost = INT64_MAX;
-  *most = 1;
+  AutoSplits a{1, 1, 1};
+  int64_t best_cost = INT64_MAX;
   for (int64_t rounds = 1; rounds <= 3; ++rounds) {
     int64_t ns = std::max<int64_t>(1, std::min<int64_t>(rounds * slots / groups, kMaxSplits));
-    if (rounds > 1 && (20 * ns < 21 * rounds * one || (holds(one) && !holds(ns)))) continue;
+    if (rounds > 1 && 20 * ns < 21 * rounds * one) continue;
     ns = std::min(ns, tiles);
-    *most = std::max(*most, ns);
+    a.most = std::max(a.most, ns);
     const int64_t per_split = (tiles + ns - 1) / ns;
     const int64_t cost = (groups * ns + slots - 1) / slots * (7 + per_split);
-    if (cost < best_cost) { best = (tiles + per_split - 1) / per_split; best_cost = cost; }
+    if (cost < best_cost) { a.count = (tiles + per_split - 1) / per_split; best_cost = cost; }
+    if (rounds == 1) a.one_round = a.count;
   }
-  return best;
+  return a;
 }
 
 // Decide the path and lay the workspace out.  Returns a status.
@@ -113,11 +113,6 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
   p->d_q = d_ck > 0 ? d_ck : d->d_c;
   p->d_u = d_ck > 0 ? d->d_c - d_ck : d->d_c;
   const size_t dq = p->d_q, du = p->d_u;
-  // does the built-in scratch hold a decode call of this many splits?
-  auto scratch_holds = [&](int64_t n) {
-    DecodePlan t;
-    return plan_decode(d, d_ck, B, max_seq, (int32_t)n, &t) == ELITEKV_OK && t.total <= (size_t)ELITEKV_NOALLOC_SCRATCH_BYTES;
-  };
   // the split maxima, sums and accumulators of `rows` heads per batch row and split; spare: what `most` splits would add
   size_t spare = 0;
   auto lay_partials = [&](size_t at, int64_t splits, int64_t most, size_t rows, size_t row_bytes) {
@@ -154,7 +149,9 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
       // it pays to give every compute unit two (more splits also mean more partials to merge)
       const int64_t slots = (decode_mfma_groups_per_cu(*d) == 2 && Bq * p->head_groups >= 16) ? 2 * kComputeUnits
                                                                                              : kComputeUnits;
-      ns = balanced_splits(Bq * p->head_groups, (seq + 15) / 16, slots, scratch_holds, &most);
+      const AutoSplits a = balanced_splits(Bq * p->head_groups, (seq + 15) / 16, slots);
+      ns = a.count; most = a.most;
+      p->least_splits = (int32_t)a.one_round;
     }
     p->n_splits = (int32_t)ns;
     p->n_part = (int32_t)ns;
@@ -188,10 +185,15 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     p->tiled = decode_tiled_supported(*d, d_ck, Bq, seq);
     const bool shorter_tiled = p->tiled || decode_tiled_supported(*d, d_ck, Bq, 1);     // with a shorter bound, at least
     int64_t ns = n_splits, most = n_splits;
-    if (ns == 0 && shorter_tiled) ns = balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits,
-                                                       scratch_holds, &most);
-    if (n_splits == 0 && !p->tiled) ns = auto_splits_generic(d, Bq, seq);
-    most = std::max(most, ns);
+    if (n_splits == 0) {
+      if (shorter_tiled) {
+        const AutoSplits a = balanced_splits(Bq * ((d->n_heads + 15) / 16), (seq + 15) / 16, kComputeUnits);
+        ns = a.count; most = a.most;
+      }
+      p->least_splits = auto_splits_generic(d, Bq, seq);
+      if (!p->tiled) ns = p->least_splits;
+      most = std::max(most, ns);
+    }
     p->n_splits = (int32_t)ns;
     p->n_part = p->n_splits;
     int64_t chunk = (seq + p->n_splits - 1) / p->n_splits;
@@ -905,13 +907,13 @@ int elitekv_decode_attn_noalloc(const elitekv_dims* dims, const void* q, const i
   int st = plan_decode(dims, 0, B, max_seq_len, n_splits, &p);
   if (st) return st;
   const size_t room = ELITEKV_NOALLOC_SCRATCH_BYTES;
-  const bool tight = p.tiled && p.total > room;
-  if (tight) {
-    // The tiled fp32 kernels: without a piece for the merged latents, and of an automatic split count as much as fits, if
-    // the buffer holds the partials of auto_splits_generic()'s count.
-    auto fits = [&](int32_t n) { return plan_decode(dims, 0, B, max_seq_len, n, &p, false, false, true) == ELITEKV_OK && p.total <= room; };
-    if (n_splits == 0 && fits(auto_splits_generic(dims, B, max_seq_len)))
-      for (n_splits = elitekv_decode_auto_splits(dims, B, max_seq_len); n_splits > 1 && !fits(n_splits);) --n_splits;
+  const bool tight = p.tiled && p.total > room;      // the tiled fp32 kernels: no piece for the merged latents then
+  if (p.total > room && (tight || n_splits == 0)) {
+    // ... and of an automatic split count as much as fits, if the buffer holds the partials of the least one
+    auto fits = [&](int32_t n) { return plan_decode(dims, 0, B, max_seq_len, n, &p, false, false, tight) == ELITEKV_OK && p.total <= room; };
+    const int32_t most = p.n_splits, least = p.least_splits;
+    if (n_splits == 0 && fits(least))
+      for (n_splits = most; n_splits > 1 && !fits(n_splits);) --n_splits;
     if (!fits(n_splits)) return ELITEKV_ESCRATCH;
   }
   if (p.total > room) return ELITEKV_ESCRATCH;

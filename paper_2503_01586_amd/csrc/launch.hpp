@@ -33,6 +33,7 @@ inline hipError_t raise_lds_limit(LdsLimit& st, const void* kernel, size_t bytes
 // Where each intermediate of one decode call lives inside the caller's workspace.
 struct DecodePlan {
   int32_t n_splits;     // sequence splits per batch row
+  int32_t least_splits; // automatic counts: the fewest that elitekv_decode_attn_noalloc makes do with
   int32_t chunk;        // cached tokens per split
   int32_t mfma;         // 1: bf16 MFMA kernels, 0: kernels in fp32 arithmetic
   int32_t tiled;        // mfma 0: 1: the tiled fp32 matrix-core kernels (tiled_f32.hip), 0: the any-shape kernels

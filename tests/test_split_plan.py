@@ -56,21 +56,6 @@ def test_workspace_of_a_longer_bound_covers_every_shorter_one(name, B):
             before = now
 
 
-@pytest.mark.parametrize("d_c", [128, 512, 1024, 1536])
-@pytest.mark.parametrize("n_h", [16, 32, 40])
-def test_several_rounds_stay_inside_the_built_in_scratch(d_c, n_h):
-    """Where the scratch of elitekv_decode_attn_noalloc holds the partials of one round, it holds those of the count taken."""
-    dims = ekv.make_dims(4096, n_h, 128, 8, d_c, "bf16")
-    need = lambda B, S, ns: ekv.elitekv_decode_workspace_bytes(dims, B, S, ns)
-    for B in range(1, 260):
-        groups = B * ((n_h + 31) // 32)
-        for S in (40, 800, 32768):
-            slots = 512 if d_c <= 768 and groups >= 16 else 256  # narrow latents: up to two work-groups per compute unit
-            one = min(-(-slots // groups), (S + 15) // 16)       # one round, rounded up
-            if need(B, S, one) <= ekv.NOALLOC_SCRATCH_BYTES:
-                assert need(B, S, ekv.elitekv_decode_auto_splits(dims, B, S)) <= ekv.NOALLOC_SCRATCH_BYTES, (B, S)
-
-
 @pytest.mark.parametrize("n_h,d_c,B,S,splits", [
     (1, 64, 128, 700, 8), (1, 16, 32, 3000, 32), (2, 64, 300, 100, 2),     # any-shape kernels: about 1024 work-groups
     (1, 64, 32, 700, 8), (2, 64, 128, 700, 2), (1, 144, 128, 700, 2),      # tiled: one round of 256
@@ -79,3 +64,9 @@ def test_one_or_two_narrow_heads(n_h, d_c, B, S, splits):
     """Long shares of one narrow head keep the any-shape fp32 kernels, which take more and shorter splits."""
     for dtype in ("fp32", "bf16"):
         assert ekv.elitekv_decode_auto_splits(ekv.make_dims(64, n_h, 64, 4, d_c, dtype), B, S) == splits
+
+
+def test_two_wave_work_groups_run_in_pairs():
+    """A 128-column latent's work-groups have two waves: a compute unit runs two of them, and 200 rows two splits."""
+    assert ekv.elitekv_decode_auto_splits(ekv.make_dims(1024, 32, 128, 4, 128, "bf16"), 200, 500) == 2
+    assert ekv.elitekv_decode_auto_splits(ekv.make_dims(1024, 32, 128, 8, 1536, "bf16"), 200, 500) == 1

@@ -59,6 +59,28 @@ def test_noalloc_two_calls_second_smaller():
     _run_both(7002, 1, [45], 48)
 
 
+def test_noalloc_takes_as_many_splits_as_fit():
+    # 33 sequences x two head groups: seven splits fill two rounds of work-groups (43 MiB with the queries), three fill one
+    # (24 MiB)
+    sh = dict(SHAPE, n_heads=40, d_c=1152, r=4)
+    dims, B, S = dims_of(sh), 33, 3000
+    need = lambda ns: ekv.elitekv_decode_workspace_bytes(dims, B, S, ns)
+    assert ekv.elitekv_decode_auto_splits(dims, B, S) == 7 and need(7) > ekv.NOALLOC_SCRATCH_BYTES
+    fit = max(n for n in range(3, 7) if need(n) <= ekv.NOALLOC_SCRATCH_BYTES)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    n = lambda *s, std=1.0: (torch.randn(*s, generator=g, device=DEV) * std).bfloat16()
+    q, W_uk, W_uv = n(B, 40, 128), n(1152, 40, 120, std=1152 ** -0.5), n(1152, 40, 128, std=1152 ** -0.5)
+    ke, c = n(B * S, 40, 8), n(B * S, 1152)
+    idx = torch.stack([torch.randperm(64, generator=g, device=DEV)[:4] for _ in range(40)]).int()
+    lens = [S - 61 * b for b in range(B)]
+    out = torch.full_like(q, float("nan"))
+    ekv.elitekv_decode_attn_noalloc(dims, q, i32([s - 1 for s in lens]), i32(lens), S, S, W_uk, W_uv, idx, ke, c, out)
+    torch.cuda.synchronize()
+    same = gpu_decode(dims, q, i32([s - 1 for s in lens]), i32(lens), S, S, W_uk, W_uv, idx, ke, c, n_splits=fit)
+    assert torch.equal(out, same)
+
+
 def test_noalloc_rejects_what_does_not_fit():
     dims = dims_of(SHAPE)
     B, S, splits = 1, 32768, 512        # 512 splits x 98 KB of partials: beyond the built-in buffer
