@@ -11,6 +11,7 @@
 // streamed once, split over column blocks and over the contraction dimension so that every
 // compute unit pulls a share.  fp32 partials go to the workspace; the finish kernel of the
 // small-batch path sums the contraction splits, rotates and stores.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -753,11 +754,15 @@ static hipError_t launch_gemm_wn(const AppendArgs& a, hipStream_t stream) {
 // The XCDs as a grid of xt token groups x 8 / xt column groups, every XCD's tiles in groups of `group` token blocks, all
 // columns of a group one after the other: the 32 compute units of an XCD then hold about group x (32 / group) tiles at any
 // moment and share their rows and weights through its L2 (with one token block after the other they asked for 32 different
-// weight blocks at once, which the Infinity Cache delivers to eight XCDs at 7.5 TB/s).  Fewest rounds first, then the
-// fewest distinct blocks.
-static GemmTileMap gemm_tile_map(int64_t tblocks, int cblocks) {
+// weight blocks at once, which the Infinity Cache delivers to eight XCDs at 7.5 TB/s).  Fewest rounds first, then no XCD
+// without work while others have a quarter more than need be (ten column blocks over eight column groups of two: 512 x 2560
+// columns x 8192 tokens, 256 x 256 tiles: 67 -> 44 us a launch), then the fewest distinct blocks.
+static GemmTileMap gemm_tile_map(int64_t T, int N, int tokens, int cols) {
+  const int64_t tblocks = (T + tokens - 1) / tokens;
+  const int cblocks = (N + cols - 1) / cols;
   GemmTileMap best{};
-  int64_t best_cost = INT64_MAX;
+  int64_t best_cost = INT64_MAX, least = INT64_MAX;            // least: tiles of the busiest XCD
+  for (int xt = 8; xt >= 1; xt /= 2) least = std::min(least, (tblocks + xt - 1) / xt * ((cblocks + 8 / xt - 1) / (8 / xt)));
   for (int xt = 8; xt >= 1; xt /= 2) {
     GemmTileMap m;
     m.xt = xt;
@@ -765,9 +770,9 @@ static GemmTileMap gemm_tile_map(int64_t tblocks, int cblocks) {
     m.cb_x = (cblocks + 8 / xt - 1) / (8 / xt);
     m.group = m.tb_x < 6 ? m.tb_x : 6;
     m.col_blocks = cblocks;
-    const int64_t rounds = ((int64_t)m.tb_x * m.cb_x + 31) / 32;
+    const int64_t tiles = (int64_t)m.tb_x * m.cb_x, rounds = (tiles + 31) / 32;
     const int at_once = (32 + m.group - 1) / m.group;
-    const int64_t cost = rounds * 1000 + m.group + (m.cb_x < at_once ? m.cb_x : at_once);
+    const int64_t cost = rounds * 10000 + (4 * tiles > 5 * least ? 1000 : 0) + m.group + std::min(m.cb_x, at_once);
     if (cost < best_cost) { best = m; best_cost = cost; }
   }
   return best;
@@ -782,7 +787,7 @@ static hipError_t launch_gemm_dma(const AppendArgs& a, hipStream_t stream) {
   const hipError_t le = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&append_gemm_dma_kernel<WN, NS, WNW, CM, SPB, KG>),
                                         L::LDS_BYTES);
   if (le != hipSuccess) return le;
-  const GemmTileMap m = gemm_tile_map((a.T + L::BN - 1) / L::BN, (N + L::COLS - 1) / L::COLS);
+  const GemmTileMap m = gemm_tile_map(a.T, N, L::BN, L::COLS);
   append_gemm_dma_kernel<WN, NS, WNW, CM, SPB, KG><<<8u * m.tb_x * m.cb_x, 64 * CM * WNW, L::LDS_BYTES, stream>>>(
       (const bf16_t*)a.x, a.pos, a.slot, a.T, (const bf16_t*)a.W_ke, (const bf16_t*)a.W_dkv,
       (const bf16_t*)a.W_dkv2, a.d_ck, a.elite_idx, (bf16_t*)a.ke_plane, (bf16_t*)a.c_plane, a.plane_rows,
@@ -798,7 +803,7 @@ static hipError_t launch_gemm_wide(const AppendArgs& a, hipStream_t stream) {
   static LdsLimit lds_limit;
   const hipError_t le = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&append_gemm_wide_kernel<NS>), L::LDS_BYTES);
   if (le != hipSuccess) return le;
-  const GemmTileMap m = gemm_tile_map((a.T + 255) / 256, (2 * d.r * d.n_heads + d.d_c + 255) / 256);
+  const GemmTileMap m = gemm_tile_map(a.T, 2 * d.r * d.n_heads + d.d_c, 256, 256);
   append_gemm_wide_kernel<NS><<<8u * m.tb_x * m.cb_x, 256, L::LDS_BYTES, stream>>>(
       (const bf16_t*)a.x, a.pos, a.slot, a.T, (const bf16_t*)a.W_ke, (const bf16_t*)a.W_dkv,
       (const bf16_t*)a.W_dkv2, a.d_ck, a.elite_idx, (bf16_t*)a.ke_plane, (bf16_t*)a.c_plane, a.plane_rows,
@@ -826,7 +831,7 @@ int append_gemm_tile(const AppendArgs& a) {
   //                        256 (alone on its unit) 3 + 0.0095 K   42 against 47 us of 128 x 128, 4096 x 1024, 2048 tokens
   // (4096 x 2048: 99 / 115 / 73 / 50 / 56 at 2048 tokens, 493 / 521 / 620 / 727 / 815 at 32768.)
   auto cost = [&](int tokens, int cols, int slots, double fixed, double per_row) {
-    const GemmTileMap m = gemm_tile_map((a.T + tokens - 1) / tokens, (N + cols - 1) / cols);
+    const GemmTileMap m = gemm_tile_map(a.T, N, tokens, cols);
     const int64_t per_xcd = (int64_t)m.tb_x * m.cb_x;
     return (double)((per_xcd + slots / 8 - 1) / (slots / 8)) * (fixed + per_row * K);
   };
