@@ -117,14 +117,15 @@ enum elitekv_path { ELITEKV_PATH_GENERIC = 0, ELITEKV_PATH_MATRIX_CORE = 1 };
 int elitekv_decode_path(const elitekv_dims* dims, int32_t d_ck);
 
 /* Which tile (tokens x columns of a work-group) the matrix-core GEMM takes for an append of T tokens (Section 3.2,
- * c = x A^kv, of more than 64 tokens; FP32: the tiled kernel in fp32 arithmetic, up to 256 tokens), and for the keys and values that elitekv_prefill_attn (T queries per sequence) rebuilds
- * of max_seq_len rows.  ELITEKV_TILE_NONE: other kernels.  WIDE: the 256 x 256 tile by four waves;
- * STAGED: rows of no whole 32-column stages, through registers.  For profiles and tests: results are the same to rounding.
+ * c = x A^kv, of more than 64 tokens), and for the keys and values of max_seq_len rows that elitekv_prefill_attn (T
+ * queries per sequence) rebuilds.  WIDE: the 256 x 256 tile by four waves; PAIRS: 128 x 128 by four waves, two work-groups
+ * on a compute unit; STAGED: rows of no whole 32-column stages, through registers; FP32: not the GEMM but the tiled append
+ * in fp32 arithmetic (up to 256 tokens); NONE: other kernels.  For profiles and tests: results are the same to rounding.
  * d_ck = 0: joint latent.  Host only.  Negative status on bad dims. */
 enum elitekv_gemm_tile {
-  ELITEKV_TILE_NONE = 0, ELITEKV_TILE_64_128 = 1, ELITEKV_TILE_128_128 = 2, ELITEKV_TILE_256_128 = 3, ELITEKV_TILE_256_256 = 4,
-  ELITEKV_TILE_256_256_WIDE = 5, ELITEKV_TILE_STAGED_64_128 = 6, ELITEKV_TILE_STAGED_256_128 = 7,
-  ELITEKV_TILE_FP32 = 8
+  ELITEKV_TILE_NONE = 0, ELITEKV_TILE_64_128 = 1, ELITEKV_TILE_128_128 = 2, ELITEKV_TILE_128_128_PAIRS = 3,
+  ELITEKV_TILE_256_256 = 4, ELITEKV_TILE_256_256_WIDE = 5, ELITEKV_TILE_STAGED_64_128 = 6,
+  ELITEKV_TILE_STAGED_256_128 = 7, ELITEKV_TILE_FP32 = 8
 };
 int32_t elitekv_append_gemm_tile(const elitekv_dims* dims, int32_t d_ck, int64_t T);
 int32_t elitekv_prefill_gemm_tile(const elitekv_dims* dims, int32_t d_ck, int64_t T, int64_t max_seq_len);

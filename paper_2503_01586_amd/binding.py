@@ -173,7 +173,7 @@ def elitekv_append(dims, x, pos, slot, W_ke, W_dkv, elite_idx, ke_plane, c_plane
     _check(st, "elitekv_append")
 
 
-(TILE_NONE, TILE_64_128, TILE_128_128, TILE_256_128, TILE_256_256, TILE_256_256_WIDE, TILE_STAGED_64_128,
+(TILE_NONE, TILE_64_128, TILE_128_128, TILE_128_128_PAIRS, TILE_256_256, TILE_256_256_WIDE, TILE_STAGED_64_128,
  TILE_STAGED_256_128, TILE_FP32) = range(9)
 PATH_GENERIC, PATH_MATRIX_CORE = 0, 1
 

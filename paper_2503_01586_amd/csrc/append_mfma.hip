@@ -821,25 +821,30 @@ int append_gemm_tile(const AppendArgs& a) {
   const int N = 2 * d.r * d.n_heads + d.d_c;
   const double K = a.d2 > d.d_model ? a.d2 : d.d_model;
   // The tile whose rounds of work-groups cost least.  A round's cost in us, fixed part (first stages from cold memory,
-  // epilogue) + contraction rows, fitted to measurements from 1000 to 32768 tokens, 768 to 5120 rows, 1024 to 9600 columns:
-  //   tokens x columns     work-groups at once     a round        measured, 1536 x 7680 rows x columns, 1000 / 2048 / 8192 tokens
-  //   256 x 256, 4 waves   256                     20 + 0.021 K   51 / 62 / 208 us
-  //   256 x 256, 8 waves   256                     13 + 0.025 K   51 / 61 / 211
-  //   256 x 128            256                     10 + 0.0145 K  35 / 66 / 232
-  //   128 x 128            256                     1.5 + 0.0118 K 39 / 78 / 270
-  //    64 x 128            512                     3 + 0.0128 K   41 / 82 / 296
-  //                        256 (alone on its unit) 3 + 0.0095 K   42 against 47 us of 128 x 128, 4096 x 1024, 2048 tokens
-  // (4096 x 2048: 99 / 115 / 73 / 50 / 56 at 2048 tokens, 493 / 521 / 620 / 727 / 815 at 32768.)
+  // epilogue) + contraction rows, fitted to measurements of every tile at 64 to 5120 rows, 384 to 9600 columns, 200 to 30000
+  // tokens: on the mean 1 % behind the best tile, 10 % with the constants fitted to 768 rows and more only (256 x 4096
+  // x 30000 tokens took the third line, 245 us, instead of the first or second, about 165).
+  //   tokens x columns     work-groups at once     a round         measured, 1536 x 7680 rows x columns, 1000 / 2048 / 8192 tokens
+  //   256 x 256, 4 waves   256                     20.1 + 0.0220 K 53 / 61 / 208 us
+  //   256 x 256, 8 waves   256                     15.7 + 0.0245 K 53 / 59 / 210
+  //   128 x 128, 8 waves   256                     7.7 + 0.0101 K  43 / 77 / 267
+  //   128 x 128, 4 waves   512                     6.7 + 0.0165 K  33 / 60 / 227
+  //    64 x 128            512                     6.9 + 0.0113 K  44 / 82 / 306
+  //                        256 (alone on its unit) 4.2 + 0.0085 K  43 against 47 us of 128 x 128, 4096 x 1024, 2048 tokens
+  // (4096 x 2048: 97 / 113 / 55 / 56 / 59 at 2048 tokens, 468 / 507 / 665 / 583 / 748 at 30000.  A 256 x 128 tile by eight waves,
+  // 36 / 63 / 230 above, was nowhere more than 3 % faster than the best of these.  The four waves are chosen only where a
+  // unit runs two of their work-groups: alone they are the slower form of 128 x 128.)
   auto cost = [&](int tokens, int cols, int slots, double fixed, double per_row) {
     const GemmTileMap m = gemm_tile_map(a.T, N, tokens, cols);
     const int64_t per_xcd = (int64_t)m.tb_x * m.cb_x;
+    if (tokens == 128 && slots == 512 && per_xcd <= 32) return 1e30;
     return (double)((per_xcd + slots / 8 - 1) / (slots / 8)) * (fixed + per_row * K);
   };
   const bool wide_ok = N >= 256 && (a.d2 == 0 || (N % 256 == 0 && split % 256 == 0));
-  const double c[5] = {wide_ok ? cost(256, 256, 256, 20., .021) : 1e30, wide_ok ? cost(256, 256, 256, 13., .025) : 1e30,
-                       cost(256, 128, 256, 10., .0145), cost(128, 128, 256, 1.5, .0118),
-                       col_blocks * ((a.T + 63) / 64) <= 256 ? cost(64, 128, 256, 3., .0095) : cost(64, 128, 512, 3., .0128)};
-  constexpr int tile[5] = {ELITEKV_TILE_256_256_WIDE, ELITEKV_TILE_256_256, ELITEKV_TILE_256_128, ELITEKV_TILE_128_128,
+  const double c[5] = {wide_ok ? cost(256, 256, 256, 20.1, .022) : 1e30, wide_ok ? cost(256, 256, 256, 15.7, .0245) : 1e30,
+                       cost(128, 128, 256, 7.7, .0101), cost(128, 128, 512, 6.7, .0165),
+                       col_blocks * ((a.T + 63) / 64) <= 256 ? cost(64, 128, 256, 4.2, .0085) : cost(64, 128, 512, 6.9, .0113)};
+  constexpr int tile[5] = {ELITEKV_TILE_256_256_WIDE, ELITEKV_TILE_256_256, ELITEKV_TILE_128_128, ELITEKV_TILE_128_128_PAIRS,
                            ELITEKV_TILE_64_128};
   int best = 4;                                                // of equal costs the smaller tile
   for (int i = 3; i >= 0; --i)
@@ -859,8 +864,8 @@ hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream) {
   switch (append_gemm_tile(a)) {
     case ELITEKV_TILE_256_256_WIDE: return launch_gemm_wide(a, stream);
     case ELITEKV_TILE_256_256: return launch_gemm_dma<4, 4, 2, 4>(a, stream);
-    case ELITEKV_TILE_256_128: return launch_gemm_dma<2, 6, 4, 2>(a, stream);
     case ELITEKV_TILE_128_128: return launch_gemm_dma<1, 6, 4, 2, 2, 2>(a, stream);
+    case ELITEKV_TILE_128_128_PAIRS: return launch_gemm_dma<2, 4, 2, 2>(a, stream);
     case ELITEKV_TILE_64_128: return launch_gemm_dma<1, 6, 2, 2>(a, stream);
     case ELITEKV_TILE_STAGED_256_128: return launch_gemm_wn<4>(a, stream);
     default: return launch_gemm_wn<1>(a, stream);

@@ -15,11 +15,11 @@ pytestmark = pytest.mark.gpu
     (2048, 8, 1408, 8100, ekv.TILE_256_256_WIDE),    # 1920 columns: the last block overlaps the one before
     (2048, 8, 1536, 8192, ekv.TILE_256_256_WIDE),    # ... whole blocks
     (1024, 8, 1408, 8100, ekv.TILE_256_256),
-    (1024, 8, 1536, 4000, ekv.TILE_256_128),
+    (1024, 8, 1536, 4000, ekv.TILE_128_128_PAIRS),
     (1024, 8, 1536, 2000, ekv.TILE_128_128),
     (1024, 4, 768, 130, ekv.TILE_64_128),
-    (32, 8, 1536, 8100, ekv.TILE_128_128),           # one stage of contraction rows
-    (160, 8, 1408, 8100, ekv.TILE_128_128),          # an odd number, one less than the ring holds
+    (32, 8, 1536, 8100, ekv.TILE_128_128_PAIRS),     # one stage of contraction rows
+    (160, 8, 1408, 8100, ekv.TILE_128_128_PAIRS),    # one more than the ring holds
     (1000, 8, 1536, 300, ekv.TILE_STAGED_64_128),    # rows that are no whole stages
     (40, 8, 7680, 4000, ekv.TILE_STAGED_256_128),
 ])
@@ -61,11 +61,12 @@ def test_append_tiles(d, r, d_c, T, tile):
     (96, 1024, 3000, ekv.TILE_256_256),
     (128, 1024, 4000, ekv.TILE_256_256),
     (1024, 160, 4000, ekv.TILE_256_256),
-    (96, 1024, 1501, ekv.TILE_256_128),              # the rings of the smaller tiles hold six
-    (1024, 192, 1501, ekv.TILE_256_128),
-    (64, 1024, 1000, ekv.TILE_128_128),
+    (96, 1024, 1501, ekv.TILE_128_128_PAIRS),        # four
+    (1024, 192, 1501, ekv.TILE_128_128_PAIRS),
+    (64, 1024, 1000, ekv.TILE_128_128),              # the rings of the other tiles hold six
     (1024, 224, 1000, ekv.TILE_128_128),
     (96, 1024, 201, ekv.TILE_64_128),
+    (32, 512, 200, ekv.TILE_64_128),
 ])
 def test_rebuild_tiles(d_ck, d_cv, S, tile):
     """The rebuilt rows, which the call leaves in its workspace: [keys without their elite dims | values] of every head."""
