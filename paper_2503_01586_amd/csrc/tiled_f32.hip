@@ -1,6 +1,7 @@
-// Decode and append kernels in fp32 arithmetic on the fp32 matrix cores: the fp32 dtype, and bf16 shapes whose
-// widths the bf16 kernels are not compiled for, as long as the widths are multiples of 16 (decode_tiled_supported,
-// append_tiled_supported).  Sums are fp32 throughout, products exact fp32 fused multiply-adds.
+// Decode and append kernels in fp32 arithmetic with the whole chip in use: the fp32 dtype, and bf16 shapes whose widths
+// the bf16 kernels are not compiled for, as long as the widths are multiples of 16 (decode_tiled_supported,
+// append_tiled_supported).  The attention's products run on the fp32 matrix cores; the others, bound by their bytes, on the
+// vector units.  Sums are fp32 throughout, products exact fp32 fused multiply-adds.
 //
 // The path of the remaining shapes (decode_generic.hip, append_generic.hip) gives a work-group one head or 256 columns
 // and walks the whole contraction serially: 64 work-groups on 256 compute units, one load in flight per lane.
@@ -122,9 +123,11 @@ static bool append_tiled_pays(const elitekv_dims& d, int64_t T) {
   const int64_t bytes = N * d.d_model * (d.dtype == ELITEKV_FP32 ? 4 : 2), tiles8 = T < 64 ? T : 64;
   return (groups + at_once - 1) / at_once * (7. + .003 * rows) <= 3. + (bytes * tiles8 > 64LL * (4 << 20) ? .105 : .06) * rows;
 }
+static bool append_tiled_covers(const elitekv_dims& d, int d_ck) {
+  return d.d_model % 4 == 0 && (2 * d.r * d.n_heads) % kTaCols == 0 && d_ck % kTaCols == 0 && (d.d_c - d_ck) % kTaCols == 0;
+}
 bool append_tiled_supported(const elitekv_dims& d, int64_t T, int d_ck) {
-  return T <= kTaMaxTokens && d.d_model % 4 == 0 && (2 * d.r * d.n_heads) % kTaCols == 0 && d_ck % kTaCols == 0 &&
-         (d.d_c - d_ck) % kTaCols == 0 && append_tiled_pays(d, T);
+  return T <= kTaMaxTokens && append_tiled_covers(d, d_ck) && append_tiled_pays(d, T);
 }
 
 template <typename T>
@@ -604,9 +607,10 @@ static hipError_t launch_decode_tiled_t(const DecodeArgs& a, const DecodePlan& p
   return hipGetLastError();
 }
 
-// (fp32 only: bf16 shapes of this path may have a faster append of their own)
+// (fp32 only: bf16 shapes of this path may have a faster append of their own.  Also where the append alone would be the
+// serial kernel's: one launch less is worth more; 64 rows, three sequences of 300 tokens: a step 21.1 us, in two launches 26.5.)
 bool front_tiled_supported(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p) {
-  return p.tiled && a.dims.dtype == ELITEKV_FP32 && a.B <= 8 && append_tiled_supported(a.dims, a.B, ap.d_ck);
+  return p.tiled && a.dims.dtype == ELITEKV_FP32 && a.B <= 8 && append_tiled_covers(a.dims, ap.d_ck);
 }
 
 hipError_t launch_front_tiled(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p, hipStream_t stream) {
@@ -617,7 +621,11 @@ hipError_t launch_front_tiled(const AppendArgs& ap, const DecodeArgs& a, const D
   A.d_c = d.d_c; A.d_ck = ap.d_ck; A.d_q = p.d_q; A.n_slices = (2 * d.r * d.n_heads + d.d_c) / kTaCols;
   A.q_blocks = (p.d_q + kTaThreads / 4 - 1) / (kTaThreads / 4);
   A.scale_log2e = kLog2e / sqrtf((float)d.head_dim);
-#define EKV_FRONT(BT)                                                                                                       front_tiled_kernel<T, BT><<<A.n_slices + A.q_blocks * d.n_heads, kTaThreads, 0, stream>>>(                                   (const T*)ap.x, (const T*)a.q, a.q_pos, ap.slot, (const T*)ap.W_ke, (const T*)ap.W_dkv, (const T*)ap.W_dkv2,              (const T*)a.W_uk, a.elite_idx, (T*)ap.ke_plane, (T*)ap.c_plane, (float*)(a.ws + p.off_qe),                                (float*)(a.ws + p.off_qt), A, rope_table(d.rope_base, d.head_dim))
+#define EKV_FRONT(BT)                                                                                           \
+  front_tiled_kernel<T, BT><<<A.n_slices + A.q_blocks * d.n_heads, kTaThreads, 0, stream>>>(                    \
+      (const T*)ap.x, (const T*)a.q, a.q_pos, ap.slot, (const T*)ap.W_ke, (const T*)ap.W_dkv,                   \
+      (const T*)ap.W_dkv2, (const T*)a.W_uk, a.elite_idx, (T*)ap.ke_plane, (T*)ap.c_plane,                      \
+      (float*)(a.ws + p.off_qe), (float*)(a.ws + p.off_qt), A, rope_table(d.rope_base, d.head_dim))
   if (a.B == 1) EKV_FRONT(1);
   else if (a.B == 2) EKV_FRONT(2);
   else if (a.B <= 4) EKV_FRONT(4);
