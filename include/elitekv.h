@@ -110,8 +110,11 @@ int elitekv_append(const elitekv_dims* dims, const void* x, const int32_t* pos, 
  * kernels (bf16; d_h 64 or 128; r = 4, 8 or 16 elite chunks per head; (d_h - 2r) a multiple of 8; d_c a
  * multiple of 128 up to 2048, or 1920; r = 16 only up to d_c 1792, the widest row whose tiles fit the LDS next to
  * 2 r = 32 elite values per head; separated latents: d_ck and d_c - d_ck whole wave slices / 64-column chunks),
- * or ELITEKV_PATH_GENERIC, the untuned fp32 vector kernels that cover every other shape (all fp32 shapes,
- * other r or d_c).  Results are the same to rounding; only the speed differs, so a caller that cares asks here.
+ * or ELITEKV_PATH_GENERIC, kernels in fp32 arithmetic that cover every other shape (all fp32 shapes, other r or d_c):
+ * tiled ones where d_c and d_ck are multiples of 16, 2r and d_h - 2r of 4, d_h of 32 and d_c <= 2048 (7B shape at 25 % of
+ * the cache, fp32: a step of two sequences of 1000 tokens 56 us; one or two heads of up to 64 latent columns keep the others
+ * where a work-group's share of a sequence is long), untuned any-shape ones (1.1 ms) for the rest.
+ * Results are the same to rounding; only the speed differs, so a caller that cares asks here.
  * d_ck = 0: joint latent; d_ck > 0: separated latents.  Host only.  Negative status on bad dims. */
 enum elitekv_path { ELITEKV_PATH_GENERIC = 0, ELITEKV_PATH_MATRIX_CORE = 1 };
 int elitekv_decode_path(const elitekv_dims* dims, int32_t d_ck);
@@ -185,12 +188,13 @@ int elitekv_decode_attn(const elitekv_dims* dims, const void* q, const int32_t* 
  * elitekv_decode_attn for callers that cannot allocate device memory or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments
  * (without ws / ws_bytes), same kernels and, with the same number of splits, bit-for-bit the same result as
- * elitekv_decode_attn; the intermediates live in a buffer of ELITEKV_NOALLOC_SCRATCH_BYTES that is part of the library's device
- * image (one copy per GPU, held until the process ends).  The call allocates and frees nothing.
+ * elitekv_decode_attn; the intermediates live in a buffer of ELITEKV_NOALLOC_SCRATCH_BYTES that is part of the
+ * library's device image (one copy per GPU, held until the process ends).  The call allocates and frees nothing.
  *   - ESCRATCH (nothing enqueued) when the call needs more than ELITEKV_NOALLOC_SCRATCH_BYTES, never where
- *     elitekv_decode_workspace_bytes(dims, B, max_seq_len, n_splits) does not exceed them; 32 MiB covers the 7B shape at 25 % cache, one sequence,
- *     32768 cached tokens with the automatic split count.  A call with the automatic count takes as many of its
- *     splits as the buffer holds, where it does not hold them all but those of one round of work-groups.
+ *     elitekv_decode_workspace_bytes(dims, B, max_seq_len, n_splits) does not exceed them; 32 MiB covers the 7B
+ *     shape at 25 % cache, one sequence, 32768 cached tokens with the automatic split count.  A call with the
+ *     automatic count takes as many of its splits as the buffer holds, where it does not hold them all but those
+ *     of one round of work-groups.
  *   - All calls on one GPU share that GPU's buffer: two calls whose kernels may overlap (different
  *     streams, no ordering between them) race.  Calls on one stream are ordered and safe.  Nothing in
  *     the buffer has to be cleared between calls.

@@ -1,6 +1,6 @@
 // Generic (any shape, fp32 or bf16 storage, fp32 VALU arithmetic) decode attention over the
-// EliteKV cache.  This is the path of the fp32 dtype and of bf16 shapes the MFMA kernels do not
-// cover.  Three kernels on one stream:
+// EliteKV cache.  This is the path of the fp32 and bf16 shapes that neither the bf16 kernels nor the tiled fp32
+// kernels (decode_tiled_supported) cover.  Three kernels on one stream:
 //   qprep  : rotate the query's elite chunks at q_pos, absorb W_uk into the rest of the query
 //            (Section 3.1 score equation, first sum; Section 5, absorption of B^k)
 //   attn   : per (split, head, batch row) online softmax over both score terms with values

@@ -654,7 +654,7 @@ int elitekv_block_step(const elitekv_dims* dims, const void* x, const int32_t* p
   a.no_out_reduce = 1;
   // (1) first pass of the append and of x W_q  (2) the query's contraction splits summed, rounded
   // (3) q-prep  (4) attention, which also finishes and stores the new rows  (5) merge +
-  // up-projection, chunk partials kept  (6) out W_o from the chunk partials  (7) sum of its splits
+  // up-projection, chunk partials kept  (6) out W_o from the chunk partials, its splits added by the last work-group
   hipError_t e = launch_block_front(ap, W_q, a, p, stream);
   if (e == hipSuccess) e = launch_qprep_rows(a, p, (float*)(a.ws + p.off_qe), (bf16_t*)(a.ws + p.off_qt), stream);
   if (e == hipSuccess) e = launch_decode_mfma(a, p, stream);

@@ -36,7 +36,7 @@ struct DecodePlan {
   int32_t least_splits; // automatic counts: the fewest that elitekv_decode_attn_noalloc makes do with
   int32_t chunk;        // cached tokens per split
   int32_t mfma;         // 1: bf16 MFMA kernels, 0: kernels in fp32 arithmetic
-  int32_t tiled;        // mfma 0: 1: the tiled fp32 matrix-core kernels (tiled_f32.hip), 0: the any-shape kernels
+  int32_t tiled;        // mfma 0: 1: the tiled fp32 kernels (tiled_f32.hip), 0: the any-shape kernels
   int32_t head_groups;  // MFMA path: groups of up to 32 heads
   int32_t up_cw;        // MFMA path: latent columns per merge/up-projection work-group
   int32_t merge_batch;  // MFMA path: 1 = the merge kernel that takes all batch rows per work-group
@@ -163,7 +163,7 @@ bool qprep_mfma_supported(const elitekv_dims& d, int d_q, int64_t B);
 bool decode_front_plan(const elitekv_dims& d, int d_ck, int d_q, int64_t B, int* ks, int* kc);
 hipError_t launch_decode_front(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 // whole-block step: the split plans of its two weight-streaming passes, its first launch (append + x W_q)
-// and its last two (out W_o from the merge's chunk partials, then the sum of the splits)
+// and its last (out W_o from the merge's chunk partials, the splits added by the last work-group of a column block)
 bool block_step_plan(const elitekv_dims& d, int64_t B, int* fr_ks, int* fr_kc, int* y_ks, int* y_kc);
 hipError_t launch_block_front(const AppendArgs& ap, const void* W_q, const DecodeArgs& a, const DecodePlan& p,
                               hipStream_t stream);   // + the sum of the query's contraction splits into ws + off_qfin
