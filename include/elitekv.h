@@ -368,7 +368,7 @@ int elitekv_slrd_prefill_attn(const elitekv_dims* dims, int32_t d_ck, const void
  *   its fresh row or from whatever row seq_len[b] - 1 of the plane holds.  seq_len[b] <= 0:
  *   nothing is attended, out[b] is 0, and the token is still stored at slot[b] if that is in range.
  *   For up to 64 sequences (bf16 shapes of the matrix-core path) the step is three launches (four
- *   from eight sequences on): the first pass of the append together with the query preparation; the
+ *   from two sequences on): the first pass of the append together with the query preparation; the
  *   attention, in which the work-group that owns the tile of a sequence's newest position first adds
  *   up the append's partial sums, rotates and stores the new row; the merge with the up-projection
  *   (from two sequences on followed by the launch that adds its column-chunk partials).  Other shapes
@@ -399,11 +399,11 @@ int elitekv_decode_step(const elitekv_dims* dims, const void* x, const void* q, 
  *   W_o   [n_h, d_h, d_model]      dims->dtype
  *   y     [B, d_model]             written, dims->dtype
  *   the other arguments as in elitekv_decode_step; ws: elitekv_block_step_workspace_bytes bytes.
- * Fewer than eight sequences (bf16 shapes of the matrix-core path): six launches -- the first pass of
+ * One sequence (bf16 shapes of the matrix-core path): six launches -- the first pass of
  * the append and of x W_q in one weight-streaming launch; the sum of the query's contraction splits; the
  * query preparation; the attention, which also finishes and stores the new rows; the merge with the
  * up-projection; out W_o read straight from the merge's column-chunk partials, its contraction splits
- * added by the last work-group of a column block.  Eight to 64 sequences, and bf16 shapes outside the matrix-core path: the composed
+ * added by the last work-group of a column block.  Two to 64 sequences, and bf16 shapes outside the matrix-core path: the composed
  * form -- q = x W_q and y = out W_o as weight-streaming launches of their own around the kernels of
  * elitekv_decode_step, q and out (rounded to dims->dtype) staying in the workspace.
  * EUNSUPPORTED unless bf16, B <= 64 and d_model and n_h d_h are multiples of 64; other errors as

@@ -7,7 +7,7 @@
 //     D[n, t]              : a lane ends up with ONE token and groups of four consecutive output
 //                            columns, so the (even, odd) pairs that RoPE rotates stay in one lane.
 //
-// append_skinny: a decoding batch (8 <= T <= 64 tokens).  The weights are the traffic; they are
+// append_skinny: a decoding batch (2 <= T <= 64 tokens).  The weights are the traffic; they are
 // streamed once, split over column blocks and over the contraction dimension so that every
 // compute unit pulls a share.  fp32 partials go to the workspace; the finish kernel of the
 // small-batch path sums the contraction splits, rotates and stores.
@@ -36,7 +36,7 @@ AppendSkinnyParams make_append_skinny_params(const AppendArgs& a, float* partial
 }
 
 bool append_skinny_supported(const elitekv_dims& d, int64_t T, int d_ck) {
-  if (d.dtype != ELITEKV_BF16 || T < 8 || T > 64) return false;
+  if (d.dtype != ELITEKV_BF16 || T < kMatrixRows || T > 64) return false;
   const int NE = 2 * d.r * d.n_heads;
   return NE % kSkCols == 0 && d.d_c % kSkCols == 0 && d_ck % kSkCols == 0 && d.d_model % 8 == 0;
 }

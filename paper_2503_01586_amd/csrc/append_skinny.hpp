@@ -1,4 +1,4 @@
-// Cache append for a decoding batch (8 <= T <= 64 tokens) on the matrix cores, first pass.
+// Cache append for a decoding batch (2 <= T <= 64 tokens) on the matrix cores, first pass.
 //   Y = X [W_ke | W_dkv]   (Section 3.2: c = x A^{kv} and the elite key rows W^k_{e,h}; Section 3.1:
 //   what a RoPElite model caches), computed transposed, Y^T[n, t] = sum_k W^T[n, k] X^T[k, t]:
 //     A (32 x 16 per step) = W^T: the weight tile sits in LDS as stored ([k][n], n contiguous) and

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void qprep_mfma_kernel(const QprepRowsParams P
 
 bool qprep_mfma_supported(const elitekv_dims& d, int d_q, int64_t B) {
   const int nd = d.head_dim - 2 * d.r;
-  return B >= 8 && d_q % 128 == 0 && nd % 8 == 0 && nd >= 16 && nd <= 128 && d.head_dim <= 128;
+  return B >= kMatrixRows && d_q % 32 == 0 && nd % 8 == 0 && nd >= 16 && nd <= 128 && d.head_dim <= 128;
 }
 
 static hipError_t launch_qprep_mfma(const DecodeArgs& a, const DecodePlan& p, float* qe, bf16_t* qt, hipStream_t stream) {
@@ -59,7 +59,7 @@ static hipError_t launch_qprep_mfma(const DecodeArgs& a, const DecodePlan& p, fl
   const int nd = d.head_dim - 2 * d.r;
   const int ks = (nd + 15) / 16;
   const size_t sm = qprep_mfma_lds(d.head_dim, d.r);
-  const dim3 grid(p.d_q / 128, d.n_heads);
+  const dim3 grid((p.d_q + 127) / 128, d.n_heads);
   const QprepRowsParams P = make_qprep_rows_params(a, p, qe, qt);
   const RopeTable rope = rope_table(d.rope_base, d.head_dim);
 #define EKV_QM(KSV) qprep_mfma_kernel<KSV><<<grid, 256, sm, stream>>>(P, rope)
@@ -270,7 +270,7 @@ hipError_t launch_merge_up(const DecodeArgs& a, const DecodePlan& p, hipStream_t
     if (e != hipSuccess || a.no_out_reduce) return e;
     const int64_t total = (int64_t)a.B * d.n_heads * d.head_dim;
     out_reduce_kernel<<<(unsigned)((total + 255) / 256), 256, 0, stream>>>(
-        (const float*)(a.ws + p.off_opart), (bf16_t*)a.out, d.head_dim, p.d_u / 128, total);
+        (const float*)(a.ws + p.off_opart), (bf16_t*)a.out, d.head_dim, (p.d_u + p.up_cw - 1) / p.up_cw, total);
     return hipGetLastError();
   }
   const float* pm = (const float*)(a.ws + p.off_m);

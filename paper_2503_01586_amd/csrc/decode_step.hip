@@ -48,7 +48,6 @@ __global__ __launch_bounds__(256) void decode_front_kernel(const AppendSmallPara
 
 bool decode_front_plan(const elitekv_dims& d, int d_ck, int d_q, int64_t B, int* ks_out, int* kc_out) {
   if (d.dtype != ELITEKV_BF16 || B < 1 || B > kAsTokens) return false;
-  if (qprep_mfma_supported(d, d_q, B)) return false;                 // eight rows and up: matrix-core kernels
   const int nd = d.head_dim - 2 * d.r;
   if (d.r < 1 || nd < 8 || nd % 8 || d.head_dim > 128) return false;
   if (!append_small_supported(d, B, d_ck > 0 ? d_ck : d.d_c)) return false;
@@ -94,24 +93,24 @@ hipError_t launch_decode_front(const AppendArgs& ap, const DecodeArgs& a, const 
        : bt == 4 ? launch_front_bt<4>(ap, a, p, stream) : launch_front_bt<8>(ap, a, p, stream);
 }
 
-// ---- whole attention block of a step (Section 2.1: q = x W^q in front, [o_0 .. o_{n_h-1}] W^o behind).
+// ---- whole attention block of a step of one sequence (Section 2.1: q = x W^q in front, [o_0 .. o_{n_h-1}] W^o behind).
 // block_front: the first pass of the append and of the query projection in one weight-streaming
 // launch (the same x, the columns of W_q simply follow the cache row's columns); q_finish adds the
 // query's split sums and rounds them (every q-prep work-group needs the whole query: summing the
 // splits there, 193 times over, was measured at 25 us).  oproj: y = out W^o by the same
 // weight-streaming body, whose x is read as the sum of the merge's column-chunk partials, so the
 // merge needs no reduction launch; the last work-group of a column block adds its contraction splits (the launch that did
-// was 3.9 us and a gap: 7B 25 %, one sequence of 4096 tokens, block 64.1 -> 61.7 us).
-template <int TT>
+// was 3.9 us and a gap: 7B 25 %, one sequence of 4096 tokens, block 64.1 -> 61.7 us).  More sequences take the composed form,
+// whose projections are on the matrix cores (7B 25 %, 2 / 4 / 7 sequences of 1000 tokens: 70.9 / 99.3 / 135.7 us this way,
+// 63.9 / 70.2 / 71.3 composed; one: 55.8 and 58.9).
 __global__ __launch_bounds__(kAsThreads) void block_front_kernel(const AppendSmallParams P) {
   extern __shared__ __attribute__((aligned(16))) float bfx[];
-  append_small_body<TT, kFrontBatch, 0>(P, blockIdx.x, blockIdx.y, 0, bfx);
+  append_small_body<1, kFrontBatch, 0>(P, blockIdx.x, blockIdx.y, 0, bfx);
 }
 
-template <int TT>
 __global__ __launch_bounds__(kAsThreads) void oproj_kernel(const AppendSmallParams P) {
   extern __shared__ __attribute__((aligned(16))) float opx[];
-  append_small_body<TT, kFrontBatch, 1>(P, blockIdx.x, blockIdx.y, 0, opx);
+  append_small_body<1, kFrontBatch, 1>(P, blockIdx.x, blockIdx.y, 0, opx);
 }
 
 // q[b, c] = bf16(sum over the contraction splits of the x W_q columns of the front pass)
@@ -140,16 +139,15 @@ static void stream_splits(int rows, int* ks, int* kc) {
 }
 
 bool block_step_plan(const elitekv_dims& d, int64_t B, int* fr_ks, int* fr_kc, int* y_ks, int* y_kc) {
-  if (B < 1 || B > kAsTokens || d.d_model % kAsCols || (d.n_heads * d.head_dim) % kAsCols) return false;
+  if (B != 1 || d.d_model % kAsCols || (d.n_heads * d.head_dim) % kAsCols) return false;
   if (d.d_model / kAsCols > d.n_heads * d.head_dim) return false;      // the arrival counters lie in the query's columns
   stream_splits(d.d_model, fr_ks, fr_kc);
   stream_splits(d.n_heads * d.head_dim, y_ks, y_kc);
   return true;
 }
 
-template <int TT>
-static hipError_t launch_block_front_tt(const AppendArgs& ap, const void* W_q, const DecodeArgs& a, const DecodePlan& p,
-                                        hipStream_t stream) {
+hipError_t launch_block_front(const AppendArgs& ap, const void* W_q, const DecodeArgs& a, const DecodePlan& p,
+                              hipStream_t stream) {
   const elitekv_dims& d = a.dims;
   const int NE = 2 * d.r * d.n_heads, q_cols = d.n_heads * d.head_dim;
   AppendSmallParams A;
@@ -158,7 +156,7 @@ static hipError_t launch_block_front_tt(const AppendArgs& ap, const void* W_q, c
   A.NE = NE; A.d_c = d.d_c; A.kc = p.fr_kc;
   A.W_q = (const bf16_t*)W_q; A.q_cols = q_cols; A.x_opart = nullptr; A.x_heads = 0; A.x_chunks = 0; A.x_dh = 1;
   const dim3 grid((NE + d.d_c + q_cols) / kAsCols, p.fr_ks);
-  block_front_kernel<TT><<<grid, kAsThreads, (size_t)p.fr_kc * TT * sizeof(float), stream>>>(A);
+  block_front_kernel<<<grid, kAsThreads, (size_t)p.fr_kc * sizeof(float), stream>>>(A);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t total = ap.T * (int64_t)q_cols;
@@ -167,37 +165,23 @@ static hipError_t launch_block_front_tt(const AppendArgs& ap, const void* W_q, c
   return hipGetLastError();
 }
 
-hipError_t launch_block_front(const AppendArgs& ap, const void* W_q, const DecodeArgs& a, const DecodePlan& p,
-                              hipStream_t stream) {
-  const int tt = front_tile(a.B);
-  return tt == 1 ? launch_block_front_tt<1>(ap, W_q, a, p, stream) : tt == 2 ? launch_block_front_tt<2>(ap, W_q, a, p, stream)
-       : tt == 4 ? launch_block_front_tt<4>(ap, W_q, a, p, stream) : launch_block_front_tt<8>(ap, W_q, a, p, stream);
-}
-
-template <int TT>
-static hipError_t launch_oproj_tt(const DecodeArgs& a, const DecodePlan& p, const void* W_o, void* y, hipStream_t stream) {
+hipError_t launch_oproj(const DecodeArgs& a, const DecodePlan& p, const void* W_o, void* y, hipStream_t stream) {
   const elitekv_dims& d = a.dims;
   AppendSmallParams A;
   A.x = nullptr; A.T = a.B; A.W_ke = nullptr; A.W_dkv = (const bf16_t*)W_o; A.W_dkv2 = nullptr;
   A.partial = (float*)(a.ws + p.off_ypart); A.d_ck = d.d_model; A.d = d.n_heads * d.head_dim; A.NE = 0; A.d_c = d.d_model;
   A.kc = p.y_kc; A.W_q = nullptr; A.q_cols = 0;
-  A.x_opart = (const float*)(a.ws + p.off_opart); A.x_heads = d.n_heads; A.x_chunks = p.d_u / p.up_cw; A.x_dh = d.head_dim;
+  A.x_opart = (const float*)(a.ws + p.off_opart); A.x_heads = d.n_heads; A.x_chunks = (p.d_u + p.up_cw - 1) / p.up_cw; A.x_dh = d.head_dim;
   A.dense_out = (bf16_t*)y; A.n_splits = p.y_ks;
   A.arrived = (int*)(a.ws + p.off_apart) + 2 * d.r * d.n_heads + d.d_c;   // cleared by q_finish, whose split sums lay there
   const dim3 grid(d.d_model / kAsCols, p.y_ks);
-  oproj_kernel<TT><<<grid, kAsThreads, (size_t)p.y_kc * TT * sizeof(float), stream>>>(A);
+  oproj_kernel<<<grid, kAsThreads, (size_t)p.y_kc * sizeof(float), stream>>>(A);
   return hipGetLastError();
 }
 
-hipError_t launch_oproj(const DecodeArgs& a, const DecodePlan& p, const void* W_o, void* y, hipStream_t stream) {
-  const int tt = front_tile(a.B);
-  return tt == 1 ? launch_oproj_tt<1>(a, p, W_o, y, stream) : tt == 2 ? launch_oproj_tt<2>(a, p, W_o, y, stream)
-       : tt == 4 ? launch_oproj_tt<4>(a, p, W_o, y, stream) : launch_oproj_tt<8>(a, p, W_o, y, stream);
-}
-
-// ---- batches of eight rows and up: the matrix-core versions of the two roles in one launch; the
-// append's split sums are then added, rotated and stored by append_finish (with many sequences the
-// new-token work-groups of the attention kernel would take compute units from its tile work-groups).
+// ---- kMatrixRows to 64 sequences: the matrix-core versions of the two roles in one launch.  Bound like the other one by the
+// latency of a cold pass over the weights, not by its products: a step of five sequences of 1000 tokens 58.3 -> 38.3 us
+// (7B 25 %), 97.0 -> 54.2 (13B 25 %).
 template <int KS, int TT>
 __global__ __launch_bounds__(256) void decode_front_mfma_kernel(const AppendSkinnyParams A, const QprepRowsParams Q,
                                                                 const RopeTable rope, int n_qprep, int q_blocks,
@@ -212,13 +196,7 @@ __global__ __launch_bounds__(256) void decode_front_mfma_kernel(const AppendSkin
   }
 }
 
-bool decode_front_mfma_supported(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p) {
-  const elitekv_dims& d = a.dims;
-  if (!p.mfma || p.fresh == 1 || ap.T != a.B) return false;
-  return qprep_mfma_supported(d, p.d_q, a.B) && append_skinny_supported(d, ap.T, ap.d_ck);
-}
-
-// Fused step for 8 to 64 sequences: the contraction splits and the rows of a split that the batched front launch
+// Fused step for kMatrixRows to 64 sequences: the contraction splits and the rows of a split that the batched front launch
 // leaves for the attention kernel's owner work-groups (no finishing launch).
 bool decode_front_mfma_plan(const elitekv_dims& d, int d_ck, int d_q, int64_t B, int* ks_out, int* kc_out) {
   if (!qprep_mfma_supported(d, d_q, B) || !append_skinny_supported(d, B, d_ck > 0 ? d_ck : d.d_c)) return false;
@@ -236,19 +214,16 @@ static hipError_t launch_front_mfma_ks(const AppendArgs& ap, const DecodeArgs& a
   int ks = append_skinny_ksplit(d);
   const int kc = append_skinny_kc(d, ks);
   ks = (d.d_model + kc - 1) / kc;            // splits that still have rows; never more than planned
-  float* partial = p.fresh == 2 ? (float*)(a.ws + p.off_apart) : (float*)ap.ws;
   const size_t sm_q = qprep_mfma_lds(d.head_dim, d.r);
   const size_t sm = sm_q > (size_t)kSkLds ? sm_q : (size_t)kSkLds;
-  const int q_blocks = p.d_q / 128, n_qprep = q_blocks * d.n_heads, n_blocks = N / kSkCols;
-  const AppendSkinnyParams A = make_append_skinny_params(ap, partial, kc);
+  const int q_blocks = (p.d_q + 127) / 128, n_qprep = q_blocks * d.n_heads, n_blocks = N / kSkCols;
+  const AppendSkinnyParams A = make_append_skinny_params(ap, (float*)(a.ws + p.off_apart), kc);
   const QprepRowsParams Q = make_qprep_rows_params(a, p, (float*)(a.ws + p.off_qe), (bf16_t*)(a.ws + p.off_qt));
   const RopeTable rope = rope_table(d.rope_base, d.head_dim);
   const unsigned grid = (unsigned)(n_qprep + n_blocks * ks);
   if (ap.T <= 32) decode_front_mfma_kernel<KS, 1><<<grid, 256, sm, stream>>>(A, Q, rope, n_qprep, q_blocks, n_blocks);
   else decode_front_mfma_kernel<KS, 2><<<grid, 256, sm, stream>>>(A, Q, rope, n_qprep, q_blocks, n_blocks);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p.fresh == 2) return e;            // fused step: the attention launch finishes the new rows
-  return launch_append_finish(ap, partial, ks, stream);
+  return hipGetLastError();                                 // the attention launch finishes the new rows
 }
 
 hipError_t launch_decode_front_mfma(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p, hipStream_t stream) {

@@ -130,11 +130,11 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     p->mfma = 1;
     p->head_groups = (d->n_heads + 31) / 32;
     int ks = 0, kc = 0;
-    if (want_fresh && B > 0 && decode_front_plan(*d, d_ck, p->d_q, B, &ks, &kc)) {
-      p->fresh = 1; p->fr_ks = ks; p->fr_kc = kc;
-      p->fr_stride = 2 * d->r * d->n_heads + d->d_c;
-    } else if (want_fresh && !block && B > 0 && decode_front_mfma_plan(*d, d_ck, p->d_q, B, &ks, &kc)) {
+    if (want_fresh && !block && B > 0 && decode_front_mfma_plan(*d, d_ck, p->d_q, B, &ks, &kc)) {
       p->fresh = 2; p->fr_ks = ks; p->fr_kc = kc;
+      p->fr_stride = 2 * d->r * d->n_heads + d->d_c;
+    } else if (want_fresh && B > 0 && (!block || B < kMatrixRows) && decode_front_plan(*d, d_ck, p->d_q, B, &ks, &kc)) {
+      p->fresh = 1; p->fr_ks = ks; p->fr_kc = kc;
       p->fr_stride = 2 * d->r * d->n_heads + d->d_c;
     }
     if (block) {
@@ -163,7 +163,7 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     p->merge_batch = merge_mfma_supported(*d, p->d_u, B, p->n_part) ? 1 : 0;
     p->up_cw = p->merge_batch ? 128 : (p->d_u % 192 == 0) ? 192 : 64;
     p->off_opart = off;
-    off = align_up(off + Bz * nh * (size_t)(p->d_u / p->up_cw) * d->head_dim * sizeof(float), 256);
+    off = align_up(off + Bz * nh * (size_t)((p->d_u + p->up_cw - 1) / p->up_cw) * d->head_dim * sizeof(float), 256);
     p->off_cnt = off;
     off = align_up(off + Bz * nh * sizeof(int32_t), 256);
     if (p->fresh) {
@@ -296,6 +296,13 @@ static size_t append_ws_bytes(const elitekv_dims* dims, int32_t d_ck, int64_t T)
   return 0;
 }
 
+// what the size functions answer: room for every smaller number of tokens too (one token takes the weight-streaming
+// kernel, whose contraction splits may be more than twice those of the matrix-core kernel)
+static size_t append_ws_reserve(const elitekv_dims* dims, int32_t d_ck, int64_t T) {
+  const size_t own = append_ws_bytes(dims, d_ck, T);
+  return own ? std::max(own, append_ws_bytes(dims, d_ck, 1)) : 0;
+}
+
 // argument checks of an append; ws_needed = 0 skips the workspace check
 static int append_check(const elitekv_dims* dims, int32_t d_ck, const void* x, const int32_t* pos,
                         const int64_t* slot, int64_t T, const void* W_ke, const void* W_dkv, const void* W_dkv2,
@@ -356,7 +363,7 @@ static int append_impl(const elitekv_dims* dims, int32_t d_ck, const void* x, co
 }
 
 size_t elitekv_append_workspace_bytes(const elitekv_dims* dims, int64_t T) {
-  return dims ? append_ws_bytes(dims, dims->d_c, T) : 0;
+  return dims ? append_ws_reserve(dims, dims->d_c, T) : 0;
 }
 
 int elitekv_append(const elitekv_dims* dims, const void* x, const int32_t* pos, const int64_t* slot,
@@ -499,12 +506,6 @@ static int step_impl(const elitekv_dims* dims, int32_t d_ck, const void* x, cons
     e = p.fresh == 2 ? launch_decode_front_mfma(ap, a, p, stream) : launch_decode_front(ap, a, p, stream);
     a.stages = 6;
     if (e == hipSuccess) e = launch_decode_mfma(a, p, stream);
-  } else if (decode_front_mfma_supported(ap, a, p)) {
-    // batches: first pass of the append + query preparation in one launch, the append's finishing
-    // launch, then attention, merge and up-projection
-    e = launch_decode_front_mfma(ap, a, p, stream);
-    a.stages = 6;
-    if (e == hipSuccess) e = launch_decode_mfma(a, p, stream);
   } else if (front_tiled_supported(ap, a, p)) {
     e = launch_front_tiled(ap, a, p, stream);
     a.stages = 6;
@@ -557,7 +558,7 @@ static hipError_t launch_projection(const elitekv_dims* dims, const void* in, co
   return append_skinny_supported(pd, T, N) ? launch_append_skinny(a, stream) : launch_append_small(a, stream);
 }
 
-// The composed form of the block step, for what the fused form does not cover (eight sequences and more, separated
+// The composed form of the block step, for what the fused form does not cover (two sequences and more, separated
 // latents): q = x W_q, the decode step, y = out W_o as launches of their own, q and out staying in the workspace.
 // Workspace: [decode-step workspace | q bf16 [B, n_h d_h] | out bf16 [B, n_h d_h] | projection partial sums].
 struct BlockLayout { size_t step, off_q, off_o, off_proj, total; };
@@ -631,7 +632,7 @@ int elitekv_block_step(const elitekv_dims* dims, const void* x, const int32_t* p
   if (B == 0) return check_dims(dims);                       // nothing to do
   DecodePlan p;
   int st = plan_decode(dims, 0, B, max_seq_len, n_splits, &p, true, true);
-  if (st == ELITEKV_EUNSUPPORTED)                            // eight sequences and more, ...: the composed form
+  if (st == ELITEKV_EUNSUPPORTED)                            // two sequences and more, ...: the composed form
     return block_composed_impl(dims, 0, x, pos, slot, seq_len, B, max_seq_len, batch_stride_rows, W_q, W_ke, W_dkv,
                                nullptr, W_uk, W_uv, W_o, elite_idx, ke_plane, c_plane, plane_rows, y, ws, ws_bytes,
                                n_splits, hip_stream);
@@ -836,7 +837,7 @@ int elitekv_slrd_param_count(const elitekv_dims* dims, int32_t d_ck, int64_t* n_
 
 size_t elitekv_slrd_append_workspace_bytes(const elitekv_dims* dims, int32_t d_ck, int64_t T) {
   if (!dims || d_ck <= 0 || d_ck >= dims->d_c) return 0;
-  return append_ws_bytes(dims, d_ck, T);
+  return append_ws_reserve(dims, d_ck, T);
 }
 
 int elitekv_slrd_append(const elitekv_dims* dims, int32_t d_ck, const void* x, const int32_t* pos,

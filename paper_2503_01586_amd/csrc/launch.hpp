@@ -29,6 +29,12 @@ inline hipError_t raise_lds_limit(LdsLimit& st, const void* kernel, size_t bytes
   return e;
 }
 
+// Rows (sequences of a step, tokens of an append, queries) from which the small kernels around the attention run on the
+// matrix cores.  Their vector-unit versions do a row's multiplications one after the other: a step of 1000 tokens per
+// sequence, vector / matrix, us (1, 2, 4, 7 sequences):
+//   7B 25 %: 29.1 / 30.6, 35.0 / 34.9, 52.6 / 40.3, 65.2 / 41.2     13B 25 %: 46.2 / 46.9, 64.0 / 48.6, 79.1 / 51.7, 106 / 58.2
+//   7B 12.5 %: 26.5 / 27.7, 32.2 / 31.5, 36.8 / 33.8, 47.6 / 33.8   S-LRD 576 + 960: 27.9 / 28.2, 31.2 / 30.6, 38.0 / 34.0, 45.8 / 35.4
+constexpr int kMatrixRows = 2;
 
 // Where each intermediate of one decode call lives inside the caller's workspace.
 struct DecodePlan {
@@ -52,8 +58,8 @@ struct DecodePlan {
   size_t off_cnt;       // MFMA path: arrival counters of the merge kernels' chunk groups   int32 [B, n_h]
   // fused decode step (fresh != 0): the cache row of the newest token of every sequence is finished (summed,
   // rotated, stored) inside the attention kernel, by the work-group whose tiles include its position,
-  // from the append's contraction-split sums.  1: fewer than eight sequences (weight-streaming front launch),
-  // 2: eight to 64 sequences (matrix-core front launch)
+  // from the append's contraction-split sums.  1: one sequence, and up to seven whose hidden width is no multiple of
+  // eight (weight-streaming front launch), 2: kMatrixRows to 64 sequences (matrix-core front launch)
   int32_t fresh;
   int32_t n_part;       // partials per batch row (= n_splits)
   int32_t fr_ks;        // contraction splits of the step's append
@@ -168,8 +174,7 @@ bool block_step_plan(const elitekv_dims& d, int64_t B, int* fr_ks, int* fr_kc, i
 hipError_t launch_block_front(const AppendArgs& ap, const void* W_q, const DecodeArgs& a, const DecodePlan& p,
                               hipStream_t stream);   // + the sum of the query's contraction splits into ws + off_qfin
 hipError_t launch_oproj(const DecodeArgs& a, const DecodePlan& p, const void* W_o, void* y, hipStream_t stream);
-// ... for batches of eight rows and up (matrix-core roles; includes the append's finishing launch)
-bool decode_front_mfma_supported(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p);
+// ... for kMatrixRows to 64 sequences (matrix-core roles)
 bool decode_front_mfma_plan(const elitekv_dims& d, int d_ck, int d_q, int64_t B, int* ks, int* kc);
 hipError_t launch_decode_front_mfma(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 bool merge_mfma_supported(const elitekv_dims& d, int d_u, int64_t B, int64_t n_splits);

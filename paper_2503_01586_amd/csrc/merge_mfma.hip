@@ -1,6 +1,7 @@
 // merge_up_mfma: log-sum-exp merge of the sequence splits, normalisation and the W_uv up-projection
 // for a decoding batch (Section 2.1, exact softmax identity; Section 3.2, B^v_J; Section 5).
-// One work-group per (chunk of 128 latent columns, head, tile of up to 32 batch rows):
+// One work-group per (chunk of 128 latent columns (the last one of a width of odd multiples of 64: 64 of them and 64 zeros),
+// head, tile of up to 32 batch rows):
 //   1. every global load of the work-group is requested up front: the split maxima and sums, the
 //      chunk of W_uv[:, head, :] (staged in LDS as stored, [k][j]), and the first sixteen split
 //      accumulators of every thread, so the kernel pays one round of memory latency;
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
 #pragma unroll
   for (int i = 0; i < WPASS; ++i) {
     const int e = i * 256 + tid, k = e / CPR, c = e % CPR;
-    wld[i] = ld16_stream(W_uv + ((int64_t)(col0 + k) * n_h + head) * DH + c * 8);
+    wld[i] = ld16_stream(W_uv + ((int64_t)min(col0 + k, d_u - 1) * n_h + head) * DH + c * 8);   // (past the end: against zeros)
   }
   //      split accumulators: thread <-> (item g [+16], 16-byte piece cl); item = (row rl, slice sl);
   //      slice sl of SL takes the splits sl, sl + SL, ...
@@ -89,11 +90,12 @@ __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
   const int64_t sstep = (int64_t)nhp * d_u;
   const bf16_t* ub[2];
   int sl_of[2], rl_of[2];
-  bool item_ok[2];
+  bool item_ok[2], load_ok[2];
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
     const int item = g + 16 * e;
     item_ok[e] = item < n_items;
+    load_ok[e] = item_ok[e] && col0 + cl * 8 < d_u;                        // the last chunk may be 64 columns wide
     rl_of[e] = item_ok[e] ? item % rows : 0;
     sl_of[e] = item_ok[e] ? item / rows : 0;
     ub[e] = part_u + (((int64_t)(b0 + rl_of[e]) * n_splits) * nhp + head) * (int64_t)d_u + col0 + cl * 8;
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
     const int e = two ? (p & 1) : 0, q = two ? (p >> 1) : p;
     const int s = sl_of[e] + q * SL;
     pre[p] = make_uint4(0, 0, 0, 0);
-    if (item_ok[e] && s < n_splits) pre[p] = *reinterpret_cast<const uint4*>(ub[e] + s * sstep);
+    if (load_ok[e] && s < n_splits) pre[p] = *reinterpret_cast<const uint4*>(ub[e] + s * sstep);
   }
   const int pre_q = two ? kMmPre / 2 : kMmPre;     // splits per item that were requested up front
 
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         u[q] = make_uint4(0, 0, 0, 0);
-        if (s0 + q * SL < n_splits) u[q] = *reinterpret_cast<const uint4*>(ub[e] + (s0 + q * SL) * sstep);
+        if (load_ok[e] && s0 + q * SL < n_splits) u[q] = *reinterpret_cast<const uint4*>(ub[e] + (s0 + q * SL) * sstep);
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q)
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
 }
 
 bool merge_mfma_supported(const elitekv_dims& d, int d_u, int64_t B, int64_t n_splits) {
-  if (B < 2 || d_u % kMmCols || (d.head_dim != 128 && d.head_dim != 64)) return false;
+  if (B < 2 || d_u % 64 || (d.head_dim != 128 && d.head_dim != 64)) return false;
   return (B < kMmRows ? B : kMmRows) * n_splits <= kMmWeightFloats;   // (any smaller row tile fits too)
 }
 
@@ -260,13 +262,13 @@ static hipError_t launch_merge_mfma_dh(const DecodeArgs& a, const DecodePlan& p,
   const elitekv_dims& d = a.dims;
   // rows per work-group: all of them (up to 32) unless that leaves compute units idle
   int rows = (int)(a.B < kMmRows ? a.B : kMmRows);
-  const int64_t groups = (int64_t)(p.d_u / kMmCols) * d.n_heads;
+  const int64_t groups = (int64_t)((p.d_u + kMmCols - 1) / kMmCols) * d.n_heads;
   while (rows > 8 && groups * ((a.B + rows - 1) / rows) < 256) rows = (rows + 1) / 2;
   const size_t sm = L::lds_bytes(rows, p.n_part);
   static LdsLimit lds_limit;
   const hipError_t le = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&merge_up_mfma_kernel<DH>), sm);
   if (le != hipSuccess) return le;
-  const dim3 grid(p.d_u / kMmCols, d.n_heads, (unsigned)((a.B + rows - 1) / rows));
+  const dim3 grid((p.d_u + kMmCols - 1) / kMmCols, d.n_heads, (unsigned)((a.B + rows - 1) / rows));
   merge_up_mfma_kernel<DH><<<grid, 256, sm, stream>>>(
       (const float*)(a.ws + p.off_m), (const float*)(a.ws + p.off_l), (const bf16_t*)(a.ws + p.off_u),
       (const bf16_t*)a.W_uv, (float*)(a.ws + p.off_opart), (int)a.B, d.n_heads, p.head_groups * 32, p.d_u,

@@ -1,4 +1,4 @@
-// Query preparation of the decode step for a batch (eight rows and up), on the matrix cores.
+// Query preparation of the decode step for a batch (two rows and up), on the matrix cores.
 // The body is a device function: it is the whole of qprep_mfma_kernel and one of the two roles of
 // the decode step's front kernel for batches.
 #pragma once
@@ -14,7 +14,9 @@ namespace ekv {
 //                          consecutive j are contiguous), kept in registers for every batch tile
 //   B (16 x 32)          = the compacted non-elite query of 32 batch rows, from LDS
 // One wave per 32 latent columns, four waves (128 columns) per work-group, all batch rows: W_uk is
-// read once.  Work-groups of the first column block also write the rotated elite query.
+// read once.  Bound by the latency of one cold pass over W_uk; the products cost the same for 2 and for 32 rows
+// (qprep_rows, which takes them one by one: 25 us for six queries of the 7B 12.5 % shape, this: 8).  Work-groups of the
+// first column block also write the rotated elite query.
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 qp_bf16x8;
 typedef __attribute__((ext_vector_type(8))) short qp_s16x8;
@@ -45,11 +47,12 @@ __device__ __forceinline__ void qprep_mfma_body(const QprepRowsParams& P, const 
   const int h = by;
   const int k0 = bx * 128 + wave * 32;
   const int n32 = lane & 31, hi = lane >> 5;
+  const bool cols = k0 < d_c;                              // the last block of a width of odd multiples of 32 columns
 
   // this lane's pieces of W_uk row (k0 + n32, h): chunks 2*ks + hi
   qp_bf16x8 A[KS];
   {
-    const bf16_t* wrow = W_uk + ((int64_t)(k0 + n32) * n_h + h) * nd;
+    const bf16_t* wrow = W_uk + ((int64_t)min(k0 + n32, d_c - 1) * n_h + h) * nd;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const int c = 2 * ks + hi;
@@ -95,7 +98,7 @@ __device__ __forceinline__ void qprep_mfma_body(const QprepRowsParams& P, const 
       }
     }
     __syncthreads();
-    for (int bt = 0; bt < rows; bt += 32) {
+    for (int bt = 0; cols && bt < rows; bt += 32) {
       qp_f32x16 acc = (qp_f32x16)(0.f);
       const uint16_t* brow = qne + (bt + n32) * ndp + hi * 8;
 #pragma unroll

@@ -1,4 +1,4 @@
-// Query preparation of the decode step for fewer than eight batch rows: the rotated elite query and
+// Query preparation of the decode step for one batch row (and for shapes outside the matrix-core version): the rotated elite query and
 // W_uk absorbed into the rest of the query (Section 3.1 score equation, first sum; Section 5,
 // absorption of B^k).  The body is a device function: it is the whole of qprep_rows_kernel, and one
 // of the two roles of the decode step's front kernel.

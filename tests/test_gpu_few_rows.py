@@ -1,0 +1,116 @@
+"""GPU parity of the matrix-core front launch, query preparation and batched merge where they begin and where a block of
+theirs is not full: from two sequences on, and latent widths that are odd multiples of 64 columns on either side of a
+separated latent.  Shapes outside those kernels (a hidden width that is no multiple of eight) keep the vector-unit ones.
+Against the float64 oracle, through the C ABI; bound max-abs-rel <= 2e-2 (bf16)."""
+import numpy as np
+import pytest
+import torch
+
+import elitekv_synth as synth
+import paper_2503_01586_amd as ekv
+from oracle import elitekv_oracle as orc
+
+from gpu_util import DEV, TOL, dev, dims_of, gpu_append, host64, i32, i64
+from test_gpu_parity import _draw, shape
+from test_gpu_slrd import _draw as _draw_slrd, gpu_slrd_decode, shape as slrd_shape
+
+pytestmark = pytest.mark.gpu
+
+# (d_model, heads, head_dim, r, d_ck, d_cv)
+SEPARATED = [(136, 8, 64, 4, 192, 192), (256, 32, 128, 8, 320, 320), (192, 40, 128, 4, 448, 448), (512, 32, 128, 8, 576, 960)]
+
+
+def _slrd_planes(sh, rng, B, stride):
+    ke, c = synth.draw_cache_planes(rng, B * stride, sh["n_heads"], sh["r"], sh["d_c"])
+    return dev(ke, "bf16"), dev(c, "bf16")
+
+
+def _latents(c, B, sh):
+    c = c.reshape(B, -1, sh["d_c"])
+    return c[..., :sh["d_ck"]], c[..., sh["d_ck"]:]
+
+
+@pytest.mark.parametrize("B", [2, 3, 7, 9, 33])
+@pytest.mark.parametrize("dims6", SEPARATED, ids=lambda t: "%d+%d" % t[4:])
+def test_separated_step(dims6, B):
+    sh = slrd_shape(*dims6, "bf16")
+    seqs = [1 + (37 * i + 15) % 83 for i in range(B)]
+    stride, n_h, d_h, d_ck = max(seqs) + 2, sh["n_heads"], sh["head_dim"], sh["d_ck"]
+    rng, idx, W_ke, A_k, A_v, B_k, B_v, x, q = _draw_slrd(sh, B, B, 40 + B)
+    dims = dims_of(sh)
+    ke, c = _slrd_planes(sh, rng, B, stride)
+    pos = np.array(seqs) - 1
+    slot = np.arange(B) * stride + pos
+    xd, qd, Wked, Akd, Avd, Bkd, Bvd = (dev(a, "bf16") for a in (x, q, W_ke, A_k, A_v, B_k, B_v))
+    out = torch.full((B, n_h, d_h), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = torch.full((ekv.elitekv_slrd_decode_step_workspace_bytes(dims, d_ck, B, max(seqs)),), 0xFF, dtype=torch.uint8, device=DEV)
+    ekv.elitekv_slrd_decode_step(dims, d_ck, xd, qd, i32(pos), i64(slot), i32(seqs), max(seqs), stride, Wked, Akd, Avd, Bkd, Bvd,
+                                 i32(idx), ke, c, out, ws)
+    torch.cuda.synchronize()
+    ke_ref, ck_ref, cv_ref = orc.slrd_append(host64(xd), pos, host64(Wked), host64(Akd), host64(Avd), idx, d_h, sh["rope_base"])
+    c_ref = np.concatenate([ck_ref, cv_ref], axis=1)
+    ke_g, c_g = host64(ke).reshape(B * stride, n_h, -1), host64(c)
+    assert orc.max_abs_rel(c_g[slot], c_ref) <= TOL["bf16"]
+    assert orc.max_abs_rel(ke_g[slot], ke_ref) <= TOL["bf16"]
+    ref = orc.slrd_decode_attn(host64(qd), pos, ke_g.reshape(B, stride, n_h, -1), *_latents(c_g, B, sh), seqs, host64(Bkd),
+                               host64(Bvd), idx, d_h, sh["rope_base"])
+    assert orc.max_abs_rel(host64(out), ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("n_splits", [1, 5])
+@pytest.mark.parametrize("dims6", SEPARATED, ids=lambda t: "%d+%d" % t[4:])
+def test_separated_decode(dims6, n_splits):
+    sh = slrd_shape(*dims6, "bf16")
+    seqs = [70, 0, 33]                                     # with a sequence that attends to nothing
+    B, stride, d_ck = len(seqs), 72, sh["d_ck"]
+    rng, idx, _, _, _, B_k, B_v, _, q = _draw_slrd(sh, 1, B, 60)
+    dims = dims_of(sh)
+    ke, c = _slrd_planes(sh, rng, B, stride)
+    qd, Bkd, Bvd = (dev(a, "bf16") for a in (q, B_k, B_v))
+    pos = np.maximum(np.array(seqs) - 1, 0)
+    out = gpu_slrd_decode(dims, d_ck, qd, i32(pos), i32(seqs), max(seqs), stride, Bkd, Bvd, i32(idx), ke, c, n_splits)
+    ref = orc.slrd_decode_attn(host64(qd), pos, host64(ke).reshape(B, stride, sh["n_heads"], -1), *_latents(host64(c), B, sh),
+                               seqs, host64(Bkd), host64(Bvd), idx, sh["head_dim"], sh["rope_base"])
+    assert orc.max_abs_rel(host64(out), ref) <= TOL["bf16"]
+    assert torch.count_nonzero(out[1]) == 0
+
+
+@pytest.mark.parametrize("B", [1, 3, 7])
+def test_hidden_width_outside_the_matrix_core_front(B):
+    sh = shape(1004, 32, 128, 8, 512, "bf16")              # rows of x are not 16-byte aligned
+    seqs = [5 + 13 * i for i in range(B)]
+    stride, n_h, d_h = max(seqs) + 1, 32, 128
+    rng, idx, W_ke, W_dkv, W_uk, W_uv, x, q = _draw(sh, B, B, 80 + B)
+    dims = dims_of(sh)
+    ke64, c64 = synth.draw_cache_planes(rng, B * stride, n_h, 8, 512)
+    ke, c = dev(ke64, "bf16"), dev(c64, "bf16")
+    pos = np.array(seqs) - 1
+    slot = np.arange(B) * stride + pos
+    xd, qd, Wked, Wdkvd, Wukd, Wuvd = (dev(a, "bf16") for a in (x, q, W_ke, W_dkv, W_uk, W_uv))
+    out = torch.full((B, n_h, d_h), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = torch.full((ekv.elitekv_decode_step_workspace_bytes(dims, B, max(seqs)),), 0xFF, dtype=torch.uint8, device=DEV)
+    ekv.elitekv_decode_step(dims, xd, qd, i32(pos), i64(slot), i32(seqs), max(seqs), stride, Wked, Wdkvd, Wukd, Wuvd, i32(idx), ke,
+                            c, out, ws)
+    torch.cuda.synchronize()
+    ke_ref, c_ref = orc.append(host64(xd), pos, host64(Wked), host64(Wdkvd), idx, d_h, sh["rope_base"])
+    ke_g, c_g = host64(ke).reshape(B * stride, n_h, -1), host64(c)
+    assert orc.max_abs_rel(c_g[slot], c_ref) <= TOL["bf16"]
+    assert orc.max_abs_rel(ke_g[slot], ke_ref) <= TOL["bf16"]
+    ref = orc.decode_attn(host64(qd), pos, ke_g.reshape(B, stride, n_h, -1), c_g.reshape(B, stride, -1), seqs, host64(Wukd),
+                          host64(Wuvd), idx, d_h, sh["rope_base"])
+    assert orc.max_abs_rel(host64(out), ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 7, 8])
+@pytest.mark.parametrize("d_model", [64, 136, 4096])       # less than a stage of the contraction, a ragged one, whole ones
+def test_append_of_few_tokens(d_model, T):
+    sh = shape(d_model, 32, 128, 8, 1536, "bf16")
+    rng, idx, W_ke, W_dkv, _, _, x, _ = _draw(sh, T, 1, 100 + T)
+    dims = dims_of(sh)
+    pos = np.array([3 * t + 11 for t in range(T)])
+    slot = np.array([T - 1 - t for t in range(T)])
+    xd, Wked, Wdkvd = (dev(a, "bf16") for a in (x, W_ke, W_dkv))
+    ke, c = gpu_append(dims, xd, i32(pos), i64(slot), Wked, Wdkvd, i32(idx), T)
+    ke_ref, c_ref = orc.append(host64(xd), pos, host64(Wked), host64(Wdkvd), idx, 128, sh["rope_base"])
+    assert orc.max_abs_rel(host64(c)[slot], c_ref) <= TOL["bf16"]
+    assert orc.max_abs_rel(host64(ke).reshape(T, 32, -1)[slot], ke_ref) <= TOL["bf16"]
