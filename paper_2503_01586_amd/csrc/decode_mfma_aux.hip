@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void merge_up_kernel(
   constexpr int LPW = DH / 8;              // lanes that cover one W_uv row
   constexpr int RPI = 64 / LPW;            // W_uv rows per wave instruction
   constexpr int NWI = CW / (4 * RPI);      // W_uv rows per thread
-  constexpr int UB = 28;                   // split accumulators requested per batch
+  constexpr int UB = CW == 128 ? 16 : 28;  // split accumulators requested per batch: 256 splits, and not many more registers
   // all arguments in one round trip of the scalar cache (else: three, one after the other, before the first load)
   asm volatile("" ::"s"(part_m), "s"(part_l), "s"(part_u), "s"(W_uv), "s"(opart), "s"(out), "s"(chunk_counters),
                "s"(fuse_out), "s"(n_h), "s"(nhp), "s"(d_c), "s"(n_splits), "s"(gridDim.x));
@@ -263,6 +263,17 @@ __global__ __launch_bounds__(256) void out_reduce_kernel(const float* __restrict
   st(out, e, a);
 }
 
+// 128 columns, or 192 where these (and only these) make no more work-groups than compute units: a work-group's time is the
+// latency of its one pass, so narrow chunks cost what wide ones do (a step of one sequence, 256 / 32000 tokens, chunks of
+// 64, 128, 192 columns, us: 7B 25 % 44.8, 29.4, 28.7 / 62.8, 48.8, 48.3; 13B 25 % 69.0, 43.3, 45.6 / 106, 82.3, 84.9; 7B
+// 12.5 % 32.5, 24.9, 26.1 / 44.0, 37.9, 37.9; 7B with 1024 columns 37.0, 27.8, - / 55.2, 46.7, -).  Widths that are
+// multiples of neither take the batched merge, which pads its last chunk.
+int merge_up_width(int n_heads, int d_u) {
+  const bool w128 = d_u % 128 == 0, w192 = d_u % 192 == 0;
+  if (w192 && (!w128 || (d_u / 192 * n_heads <= 256 && d_u / 128 * n_heads > 256))) return 192;
+  return w128 ? 128 : 0;
+}
+
 hipError_t launch_merge_up(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream) {
   const elitekv_dims& d = a.dims;
   if (p.merge_batch) {
@@ -278,7 +289,7 @@ hipError_t launch_merge_up(const DecodeArgs& a, const DecodePlan& p, hipStream_t
   const bf16_t* pu = (const bf16_t*)(a.ws + p.off_u);
   float* opart = (float*)(a.ws + p.off_opart);
   const int cw = p.up_cw;
-  const dim3 grid(p.d_u / cw, d.n_heads, (unsigned)a.B);
+  const dim3 grid(p.d_u / cw, d.n_heads, 1);                 // one row
   const int nhp = p.head_groups * 32;
 #define EKV_MU(CW, DH)                                                                              \
   do {                                                                                              \
@@ -289,7 +300,7 @@ hipError_t launch_merge_up(const DecodeArgs& a, const DecodePlan& p, hipStream_t
                                                        p.d_u, p.n_part);                            \
   } while (0)
   if (cw == 192) { if (d.head_dim == 128) EKV_MU(192, 128); else EKV_MU(192, 64); }
-  else { if (d.head_dim == 128) EKV_MU(64, 128); else EKV_MU(64, 64); }
+  else { if (d.head_dim == 128) EKV_MU(128, 128); else EKV_MU(128, 64); }
 #undef EKV_MU
   return hipGetLastError();
 }

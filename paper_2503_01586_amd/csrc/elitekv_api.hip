@@ -160,8 +160,8 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     p->chunk = (int32_t)chunk;
     p->off_qt = off; off = align_up(off + Bz * (size_t)p->head_groups * 32 * dq * 2, 256);   // head groups padded to 32
     off = lay_partials(off, ns, most, p->head_groups * 32, du * 2);
-    p->merge_batch = merge_mfma_supported(*d, p->d_u, B, p->n_part) ? 1 : 0;
-    p->up_cw = p->merge_batch ? 128 : (p->d_u % 192 == 0) ? 192 : 64;
+    p->merge_batch = merge_mfma_supported(*d, p->d_u, Bq) ? 1 : 0;
+    p->up_cw = p->merge_batch ? 128 : merge_up_width(d->n_heads, p->d_u);
     p->off_opart = off;
     off = align_up(off + Bz * nh * (size_t)((p->d_u + p->up_cw - 1) / p->up_cw) * d->head_dim * sizeof(float), 256);
     p->off_cnt = off;

@@ -177,8 +177,9 @@ hipError_t launch_oproj(const DecodeArgs& a, const DecodePlan& p, const void* W_
 // ... for kMatrixRows to 64 sequences (matrix-core roles)
 bool decode_front_mfma_plan(const elitekv_dims& d, int d_ck, int d_q, int64_t B, int* ks, int* kc);
 hipError_t launch_decode_front_mfma(const AppendArgs& ap, const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
-bool merge_mfma_supported(const elitekv_dims& d, int d_u, int64_t B, int64_t n_splits);
+bool merge_mfma_supported(const elitekv_dims& d, int d_u, int64_t B);
 hipError_t launch_merge_mfma(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
+int merge_up_width(int n_heads, int d_u);     // latent columns per work-group of the one-row merge; 0: the batched merge
 hipError_t launch_merge_up(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 hipError_t launch_decode_mfma(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream);
 // many queries per sequence: keys and values rebuilt from the latent once per cached row (with the append's

@@ -251,17 +251,18 @@ __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
   }
 }
 
-bool merge_mfma_supported(const elitekv_dims& d, int d_u, int64_t B, int64_t n_splits) {
-  if (B < 2 || d_u % 64 || (d.head_dim != 128 && d.head_dim != 64)) return false;
-  return (B < kMmRows ? B : kMmRows) * n_splits <= kMmWeightFloats;   // (any smaller row tile fits too)
+// Two rows and more, and a single one whose width the one-row merge does not take.
+bool merge_mfma_supported(const elitekv_dims& d, int d_u, int64_t B) {
+  return (B >= 2 || merge_up_width(d.n_heads, d_u) == 0) && d_u % 64 == 0 && (d.head_dim == 128 || d.head_dim == 64);
 }
 
 template <int DH>
 static hipError_t launch_merge_mfma_dh(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream) {
   using L = MergeMfmaLayout<DH>;
   const elitekv_dims& d = a.dims;
-  // rows per work-group: all of them (up to 32) unless that leaves compute units idle
+  // rows per work-group: all of them (up to 32, and up to the weights its LDS holds) unless that leaves compute units idle
   int rows = (int)(a.B < kMmRows ? a.B : kMmRows);
+  if (rows * p.n_part > kMmWeightFloats) rows = kMmWeightFloats / p.n_part;       // at least four: a row has up to 1024 splits
   const int64_t groups = (int64_t)((p.d_u + kMmCols - 1) / kMmCols) * d.n_heads;
   while (rows > 8 && groups * ((a.B + rows - 1) / rows) < 256) rows = (rows + 1) / 2;
   const size_t sm = L::lds_bytes(rows, p.n_part);

@@ -10,7 +10,7 @@ import elitekv_synth as synth
 import paper_2503_01586_amd as ekv
 from oracle import elitekv_oracle as orc
 
-from gpu_util import DEV, TOL, dev, dims_of, gpu_append, host64, i32, i64
+from gpu_util import DEV, TOL, dev, dims_of, gpu_append, gpu_decode, host64, i32, i64
 from test_gpu_parity import _draw, shape
 from test_gpu_slrd import _draw as _draw_slrd, gpu_slrd_decode, shape as slrd_shape
 
@@ -114,3 +114,30 @@ def test_append_of_few_tokens(d_model, T):
     ke_ref, c_ref = orc.append(host64(xd), pos, host64(Wked), host64(Wdkvd), idx, 128, sh["rope_base"])
     assert orc.max_abs_rel(host64(c)[slot], c_ref) <= TOL["bf16"]
     assert orc.max_abs_rel(host64(ke).reshape(T, 32, -1)[slot], ke_ref) <= TOL["bf16"]
+
+
+# every chunk width of the one-row merge, the batched merge for a single row (a width of neither), more splits than one pass
+# of either takes, and row tiles cut down to the weights the LDS holds
+@pytest.mark.parametrize("B, n_splits", [(1, 1), (1, 300), (1, 1024), (9, 1024)])
+@pytest.mark.parametrize("n_h, d_ck, d_c", [(32, 0, 128), (32, 0, 768), (32, 0, 1024), (32, 0, 1536), (40, 0, 1920), (32, 320, 640),
+                                            (32, 576, 1536)])
+def test_merge_widths(n_h, d_ck, d_c, B, n_splits):
+    r, d_h, stride = 4, 128, 700
+    seqs = [690 - 71 * b for b in range(B)]
+    rng = np.random.default_rng(d_c + B + n_splits)
+    idx = synth.draw_elite_idx(rng, n_h, d_h, r)
+    dk, dv = (d_ck, d_c - d_ck) if d_ck else (d_c, d_c)
+    _, _, W_uk, _ = synth.draw_weights(rng, 64, n_h, d_h, r, dk)
+    _, _, _, W_uv = synth.draw_weights(rng, 64, n_h, d_h, r, dv)
+    ke64, c64 = synth.draw_cache_planes(rng, B * stride, n_h, r, d_c)
+    q = synth.draw_query(rng, B, n_h, d_h)
+    dims = ekv.make_dims(64, n_h, d_h, r, d_c, "bf16", 10000.0)
+    ke, c, qd, Wukd, Wuvd = (dev(a, "bf16") for a in (ke64, c64, q, W_uk, W_uv))
+    pos = np.array(seqs) - 1
+    args = (qd, i32(pos), i32(seqs), max(seqs), stride, Wukd, Wuvd, i32(idx), ke, c, n_splits)
+    out = gpu_slrd_decode(dims, d_ck, *args) if d_ck else gpu_decode(dims, *args)
+    keh, ch = host64(ke).reshape(B, stride, n_h, -1), host64(c).reshape(B, stride, -1)
+    rest = (seqs, host64(Wukd), host64(Wuvd), idx, d_h, 10000.0)
+    ref = (orc.slrd_decode_attn(host64(qd), pos, keh, ch[..., :dk], ch[..., dk:], *rest) if d_ck
+           else orc.decode_attn(host64(qd), pos, keh, ch, *rest))
+    assert orc.max_abs_rel(host64(out), ref) <= TOL["bf16"]
