@@ -360,10 +360,12 @@ __global__ __launch_bounds__(64 * CM * WNW) void append_gemm_dma_kernel(
     const bf16_t* __restrict__ W_ke, const bf16_t* __restrict__ W_dkv, const bf16_t* __restrict__ W_dkv2, int d_ck,
     const int32_t* __restrict__ elite_idx, bf16_t* __restrict__ ke_plane, bf16_t* __restrict__ c_plane,
     int64_t plane_rows, int d, int n_h, int d_h, int r, int d_c, RopeTable rope, int64_t x_ld, int x_off2, int d2,
-    GemmTileMap map) {
+    GemmTileMap map, int* clear, int n_clear) {
   using L = GemmDmaLayout<WN, NS, WNW, CM>;
   extern __shared__ __attribute__((aligned(16))) char gsm[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0)
+    for (int i = tid; i < n_clear; i += blockDim.x) clear[i] = 0;
   static_assert(KG == 1 || (KG == 2 && WN == 1 && WNW == 4 && CM == 2), "contraction groups: eight waves on 128 x 128");
   constexpr int WNC = KG * WN;                     // 32-token tiles a wave accumulates
   constexpr int KSN = 2 / KG;                      // k-steps of a stage a wave multiplies
@@ -585,10 +587,12 @@ __global__ __launch_bounds__(256, 1) void append_gemm_wide_kernel(
     const bf16_t* __restrict__ W_ke, const bf16_t* __restrict__ W_dkv, const bf16_t* __restrict__ W_dkv2, int d_ck,
     const int32_t* __restrict__ elite_idx, bf16_t* __restrict__ ke_plane, bf16_t* __restrict__ c_plane,
     int64_t plane_rows, int d, int n_h, int d_h, int r, int d_c, RopeTable rope, int64_t x_ld, int x_off2, int d2,
-    GemmTileMap map) {
+    GemmTileMap map, int* clear, int n_clear) {
   using L = GemmWideLayout<NS>;
   extern __shared__ __attribute__((aligned(16))) char gsm[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0)
+    for (int i = tid; i < n_clear; i += blockDim.x) clear[i] = 0;
   const int wm = wave & 1, wn = wave >> 1;
   const int n32 = lane & 31, hi = lane >> 5, i16 = lane & 15, q16 = lane >> 4;
   const int NE = 2 * r * n_h, N = NE + d_c;
@@ -792,7 +796,7 @@ static hipError_t launch_gemm_dma(const AppendArgs& a, hipStream_t stream) {
       (const bf16_t*)a.x, a.pos, a.slot, a.T, (const bf16_t*)a.W_ke, (const bf16_t*)a.W_dkv,
       (const bf16_t*)a.W_dkv2, a.d_ck, a.elite_idx, (bf16_t*)a.ke_plane, (bf16_t*)a.c_plane, a.plane_rows,
       d.d_model, d.n_heads, d.head_dim, d.r, d.d_c, rope_table(d.rope_base, d.head_dim),
-      a.x_ld ? a.x_ld : (int64_t)d.d_model, a.x_off2, a.d2, m);
+      a.x_ld ? a.x_ld : (int64_t)d.d_model, a.x_off2, a.d2, m, a.clear, a.n_clear);
   return hipGetLastError();
 }
 
@@ -808,7 +812,7 @@ static hipError_t launch_gemm_wide(const AppendArgs& a, hipStream_t stream) {
       (const bf16_t*)a.x, a.pos, a.slot, a.T, (const bf16_t*)a.W_ke, (const bf16_t*)a.W_dkv,
       (const bf16_t*)a.W_dkv2, a.d_ck, a.elite_idx, (bf16_t*)a.ke_plane, (bf16_t*)a.c_plane, a.plane_rows,
       d.d_model, d.n_heads, d.head_dim, d.r, d.d_c, rope_table(d.rope_base, d.head_dim),
-      a.x_ld ? a.x_ld : (int64_t)d.d_model, a.x_off2, a.d2, m);
+      a.x_ld ? a.x_ld : (int64_t)d.d_model, a.x_off2, a.d2, m, a.clear, a.n_clear);
   return hipGetLastError();
 }
 

@@ -122,6 +122,9 @@ struct AppendArgs {
   // T <= 64 append kernels run with r = 0 and leave x W_dkv as dense rows [T, d_c] of the storage type there;
   // no rotation, no planes, pos / slot / elite_idx unused.
   void* dense_out = nullptr;
+  // Direct-load GEMM kernels only: zeroed on the way, for a launch behind this one that counts in them
+  int* clear = nullptr;
+  int32_t n_clear = 0;
 };
 
 struct MhaArgs {

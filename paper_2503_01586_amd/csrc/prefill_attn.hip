@@ -15,19 +15,29 @@
 //                          order) | q's non-elite dims, ascending], scaled by log2(e)/sqrt(d_h)
 //                          (Section 3.1 score equation)
 //
-// Step 2, one work-group = 4 waves x 32 or 64 queries of one (sequence, head); a 64-key tile of K and V
-// comes in by direct global->LDS loads, double-buffered.  Per wave and tile:
+// Step 2, one work-group (4 waves, one per SIMD; 131 KB of LDS, so one per compute unit) = 128 or 256 queries of one
+// (sequence, head), 32 or 64 per wave; 64-key tiles of K and V come in by direct global->LDS loads into a ring of four.
+// Per wave and tile:
 //   S^T[key, query]   32x32x16 MFMA, A = key rows from LDS (16-byte reads), B = the wave's queries,
 //                     held in registers for the whole pass;
 //   softmax           a lane owns ONE query (the MFMA output column) and 16 keys per 32-key block,
-//                     its partner lane (l ^ 32) the other 16: the row maximum is an in-lane
-//                     reduction plus one shuffle;
+//                     its partner lane (l ^ 32) the other 16.  No maximum is taken per tile: the running one stays until
+//                     a lane's 16 probabilities add up to more than 2^8 (none of them can then be larger), and only such
+//                     a block is formed again with a raised maximum;
 //   O^T[dim, query]   32x32x16 MFMA, B = the probabilities straight from the score registers (the
 //                     keys of a k-step are taken in the order the score tile leaves them in a lane),
 //                     A = V read transposed from LDS (ds_read_b64_tr_b16) in that same key order.
-// Query blocks are handed out in pairs (i, last - i): under a causal mask every work-group then
-// has the same number of key tiles.  Work-groups of one (sequence, head) share an XCD, so the
-// tiles the later query blocks re-read come from that XCD's L2.
+// What bounds it: the matrix cores' power.  The loop alone, on zeros, takes 2800 cycles for the 64 MFMAs (2110 cycles) of 64
+// queries per wave; in a launch on all compute units a tile of 256 queries takes 1.9 us = 1120 TFLOP/s, where a library
+// product of 8192^3 reaches 1206.  To get there every vector instruction and LDS read stands behind an MFMA of its wave by hand
+// (left to the compiler they follow each other), 64 queries per wave halve the LDS reads per MFMA, and the accumulators of
+// the values live in AGPRs, the scores in VGPRs.  Before: 1.35 - 1.6 us per tile of 128 queries, from maxima, addresses
+// multiplied out per load, and MFMAs that waited for all of it; 7B 25 %, 2048 tokens 74 -> 63 us, 13B, 2 x 1021 over 8000 rows
+// 590 - 690 -> 350 - 420.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -44,7 +54,14 @@ constexpr int kPfTile = 64;                      // keys per tile
 constexpr int kPfRow = kPfDh * 2;                // bytes of a staged K or V row
 constexpr int kPfPlane = kPfTile * kPfRow;       // one K (or V) tile: 16 KiB
 constexpr int kPfStage = 2 * kPfPlane;           // K + V
-constexpr int kPfLds = 2 * kPfStage + 64 + 256;  // two stages + the block's reduction scratch + the head's chunk order
+constexpr int kPfRing = 4;                       // stages
+constexpr int kPfLds = kPfRing * kPfStage + 64 + 256;   // stages + the block's reduction scratch + the head's chunk order
+
+// Work-groups of a launch (one per compute unit), and the state that a work-group leaves of an unfinished block: (maximum, sum)
+// of every query, its accumulators
+constexpr int kPfGroups = 256;
+constexpr size_t kPfPartBytes = (size_t)256 * 16 * (2 + 2 * (kPfDh / 32) * 4);
+constexpr size_t kPfStates = 2 * kPfGroups * kPfPartBytes, kPfCounts = kPfGroups * sizeof(int);
 
 struct PrefillParams {
   const bf16_t* q;           // [B * T, n_h, d_h]  queries as the caller holds them (un-rotated)
@@ -56,14 +73,28 @@ struct PrefillParams {
   bf16_t* out;               // [B * T, n_h, d_h]
   int n_h, T, B;
   int nqb;                   // query blocks per sequence
-  int npair;                 // work-groups per (sequence, head): pairs of query blocks, or single blocks
-  int paired;                // 1: a work-group takes the blocks (last - i, i) one after the other; 0: block last - i only
+  int groups;                // work-groups among which the tiles are divided; 0: a work-group per block
+  int head_tiles;            // key tiles of a (sequence, head)'s query blocks, as pf_block_tiles counts them
+  int stretch, longer;       // tiles per work-group, and how many (the first ones) have one more
+  int shift;                 // (a line of 2^30 tiles and more is counted in larger units)
+  float* part;               // two states of an unfinished block per work-group
+  int* arrived;              // per work-group: pieces left of the divided block that it has the first one of; cleared by the rebuild
   float scale;               // log2(e) / sqrt(d_h)
   int64_t S;                 // rows per sequence in kv
   int64_t NKV, NK;           // row width of kv; first value column
   int64_t batch_stride_rows, plane_rows, max_seq_len;
   RopeTable rope;
 };
+
+// Key tiles of query block i (of `block` queries) of a sequence whose last T of S rows the queries are: what the host, which
+// does not see the lengths, divides among the work-groups
+__host__ __device__ inline int pf_block_tiles(int64_t S, int64_t T, int i, int block, int shift) {
+  int64_t end = (int64_t)(i + 1) * block;
+  if (end > T) end = T;
+  int64_t seen = S - T + end;
+  if (seen < 1) seen = 1;
+  return (int)((seen + kPfTile - 1) / kPfTile >> shift) + (shift > 0);
+}
 
 // staged rows are 16 chunks of 16 bytes; chunk c of row `row` sits at chunk c ^ pf_swz(row): 16 rows read at
 // one logical chunk cover all 64 banks, and the 4 rows x 32 bytes of a transposed read cover 4 different
@@ -82,32 +113,113 @@ __device__ __forceinline__ uint32_t pf_pack2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// log2-domain slack before a query's running maximum is raised: probabilities stay below 2^8
-constexpr float kPfSlack = 8.f;
+#define EKV_INLINE __attribute__((always_inline))
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
 
-// QB = 32-query blocks per wave: a work-group handles 4 * 32 * QB queries.  QB = 1 is what is launched:
-// two work-groups share a compute unit, so a SIMD has one wave's softmax arithmetic to run beside the
-// other wave's MFMAs.  (QB = 2: every K and V fragment read from LDS would feed two MFMAs, at one wave per SIMD.)
+// a query's running maximum is raised when a lane's 16 probabilities of a 32-key block add up to more than this: none is larger
+constexpr float kPfSumLimit = 256.f;
+
+// QB: 32-query blocks per wave; a work-group (one per compute unit, one wave per SIMD) has 128 QB queries of one head.
 template <int TWO_R, int QB>
-__global__ __launch_bounds__(256, QB == 1 ? 2 : 1) void prefill_attn_kernel(const PrefillParams p) {
+__global__ __launch_bounds__(256, 1) void prefill_attn_kernel(const PrefillParams p) {
   constexpr int KCH = TWO_R / 8;                 // leading 16-byte chunks of a key row that come from the elite plane
   constexpr int R = TWO_R / 2;
-  constexpr int QBLK = 128 * QB;                 // queries per work-group pass
+  constexpr int QBLK = 128 * QB;                 // queries per work-group
+  constexpr int KS = kPfDh / 16, DT = kPfDh / 32;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  int* red = reinterpret_cast<int*>(smem + 2 * kPfStage);
+  int* red = reinterpret_cast<int*>(smem + kPfRing * kPfStage);
   int* order = red + 16;                         // order[pp]: the chunk of q that is pair pp of the packed query
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n32 = lane & 31, g = lane >> 5, i16 = lane & 15, q16 = lane >> 4;
 
-  // work-groups go to the eight XCDs round-robin by linear index: all query blocks of one
-  // (sequence, head) get indices that are equal modulo 8
-  const int xcd = blockIdx.x & 7, seqi = blockIdx.x >> 3;
-  const int ph = (seqi / p.npair) * 8 + xcd;
-  if (ph >= p.B * p.n_h) return;
-  const int pr = seqi % p.npair;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem);
+
+  // Work-groups go to the eight XCDs round-robin by linear index.  Divided: an XCD gets one stretch of the line of all tiles,
+  // a work-group a part of it.  A work-group per block: the blocks of a head on one XCD, those that see the most keys first.
+  int wg, at, line_end;
+  if (p.groups > 0) {
+    const int per_xcd = (p.groups + 7) / 8;
+    wg = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (wg >= p.groups) return;
+    at = wg * p.stretch + min(wg, p.longer);
+    line_end = at + p.stretch + (wg < p.longer ? 1 : 0);
+  } else {
+    const int heads8 = (p.B * p.n_h + 7) / 8 * 8;
+    wg = blockIdx.x / heads8;                    // place among the head's blocks
+    const int head = blockIdx.x % heads8;
+    if (head >= p.B * p.n_h) return;
+    at = head * p.head_tiles;
+    for (int i = 0; i < wg; ++i) at += pf_block_tiles(p.S, p.T, p.nqb - 1 - i, QBLK, p.shift);
+    line_end = at + 1;                           // (the block's tiles follow below)
+  }
+  auto owner = [&](int t) EKV_INLINE {           // of tile t of the line
+    const int split = p.longer * (p.stretch + 1);
+    return t < split ? t / (p.stretch + 1) : p.longer + (t - split) / p.stretch;
+  };
+  while (at < line_end) {
+  // the next block of the stretch (a head's blocks lie in falling order), its tiles lo .. hi - 1 of `tiles`
+  const int ph = at / p.head_tiles;
+  int first = ph * p.head_tiles;                 // of the block, on the line
+  int qblk = p.nqb - 1, tiles = pf_block_tiles(p.S, p.T, qblk, QBLK, p.shift);
+  while (first + tiles <= at) {
+    first += tiles;
+    tiles = pf_block_tiles(p.S, p.T, --qblk, QBLK, p.shift);
+  }
+  const int lo = at - first, hi = p.groups > 0 ? min(tiles, line_end - first) : tiles;
+  at = first + hi;
+  int piece = 0, pieces = 1;
+  if (hi - lo < tiles) {
+    piece = wg - owner(first);
+    pieces = owner(first + tiles - 1) - owner(first) + 1;
+  }
   const int b = ph / p.n_h, h = ph % p.n_h;
   const int64_t row0 = (int64_t)b * p.batch_stride_rows;
-  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem);
+  __syncthreads();                               // the block before is done with the LDS
+
+  // ---- the wave's rows of q, as the caller holds them, into the last stages (four rows of 16 chunks per load; chunk c of
+  // row i lies at chunk c ^ (i & 15): the gather below reads one chunk of 32 rows at a time)
+  const int tq0 = qblk * QBLK + wave * (32 * QB);
+#pragma unroll
+  for (int a = 0; a < QB; ++a)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = u * 4 + (lane >> 4);
+      const int t = min(tq0 + a * 32 + i, p.T - 1);           // past the last query: computed like it, never stored
+      const bf16_t* src = p.q + (((int64_t)b * p.T + t) * p.n_h + h) * kPfDh + ((lane & 15) ^ (i & 15)) * 8;
+      pf_dma16(src, lds0 + (kPfRing - 1 - a) * kPfStage + wave * 8192 + u * 1024);
+    }
+  int len[QB];
+  int32_t q_at[QB];
+  float m_run[QB], l_run[QB];
+  // the block's largest visible length bounds the key loop; keys below the wave's smallest need no mask
+  int wmax = 0, wmin = 0x7fffffff;
+#pragma unroll
+  for (int a = 0; a < QB; ++a) {
+    const int tq = tq0 + a * 32 + n32;
+    const int64_t qrow = (int64_t)b * p.T + min(tq, p.T - 1);
+    int64_t len64 = p.kv_len[qrow];
+    q_at[a] = p.q_pos[qrow];
+    len64 = min(len64, p.max_seq_len);
+    len64 = min(len64, p.plane_rows - row0);
+    len64 = min(len64, p.S);
+    len[a] = (int)max(len64, (int64_t)0);
+    wmax = max(wmax, len[a]);
+    wmin = min(wmin, len[a]);
+    l_run[a] = 0.f;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    wmax = max(wmax, __shfl_xor(wmax, o, kWave));
+    wmin = min(wmin, __shfl_xor(wmin, o, kWave));
+  }
+  wmin = __builtin_amdgcn_readfirstlane(wmin);
+  if (lane == 0) red[wave] = wmax;
 
   // ---- the packed query's dim order (Section 3.1 score equation): the head's elite chunks in slot
   // order, then the other chunks ascending -- the order of a rebuilt key row [ke | c B^k]
@@ -121,12 +233,86 @@ __global__ __launch_bounds__(256, QB == 1 ? 2 : 1) void prefill_attn_kernel(cons
     order[lane] = 0;                                               // (repeated elite indices leave holes: keep them in range)
     if (pp < kPfDh / 2) order[pp] = lane;
   }
+  __syncthreads();
+  const int kv_hi = __builtin_amdgcn_readfirstlane(max(max(red[0], red[1]), max(red[2], red[3])));
+  // this work-group's tiles: the same share of the block's real ones
+  const int real = (kv_hi + kPfTile - 1) / kPfTile;
+  const int tile0 = real == tiles ? lo : (int)((int64_t)lo * real / tiles);
+  const int ntiles = (real == tiles ? hi : (int)((int64_t)hi * real / tiles)) - tile0;
+#pragma unroll
+  for (int a = 0; a < QB; ++a) m_run[a] = len[a] > tile0 * kPfTile ? -INFINITY : 0.f;   // (sees nothing: all its probabilities are 0)
 
-  // ---- loader: wave w fills rows 16w .. 16w+15 of the K tile and of the V tile, four rows per load;
-  // lane l fills (row l/16, chunk position l%16) and fetches the logical chunk the swizzle puts there
-  const int ld_r = lane >> 4;
+  // ---- loader: load u of wave w fills rows 16u + 4w .. + 3 of the K tile and of the V tile; lane l fills (row l/16, chunk
+  // position l%16) and fetches the logical chunk the swizzle puts there: the same one for every u, so a lane has one
+  // running pointer into the keys (elite plane or rebuilt rows) and one into the values, moved on by 16 rows per load
+  const int ld_row = wave * 4 + (lane >> 4);
+  const int lc = (lane & 15) ^ pf_swz(ld_row);
   const char* kv_seq = reinterpret_cast<const char*>(p.kv) + (int64_t)b * p.S * p.NKV * 2;
   const char* ke_seq = reinterpret_cast<const char*>(p.ke_plane) + (row0 * p.n_h + h) * (int64_t)(TWO_R * 2);
+  const bool from_ke = KCH > 0 && lc < KCH;
+  const int v_step = (int)p.NKV * 2, k_step = from_ke ? p.n_h * (TWO_R * 2) : v_step;        // bytes per row
+  const int64_t row_first = (int64_t)tile0 * kPfTile + ld_row;
+  const char* k_ptr = (from_ke ? ke_seq + lc * 16 : kv_seq + ((int64_t)h * (kPfDh - TWO_R) + (lc - KCH) * 8) * 2) +
+                      row_first * k_step;
+  const char* v_ptr = kv_seq + (p.NK + (int64_t)h * kPfDh + lc * 8) * 2 + row_first * v_step;
+  // the loads of a tile (e = 2 u: keys, 2 u + 1: values), in this order, tile after tile.  WHOLE: all of its rows are visible
+  auto issue_load = [&](int tile, int e, auto whole) EKV_INLINE {
+    const int u = e >> 1;
+    const uint32_t dst = lds0 + (tile & (kPfRing - 1)) * kPfStage + wave * 1024 + u * 4096 + (e & 1) * kPfPlane;
+    const char*& ptr = e & 1 ? v_ptr : k_ptr;
+    const int step = e & 1 ? v_step : k_step;
+    const char* src = ptr;
+    if constexpr (!decltype(whole)::value)                    // rows past the end repeat the last visible one
+      src += min(kv_hi - 1 - ((tile0 + tile) * kPfTile + u * 16 + ld_row), 0) * step;
+    pf_dma16(src, dst);
+    ptr += 16 * step;
+  };
+  // tile t is requested from the middle of iteration t - 3 to the middle of iteration t - 2, the first ones here
+  constexpr int NU = 2 * QB, NG = 2 * NU, kPerGroup = 8 / NG; // units and groups of MFMAs of a tile, loads per group (below)
+  constexpr int kAhead = kPfRing - QB;                        // tiles requested while the last stages hold the queries
+  auto request = [&](int t) EKV_INLINE {
+    const int n = t == kPfRing - 2 ? 2 * kPerGroup : 8;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (e < n) issue_load(t, e, std::false_type{});
+  };
+#pragma unroll
+  for (int t = 0; t < kAhead; ++t)
+    if (t < ntiles && t < kPfRing - 1) request(t);
+  // the queries have landed (the tiles' loads are behind them)
+  constexpr int kBehind = (kAhead - 1) * 8 + (kAhead == kPfRing - 1 ? 2 * kPerGroup : 8);
+  if (ntiles >= kAhead) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kBehind) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+  // the wave's queries as the B operand: lane = query n32, packed dims 16*ks + 8*g .. of block a, gathered pair by
+  // pair in the packed order; elite pairs (the first R) rotated to the query's position (Section 2.2, eq. 1a);
+  // everything scaled by log2(e)/sqrt(d_h)
+  pf_bf16x8 Qb[QB][KS];
+#pragma unroll
+  for (int a = 0; a < QB; ++a) {
+    const char* raw_row = smem + (kPfRing - 1 - a) * kPfStage + wave * 8192 + n32 * 256;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint32_t w[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int pp = 8 * ks + 4 * g + j;
+        const int ch = order[pp];
+        const uint32_t raw = *reinterpret_cast<const uint32_t*>(raw_row + (((ch >> 2) ^ (n32 & 15)) << 4) + (ch & 3) * 4);
+        float x = bf16_bits_to_f32(raw & 0xffffu), y = bf16_bits_to_f32(raw >> 16);
+        if (8 * ks < R) {                                     // k-steps that can hold elite pairs (compile-time)
+          if (pp < R) {
+            float sn, cs;
+            rope_sincos_poly(q_at[a], p.rope.theta[ch], &sn, &cs);
+            const float x2 = x * cs - y * sn, y2 = x * sn + y * cs;
+            x = x2; y = y2;
+          }
+        }
+        w[j] = pf_pack2(x * p.scale, y * p.scale);
+      }
+      Qb[a][ks] = __builtin_bit_cast(pf_bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
+    }
+  }
 
   // ---- LDS read offsets
   // keys as the A operand of S^T: row kb*32 + n32, logical chunk 2*ks + g
@@ -140,225 +326,259 @@ __global__ __launch_bounds__(256, QB == 1 ? 2 : 1) void prefill_attn_kernel(cons
   const int v_hi_swz = ((i16 >> 2) << 2) | ((g + 2) & 3);
   const int v_byte = (i16 & 1) << 3;
 
-  for (int half = 0; half < 2; ++half) {
-    const int qblk = half == 0 ? p.nqb - 1 - pr : pr;
-    if (half == 1 && (!p.paired || qblk == p.nqb - 1 - pr)) break;   // single blocks; the middle block of an odd count
-    int len[QB];
-    int64_t qrow[QB];
-    bool q_ok[QB];
-    int wmax = 0;
+  pf_f32x16 oacc[QB][DT];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const int tq = qblk * QBLK + (wave * QB + qb) * 32 + n32;   // this lane's query of block qb
-      q_ok[qb] = tq < p.T;
-      qrow[qb] = (int64_t)b * p.T + (q_ok[qb] ? tq : p.T - 1);
-      int64_t len64 = q_ok[qb] ? (int64_t)p.kv_len[qrow[qb]] : 0;
-      len64 = min(len64, p.max_seq_len);
-      len64 = min(len64, p.plane_rows - row0);
-      len64 = min(len64, p.S);
-      len[qb] = (int)max(len64, (int64_t)0);
-      wmax = max(wmax, len[qb]);
-    }
-    // the block's largest visible length bounds the key loop
+  for (int a = 0; a < QB; ++a)
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) wmax = max(wmax, __shfl_xor(wmax, o, kWave));
-    __syncthreads();                                          // the previous block is done with red[] and the tiles
-    if (lane == 0) red[wave] = wmax;
-    __syncthreads();                                          // (also: order[] is complete)
-    const int kv_hi = max(max(red[0], red[1]), max(red[2], red[3]));
-    const int ntiles = (kv_hi + kPfTile - 1) / kPfTile;
+    for (int dt = 0; dt < DT; ++dt) oacc[a][dt] = (pf_f32x16)(0.f);
 
-    // the loads of a tile in four parts (u = 0..3: four rows of K and of V per wave each); a tile index past the
-    // last one stands for the last one (such copies are never read)
-    auto issue_part = [&](int tile, int buf, int u) {
-      const uint32_t kl = __builtin_amdgcn_readfirstlane(lds0 + buf * kPfStage + wave * 4096);
-      tile = min(tile, ntiles - 1);
-      {
-        const int row = wave * 16 + u * 4 + ld_r;
-        const int lc = (lane & 15) ^ pf_swz(row);
-        const int64_t t = min(tile * kPfTile + row, kv_hi - 1);   // rows past the end repeat the last visible one
-        const char* krow = kv_seq + t * p.NKV * 2 + ((int64_t)h * (kPfDh - TWO_R) + (lc - KCH) * 8) * 2;
-        const char* erow = ke_seq + t * (int64_t)p.n_h * (TWO_R * 2) + lc * 16;
-        pf_dma16((KCH > 0 && lc < KCH) ? erow : krow, kl + u * 1024);
-        const char* vrow = kv_seq + t * p.NKV * 2 + (p.NK + (int64_t)h * kPfDh + lc * 8) * 2;
-        pf_dma16(vrow, kl + kPfPlane + u * 1024);
+  // register v of a score block (32 keys from key_blk on) is key key_blk + 8*(v/4) + 4*g + v%4 for this lane's query
+  auto mask = [&](pf_f32x16& s, int a, int key_blk) EKV_INLINE {
+    const int rest = len[a] - key_blk - 4 * g;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = 8 * (v >> 2) + (v & 3) < rest ? s[v] : -INFINITY;
+  };
+  // two probabilities of a block (log2 domain: the packed query carries log2(e)/sqrt(d_h))
+  auto soft2 = [&](const pf_f32x16& s, int i, float m, uint32_t (&w)[8], float& psum) EKV_INLINE {
+    const float p0 = __builtin_amdgcn_exp2f(s[2 * i] - m), p1 = __builtin_amdgcn_exp2f(s[2 * i + 1] - m);
+    psum += p0;
+    psum += p1;
+    w[i] = pf_pack2(p0, p1);
+  };
+  // a block whose probabilities grew too large for the running maximum (the first one always): raised, and formed again
+  auto raise = [&](const pf_f32x16& s, int a, uint32_t (&w)[8], float& psum) EKV_INLINE {
+    float t = s[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) t = fmaxf(t, s[v]);
+    t = fmaxf(t, __shfl_xor(t, 32, kWave));
+    const float other = __shfl_xor(psum, 32, kWave);          // the other sixteen keys of this lane's query
+    const float m_new = psum <= kPfSumLimit && other <= kPfSumLimit ? m_run[a] : fmaxf(m_run[a], t);
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;     // nothing visible yet: every exponential below is 0
+    const float alpha = __builtin_amdgcn_exp2f(m_run[a] - m_use);
+    m_run[a] = m_new;
+    l_run[a] *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      // the accumulators stay in the AGPRs on both sides of the branch (left alone, the compiler moves them to VGPRs around
+      // it in every tile); the wait states are those between an MFMA and a read of its result, and a write and the next MFMA
+      asm volatile("s_nop 15\n\ts_nop 7" : "+a"(oacc[a][dt]));
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        float y, z;
+        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(y) : "a"(oacc[a][dt][j]));
+        y *= alpha;
+        asm volatile("v_accvgpr_write_b32 %0, %1\n\ts_nop 2" : "=a"(z) : "v"(y));
+        oacc[a][dt][j] = z;
       }
+      asm volatile("" : "+a"(oacc[a][dt]));
+    }
+    psum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) soft2(s, i, m_use, w, psum);
+  };
+
+  pf_bf16x8 kf[2][KS], vf[2][8];
+  auto read_k = [&](const char* Kt, int kb, int ks) EKV_INLINE {
+    kf[kb][ks] = *reinterpret_cast<const pf_bf16x8*>(Kt + k_row_off + (((2 * ks + g) ^ k_swz) << 4) + kb * 32 * kPfRow);
+  };
+  // a value fragment of a block: k-slot (g, j) of k-step s2 is key 16*s2 + 8*(j/4) + 4*g + j%4
+  auto read_v = [&](const char* Vt, int kb, int i) EKV_INLINE {
+    const int s2 = i >> 2, ch = 4 * (i & 3) + v_ch;
+    const char* vlo = Vt + (kb * 32 + 16 * s2 + v_r) * kPfRow + v_byte;
+    const pf_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((pf_lds_s16x4_t*)(vlo + ((ch ^ v_lo_swz) << 4)));
+    const pf_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((pf_lds_s16x4_t*)(vlo + 8 * kPfRow + ((ch ^ v_hi_swz) << 4)));
+    vf[kb][i] = __builtin_bit_cast(pf_bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+
+  if (ntiles > 0) {
+    if (ntiles >= kAhead) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kBehind - 8) : "memory");   // tile 0 has landed
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                                          // ... everyone's; and everyone's queries are in registers
+#pragma unroll
+    for (int t = kAhead; t < kPfRing - 1; ++t)
+      if (t < ntiles) request(t);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) read_k(smem, 0, ks);
+  }
+
+  // A tile is 4 QB groups of eight MFMAs: the scores of the units (32 keys, 32 queries) u = kb QB + a, then their values.  The
+  // order is written out (the asm statements and barriers keep it): a wave's vector instructions and LDS reads stand
+  // behind MFMAs of the same wave, which they overlap.
+  constexpr int kPairs = 8 * NU, kSlots = 8 * (QB == 1 ? 2 : 6);   // pairs of probabilities, spread over the groups 1 ..
+  // Tiles count from this work-group's first.  CLEAN: every key is visible to the wave, and tile it + 3 is there and whole
+  auto tile = [&](int it, auto clean) EKV_INLINE {
+    constexpr bool CLEAN = decltype(clean)::value;
+    const char* Kt = smem + (it & (kPfRing - 1)) * kPfStage;
+    const char* Vt = Kt + kPfPlane;
+    const char* Kn = smem + ((it + 1) & (kPfRing - 1)) * kPfStage;
+    const int key0 = (tile0 + it) * kPfTile;
+    pf_f32x16 s[NU];
+    uint32_t w[NU][8];
+    float ps[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) { s[u] = (pf_f32x16)(0.f); ps[u] = 0.f; }
+#pragma unroll
+    for (int a = 0; a < QB; ++a)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(Qb[a][ks]));
+    static_for<NG>([&](auto gic) EKV_INLINE {
+      constexpr int gi = decltype(gic)::value, u = gi % NU, kb = u / QB, a = u % QB;
+      if constexpr (gi == NG - 2) {
+        // tile it + 1 has landed (eight loads of tile it + 2 may be out); everyone is done with tile it - 1
+        if (CLEAN || it + 2 < ntiles) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+      }
+      static_for<8>([&](auto ic) EKV_INLINE {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (gi < NU) {
+          s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][i], Qb[a][i], s[u], 0, 0, 0);
+          asm volatile("" : "+v"(s[u]));
+        } else {
+          constexpr int s2 = i >> 2, dt = i & 3;
+          const pf_bf16x8 P = __builtin_bit_cast(pf_bf16x8, make_uint4(w[u][4 * s2], w[u][4 * s2 + 1], w[u][4 * s2 + 2], w[u][4 * s2 + 3]));
+          // (a group's probabilities may have been formed again just before it: two wait states ahead of the first read)
+          if constexpr (i == 0) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(oacc[a][dt]) : "v"(vf[kb][i]), "v"(P));
+          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(oacc[a][dt]) : "v"(vf[kb][i]), "v"(P));
+        }
+        // the operands of the next group that needs new ones
+        if constexpr (gi == QB - 1) read_k(Kt, 1, i);
+        if constexpr (gi == 2 * QB - 1) read_v(Vt, 0, i);
+        if constexpr (gi == 3 * QB - 1) read_v(Vt, 1, i);
+        if constexpr (gi == 4 * QB - 1) read_k(Kn, 0, i);     // (behind the last tile: whatever lies there, unused)
+        // one load at a time, from the barrier on: the first of tile it + 3 here, the rest of tile it + 2 before it
+        if constexpr (i % (8 / kPerGroup) == 0) {
+          constexpr int e = ((gi + 2) % NG) * kPerGroup + i / (8 / kPerGroup);
+          const int t = it + kPfRing - (gi >= NG - 2 ? 1 : 2);
+          if (CLEAN || t < ntiles) issue_load(t, e, clean);
+        }
+        constexpr int slot = (gi - 1) * 8 + i;
+        if constexpr (slot >= 0 && slot < kSlots) {
+          constexpr int from = slot * kPairs / kSlots, to = (slot + 1) * kPairs / kSlots;
+          static_for<to - from>([&](auto pc) EKV_INLINE {
+            constexpr int pp = from + decltype(pc)::value, u2 = pp / 8, a2 = u2 % QB;
+            soft2(s[u2], pp % 8, m_run[a2], w[u2], ps[u2]);
+            asm volatile("" : "+v"(w[u2][pp % 8]), "+v"(ps[u2]));
+            // units complete: those of the first 32 keys are looked at together, of the others each before its values' turn
+            constexpr bool first = u2 < QB;
+            if constexpr (first ? pp == 8 * QB - 1 : pp % 8 == 7) {
+              constexpr int u0 = first ? 0 : u2, n = first ? QB : 1, a0 = u0 % QB;
+              bool fits = true;
+#pragma unroll
+              for (int x = 0; x < n; ++x) fits &= ps[u0 + x] <= kPfSumLimit;
+              if (__builtin_expect(__any(!fits), 0)) {
+#pragma unroll
+                for (int x = 0; x < n; ++x) raise(s[u0 + x], a0 + x, w[u0 + x], ps[u0 + x]);
+              }
+#pragma unroll
+              for (int x = 0; x < n; ++x) l_run[a0 + x] += ps[u0 + x];
+            }
+          });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if constexpr (gi < NU && !CLEAN) {
+        if (key0 + (gi / QB + 1) * 32 > wmin) mask(s[gi], gi % QB, key0 + gi / QB * 32);
+      }
+    });
+    // The compiler does not know the value products for MFMAs: their last results are complete before it may move them.
+    asm volatile("s_nop 15");
+  };
+  const int n_clean = min(min(wmin / kPfTile, kv_hi / kPfTile - (kPfRing - 1)) - tile0, ntiles - (kPfRing - 1));
+  int it = 0;
+  for (; it < n_clean; ++it) tile(it, std::true_type{});
+  for (; it < ntiles; ++it) tile(it, std::false_type{});
+
+  float l_tot[QB];
+#pragma unroll
+  for (int a = 0; a < QB; ++a) l_tot[a] = l_run[a] + __shfl_xor(l_run[a], 32, kWave);
+
+  // ---- a block of several work-groups: each leaves its state (maximum, sum, accumulators), the last one to arrive adds them
+  // up in the order of the pieces.  Device-scope stores, acknowledged before the count.
+  if (pieces > 1) {
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    constexpr int kDevice = 16;                  // sc1: device scope
+    const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(p.part, 0, (uint32_t)kPfStates, 0x00020000);
+    const uint32_t mine = (uint32_t)(2 * wg + (piece == 0)) * (uint32_t)kPfPartBytes;
+    auto put = [&](int i, float x, float y, float z, float t) EKV_INLINE {
+      const u32x4 v = {__float_as_uint(x), __float_as_uint(y), __float_as_uint(z), __float_as_uint(t)};
+      __builtin_amdgcn_raw_buffer_store_b128(v, part, tid * 16, mine + i * 4096, kDevice);
     };
-    auto issue = [&](int tile, int buf) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) issue_part(tile, buf, u);
+    for (int a = 0; a < QB; ++a) {
+      put(a, l_tot[a] > 0.f ? m_run[a] : -INFINITY, l_tot[a], 0.f, 0.f);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          put(2 + (a * DT + dt) * 4 + j, oacc[a][dt][4 * j], oacc[a][dt][4 * j + 1], oacc[a][dt][4 * j + 2], oacc[a][dt][4 * j + 3]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0)
+      red[0] = __hip_atomic_fetch_add(p.arrived + (wg - piece), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(red[0]) != pieces - 1) continue;
+    float m_all[QB];
+#pragma unroll
+    for (int a = 0; a < QB; ++a) {
+      m_all[a] = -INFINITY;
+      l_tot[a] = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) oacc[a][dt] = (pf_f32x16)(0.f);
+    }
+    auto get = [&](int j, int i) EKV_INLINE {    // of piece j of the block
+      const uint32_t theirs = (uint32_t)(2 * (wg - piece + j) + (j == 0)) * (uint32_t)kPfPartBytes;
+      return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(part, tid * 16, theirs + i * 4096, kDevice));
     };
-    if (ntiles > 0) issue(0, 0);                              // in flight while the queries are prepared
-
-    // the wave's queries as the B operand: lane = query n32, packed dims 16*ks + 8*g .. of block qb,
-    // gathered pair by pair from q in the packed order; elite pairs (the first R) rotated to the
-    // query's position (Section 2.2, eq. 1a); everything scaled by log2(e)/sqrt(d_h)
-    pf_bf16x8 Qb[QB][kPfDh / 16];
+    for (int j = 0; j < pieces; ++j) {
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const bf16_t* qsrc = p.q + (qrow[qb] * p.n_h + h) * kPfDh;
-      const int32_t qp = p.q_pos[qrow[qb]];
-#pragma unroll
-      for (int ks = 0; ks < kPfDh / 16; ++ks) {
-        uint32_t w[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int pp = 8 * ks + 4 * g + j;
-          const int ch = order[pp];
-          const uint32_t raw = *reinterpret_cast<const uint32_t*>(qsrc + 2 * ch);
-          float a = bf16_bits_to_f32(raw & 0xffffu), c = bf16_bits_to_f32(raw >> 16);
-          if (8 * ks < R) {                                   // k-steps that can hold elite pairs (compile-time)
-            if (pp < R) {
-              float sn, cs;
-              rope_sincos_poly(qp, p.rope.theta[ch], &sn, &cs);
-              const float a2 = a * cs - c * sn, c2 = a * sn + c * cs;
-              a = a2; c = c2;
-            }
-          }
-          w[j] = pf_pack2(a * p.scale, c * p.scale);
-        }
-        Qb[qb][ks] = __builtin_bit_cast(pf_bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
-      }
+      for (int a = 0; a < QB; ++a) m_all[a] = fmaxf(m_all[a], get(j, a).x);
     }
-
-    pf_f32x16 oacc[QB][kPfDh / 32];
-    float m_run[QB], l_run[QB];
+    for (int j = 0; j < pieces; ++j) {
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
+      for (int a = 0; a < QB; ++a) {
+        float4 o[DT * 4];                        // all requested before the first is used
+        const float4 ml = get(j, a);
 #pragma unroll
-      for (int dt = 0; dt < kPfDh / 32; ++dt) oacc[qb][dt] = (pf_f32x16)(0.f);
-      m_run[qb] = -INFINITY;
-      l_run[qb] = 0.f;
-    }
-
-    for (int it = 0; it < ntiles; ++it) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's part of tile `it` has landed
-      __syncthreads();                                        // ... everyone's; and tile it-1 has been read by all
-      const char* Kt = smem + (it & 1) * kPfStage;
-      const char* Vt = Kt + kPfPlane;
-      const int key0 = it * kPfTile;
-
-      // ---- scores: two 32-key blocks per query block.  All key fragments of the tile are requested
-      // before the first MFMA (the compiler would otherwise read each one right before its use and
-      // expose the LDS latency sixteen times); sched_barrier keeps the requests where they are.
-      pf_bf16x8 kf[kPfDh / 16][2];
+        for (int i = 0; i < DT * 4; ++i) o[i] = get(j, 2 + a * DT * 4 + i);
+        __builtin_amdgcn_sched_barrier(0);
+        const float w = ml.y > 0.f ? __builtin_amdgcn_exp2f(ml.x - m_all[a]) : ml.y;    // (a sum that is not a number stays one)
+        l_tot[a] += w * ml.y;
 #pragma unroll
-      for (int ks = 0; ks < kPfDh / 16; ++ks) {
-        const int off = k_row_off + (((2 * ks + g) ^ k_swz) << 4);
-        kf[ks][0] = *reinterpret_cast<const pf_bf16x8*>(Kt + off);
-        kf[ks][1] = *reinterpret_cast<const pf_bf16x8*>(Kt + off + 32 * kPfRow);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      pf_f32x16 sacc[QB][2];
+        for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) { sacc[qb][0] = (pf_f32x16)(0.f); sacc[qb][1] = (pf_f32x16)(0.f); }
-      // The next tile's loads are requested BEHIND the first score MFMAs: vector work (here the address
-      // arithmetic) overlaps MFMAs of the same wave that were issued before it, not those of the other wave.
-#pragma unroll
-      for (int ks = 0; ks < kPfDh / 16; ++ks) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          sacc[qb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks][0], Qb[qb][ks], sacc[qb][0], 0, 0, 0);
-          sacc[qb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks][1], Qb[qb][ks], sacc[qb][1], 0, 0, 0);
-        }
-        if (ks < 4) {
-          asm volatile("" : "+v"(sacc[0][1]));                // (keeps the MFMAs above the requests below)
-          issue_part(it + 1, (it + 1) & 1, ks);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      // ---- value fragments of the first 32 keys, requested ahead of the softmax arithmetic.
-      // k-slot (g, j) of k-step (kb, s2) is key kb*32 + 16*s2 + 8*(j/4) + 4*g + j%4
-      pf_bf16x8 vf[2][2][kPfDh / 32];
-      auto read_v = [&](int kb) {
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          const char* vlo = Vt + (kb * 32 + 16 * s2 + v_r) * kPfRow + v_byte;
-#pragma unroll
-          for (int dt = 0; dt < kPfDh / 32; ++dt) {
-            const int ch = 4 * dt + v_ch;
-            const pf_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((pf_lds_s16x4_t*)(vlo + ((ch ^ v_lo_swz) << 4)));
-            const pf_s16x4 hi =
-                __builtin_amdgcn_ds_read_tr16_b64_v4i16((pf_lds_s16x4_t*)(vlo + 8 * kPfRow + ((ch ^ v_hi_swz) << 4)));
-            vf[kb][s2][dt] = __builtin_bit_cast(pf_bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          }
-        }
-      };
-      read_v(0);
-      __builtin_amdgcn_sched_barrier(0);
-      pf_bf16x8 Pb[QB][2][2];
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        // register v of block kb is key key0 + kb*32 + 8*(v/4) + 4*g + v%4 for this lane's query
-        if (__any(key0 + kPfTile > len[qb])) {
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int key = key0 + kb * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-              sacc[qb][kb][v] = key < len[qb] ? sacc[qb][kb][v] : -INFINITY;
-            }
-        }
-        // ---- online softmax (log2 domain: the packed query carries log2(e)/sqrt(d_h))
-        float t0 = fmaxf(sacc[qb][0][0], sacc[qb][1][0]);
-#pragma unroll
-        for (int v = 1; v < 16; ++v) t0 = fmaxf(t0, fmaxf(sacc[qb][0][v], sacc[qb][1][v]));
-        const float tmax = fmaxf(t0, __shfl_xor(t0, 32, kWave));
-        // the reference maximum is raised only when a score exceeds it by more than the slack
-        const float m_new = (tmax > m_run[qb] + kPfSlack || m_run[qb] == -INFINITY) ? tmax : m_run[qb];
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;  // nothing visible yet: every exponential below is 0
-        const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_use);
-        m_run[qb] = m_new;
-        float psum = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const float pv = __builtin_amdgcn_exp2f(sacc[qb][kb][8 * s2 + j] - m_use);
-              psum += pv;
-              Pb[qb][kb][s2][j] = (__bf16)pv;
-            }
-        l_run[qb] = l_run[qb] * alpha + psum;
-        if (__any(alpha != 1.f)) {
-#pragma unroll
-          for (int dt = 0; dt < kPfDh / 32; ++dt) oacc[qb][dt] *= alpha;
-        }
-      }
-      // ---- values: the fragments of the second 32 keys are requested before the first MFMAs
-      read_v(1);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-          for (int dt = 0; dt < kPfDh / 32; ++dt)
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-              oacc[qb][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kb][s2][dt], Pb[qb][kb][s2], oacc[qb][dt], 0, 0, 0);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the spare copy of the last tile has landed before the stages are reused
-
-    // ---- normalise and store: register 4*j + i of tile dt is dim 32*dt + 8*j + 4*g + i of the lane's query
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32, kWave);
-      const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;     // a query that sees nothing gets a zero row
-      if (q_ok[qb]) {
-        bf16_t* orow = p.out + (qrow[qb] * p.n_h + h) * kPfDh + 4 * g;
-#pragma unroll
-        for (int dt = 0; dt < kPfDh / 32; ++dt)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            uint2 pk;
-            pk.x = pf_pack2(oacc[qb][dt][4 * j] * inv, oacc[qb][dt][4 * j + 1] * inv);
-            pk.y = pf_pack2(oacc[qb][dt][4 * j + 2] * inv, oacc[qb][dt][4 * j + 3] * inv);
-            *reinterpret_cast<uint2*>(orow + 32 * dt + 8 * j) = pk;
+          for (int i = 0; i < 4; ++i) {
+            oacc[a][dt][4 * i] = fmaf(w, o[dt * 4 + i].x, oacc[a][dt][4 * i]);
+            oacc[a][dt][4 * i + 1] = fmaf(w, o[dt * 4 + i].y, oacc[a][dt][4 * i + 1]);
+            oacc[a][dt][4 * i + 2] = fmaf(w, o[dt * 4 + i].z, oacc[a][dt][4 * i + 2]);
+            oacc[a][dt][4 * i + 3] = fmaf(w, o[dt * 4 + i].w, oacc[a][dt][4 * i + 3]);
           }
       }
     }
+  }
+
+  // ---- normalise and store, whole rows at a time: register 4*j + i of tile dt is dim 32*dt + 8*j + 4*g + i of the lane's
+  // query.  Through the wave's part of two stages that nobody reads any more (8-byte stores to 32 rows at once took 4 us).
+#pragma unroll
+  for (int a = 0; a < QB; ++a) {
+    char* rows = smem + ((ntiles + 1 + a) & (kPfRing - 1)) * kPfStage + wave * 8192;
+    const float inv = l_tot[a] > 0.f ? 1.f / l_tot[a] : 0.f;  // a query that sees nothing gets a zero row
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        uint2 pk;
+        pk.x = pf_pack2(oacc[a][dt][4 * j] * inv, oacc[a][dt][4 * j + 1] * inv);
+        pk.y = pf_pack2(oacc[a][dt][4 * j + 2] * inv, oacc[a][dt][4 * j + 3] * inv);
+        *reinterpret_cast<uint2*>(rows + n32 * 256 + (((4 * dt + j) ^ (n32 & 15)) << 4) + g * 8) = pk;
+      }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = u * 4 + (lane >> 4), tq = tq0 + a * 32 + i;
+      const uint4 v = *reinterpret_cast<const uint4*>(rows + i * 256 + (((lane & 15) ^ (i & 15)) << 4));
+      if (tq < p.T) *reinterpret_cast<uint4*>(p.out + (((int64_t)b * p.T + tq) * p.n_h + h) * kPfDh + (lane & 15) * 8) = v;
+    }
+  }
   }
 }
 
@@ -400,28 +620,102 @@ AppendArgs prefill_rebuild_args(const elitekv_dims& d, int d_ck, int64_t rows) {
 
 static size_t pf_align(size_t v) { return (v + 255) / 256 * 256; }
 
-// workspace: the rebuilt K/V rows of all sequences
+// workspace: the states of unfinished blocks and the arrival counts (of a fixed size: one sized for some T serves every other),
+// the rebuilt K/V rows of all sequences
 size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len) {
   (void)T;
-  return pf_align((size_t)B * (size_t)max_seq_len * (size_t)rebuild_dims(d).d_c * 2);
+  return kPfStates + kPfCounts + pf_align((size_t)B * (size_t)max_seq_len * (size_t)rebuild_dims(d).d_c * 2);
+}
+
+// Blocks of 128 or 256 queries, and a work-group per block or the tiles of all blocks divided evenly (in stretches of at
+// least eight): whichever takes least by the measured times of a tile and of a block's first and last steps, blocks being
+// handed out to the compute units in falling order.
+static void pf_line(PrefillParams& p, int block) {
+  p.nqb = (p.T + block - 1) / block;
+  const int64_t heads = (int64_t)p.B * p.n_h;
+  int64_t line;
+  for (p.shift = 0;; ++p.shift) {
+    int64_t n = 0;
+    for (int i = 0; i < p.nqb; ++i) n += pf_block_tiles(p.S, p.T, i, block, p.shift);
+    p.head_tiles = (int)n;
+    line = heads * n;
+    if (line < (1LL << 30)) break;
+  }
+  p.groups = (int)std::min<int64_t>(kPfGroups, std::max<int64_t>(heads * p.nqb, line / 8));
+  p.stretch = (int)(line / p.groups);
+  p.longer = (int)(line % p.groups);
+}
+
+// us a launch takes with a work-group per block: the compute units that are free first take the next heads' blocks
+static double pf_time_blocks(const PrefillParams& p, int block, double tile_us, double block_us) {
+  constexpr int kMost = 256;                                 // steps followed; of longer launches the mean will do
+  struct { double until; int64_t units; } busy[kMost + 2] = {{0.0, kPfGroups}};   // ascending
+  int n = 1;
+  const int64_t heads = (int64_t)p.B * p.n_h;
+  double all = 0, last = 0;
+  int64_t steps = 0;
+  for (int i = p.nqb - 1; i >= 0; --i) {
+    const double t = block_us + tile_us * (double)((int64_t)pf_block_tiles(p.S, p.T, i, block, p.shift) << p.shift);
+    all += t * heads;
+    if ((steps += heads / kPfGroups + 2) > kMost) continue;
+    for (int64_t left = heads; left > 0;) {
+      const int64_t k = std::min(left, busy[0].units);
+      const double until = busy[0].until + t;
+      left -= k;
+      if ((busy[0].units -= k) == 0) std::copy(busy + 1, busy + n--, busy);
+      int at = 0;
+      while (at < n && busy[at].until < until) ++at;
+      if (at < n && busy[at].until == until) {
+        busy[at].units += k;
+      } else {
+        std::copy_backward(busy + at, busy + n, busy + n + 1);
+        busy[at] = {until, k};
+        ++n;
+      }
+      last = std::max(last, until);
+    }
+  }
+  return std::max(last, all / kPfGroups);
+}
+
+// Measured (us, 7B 25 % and 13B 25 % shapes, 128 to 2048 queries over up to 8000 rows), blocks of 128 / 256 queries: a tile
+// 1.15 / 1.9 with all compute units at work, a block's first and last steps 9 / 14, a piece of a divided block to be added up
+// 2.5 / 4; the rule's times are within a tenth of the measured ones of most sizes.  The four ways, queries x rows:
+//   128 x 8000, 32 heads: 57 divided, 132 a work-group per block; 86 / 192 with 256-query blocks
+//   2048 x 2048: 93 / 63, 87 / 70;  2 sequences: 151 / 125, 144 / 105
+//   2 x 1021 x 8000, 40 heads: 474 / 492, 407 / 464
+static int pf_plan(PrefillParams& p) {
+  double best = 0;
+  PrefillParams q = p;
+  int width = 0;
+  for (int block = 128; block <= 256; block += 128) {
+    const bool wide = block == 256;
+    const double tile_us = wide ? 1.9 : 1.15, block_us = wide ? 14 : 9, piece_us = wide ? 4 : 2.5;
+    PrefillParams c = p;
+    pf_line(c, block);
+    const double stretch = (double)((int64_t)(c.stretch + 1) << c.shift);
+    const double most = (double)((int64_t)pf_block_tiles(p.S, p.T, c.nqb - 1, block, c.shift) << c.shift);
+    const double divided = 6 + stretch * tile_us + block_us * (1.0 + (double)p.B * p.n_h * c.nqb / c.groups) +
+                           piece_us * std::ceil(most / stretch);
+    const double single = 3 + pf_time_blocks(c, block, tile_us, block_us);
+    if (single <= divided) c.groups = 0;
+    if (width == 0 || std::min(single, divided) < best) {
+      best = std::min(single, divided);
+      q = c;
+      width = block;
+    }
+  }
+  p = q;
+  return width;
 }
 
 template <int TWO_R, int QB>
-static hipError_t launch_pf(PrefillParams& p, int64_t B, int64_t T, hipStream_t stream) {
-  p.nqb = (int)((T + 128 * QB - 1) / (128 * QB));
-  const int64_t pairs = (B * p.n_h + 7) / 8 * 8;             // (sequence, head) pairs, padded to whole rounds of the XCDs
-  // Pairs of blocks give every work-group the same number of key tiles, but a work-group runs its two blocks one
-  // after the other.  When single blocks still make at most one work-group per compute unit (a prompt of up to 1024
-  // tokens of one 32-head sequence), the pairs would leave half of the compute units idle: then every block gets a
-  // work-group of its own, heaviest first (0.085 -> 0.073 ms at 1024 tokens, 7B 25 %).  With more blocks than compute
-  // units the pairs are faster (2048 tokens: 0.138 against 0.153 ms with single blocks, whose heaviest two share a
-  // compute unit and set the launch's length).
-  p.paired = pairs * p.nqb > 256 ? 1 : 0;
-  p.npair = p.paired ? (p.nqb + 1) / 2 : p.nqb;
+static hipError_t launch_pf(const PrefillParams& p, hipStream_t stream) {
   static LdsLimit lim;
   const hipError_t e = raise_lds_limit(lim, reinterpret_cast<const void*>(&prefill_attn_kernel<TWO_R, QB>), kPfLds);
   if (e != hipSuccess) return e;
-  prefill_attn_kernel<TWO_R, QB><<<(unsigned)(pairs * p.npair), 256, kPfLds, stream>>>(p);
+  const int64_t grid = p.groups > 0 ? (p.groups + 7) / 8 * 8 : ((int64_t)p.B * p.n_h + 7) / 8 * 8 * p.nqb;
+  prefill_attn_kernel<TWO_R, QB><<<(unsigned)grid, 256, kPfLds, stream>>>(p);
   return hipGetLastError();
 }
 
@@ -430,13 +724,15 @@ hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipSt
   const int64_t S = a.max_seq_len;
   const elitekv_dims gd = rebuild_dims(d);
   const int64_t NK = (int64_t)d.n_heads * (d.head_dim - 2 * d.r), NKV = gd.d_c;
-  bf16_t* kv = reinterpret_cast<bf16_t*>(a.ws);
+  int* arrived = reinterpret_cast<int*>(a.ws + kPfStates);
+  bf16_t* kv = reinterpret_cast<bf16_t*>(a.ws + kPfStates + kPfCounts);
 
   // K/V of every sequence's first S rows (rows past the end of the planes are left out)
   // Sequences that lie back to back in the planes (stride == max_seq_len) are one GEMM over all their rows;
   // otherwise one launch per sequence.
   const bool packed = a.batch_stride_rows == S && B > 1;
   hipError_t e = hipSuccess;
+  bool any = false;
   for (int64_t b = 0; b < (packed ? 1 : B); ++b) {
     const int64_t row0 = b * a.batch_stride_rows;
     const int64_t want = packed ? B * S : S;
@@ -446,8 +742,10 @@ hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipSt
     g.W_dkv = a.W_uk; g.W_dkv2 = a.W_uv;
     g.x = (const bf16_t*)a.c_plane + row0 * d.d_c;             // (no slots: rows written in place)
     g.c_plane = kv + b * S * NKV; g.plane_rows = want;
+    g.clear = arrived; g.n_clear = kPfGroups;
     e = launch_append_gemm(g, stream);
     if (e != hipSuccess) return e;
+    any = true;
   }
 
   PrefillParams p;
@@ -455,12 +753,14 @@ hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipSt
   p.ke_plane = (const bf16_t*)a.ke_plane; p.kv = kv; p.kv_len = a.seq_len; p.out = (bf16_t*)a.out;
   p.n_h = d.n_heads; p.T = (int)T; p.B = (int)B;
   p.scale = kLog2e / sqrtf((float)d.head_dim);
-  p.S = S; p.NKV = NKV; p.NK = NK;
+  p.S = any ? S : 0;                                         // planes without rows: nothing to see, every block one empty tile
+  p.NKV = NKV; p.NK = NK;
   p.batch_stride_rows = a.batch_stride_rows; p.plane_rows = a.plane_rows; p.max_seq_len = a.max_seq_len;
   p.rope = rope_table(d.rope_base, d.head_dim);
-  // one 32-query block per wave: with two (every LDS fragment feeding two MFMAs, one wave per SIMD) the
-  // compiler does not interleave one block's softmax with the other's MFMAs, and it measured 20 % slower
-  return 2 * d.r == 16 ? launch_pf<16, 1>(p, B, T, stream) : launch_pf<8, 1>(p, B, T, stream);
+  p.part = reinterpret_cast<float*>(a.ws); p.arrived = arrived;
+  const bool wide = pf_plan(p) == 256;
+  if (wide) return 2 * d.r == 16 ? launch_pf<16, 2>(p, stream) : launch_pf<8, 2>(p, stream);
+  return 2 * d.r == 16 ? launch_pf<16, 1>(p, stream) : launch_pf<8, 1>(p, stream);
 }
 
 }  // namespace ekv
