@@ -787,10 +787,10 @@ static int prefill_impl(const elitekv_dims* dims, int32_t d_ck, const void* q, c
   if (!aligned16(q) || !aligned16(W_uk) || !aligned16(W_uv) || !aligned16(ke_plane) || !aligned16(c_plane) ||
       !aligned16(out) || !aligned16(ws))
     return ELITEKV_EALIGN;
-  if (ws_bytes < prefill_flash_workspace(*dims, B, T, max_seq_len)) return ELITEKV_EWORKSPACE;
+  if (ws_bytes < prefill_flash_min_workspace(*dims, B, max_seq_len)) return ELITEKV_EWORKSPACE;
   const DecodeArgs a = decode_args(dims, d_ck, q, q_pos, kv_len, B * T, max_seq_len, batch_stride_rows, W_uk, W_uv,
                                    elite_idx, ke_plane, c_plane, plane_rows, out, ws, 7, (int32_t)T);
-  return launch_prefill_flash(a, B, T, (hipStream_t)hip_stream) == hipSuccess ? ELITEKV_OK : ELITEKV_EHIP;
+  return launch_prefill_flash(a, B, T, ws_bytes, (hipStream_t)hip_stream) == hipSuccess ? ELITEKV_OK : ELITEKV_EHIP;
 }
 
 size_t elitekv_prefill_attn_workspace_bytes(const elitekv_dims* dims, int64_t B, int64_t T, int64_t max_seq_len) {

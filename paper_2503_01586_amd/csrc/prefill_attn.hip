@@ -620,13 +620,6 @@ AppendArgs prefill_rebuild_args(const elitekv_dims& d, int d_ck, int64_t rows) {
 
 static size_t pf_align(size_t v) { return (v + 255) / 256 * 256; }
 
-// workspace: the states of unfinished blocks and the arrival counts (of a fixed size: one sized for some T serves every other),
-// the rebuilt K/V rows of all sequences
-size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len) {
-  (void)T;
-  return kPfStates + kPfCounts + pf_align((size_t)B * (size_t)max_seq_len * (size_t)rebuild_dims(d).d_c * 2);
-}
-
 // Blocks of 128 or 256 queries, and a work-group per block or the tiles of all blocks divided evenly (in stretches of at
 // least eight): whichever takes least by the measured times of a tile and of a block's first and last steps, blocks being
 // handed out to the compute units in falling order.
@@ -684,7 +677,7 @@ static double pf_time_blocks(const PrefillParams& p, int block, double tile_us, 
 //   128 x 8000, 32 heads: 57 divided, 132 a work-group per block; 86 / 192 with 256-query blocks
 //   2048 x 2048: 93 / 63, 87 / 70;  2 sequences: 151 / 125, 144 / 105
 //   2 x 1021 x 8000, 40 heads: 474 / 492, 407 / 464
-static int pf_plan(PrefillParams& p) {
+static int pf_plan(PrefillParams& p, bool room) {
   double best = 0;
   PrefillParams q = p;
   int width = 0;
@@ -698,15 +691,38 @@ static int pf_plan(PrefillParams& p) {
     const double divided = 6 + stretch * tile_us + block_us * (1.0 + (double)p.B * p.n_h * c.nqb / c.groups) +
                            piece_us * std::ceil(most / stretch);
     const double single = 3 + pf_time_blocks(c, block, tile_us, block_us);
-    if (single <= divided) c.groups = 0;
-    if (width == 0 || std::min(single, divided) < best) {
-      best = std::min(single, divided);
+    if (!room || single <= divided) c.groups = 0;
+    const double us = c.groups > 0 ? divided : single;
+    if (width == 0 || us < best) {
+      best = us;
       q = c;
       width = block;
     }
   }
   p = q;
   return width;
+}
+
+// Workspace: the rebuilt K/V rows of all sequences; behind them, where blocks are divided, the states of unfinished ones and
+// the arrival counts.  A call without room for those has no block divided.  The size asks for the room from the first of the
+// steps 64, 76, 90 ... (up to the one that covers max_seq_len) on at which blocks would be divided, so it never falls.
+static size_t pf_rows_bytes(const elitekv_dims& d, int64_t B, int64_t max_seq_len) {
+  return pf_align((size_t)B * (size_t)max_seq_len * (size_t)rebuild_dims(d).d_c * 2);
+}
+size_t prefill_flash_min_workspace(const elitekv_dims& d, int64_t B, int64_t max_seq_len) {
+  return pf_rows_bytes(d, B, max_seq_len);
+}
+size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len) {
+  const size_t rows = pf_rows_bytes(d, B, max_seq_len);
+  PrefillParams p{};
+  p.n_h = d.n_heads; p.B = (int)B; p.T = (int)T;
+  if (B < 1 || B * T > (1LL << 24) || B * d.n_heads > (1 << 20)) return rows;    // (refused by the call)
+  for (double step = 64; step < 1.1892 * (double)max_seq_len; step *= 1.1892) {
+    p.S = (int64_t)step;
+    pf_plan(p, true);
+    if (p.groups > 0) return rows + kPfStates + kPfCounts;
+  }
+  return rows;
 }
 
 template <int TWO_R, int QB>
@@ -719,13 +735,15 @@ static hipError_t launch_pf(const PrefillParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipStream_t stream) {
+hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, size_t ws_bytes, hipStream_t stream) {
   const elitekv_dims& d = a.dims;
   const int64_t S = a.max_seq_len;
   const elitekv_dims gd = rebuild_dims(d);
   const int64_t NK = (int64_t)d.n_heads * (d.head_dim - 2 * d.r), NKV = gd.d_c;
-  int* arrived = reinterpret_cast<int*>(a.ws + kPfStates);
-  bf16_t* kv = reinterpret_cast<bf16_t*>(a.ws + kPfStates + kPfCounts);
+  const size_t rows_bytes = pf_rows_bytes(d, B, S);
+  const bool room = ws_bytes >= rows_bytes + kPfStates + kPfCounts;
+  bf16_t* kv = reinterpret_cast<bf16_t*>(a.ws);
+  int* arrived = room ? reinterpret_cast<int*>(a.ws + rows_bytes + kPfStates) : nullptr;
 
   // K/V of every sequence's first S rows (rows past the end of the planes are left out)
   // Sequences that lie back to back in the planes (stride == max_seq_len) are one GEMM over all their rows;
@@ -742,7 +760,7 @@ hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipSt
     g.W_dkv = a.W_uk; g.W_dkv2 = a.W_uv;
     g.x = (const bf16_t*)a.c_plane + row0 * d.d_c;             // (no slots: rows written in place)
     g.c_plane = kv + b * S * NKV; g.plane_rows = want;
-    g.clear = arrived; g.n_clear = kPfGroups;
+    g.clear = arrived; g.n_clear = room ? kPfGroups : 0;
     e = launch_append_gemm(g, stream);
     if (e != hipSuccess) return e;
     any = true;
@@ -757,8 +775,8 @@ hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, hipSt
   p.NKV = NKV; p.NK = NK;
   p.batch_stride_rows = a.batch_stride_rows; p.plane_rows = a.plane_rows; p.max_seq_len = a.max_seq_len;
   p.rope = rope_table(d.rope_base, d.head_dim);
-  p.part = reinterpret_cast<float*>(a.ws); p.arrived = arrived;
-  const bool wide = pf_plan(p) == 256;
+  p.part = reinterpret_cast<float*>(a.ws + rows_bytes); p.arrived = arrived;
+  const bool wide = pf_plan(p, room) == 256;
   if (wide) return 2 * d.r == 16 ? launch_pf<16, 2>(p, stream) : launch_pf<8, 2>(p, stream);
   return 2 * d.r == 16 ? launch_pf<16, 1>(p, stream) : launch_pf<8, 1>(p, stream);
 }

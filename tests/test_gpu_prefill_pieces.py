@@ -53,3 +53,19 @@ def test_planes_without_rows():
                              plane_rows=0)
     torch.cuda.synchronize()
     assert torch.count_nonzero(out) == 0 and not torch.isnan(out).any()
+
+
+def test_a_workspace_of_the_rebuilt_rows_alone():
+    """No room for the states of divided blocks: a work-group per block, the same result up to the order of the sums."""
+    sh, rows, T, B, stride, rng, idx, qd, q_pos, kv_len, ked, cd, Wukd, Wuvd, dims, o, n_sample, S = _run("pieces_one_block")
+    least = -(-B * S * sh["n_heads"] * (2 * 128 - 2 * sh["r"]) * 2 // 256) * 256
+    assert ekv.elitekv_prefill_attn_workspace_bytes(dims, B, T, S) > least
+    out = torch.full((B, T, sh["n_heads"], 128), float("nan"), dtype=torch.bfloat16, device=DEV)
+    call = lambda n: ekv.elitekv_prefill_attn(dims, qd, i32(q_pos.reshape(-1)), i32(kv_len.reshape(-1)), S, stride, Wukd, Wuvd,
+                                              i32(idx), ked, cd, out, torch.full((n,), 0xFF, dtype=torch.uint8, device=DEV))
+    with pytest.raises(ekv.EliteKVError):
+        call(least - 1)
+    call(least)
+    torch.cuda.synchronize()
+    # both round fp32 sums to bf16: 2^-8 of the value, and the probabilities' bf16 rounding under another maximum
+    assert np.max(np.abs(host64(out) - o)) <= 2 * TOL["bf16"] * np.max(np.abs(o))
