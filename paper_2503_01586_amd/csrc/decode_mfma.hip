@@ -802,7 +802,8 @@ hipError_t launch_decode_mfma(const DecodeArgs& a, const DecodePlan& p, hipStrea
   prm.batch = (int)a.B;
   const bool rows_to_xcds = a.B >= 8 && a.B % 8 == 0 && a.q_per_seq == 1;
   prm.pair_map = p.head_groups == 2 ? (rows_to_xcds ? 3 : 1) : rows_to_xcds ? 2 : 0;
-  if (a.q_per_seq > 1 && (int64_t)p.n_splits * a.B * p.head_groups < (1 << 30)) prm.pair_map = 4;
+  // (two readers gain nothing: 1 x 2 queries of 32768 tokens 74.3 against 78.0 us, 16 x 2 of 4096 at 7B 12.5 % 75.2 / 77.8)
+  if (a.q_per_seq > 1 && a.q_per_seq * p.head_groups > 2 && (int64_t)p.n_splits * a.B * p.head_groups < (1 << 30)) prm.pair_map = 4;
   prm.d_q = p.d_q; prm.d_u = p.d_u; prm.q_per_seq = a.q_per_seq; prm.q_slice = slice_width(d.d_c);
   prm.n_part = p.n_part; prm.fresh = p.fresh;
   // fr_slot is read (through the scalar cache) by every work-group of every launch; outside a fused step it points
