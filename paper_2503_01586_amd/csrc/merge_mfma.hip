@@ -10,9 +10,11 @@
 //      added in a fixed order and normalised into ubar [rows][128] (fp32);
 //   4. o[row, j] += ubar[row, :] W_uv[:, j] on the matrix cores: M = 32 batch rows, one 32-column
 //      tile of the head's d_h outputs per wave, K = the chunk's 128 columns in eight steps; ubar goes
-//      in as bf16 high part + bf16 remainder (two MFMAs per step: 16 mantissa bits), W_uv is read
-//      transposed from LDS (ds_read_b64_tr_b16);
+//      in as bf16 high part + bf16 remainder (two MFMAs per step: 16 mantissa bits), or whole, in three
+//      bf16 pieces (see WHOLE below); W_uv is read transposed from LDS (ds_read_b64_tr_b16);
 //   5. the chunk's partial outputs go to opart; out_reduce adds the chunks in a fixed order.
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -43,7 +45,10 @@ struct MergeMfmaLayout {
   }
 };
 
-// WHOLE: d_u is a multiple of 128 (the bounds of a narrower last chunk cost 0.4 us of a step of 64 rows)
+// WHOLE: d_u is a multiple of 128 and a tile of up to 32 rows has all its merge weights in LDS (the bounds of a narrower last
+// chunk cost 0.4 us of a step of 64 rows).  The other calls multiply the merged latent by W_uv in full fp32, as merge_up_kernel
+// does, to which they would go otherwise: three pieces of eight mantissa bits instead of two (S-LRD 576 + 960, three sequences of
+// 5001 tokens: 39.6 -> 40.0 us a step; sixteen bits are off by a sixteenth where two columns cancel to 2^-13).
 template <int DH, bool WHOLE>
 __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
     const float* __restrict__ part_m, const float* __restrict__ part_l, const bf16_t* __restrict__ part_u,
@@ -226,12 +231,21 @@ __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
       float4 f1 = *reinterpret_cast<const float4*>(up + 4);
       if (n32 >= rows) f0 = f1 = make_float4(0.f, 0.f, 0.f, 0.f);           // rows past the tile
       const float f[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
-      mm_bf16x8 a_hi, a_lo;
+      mm_bf16x8 a_hi, a_lo, a_last;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const __bf16 h = (__bf16)f[i];
-        a_hi[i] = h;
-        a_lo[i] = (__bf16)(f[i] - (float)h);
+        if constexpr (WHOLE) {
+          const __bf16 h = (__bf16)f[i];
+          a_hi[i] = h;
+          a_lo[i] = (__bf16)(f[i] - (float)h);
+        } else {                                             // cut, not rounded: no piece is infinite unless f is
+          const float h = __uint_as_float(__float_as_uint(f[i]) & 0xffff0000u);
+          const float rest = fabsf(f[i]) < INFINITY ? f[i] - h : 0.f;
+          const float l = __uint_as_float(__float_as_uint(rest) & 0xffff0000u);
+          a_hi[i] = (__bf16)h;
+          a_lo[i] = (__bf16)l;
+          a_last[i] = (__bf16)(rest - l);
+        }
       }
       const char* base = wst + tr0 + ks * 16 * WROW;
       const mm_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((mm_lds_s16x4_t*)(base));
@@ -239,6 +253,7 @@ __global__ __launch_bounds__(256) void merge_up_mfma_kernel(
       const mm_bf16x8 b = __builtin_bit_cast(mm_bf16x8, __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, b, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_lo, b, acc, 0, 0, 0);
+      if constexpr (!WHOLE) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_last, b, acc, 0, 0, 0);
     }
     // D[row, j]: this lane holds column j = 32*nt + n32 and rows 8*g4 + 4*hi + {0..3}
     const int j = nt * 32 + n32;
@@ -279,7 +294,7 @@ static hipError_t launch_merge_mfma_dh(const DecodeArgs& a, const DecodePlan& p,
 }
 
 hipError_t launch_merge_mfma(const DecodeArgs& a, const DecodePlan& p, hipStream_t stream) {
-  const bool whole = p.d_u % kMmCols == 0;
+  const bool whole = p.d_u % kMmCols == 0 && std::min<int64_t>(a.B, kMmRows) * p.n_part <= kMmWeightFloats;
   if (a.dims.head_dim == 128)
     return whole ? launch_merge_mfma_dh<128, true>(a, p, stream) : launch_merge_mfma_dh<128, false>(a, p, stream);
   return whole ? launch_merge_mfma_dh<64, true>(a, p, stream) : launch_merge_mfma_dh<64, false>(a, p, stream);

@@ -141,3 +141,41 @@ def test_merge_widths(n_h, d_ck, d_c, B, n_splits):
     ref = (orc.slrd_decode_attn(host64(qd), pos, keh, ch[..., :dk], ch[..., dk:], *rest) if d_ck
            else orc.decode_attn(host64(qd), pos, keh, ch, *rest))
     assert orc.max_abs_rel(host64(out), ref) <= TOL["bf16"]
+
+
+def _equal_weights(n_h, d_ck, d_c, B, columns):
+    """A call whose queries are zero over three splits of 16 rows, a tile each: every row counts the same, so the merged latent of column j
+    is the mean of columns[j]'s three values.  W_uv has ones for these columns and zeros for the others."""
+    r, d_h, S = 4, 128, 48
+    dk, dv = (d_ck, d_c - d_ck) if d_ck else (d_c, d_c)
+    c = torch.zeros(B, S, d_c)
+    W_uv = torch.zeros(dv, n_h, d_h)
+    for j, values in enumerate(columns):
+        c[:, :, d_c - dv + j] = torch.tensor(values).repeat_interleave(16)
+        W_uv[j] = 1
+    z = lambda *size: torch.zeros(*size, dtype=torch.bfloat16, device=DEV)
+    idx = i32(np.tile(np.arange(r), (n_h, 1)))
+    dims = ekv.make_dims(64, n_h, d_h, r, d_c, "bf16", 10000.0)
+    args = (z(B, n_h, d_h), i32([S - 1] * B), i32([S] * B), S, S, z(dk, n_h, d_h - 2 * r), W_uv.bfloat16().to(DEV), idx,
+            z(B * S, n_h, 2 * r), c.bfloat16().reshape(B * S, d_c).to(DEV))
+    return lambda ns: host64(gpu_slrd_decode(dims, d_ck, *args, ns) if d_ck else gpu_decode(dims, *args, ns))
+
+
+# the separated values of an odd width, a single row of a width of neither chunk, a width of whole chunks whose rows have more
+# splits than the LDS holds weights
+FULL_WIDTH = [(32, 320, 640, 2, 3), (40, 448, 896, 33, 3), (32, 320, 640, 1, 3), (32, 0, 256, 9, 1024), (8, 192, 384, 1, 3)]
+
+
+@pytest.mark.parametrize("n_h, d_ck, d_c, B, n_splits", FULL_WIDTH)
+def test_merged_latent_is_multiplied_in_full(n_h, d_ck, d_c, B, n_splits):
+    """Two columns whose merged values cancel but for 2^-13 / 3.  Sixteen bits of them would be wrong by 2^-17 or so, a
+    sixteenth of that; fp32 products and sums by at most 2^-22 (sixteen roundings of 2^-26), the bf16 result by 2^-9 of it."""
+    out = _equal_weights(n_h, d_ck, d_c, B, [(1.0, 2.0 ** -6, 2.0 ** -13), (-1.0, -2.0 ** -6, 0.0)])(n_splits)
+    want = 2.0 ** -13 / 3
+    assert np.max(np.abs(out - want)) <= 2.0 ** -22 + 2.0 ** -9 * want
+
+
+@pytest.mark.parametrize("n_h, d_ck, d_c, B, n_splits", [f for f in FULL_WIDTH if f[1]])
+def test_infinite_values_stay_infinite(n_h, d_ck, d_c, B, n_splits):
+    out = _equal_weights(n_h, d_ck, d_c, B, [(1.0, float("inf"), 2.0)])(n_splits)
+    assert np.all(out == np.inf)
