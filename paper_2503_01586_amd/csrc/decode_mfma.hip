@@ -21,6 +21,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "reader_map.hpp"
 
 namespace ekv {
 
@@ -47,6 +48,7 @@ struct AttnMfmaParams {
   int n_h, d_c, n_splits, chunk, head_groups;
   int batch, pair_map;    // pair_map: 1-D grid, the two head groups of an item share an XCD (2: one head group, every batch row on one XCD)
                           // 4: 1-D grid, the readers of a split (queries x head groups) follow each other on an XCD
+  int reader_run;         // pair_map 4: work-groups that stay together on an XCD (reader_map.hpp)
   int q_per_seq;          // query rows per sequence (several queries share the cache rows of a sequence)
   int d_q, d_u;           // widths of the absorbed query and of the latent accumulators (d_c when joint)
   int q_slice;            // column slice per wave (DC_W), as the query preparation laid qt out
@@ -249,13 +251,14 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     if (b >= p.batch) return;
   } else if (p.pair_map == 4) {
     // Several queries per sequence: the work-groups that read the same rows (a split of one sequence, every query and head
-    // group) follow each other on one XCD, and all but the first of them find the rows in its L2; every other one swaps
-    // neighbouring tiles, so that not all of them ask for the same lines at once.  Spread over the XCDs as they came, each
-    // L2 fetched its own copy: us for an append and its queries, before / without the swap / now: 4 x 5 queries of 4096 tokens
+    // group) follow each other on one XCD in runs, and all but the first of a run find the rows in its L2 (reader_map.hpp);
+    // every other one swaps neighbouring tiles, so that not all of them ask for the same lines at once.  Spread over the XCDs
+    // as they came, each L2 fetched its own copy: us for an append and its queries, before / without the swap / now:
+    // 4 x 5 queries of 4096 tokens
     // 89.9 / 86.7 / 86.0, 8 x 8 of 8192 297 / 295 / 280, 1 x 5 of 4096 56.0 / 53.7 / 53.4; 13B 4 x 5 of 4096 154 / 160 / 151.
-    const int readers = p.q_per_seq * p.head_groups, all = p.n_splits * p.batch * p.head_groups;
-    const int item_wg = (int)(blockIdx.x & 7) * ((all + 7) / 8) + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= (all + 7) / 8 || item_wg >= all) return;
+    const int readers = p.q_per_seq * p.head_groups;
+    const int item_wg = reader_place(blockIdx.x, p.n_splits * p.batch * p.head_groups, p.reader_run);
+    if (item_wg < 0) return;
     const int item = item_wg / readers, reader = item_wg % readers;
     split = item % p.n_splits;
     hg = reader % p.head_groups;
@@ -802,8 +805,12 @@ hipError_t launch_decode_mfma(const DecodeArgs& a, const DecodePlan& p, hipStrea
   prm.batch = (int)a.B;
   const bool rows_to_xcds = a.B >= 8 && a.B % 8 == 0 && a.q_per_seq == 1;
   prm.pair_map = p.head_groups == 2 ? (rows_to_xcds ? 3 : 1) : rows_to_xcds ? 2 : 0;
+  prm.reader_run = 0;
   // (two readers gain nothing: 1 x 2 queries of 32768 tokens 74.3 against 78.0 us, 16 x 2 of 4096 at 7B 12.5 % 75.2 / 77.8)
-  if (a.q_per_seq > 1 && a.q_per_seq * p.head_groups > 2 && (int64_t)p.n_splits * a.B * p.head_groups < (1 << 30)) prm.pair_map = 4;
+  if (a.q_per_seq > 1 && a.q_per_seq * p.head_groups > 2 && (int64_t)p.n_splits * a.B * p.head_groups < (1 << 30)) {
+    prm.pair_map = 4;
+    prm.reader_run = reader_run(a.q_per_seq * p.head_groups, (int)(p.n_splits * a.B * p.head_groups));
+  }
   prm.d_q = p.d_q; prm.d_u = p.d_u; prm.q_per_seq = a.q_per_seq; prm.q_slice = slice_width(d.d_c);
   prm.n_part = p.n_part; prm.fresh = p.fresh;
   // fr_slot is read (through the scalar cache) by every work-group of every launch; outside a fused step it points
