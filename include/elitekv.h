@@ -272,6 +272,15 @@ int elitekv_multiquery_attn(const elitekv_dims* dims, const void* q, const int32
  * Errors as elitekv_decode_attn; EUNSUPPORTED if B * T > 2^24.
  * ------------------------------------------------------------------------------------------- */
 size_t elitekv_prefill_attn_workspace_bytes(const elitekv_dims* dims, int64_t B, int64_t T, int64_t max_seq_len);
+/* Which way elitekv_prefill_attn takes for these sizes and a workspace of ws_bytes.  ABSORBED: the queries go to
+ * elitekv_multiquery_attn; PAIRS: two work-groups per compute unit, 128 queries at a time; 128 / 256: one work-group per
+ * compute unit, blocks of as many queries; DIVIDED: a block's rows divided among work-groups.  For profiles and tests:
+ * results are the same to rounding.  d_ck = 0: joint latent.  Host only.  Negative status on bad dims. */
+enum elitekv_prefill_way {
+  ELITEKV_PREFILL_ABSORBED = 0, ELITEKV_PREFILL_PAIRS = 1, ELITEKV_PREFILL_128 = 2, ELITEKV_PREFILL_256 = 3,
+  ELITEKV_PREFILL_128_DIVIDED = 4, ELITEKV_PREFILL_256_DIVIDED = 5
+};
+int32_t elitekv_prefill_plan(const elitekv_dims* dims, int32_t d_ck, int64_t B, int64_t T, int64_t max_seq_len, size_t ws_bytes);
 int elitekv_prefill_attn(const elitekv_dims* dims, const void* q, const int32_t* q_pos, const int32_t* kv_len,
                          int64_t B, int64_t T, int64_t max_seq_len, int64_t batch_stride_rows, const void* W_uk,
                          const void* W_uv, const int32_t* elite_idx, const void* ke_plane, const void* c_plane,

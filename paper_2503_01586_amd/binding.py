@@ -50,6 +50,7 @@ def _load():
         "elitekv_append": (C.c_int, [DP, P, P, P, I64, P, P, P, P, P, I64, P, SZ, P]),
         "elitekv_append_gemm_tile": (I32, [DP, I32, I64]),
         "elitekv_prefill_gemm_tile": (I32, [DP, I32, I64, I64]),
+        "elitekv_prefill_plan": (I32, [DP, I32, I64, I64, I64, SZ]),
         "elitekv_decode_path": (C.c_int, [DP, I32]),
         "elitekv_decode_auto_splits": (I32, [DP, I64, I64]),
         "elitekv_decode_workspace_bytes": (SZ, [DP, I64, I64, I32]),
@@ -189,6 +190,16 @@ def elitekv_prefill_gemm_tile(dims, T, max_seq_len, d_ck=0) -> int:
     st = _lib.elitekv_prefill_gemm_tile(C.byref(dims), int(d_ck), int(T), int(max_seq_len))
     if st < 0:
         raise EliteKVError(st, "elitekv_prefill_gemm_tile")
+    return st
+
+
+(PREFILL_ABSORBED, PREFILL_PAIRS, PREFILL_128, PREFILL_256, PREFILL_128_DIVIDED, PREFILL_256_DIVIDED) = range(6)
+
+
+def elitekv_prefill_plan(dims, B, T, max_seq_len, ws_bytes, d_ck=0) -> int:
+    st = _lib.elitekv_prefill_plan(C.byref(dims), int(d_ck), int(B), int(T), int(max_seq_len), int(ws_bytes))
+    if st < 0:
+        raise EliteKVError(st, "elitekv_prefill_plan")
     return st
 
 

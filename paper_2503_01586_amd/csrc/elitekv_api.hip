@@ -395,6 +395,15 @@ int32_t elitekv_prefill_gemm_tile(const elitekv_dims* dims, int32_t d_ck, int64_
   return append_gemm_tile(prefill_rebuild_args(*dims, d_ck, max_seq_len));
 }
 
+int32_t elitekv_prefill_plan(const elitekv_dims* dims, int32_t d_ck, int64_t B, int64_t T, int64_t max_seq_len, size_t ws_bytes) {
+  const int st = check_dims(dims);
+  if (st) return st;
+  if (B < 1 || T < 1 || max_seq_len < 0 || d_ck < 0 || d_ck >= dims->d_c) return ELITEKV_EINVAL;
+  if (!prefill_flash_supported(*dims, d_ck, T, max_seq_len)) return ELITEKV_PREFILL_ABSORBED;
+  if (B * T > (1LL << 24) || B * dims->n_heads > (1 << 20)) return ELITEKV_EUNSUPPORTED;
+  return prefill_flash_plan(*dims, B, T, max_seq_len, ws_bytes);
+}
+
 int elitekv_decode_path(const elitekv_dims* dims, int32_t d_ck) {
   DecodePlan p;
   const int st = plan_decode(dims, d_ck, 1, 16, 0, &p);

@@ -191,6 +191,7 @@ bool prefill_flash_supported(const elitekv_dims& d, int d_ck, int64_t T, int64_t
 AppendArgs prefill_rebuild_args(const elitekv_dims& d, int d_ck, int64_t rows);   // the rebuild's GEMM, without its pointers
 size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len);
 size_t prefill_flash_min_workspace(const elitekv_dims& d, int64_t B, int64_t max_seq_len);
+int prefill_flash_plan(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len, size_t ws_bytes);   // an elitekv_prefill_way
 hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, size_t ws_bytes, hipStream_t stream);
 hipError_t launch_mha_decode(const MhaArgs& a, hipStream_t stream);
 size_t search_workspace_bytes(int64_t T, int n_h);

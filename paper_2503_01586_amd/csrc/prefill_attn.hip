@@ -10,7 +10,7 @@
 //
 //   1. the matrix-core GEMM of the cache append (launch_append_gemm) run on the latent rows:
 //                          KV[j, :] = c_j [B^k_J | B^v_J]   (no elite columns, no rotation)
-//   2. prefill_attn_kernel flash attention: S^T = K Q^T, online softmax, O^T += V^T P^T, with the
+//   2. prefill_attn_kernel (here; prefill_pairs.hip has another for blocks of few tiles and launches of many of them) flash attention: S^T = K Q^T, online softmax, O^T += V^T P^T, with the
 //                          query packed on the way in: q^ = [R(pos theta_i) q_i for i in I_h (slot
 //                          order) | q's non-elite dims, ascending], scaled by log2(e)/sqrt(d_h)
 //                          (Section 3.1 score equation)
@@ -38,22 +38,10 @@
 #include <cmath>
 #include <type_traits>
 
-#include "common.hpp"
-#include "launch.hpp"
+#include "prefill_common.hpp"
 
 namespace ekv {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 pf_bf16x8;
-typedef __attribute__((ext_vector_type(16))) float pf_f32x16;
-typedef __attribute__((ext_vector_type(4))) short pf_s16x4;
-typedef __attribute__((ext_vector_type(8))) short pf_s16x8;
-typedef __attribute__((address_space(3))) pf_s16x4 pf_lds_s16x4_t;
-
-constexpr int kPfDh = 128;                       // head dim of the compiled kernel
-constexpr int kPfTile = 64;                      // keys per tile
-constexpr int kPfRow = kPfDh * 2;                // bytes of a staged K or V row
-constexpr int kPfPlane = kPfTile * kPfRow;       // one K (or V) tile: 16 KiB
-constexpr int kPfStage = 2 * kPfPlane;           // K + V
 constexpr int kPfRing = 4;                       // stages
 constexpr int kPfLds = kPfRing * kPfStage + 64 + 256;   // stages + the block's reduction scratch + the head's chunk order
 
@@ -62,56 +50,6 @@ constexpr int kPfLds = kPfRing * kPfStage + 64 + 256;   // stages + the block's 
 constexpr int kPfGroups = 256;
 constexpr size_t kPfPartBytes = (size_t)256 * 16 * (2 + 2 * (kPfDh / 32) * 4);
 constexpr size_t kPfStates = 2 * kPfGroups * kPfPartBytes, kPfCounts = kPfGroups * sizeof(int);
-
-struct PrefillParams {
-  const bf16_t* q;           // [B * T, n_h, d_h]  queries as the caller holds them (un-rotated)
-  const int32_t* q_pos;      // [B * T]
-  const int32_t* elite_idx;  // [n_h, r]
-  const bf16_t* ke_plane;    // [plane_rows, n_h, 2r]
-  const bf16_t* kv;          // [B, S, NKV]  rebuilt [non-elite key dims of every head | values of every head]
-  const int32_t* kv_len;     // [B * T] rows of its sequence each query attends to
-  bf16_t* out;               // [B * T, n_h, d_h]
-  int n_h, T, B;
-  int nqb;                   // query blocks per sequence
-  int groups;                // work-groups among which the tiles are divided; 0: a work-group per block
-  int head_tiles;            // key tiles of a (sequence, head)'s query blocks, as pf_block_tiles counts them
-  int stretch, longer;       // tiles per work-group, and how many (the first ones) have one more
-  int shift;                 // (a line of 2^30 tiles and more is counted in larger units)
-  float* part;               // two states of an unfinished block per work-group
-  int* arrived;              // per work-group: pieces left of the divided block that it has the first one of; cleared by the rebuild
-  float scale;               // log2(e) / sqrt(d_h)
-  int64_t S;                 // rows per sequence in kv
-  int64_t NKV, NK;           // row width of kv; first value column
-  int64_t batch_stride_rows, plane_rows, max_seq_len;
-  RopeTable rope;
-};
-
-// Key tiles of query block i (of `block` queries) of a sequence whose last T of S rows the queries are: what the host, which
-// does not see the lengths, divides among the work-groups
-__host__ __device__ inline int pf_block_tiles(int64_t S, int64_t T, int i, int block, int shift) {
-  int64_t end = (int64_t)(i + 1) * block;
-  if (end > T) end = T;
-  int64_t seen = S - T + end;
-  if (seen < 1) seen = 1;
-  return (int)((seen + kPfTile - 1) / kPfTile >> shift) + (shift > 0);
-}
-
-// staged rows are 16 chunks of 16 bytes; chunk c of row `row` sits at chunk c ^ pf_swz(row): 16 rows read at
-// one logical chunk cover all 64 banks, and the 4 rows x 32 bytes of a transposed read cover 4 different
-// 64-byte windows
-__device__ __forceinline__ int pf_swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-
-__device__ __forceinline__ void pf_dma16(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
-}
-
-__device__ __forceinline__ uint32_t pf_pack2(float lo, float hi) {
-  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-  bf16x2 v;
-  v[0] = (__bf16)lo;
-  v[1] = (__bf16)hi;
-  return __builtin_bit_cast(uint32_t, v);
-}
 
 #define EKV_INLINE __attribute__((always_inline))
 template <int N, int I = 0, typename F>
@@ -621,8 +559,7 @@ AppendArgs prefill_rebuild_args(const elitekv_dims& d, int d_ck, int64_t rows) {
 static size_t pf_align(size_t v) { return (v + 255) / 256 * 256; }
 
 // Blocks of 128 or 256 queries, and a work-group per block or the tiles of all blocks divided evenly (in stretches of at
-// least eight): whichever takes least by the measured times of a tile and of a block's first and last steps, blocks being
-// handed out to the compute units in falling order.
+// least eight).
 static void pf_line(PrefillParams& p, int block) {
   p.nqb = (p.T + block - 1) / block;
   const int64_t heads = (int64_t)p.B * p.n_h;
@@ -671,33 +608,53 @@ static double pf_time_blocks(const PrefillParams& p, int block, double tile_us, 
   return std::max(last, all / kPfGroups);
 }
 
-// Measured (us, 7B 25 % and 13B 25 % shapes, 128 to 2048 queries over up to 8000 rows), blocks of 128 / 256 queries: a tile
-// 1.15 / 1.9 with all compute units at work, a block's first and last steps 9 / 14, a piece of a divided block to be added up
-// 2.5 / 4; the rule's times are within a tenth of the measured ones of most sizes.  The four ways, queries x rows:
+// What a launch takes, us: a tile of a block, a block's first and last steps, a piece of a divided block to be added up
+struct PfCosts { double tile, block, piece; };
+
+static double pf_launch_us(const PrefillParams& c, int block, const PfCosts& k) {
+  if (c.groups == 0) return 3 + pf_time_blocks(c, block, k.tile, k.block);
+  const double stretch = (double)((int64_t)(c.stretch + 1) << c.shift);
+  const double most = (double)((int64_t)pf_block_tiles(c.S, c.T, c.nqb - 1, block, c.shift) << c.shift);
+  return 6 + stretch * k.tile + k.block * (1.0 + (double)c.B * c.n_h * c.nqb / c.groups) + k.piece * std::ceil(most / stretch);
+}
+
+// The way a launch goes: the block's width, and p.groups; 0: the kernel of prefill_pairs.hip.
+// Of this file's kernel, measured alone (us, 7B 25 % and 13B 25 % shapes, 128 to 2048 queries over up to 8000 rows), blocks of
+// 128 / 256 queries: a tile 1.15 / 1.9 with all compute units at work, a block's first and last steps 9 / 14, a piece 2.5 / 4.
+// The four ways, queries x rows:
 //   128 x 8000, 32 heads: 57 divided, 132 a work-group per block; 86 / 192 with 256-query blocks
 //   2048 x 2048: 93 / 63, 87 / 70;  2 sequences: 151 / 125, 144 / 105
 //   2 x 1021 x 8000, 40 heads: 474 / 492, 407 / 464
+// Against the other kernel by what passes one after the other take, where the chip is warm and another tile's products cost
+// power: 0.98 / 1.61 a tile, 13.2 / 25.5 a block, fitted together with that kernel's to their difference (pf_pairs_us).  The
+// choice costs at most 4 % of a pass and rarely more than 1 (862 of them, an append and its queries); this file's kernel
+// alone would cost up to 7 % in batches of short prompts, the other one alone up to 56 % over long contexts:
+//   queries x rows, this kernel / pairs: 64 x 128 44.2 / 41.8, 2048 x 2048 161 / 171, 8 x 512 x 512 332 / 320,
+//   32 x 300 x 600 1403 / 1336, 128 x 8000 294 / 366; 13B 8 x 1024 x 1024 933 / 872, 2 x 1021 x 8000 1055 / 1259
 static int pf_plan(PrefillParams& p, bool room) {
+  constexpr PfCosts kAlone[2] = {{1.15, 9, 2.5}, {1.9, 14, 4}}, kWarm[2] = {{0.98, 13.2, 2.5}, {1.61, 25.5, 4}};
   double best = 0;
   PrefillParams q = p;
   int width = 0;
   for (int block = 128; block <= 256; block += 128) {
-    const bool wide = block == 256;
-    const double tile_us = wide ? 1.9 : 1.15, block_us = wide ? 14 : 9, piece_us = wide ? 4 : 2.5;
+    const PfCosts& k = kAlone[block == 256];
     PrefillParams c = p;
     pf_line(c, block);
-    const double stretch = (double)((int64_t)(c.stretch + 1) << c.shift);
-    const double most = (double)((int64_t)pf_block_tiles(p.S, p.T, c.nqb - 1, block, c.shift) << c.shift);
-    const double divided = 6 + stretch * tile_us + block_us * (1.0 + (double)p.B * p.n_h * c.nqb / c.groups) +
-                           piece_us * std::ceil(most / stretch);
-    const double single = 3 + pf_time_blocks(c, block, tile_us, block_us);
-    if (!room || single <= divided) c.groups = 0;
+    const double divided = pf_launch_us(c, block, k);
+    PrefillParams s = c;
+    s.groups = 0;
+    const double single = pf_launch_us(s, block, k);
+    if (!room || single <= divided) c = s;
     const double us = c.groups > 0 ? divided : single;
     if (width == 0 || us < best) {
       best = us;
       q = c;
       width = block;
     }
+  }
+  if (pf_pairs_us(p) < pf_launch_us(q, width, kWarm[width == 256])) {
+    p.groups = 0;
+    return 0;
   }
   p = q;
   return width;
@@ -743,14 +700,25 @@ hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, size_
   const size_t rows_bytes = pf_rows_bytes(d, B, S);
   const bool room = ws_bytes >= rows_bytes + kPfStates + kPfCounts;
   bf16_t* kv = reinterpret_cast<bf16_t*>(a.ws);
-  int* arrived = room ? reinterpret_cast<int*>(a.ws + rows_bytes + kPfStates) : nullptr;
+
+  PrefillParams p{};
+  p.q = (const bf16_t*)a.q; p.q_pos = a.q_pos; p.elite_idx = a.elite_idx;
+  p.ke_plane = (const bf16_t*)a.ke_plane; p.kv = kv; p.kv_len = a.seq_len; p.out = (bf16_t*)a.out;
+  p.n_h = d.n_heads; p.T = (int)T; p.B = (int)B;
+  p.scale = kLog2e / sqrtf((float)d.head_dim);
+  p.S = a.plane_rows > 0 ? S : 0;                            // planes without rows: nothing to see, every block one empty tile
+  p.NKV = NKV; p.NK = NK;
+  p.batch_stride_rows = a.batch_stride_rows; p.plane_rows = a.plane_rows; p.max_seq_len = a.max_seq_len;
+  p.rope = rope_table(d.rope_base, d.head_dim);
+  const int width = pf_plan(p, room);
+  p.part = reinterpret_cast<float*>(a.ws + rows_bytes);
+  p.arrived = p.groups > 0 ? reinterpret_cast<int*>(a.ws + rows_bytes + kPfStates) : nullptr;
 
   // K/V of every sequence's first S rows (rows past the end of the planes are left out)
   // Sequences that lie back to back in the planes (stride == max_seq_len) are one GEMM over all their rows;
   // otherwise one launch per sequence.
   const bool packed = a.batch_stride_rows == S && B > 1;
   hipError_t e = hipSuccess;
-  bool any = false;
   for (int64_t b = 0; b < (packed ? 1 : B); ++b) {
     const int64_t row0 = b * a.batch_stride_rows;
     const int64_t want = packed ? B * S : S;
@@ -760,25 +728,22 @@ hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, size_
     g.W_dkv = a.W_uk; g.W_dkv2 = a.W_uv;
     g.x = (const bf16_t*)a.c_plane + row0 * d.d_c;             // (no slots: rows written in place)
     g.c_plane = kv + b * S * NKV; g.plane_rows = want;
-    g.clear = arrived; g.n_clear = room ? kPfGroups : 0;
+    g.clear = p.arrived; g.n_clear = p.groups > 0 ? kPfGroups : 0;
     e = launch_append_gemm(g, stream);
     if (e != hipSuccess) return e;
-    any = true;
   }
-
-  PrefillParams p;
-  p.q = (const bf16_t*)a.q; p.q_pos = a.q_pos; p.elite_idx = a.elite_idx;
-  p.ke_plane = (const bf16_t*)a.ke_plane; p.kv = kv; p.kv_len = a.seq_len; p.out = (bf16_t*)a.out;
-  p.n_h = d.n_heads; p.T = (int)T; p.B = (int)B;
-  p.scale = kLog2e / sqrtf((float)d.head_dim);
-  p.S = any ? S : 0;                                         // planes without rows: nothing to see, every block one empty tile
-  p.NKV = NKV; p.NK = NK;
-  p.batch_stride_rows = a.batch_stride_rows; p.plane_rows = a.plane_rows; p.max_seq_len = a.max_seq_len;
-  p.rope = rope_table(d.rope_base, d.head_dim);
-  p.part = reinterpret_cast<float*>(a.ws + rows_bytes); p.arrived = arrived;
-  const bool wide = pf_plan(p, room) == 256;
-  if (wide) return 2 * d.r == 16 ? launch_pf<16, 2>(p, stream) : launch_pf<8, 2>(p, stream);
+  if (width == 0) return launch_prefill_pairs(p, 2 * d.r, stream);
+  if (width == 256) return 2 * d.r == 16 ? launch_pf<16, 2>(p, stream) : launch_pf<8, 2>(p, stream);
   return 2 * d.r == 16 ? launch_pf<16, 1>(p, stream) : launch_pf<8, 1>(p, stream);
+}
+
+int prefill_flash_plan(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len, size_t ws_bytes) {
+  PrefillParams p{};
+  p.n_h = d.n_heads; p.T = (int)T; p.B = (int)B; p.S = max_seq_len;
+  const int width = pf_plan(p, ws_bytes >= pf_rows_bytes(d, B, max_seq_len) + kPfStates + kPfCounts);
+  if (width == 0) return ELITEKV_PREFILL_PAIRS;
+  return width == 256 ? (p.groups > 0 ? ELITEKV_PREFILL_256_DIVIDED : ELITEKV_PREFILL_256)
+                      : (p.groups > 0 ? ELITEKV_PREFILL_128_DIVIDED : ELITEKV_PREFILL_128);
 }
 
 }  // namespace ekv
