@@ -626,13 +626,13 @@ static double pf_launch_us(const PrefillParams& c, int block, const PfCosts& k) 
 //   2048 x 2048: 93 / 63, 87 / 70;  2 sequences: 151 / 125, 144 / 105
 //   2 x 1021 x 8000, 40 heads: 474 / 492, 407 / 464
 // Against the other kernel by what passes one after the other take, where the chip is warm and another tile's products cost
-// power: 0.98 / 1.61 a tile, 13.2 / 25.5 a block, fitted together with that kernel's to their difference (pf_pairs_us).  The
-// choice costs at most 4 % of a pass and rarely more than 1 (862 of them, an append and its queries); this file's kernel
+// power: 0.95 / 1.5 a tile, 13.8 / 25.4 a block, fitted together with that kernel's to their difference (pf_pairs_us).  The
+// choice costs more than 1 % of a pass in 31 of 862 (an append and its queries), at most 5.5; this file's kernel
 // alone would cost up to 7 % in batches of short prompts, the other one alone up to 56 % over long contexts:
 //   queries x rows, this kernel / pairs: 64 x 128 44.2 / 41.8, 2048 x 2048 161 / 171, 8 x 512 x 512 332 / 320,
-//   32 x 300 x 600 1403 / 1336, 128 x 8000 294 / 366; 13B 8 x 1024 x 1024 933 / 872, 2 x 1021 x 8000 1055 / 1259
+//   32 x 300 x 600 1403 / 1336, 128 x 8000 289 / 412; 13B 8 x 1024 x 1024 933 / 872, 2 x 1021 x 8000 1055 / 1259
 static int pf_plan(PrefillParams& p, bool room) {
-  constexpr PfCosts kAlone[2] = {{1.15, 9, 2.5}, {1.9, 14, 4}}, kWarm[2] = {{0.98, 13.2, 2.5}, {1.61, 25.5, 4}};
+  constexpr PfCosts kAlone[2] = {{1.15, 9, 2.5}, {1.9, 14, 4}}, kWarm[2] = {{0.95, 13.8, 2.5}, {1.5, 25.4, 4}};
   double best = 0;
   PrefillParams q = p;
   int width = 0;

@@ -284,17 +284,19 @@ static int64_t pp_blocks(const PrefillParams& p) { return ((int64_t)p.T + 127) /
 static int64_t pp_heads(const PrefillParams& p) { return ((int64_t)p.B * p.n_h + 7) / 8 * 8; }   // whole rounds of the XCDs
 static bool pp_paired(const PrefillParams& p) { return pp_heads(p) * pp_blocks(p) > 256; }
 
-// us a launch takes.  A block: its first and last steps, its tiles, the stores of its rows; alone on a compute unit 9.3 +
-// 1.22 a tile + 3.6 for 128 rows, of two that share one 20 + 1.8 + 0.8.  Pairs are counted as rounds of 512 work-groups, the
-// last one of 256 and fewer at the speed of a work-group that is alone, by a share of 0.78, and as evenly divided work by the
-// rest.  Fitted, with the other kernel's times (pf_plan), to the difference of both in 862 passes (an append and its
-// queries, one after the other; 32 and 40 heads, 1 to 32 sequences, 48 to 2048 queries over up to 8000 rows).
+// us a launch takes.  A block: its first and last steps, its tiles, the stores of its rows; alone on a compute unit 9.2 +
+// 1.28 a tile + 3.8 for 128 rows, of two that share one 20.3 + 1.74 (and 0.003 more per tile of the longest block, as less of
+// the keys and values stays in the L2s) + 0.87.  Pairs are counted as rounds of 512 work-groups, the last one of 256 and fewer
+// at the speed of a work-group that is alone, by a share of 0.82, and as evenly divided work by the rest.  Fitted, with the
+// other kernel's times (pf_plan), to the difference of both in 862 passes (an append and its queries, one after the other; 32
+// and 40 heads, 1 to 32 sequences, 48 to 2048 queries over up to 8000 rows).
 double pf_pairs_us(const PrefillParams& p) {
   const int64_t n = pp_blocks(p), heads = (int64_t)p.B * p.n_h;
   auto tiles = [&](int64_t i) { return (double)pf_block_tiles(p.S, p.T, (int)i, 128, 0); };
   auto rows = [&](int64_t i) { return (double)(std::min<int64_t>(p.T, (i + 1) * 128) - i * 128) / 128; };
-  auto alone = [&](int64_t i) { return 9.3 + 1.22 * tiles(i) + 3.6 * rows(i); };
-  auto shared = [&](int64_t i) { return 20 + 1.8 * tiles(i) + 0.8 * rows(i); };
+  auto alone = [&](int64_t i) { return 9.2 + 1.28 * tiles(i) + 3.8 * rows(i); };
+  const double tile_us = 1.74 + 0.003 * tiles(n - 1);
+  auto shared = [&](int64_t i) { return 20.3 + tile_us * tiles(i) + 0.87 * rows(i); };
   if (!pp_paired(p)) {
     double most = 0;
     for (int64_t i = 0; i < n; ++i) most = std::max(most, alone(i));
@@ -305,7 +307,7 @@ double pf_pairs_us(const PrefillParams& p) {
   for (int64_t i = 0; i < n; ++i) work += shared(i) * heads;
   const double one = alone(n - 1) + (n > 1 ? alone(0) : 0), two = shared(n - 1) + (n > 1 ? shared(0) : 0);
   const double rounds = (double)(groups / 512) * (work / groups) + (rest == 0 ? 0 : rest <= 256 ? one : two);
-  return 3.5 + 0.78 * rounds + 0.22 * std::max(work / 512, one);
+  return 3.5 + 0.82 * rounds + 0.18 * std::max(work / 512, one);
 }
 
 template <int TWO_R>
