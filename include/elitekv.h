@@ -267,8 +267,9 @@ int elitekv_multiquery_attn(const elitekv_dims* dims, const void* q, const int32
  * Rows of a sequence beyond the largest kv_len of its queries are never read by the attention, but
  * the first max_seq_len rows of the latent plane are read by the rebuild.
  * Workspace: the _workspace_bytes function: B * max_seq_len * n_h * (2 d_h - 2 r) * 2 bytes for the rebuilt rows, which a
- * call must have, and 70 MB more from the lengths on at which query blocks are divided among work-groups; a call
- * without these has none divided.
+ * call must have, and from 513 rows on 70 MB more, in which query blocks may be divided among work-groups; a call
+ * without these has none divided (128 queries over 8000 rows then take twice as long).  On this path the size does not depend
+ * on T and does not fall as B or max_seq_len grows; a call of fewer than 48 queries needs what its own sizes say.
  * Errors as elitekv_decode_attn; EUNSUPPORTED if B * T > 2^24.
  * ------------------------------------------------------------------------------------------- */
 size_t elitekv_prefill_attn_workspace_bytes(const elitekv_dims* dims, int64_t B, int64_t T, int64_t max_seq_len);

@@ -769,7 +769,7 @@ int elitekv_multiquery_attn(const elitekv_dims* dims, const void* q, const int32
 
 static size_t prefill_ws_impl(const elitekv_dims* dims, int32_t d_ck, int64_t B, int64_t T, int64_t max_seq_len) {
   if (check_dims(dims) || B < 0 || T < 1 || max_seq_len < 0) return 0;
-  if (prefill_flash_supported(*dims, d_ck, T, max_seq_len)) return prefill_flash_workspace(*dims, B, T, max_seq_len);
+  if (prefill_flash_supported(*dims, d_ck, T, max_seq_len)) return prefill_flash_workspace(*dims, B, max_seq_len);
   return d_ck ? elitekv_slrd_multiquery_workspace_bytes(dims, d_ck, B, T, max_seq_len, 0)
               : elitekv_multiquery_workspace_bytes(dims, B, T, max_seq_len, 0);
 }

@@ -189,7 +189,7 @@ hipError_t launch_decode_mfma(const DecodeArgs& a, const DecodePlan& p, hipStrea
 // matrix-core GEMM), then flash attention; a.B = B * T query rows, a.seq_len = the visible rows of each
 bool prefill_flash_supported(const elitekv_dims& d, int d_ck, int64_t T, int64_t max_seq_len);
 AppendArgs prefill_rebuild_args(const elitekv_dims& d, int d_ck, int64_t rows);   // the rebuild's GEMM, without its pointers
-size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len);
+size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t max_seq_len);
 size_t prefill_flash_min_workspace(const elitekv_dims& d, int64_t B, int64_t max_seq_len);
 int prefill_flash_plan(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len, size_t ws_bytes);   // an elitekv_prefill_way
 hipError_t launch_prefill_flash(const DecodeArgs& a, int64_t B, int64_t T, size_t ws_bytes, hipStream_t stream);

@@ -608,6 +608,9 @@ static double pf_time_blocks(const PrefillParams& p, int block, double tile_us, 
   return std::max(last, all / kPfGroups);
 }
 
+// Rows from which on blocks are divided: a stretch is eight tiles at least, so there must be longer blocks than that.
+constexpr int64_t kPfDividedRows = 8 * kPfTile + 1;
+
 // What a launch takes, us: a tile of a block, a block's first and last steps, a piece of a divided block to be added up
 struct PfCosts { double tile, block, piece; };
 
@@ -644,7 +647,7 @@ static int pf_plan(PrefillParams& p, bool room) {
     PrefillParams s = c;
     s.groups = 0;
     const double single = pf_launch_us(s, block, k);
-    if (!room || single <= divided) c = s;
+    if (!room || p.S < kPfDividedRows || single <= divided) c = s;
     const double us = c.groups > 0 ? divided : single;
     if (width == 0 || us < best) {
       best = us;
@@ -660,26 +663,18 @@ static int pf_plan(PrefillParams& p, bool room) {
   return width;
 }
 
-// Workspace: the rebuilt K/V rows of all sequences; behind them, where blocks are divided, the states of unfinished ones and
-// the arrival counts.  A call without room for those has no block divided.  The size asks for the room from the first of the
-// steps 64, 76, 90 ... (up to the one that covers max_seq_len) on at which blocks would be divided, so it never falls.
+// Workspace: the rebuilt K/V rows of all sequences; behind them, where blocks may be divided, the states of unfinished ones and
+// the arrival counts.  A call without room for those has no block divided.  The size asks for the room from kPfDividedRows on
+// whatever the other sizes are (fewer queries or sequences are divided rather than more), so that it never falls as any of
+// them grows: a workspace for the longest chunk serves every shorter one as well.
 static size_t pf_rows_bytes(const elitekv_dims& d, int64_t B, int64_t max_seq_len) {
   return pf_align((size_t)B * (size_t)max_seq_len * (size_t)rebuild_dims(d).d_c * 2);
 }
 size_t prefill_flash_min_workspace(const elitekv_dims& d, int64_t B, int64_t max_seq_len) {
   return pf_rows_bytes(d, B, max_seq_len);
 }
-size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t T, int64_t max_seq_len) {
-  const size_t rows = pf_rows_bytes(d, B, max_seq_len);
-  PrefillParams p{};
-  p.n_h = d.n_heads; p.B = (int)B; p.T = (int)T;
-  if (B < 1 || B * T > (1LL << 24) || B * d.n_heads > (1 << 20)) return rows;    // (refused by the call)
-  for (double step = 64; step < 1.1892 * (double)max_seq_len; step *= 1.1892) {
-    p.S = (int64_t)step;
-    pf_plan(p, true);
-    if (p.groups > 0) return rows + kPfStates + kPfCounts;
-  }
-  return rows;
+size_t prefill_flash_workspace(const elitekv_dims& d, int64_t B, int64_t max_seq_len) {
+  return pf_rows_bytes(d, B, max_seq_len) + (max_seq_len >= kPfDividedRows ? kPfStates + kPfCounts : 0);
 }
 
 template <int TWO_R, int QB>

@@ -70,3 +70,26 @@ def test_two_wave_work_groups_run_in_pairs():
     """A 128-column latent's work-groups have two waves: a compute unit runs two of them, and 200 rows two splits."""
     assert ekv.elitekv_decode_auto_splits(ekv.make_dims(1024, 32, 128, 4, 128, "bf16"), 200, 500) == 2
     assert ekv.elitekv_decode_auto_splits(ekv.make_dims(1024, 32, 128, 8, 1536, "bf16"), 200, 500) == 1
+
+
+@pytest.mark.parametrize("name", ["7b_25", "13b_25", "7b_12"])
+def test_a_prefill_workspace_serves_every_shorter_chunk(name):
+    """Sized for the longest chunk, or for more sequences, a workspace has room for the divided blocks of the shorter ones too:
+    a call goes the same way in it as in one of its own size."""
+    *shape, dtype, d_ck = FORMS[name]
+    dims = ekv.make_dims(*shape, dtype)
+    size = lambda B, T, S: ekv.elitekv_prefill_attn_workspace_bytes(dims, B, T, S)
+    chunks, rows, batches = (48, 128, 300, 656, 1024, 1808, 2048), (65, 512, 513, 1400, 2048, 8000), (1, 2, 5, 16)
+    for B in batches:
+        for S in rows:
+            for T in chunks:
+                if T > S:
+                    continue
+                held = size(B, T, S)
+                assert held >= size(B, T, S - 1 if S > 66 else S)
+                for b in (b for b in batches if b <= B):
+                    for t in (t for t in chunks if t <= T):
+                        assert held >= size(b, t, S)
+                        for s in (s for s in rows if t <= s <= S):
+                            assert (ekv.elitekv_prefill_plan(dims, b, t, s, held) ==
+                                    ekv.elitekv_prefill_plan(dims, b, t, s, 1 << 40)), (b, t, s, B, T, S)
