@@ -139,7 +139,9 @@ int32_t elitekv_decode_auto_splits(const elitekv_dims* dims, int64_t B, int64_t 
 
 /* Workspace (device bytes) for elitekv_decode_attn.  n_splits == 0 means "auto". 0 on bad dims.
  * For a given B this size, and that of every decode entry point below, never falls as max_seq_len grows: a workspace
- * allocated for the longest bound serves every shorter one. */
+ * allocated for the longest bound serves every shorter one.  Those of the steps and blocks (elitekv_decode_step, _block_step,
+ * _slrd_decode_step, _slrd_block_step) do not fall either as B grows to 64: they serve every smaller batch.  The others may
+ * fall in places as B grows; ask for each. */
 size_t elitekv_decode_workspace_bytes(const elitekv_dims* dims, int64_t B, int64_t max_seq_len,
                                       int32_t n_splits);
 

@@ -212,6 +212,16 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
   return ELITEKV_OK;
 }
 
+// What the size functions of the step and the block answer: room for every smaller number of sequences up to 64 too.  The need
+// falls here and there as sequences are added (fewer splits each, other kernels), and a batch shrinks while it is served.
+template <typename F>
+static size_t most_of_fewer(int64_t B, F&& of) {
+  const size_t own = of(B);
+  size_t most = own;
+  for (int64_t b = 1; own && b < B && b <= 64; ++b) most = std::max(most, of(b));
+  return most;
+}
+
 static int plan_mha(const elitekv_dims* d, int64_t B, int64_t max_seq, int32_t n_splits, int32_t* ns_out,
                     int32_t* chunk_out, size_t* bytes) {
   int st = check_dims(d);
@@ -528,7 +538,7 @@ static int step_impl(const elitekv_dims* dims, int32_t d_ck, const void* x, cons
 
 size_t elitekv_decode_step_workspace_bytes(const elitekv_dims* dims, int64_t B, int64_t max_seq_len,
                                            int32_t n_splits) {
-  return step_ws_bytes(dims, 0, B, max_seq_len, n_splits);
+  return most_of_fewer(B, [&](int64_t b) { return step_ws_bytes(dims, 0, b, max_seq_len, n_splits); });
 }
 
 int elitekv_decode_step(const elitekv_dims* dims, const void* x, const void* q, const int32_t* pos,
@@ -626,10 +636,12 @@ static int block_composed_impl(const elitekv_dims* dims, int32_t d_ck, const voi
 }
 
 size_t elitekv_block_step_workspace_bytes(const elitekv_dims* dims, int64_t B, int64_t max_seq_len, int32_t n_splits) {
-  DecodePlan p;
-  if (plan_decode(dims, 0, B, max_seq_len, n_splits, &p, true, true) == ELITEKV_OK) return p.reserve;
-  BlockLayout L;
-  return block_composed_layout(dims, 0, B, max_seq_len, n_splits, &L, true) ? L.total : 0;
+  return most_of_fewer(B, [&](int64_t b) -> size_t {
+    DecodePlan p;
+    if (plan_decode(dims, 0, b, max_seq_len, n_splits, &p, true, true) == ELITEKV_OK) return p.reserve;
+    BlockLayout L;
+    return block_composed_layout(dims, 0, b, max_seq_len, n_splits, &L, true) ? L.total : 0;
+  });
 }
 
 int elitekv_block_step(const elitekv_dims* dims, const void* x, const int32_t* pos, const int64_t* slot,
@@ -674,9 +686,11 @@ int elitekv_block_step(const elitekv_dims* dims, const void* x, const int32_t* p
 
 size_t elitekv_slrd_block_step_workspace_bytes(const elitekv_dims* dims, int32_t d_ck, int64_t B, int64_t max_seq_len,
                                                int32_t n_splits) {
-  BlockLayout L;
   if (!dims || d_ck <= 0 || d_ck >= dims->d_c) return 0;
-  return block_composed_layout(dims, d_ck, B, max_seq_len, n_splits, &L, true) ? L.total : 0;
+  return most_of_fewer(B, [&](int64_t b) -> size_t {
+    BlockLayout L;
+    return block_composed_layout(dims, d_ck, b, max_seq_len, n_splits, &L, true) ? L.total : 0;
+  });
 }
 
 int elitekv_slrd_block_step(const elitekv_dims* dims, int32_t d_ck, const void* x, const int32_t* pos,
@@ -698,7 +712,7 @@ int elitekv_slrd_block_step(const elitekv_dims* dims, int32_t d_ck, const void* 
 size_t elitekv_slrd_decode_step_workspace_bytes(const elitekv_dims* dims, int32_t d_ck, int64_t B,
                                                 int64_t max_seq_len, int32_t n_splits) {
   if (!dims || d_ck <= 0 || d_ck >= dims->d_c) return 0;
-  return step_ws_bytes(dims, d_ck, B, max_seq_len, n_splits);
+  return most_of_fewer(B, [&](int64_t b) { return step_ws_bytes(dims, d_ck, b, max_seq_len, n_splits); });
 }
 
 int elitekv_slrd_decode_step(const elitekv_dims* dims, int32_t d_ck, const void* x, const void* q,

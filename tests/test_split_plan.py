@@ -93,3 +93,23 @@ def test_a_prefill_workspace_serves_every_shorter_chunk(name):
                         for s in (s for s in rows if t <= s <= S):
                             assert (ekv.elitekv_prefill_plan(dims, b, t, s, held) ==
                                     ekv.elitekv_prefill_plan(dims, b, t, s, 1 << 40)), (b, t, s, B, T, S)
+
+
+@pytest.mark.parametrize("name", list(FORMS))
+@pytest.mark.parametrize("S", [100, 1000, 4096, 32768])
+def test_a_step_workspace_serves_fewer_sequences(name, S):
+    """A batch shrinks while it is served: the step's and the block's workspace never fall as sequences are added."""
+    *shape, dtype, d_ck = FORMS[name]
+    dims = ekv.make_dims(*shape, dtype)
+    sizes = {
+        "step": lambda B: ekv.elitekv_decode_step_workspace_bytes(dims, B, S),
+        "slrd_step": lambda B: ekv.elitekv_slrd_decode_step_workspace_bytes(dims, d_ck, B, S),
+        "block": lambda B: ekv.elitekv_block_step_workspace_bytes(dims, B, S),
+        "slrd_block": lambda B: ekv.elitekv_slrd_block_step_workspace_bytes(dims, d_ck, B, S),
+    }
+    for form, of in sizes.items():
+        before = 0
+        for B in range(1, 65):
+            now = of(B)
+            assert now >= before, (form, B, before, now)
+            before = now
