@@ -96,8 +96,9 @@ static AutoSplits balanced_splits(int64_t groups, int64_t tiles, int64_t slots) 
 // d_ck = 0: joint latent; d_ck > 0: separated latents, a cache row is [c^k (d_ck) | c^v (d_c - d_ck)]
 // want_fresh: plan the fused decode step (the newest token enters as one more split) if the kernels cover it
 // block: plan the whole-block step (EUNSUPPORTED unless the fused step's kernels cover the shape)
-// tight: the tiled fp32 kernels leave the merged latents in the place of every row's first split instead of a piece of
-// their own (the same results; the partials are used up, where otherwise the merge can be repeated)
+// tight: the tiled fp32 kernels leave the merged latents in the place of every row's first split, the matrix-core path the
+// up-projection's partials in the place of the prepared queries, instead of a piece of their own (the same results; what was
+// there is used up, where otherwise a stage can be repeated)
 static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t max_seq, int32_t n_splits,
                        DecodePlan* p, bool want_fresh = false, bool block = false, bool tight = false) {
   int st = check_dims(d);
@@ -159,11 +160,13 @@ static int plan_decode(const elitekv_dims* d, int32_t d_ck, int64_t B, int64_t m
     chunk = (chunk + 31) / 32 * 32;
     p->chunk = (int32_t)chunk;
     p->off_qt = off; off = align_up(off + Bz * (size_t)p->head_groups * 32 * dq * 2, 256);   // head groups padded to 32
-    off = lay_partials(off, ns, most, p->head_groups * 32, du * 2);
     p->merge_batch = merge_mfma_supported(*d, p->d_u, Bq) ? 1 : 0;
     p->up_cw = p->merge_batch ? 128 : merge_up_width(d->n_heads, p->d_u);
-    p->off_opart = off;
-    off = align_up(off + Bz * nh * (size_t)((p->d_u + p->up_cw - 1) / p->up_cw) * d->head_dim * sizeof(float), 256);
+    const size_t opart = align_up(Bz * nh * (size_t)((p->d_u + p->up_cw - 1) / p->up_cw) * d->head_dim * sizeof(float), 256);
+    if (tight) off = std::max(off, opart);
+    off = lay_partials(off, ns, most, p->head_groups * 32, du * 2);
+    p->off_opart = tight ? 0 : off;
+    if (!tight) off += opart;
     p->off_cnt = off;
     off = align_up(off + Bz * nh * sizeof(int32_t), 256);
     if (p->fresh) {
@@ -931,7 +934,9 @@ int elitekv_decode_attn_noalloc(const elitekv_dims* dims, const void* q, const i
   int st = plan_decode(dims, 0, B, max_seq_len, n_splits, &p);
   if (st) return st;
   const size_t room = ELITEKV_NOALLOC_SCRATCH_BYTES;
-  const bool tight = p.tiled && p.total > room;      // the tiled fp32 kernels: no piece for the merged latents then
+  // no piece for the merged latents then (tiled fp32 kernels), or none for the up-projection's partials (matrix-core path; an
+  // automatic count falls instead)
+  const bool tight = p.total > room && (p.tiled || (p.mfma && n_splits > 0));
   if (p.total > room && (tight || n_splits == 0)) {
     // ... and of an automatic split count as much as fits, if the buffer holds the partials of the least one
     auto fits = [&](int32_t n) { return plan_decode(dims, 0, B, max_seq_len, n, &p, false, false, tight) == ELITEKV_OK && p.total <= room; };

@@ -332,6 +332,17 @@ def test_noalloc_entry_point_rejects_oversized_calls_on_the_host():
     assert st == ekv.EINVAL
 
 
+@pytest.mark.parametrize("shape,ns,taken", [((5120, 40, 128, 8, 1920), 134, True), ((5120, 40, 128, 8, 1920), 137, False),
+                                            ((4096, 32, 128, 4, 768), 330, True)])
+def test_noalloc_holds_the_splits_it_always_held(shape, ns, taken):
+    """The scratch check comes first, the pointer check (q is NULL) after it: nothing is launched either way."""
+    import ctypes as C
+    p = 4096   # never dereferenced
+    st = ekv.raw().elitekv_decode_attn_noalloc(C.byref(ekv.make_dims(*shape, "bf16")), None, p, p, 1, 32768, 32768, p, p, p, p, p,
+                                               32768, p, ns, None)
+    assert (st != ekv.ESCRATCH) == taken and st != ekv.OK
+
+
 def test_append_rejects_head_dims_beyond_the_rope_table():
     """head_dim > 256 would index past the 128 chunk frequencies the append kernels are given:
     refused on the host (EUNSUPPORTED, the limit the decode path has), also through the S-LRD append

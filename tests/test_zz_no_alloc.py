@@ -88,3 +88,23 @@ def test_noalloc_rejects_what_does_not_fit():
     p = torch.zeros(16, dtype=torch.uint8, device=DEV).data_ptr()
     st = ekv.raw().elitekv_decode_attn_noalloc(C.byref(dims), p, p, p, B, S, S, p, p, p, p, p, B * S, p, splits, None)
     assert st == ekv.ESCRATCH
+
+
+def test_noalloc_with_as_many_splits_as_the_queries_leave_room_for():
+    """134 splits of one sequence of the 13B shape: the buffer holds everything but the up-projection's partials, which take the
+    place of the prepared queries."""
+    sh = dict(SHAPE, n_heads=40, d_c=1920)
+    dims, S, ns = dims_of(sh), 3000, 134
+    assert ekv.elitekv_decode_workspace_bytes(dims, 1, S, ns) > ekv.NOALLOC_SCRATCH_BYTES
+    g = torch.Generator(device=DEV)
+    g.manual_seed(6)
+    n = lambda *s, std=1.0: (torch.randn(*s, generator=g, device=DEV) * std).bfloat16()
+    q, W_uk, W_uv = n(1, 40, 128), n(1920, 40, 112, std=1920 ** -0.5), n(1920, 40, 128, std=1920 ** -0.5)
+    ke, c = n(S, 40, 16), n(S, 1920)
+    idx = torch.stack([torch.randperm(64, generator=g, device=DEV)[:8] for _ in range(40)]).int()
+    want = gpu_decode(dims, q, i32([S - 1]), i32([S]), S, S, W_uk, W_uv, idx, ke, c, n_splits=ns)
+    for _ in range(2):
+        out = torch.full_like(q, float("nan"))
+        ekv.elitekv_decode_attn_noalloc(dims, q, i32([S - 1]), i32([S]), S, S, W_uk, W_uv, idx, ke, c, out, n_splits=ns)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
