@@ -75,7 +75,7 @@ int elitekv_param_count(const elitekv_dims* dims, int64_t* n_params);
  * every entry must lie in [0, d_h/2) and be distinct within its head.  EINDEX otherwise. */
 int elitekv_validate_elite_idx(const elitekv_dims* dims, const int32_t* idx_host);
 
-/* Workspace (device bytes) elitekv_append needs for T tokens.  0 on bad dims. */
+/* Workspace (device bytes) for elitekv_append of up to T tokens: it never falls as T grows.  0 on bad dims. */
 size_t elitekv_append_workspace_bytes(const elitekv_dims* dims, int64_t T);
 
 /*
@@ -94,7 +94,8 @@ size_t elitekv_append_workspace_bytes(const elitekv_dims* dims, int64_t T);
  *   elite_idx  [n_h, r] int32               DEVICE copy of I_h (validate on the host beforehand)
  *   ke_plane   [plane_rows, n_h, 2r]        written, dims->dtype (may be NULL when r == 0)
  *   c_plane    [plane_rows, d_c]            written, dims->dtype
- *   ws         workspace of at least elitekv_append_workspace_bytes(dims, T) (may be NULL if 0)
+ *   ws         workspace of at least elitekv_append_workspace_bytes(dims, T) (may be NULL if 0; more than 64 tokens use
+ *              none themselves)
  *   hip_stream a hipStream_t (NULL = the default stream)
  *
  * T == 0 is a successful no-op.  Errors: EINVAL, ENULL, EALIGN (pointers must be 16-byte aligned),
@@ -303,7 +304,7 @@ int elitekv_prefill_attn(const elitekv_dims* dims, const void* q, const int32_t*
 /* Section 3.2, storage cost with S-LRD: 2 r n_h d + d_ck (d + d_h n_h - 2 r n_h) + d_cv (d + d_h n_h). */
 int elitekv_slrd_param_count(const elitekv_dims* dims, int32_t d_ck, int64_t* n_params);
 
-/* Workspace bytes elitekv_slrd_append needs for T tokens (host only; may be 0). */
+/* Workspace bytes for elitekv_slrd_append of up to T tokens (host only; may be 0). */
 size_t elitekv_slrd_append_workspace_bytes(const elitekv_dims* dims, int32_t d_ck, int64_t T);
 
 /*

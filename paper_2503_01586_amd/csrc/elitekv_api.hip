@@ -309,11 +309,13 @@ static size_t append_ws_bytes(const elitekv_dims* dims, int32_t d_ck, int64_t T)
   return 0;
 }
 
-// what the size functions answer: room for every smaller number of tokens too (one token takes the weight-streaming
-// kernel, whose contraction splits may be more than twice those of the matrix-core kernel)
+// what the size functions answer: room for every smaller number of tokens too (more than 64 need none themselves, but the last
+// chunk of a prompt may be short; one token takes the weight-streaming kernel, whose contraction splits may be more than twice
+// those of the matrix-core kernel)
 static size_t append_ws_reserve(const elitekv_dims* dims, int32_t d_ck, int64_t T) {
-  const size_t own = append_ws_bytes(dims, d_ck, T);
-  return own ? std::max(own, append_ws_bytes(dims, d_ck, 1)) : 0;
+  size_t most = 0;
+  for (int64_t t = 1; t <= std::min<int64_t>(T, 64); ++t) most = std::max(most, append_ws_bytes(dims, d_ck, t));
+  return most;
 }
 
 // argument checks of an append; ws_needed = 0 skips the workspace check

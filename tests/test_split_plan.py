@@ -113,3 +113,13 @@ def test_a_step_workspace_serves_fewer_sequences(name, S):
             now = of(B)
             assert now >= before, (form, B, before, now)
             before = now
+
+
+@pytest.mark.parametrize("name", list(FORMS))
+def test_an_append_workspace_serves_fewer_tokens(name):
+    """The last chunk of a prompt is short: what was allocated for whole ones is enough for it."""
+    *shape, dtype, d_ck = FORMS[name]
+    dims = ekv.make_dims(*shape, dtype)
+    for of in (lambda T: ekv.elitekv_append_workspace_bytes(dims, T), lambda T: ekv.elitekv_slrd_append_workspace_bytes(dims, d_ck, T)):
+        sizes = [of(T) for T in list(range(0, 70)) + [128, 300, 2048, 100000]]
+        assert sizes == sorted(sizes)
