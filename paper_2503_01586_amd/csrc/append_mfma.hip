@@ -303,7 +303,6 @@ __global__ __launch_bounds__(256) void append_gemm_kernel(
 //   tokens   [BN t][32 k]:  blocks of 16 rows x 64 bytes, pieces XOR-swizzled by row.
 // Needs d_model % 32 == 0 (whole stages); other shapes take append_gemm_kernel.
 // ---------------------------------------------------------------------------------------------
-constexpr int kGdStage = 32;                    // contraction rows per stage
 
 __device__ __forceinline__ int gd_swz8(int row) { return ((row & 3) << 1) | ((row >> 2) & 1); }
 // token blocks (16 rows x 64 bytes): a 16-byte read of 16 lanes = 16 rows at one logical piece; the four
@@ -865,7 +864,10 @@ hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream) {
     if (d.d_model % kGdStage || a.d2 % kGdStage || a.x_off2 % 8 || a.x_ld % 8 || (a.d2 > 0 && split % kGmCols))
       return hipErrorInvalidValue;
   }
-  switch (append_gemm_tile(a)) {
+  const int tile = append_gemm_tile(a);
+  if (a.n_clear > 0 && (tile == ELITEKV_TILE_STAGED_64_128 || tile == ELITEKV_TILE_STAGED_256_128))
+    return hipErrorInvalidValue;                               // these do not clear
+  switch (tile) {
     case ELITEKV_TILE_256_256_WIDE: return launch_gemm_wide(a, stream);
     case ELITEKV_TILE_256_256: return launch_gemm_dma<4, 4, 2, 4>(a, stream);
     case ELITEKV_TILE_128_128: return launch_gemm_dma<1, 6, 4, 2, 2, 2>(a, stream);

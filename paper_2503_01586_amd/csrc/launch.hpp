@@ -151,6 +151,7 @@ size_t append_skinny_workspace(const elitekv_dims& d, int64_t T);
 hipError_t launch_append_skinny(const AppendArgs& a, hipStream_t stream);
 bool append_gemm_supported(const elitekv_dims& d, int64_t T, int d_ck);
 hipError_t launch_append_gemm(const AppendArgs& a, hipStream_t stream);
+constexpr int kGdStage = 32;                    // contraction rows per stage of the direct-load GEMM kernels
 int append_gemm_tile(const AppendArgs& a);      // the elitekv_gemm_tile that launch_append_gemm takes
 bool append_tiled_supported(const elitekv_dims& d, int64_t T, int d_ck);
 hipError_t launch_append_tiled(const AppendArgs& a, hipStream_t stream);

@@ -538,11 +538,11 @@ bool prefill_flash_supported(const elitekv_dims& d, int d_ck, int64_t T, int64_t
   if (d.dtype != ELITEKV_BF16 || d.head_dim != kPfDh) return false;
   // separated latents: keys are rebuilt from the first d_ck columns of a latent row and values from the rest,
   // each slice in whole contraction stages, and no 128-column block of the rebuilt row lies across the two
-  if (d_ck < 0 || d_ck >= d.d_c || d_ck % 32) return false;
+  if (d_ck < 0 || d_ck >= d.d_c || d_ck % kGdStage) return false;
   if (d_ck > 0 && (d.n_heads * (d.head_dim - 2 * d.r)) % 128) return false;
   if (T < kPfMinQueries) return false;
   if (2 * d.r != 8 && 2 * d.r != 16) return false;
-  if (d.d_c % 32 || T < 1 || max_seq_len <= 64 || max_seq_len > (1 << 30)) return false;
+  if (d.d_c % kGdStage || T < 1 || max_seq_len <= 64 || max_seq_len > (1 << 30)) return false;
   const elitekv_dims g = rebuild_dims(d);
   return append_gemm_supported(g, max_seq_len, d.n_heads * (d.head_dim - 2 * d.r));
 }

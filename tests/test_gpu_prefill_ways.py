@@ -146,3 +146,15 @@ def test_what_was_measured_as_the_faster_way(dims5, B, T, S, way):
     """Short prompts and batches of them: two work-groups to a compute unit; long ones: one."""
     dims = ekv.make_dims(*dims5, "bf16")
     assert ekv.elitekv_prefill_plan(dims, B, T, S, 1 << 40) == way
+
+
+@pytest.mark.parametrize("d_c, d_ck", [(64, 0), (96, 32), (160, 0), (160, 96), (256, 224), (320, 160), (1536, 0), (1536, 576)])
+@pytest.mark.parametrize("n_h, r", [(8, 8), (16, 4), (40, 8)])
+def test_the_rebuild_clears_the_arrival_counts(n_h, r, d_c, d_ck):
+    """Divided blocks count arrivals in memory that the rebuild's GEMM clears; its staged tiles do not."""
+    dims = ekv.make_dims(64, n_h, 128, r, d_c, "bf16")
+    for S in (513, 1500, 8000):
+        for T in (64, 500):
+            if ekv.elitekv_prefill_plan(dims, 1, T, S, 1 << 40, d_ck) != ekv.PREFILL_ABSORBED:
+                assert ekv.elitekv_prefill_gemm_tile(dims, T, S, d_ck) not in (ekv.TILE_NONE, ekv.TILE_STAGED_64_128,
+                                                                              ekv.TILE_STAGED_256_128)
