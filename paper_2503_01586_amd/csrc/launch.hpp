@@ -58,7 +58,7 @@ struct DecodePlan {
   size_t off_cnt;       // MFMA path: arrival counters of the merge kernels' chunk groups   int32 [B, n_h]
   // fused decode step (fresh != 0): the cache row of the newest token of every sequence is finished (summed,
   // rotated, stored) inside the attention kernel, by the work-group whose tiles include its position,
-  // from the append's contraction-split sums.  1: one sequence, and up to seven whose hidden width is no multiple of
+  // from the append's contraction-split sums.  1: one sequence, and up to eight whose hidden width is no multiple of
   // eight (weight-streaming front launch), 2: kMatrixRows to 64 sequences (matrix-core front launch)
   int32_t fresh;
   int32_t n_part;       // partials per batch row (= n_splits)

@@ -23,7 +23,7 @@ BLOCK_CASES = {
     "bf16_13b_two_sequences": (shape(5120, 40, 128, 8, 1920, "bf16"), [70, 9]),
     "bf16_7b_12pct_one_sequence": (shape(4096, 32, 128, 4, 768, "bf16"), [55]),
     "bf16_small_hidden_head_dim_64": (shape(768, 16, 64, 8, 512, "bf16"), [40, 3]),
-    # eight sequences and more: the composed form (projections around the decode step's kernels)
+    # more sequences in the composed form (two and up: projections around the decode step's kernels)
     "bf16_7b_eight_sequences": (shape(4096, 32, 128, 8, 1536, "bf16"), [9, 40, 3, 77, 120, 16, 15, 64]),
     "bf16_13b_sixteen_sequences": (shape(5120, 40, 128, 8, 1920, "bf16"), [10 + 5 * i for i in range(16)]),
     "bf16_7b_12pct_forty_sequences": (shape(4096, 32, 128, 4, 768, "bf16"), [3 + (7 * i) % 90 for i in range(40)]),
@@ -100,7 +100,7 @@ def test_block_step_equals_projections_around_the_decode_step():
 def test_block_step_argument_errors():
     big = ekv.make_dims(4096, 32, 128, 8, 1536, "bf16")
     assert ekv.elitekv_block_step_workspace_bytes(big, 1, 4096) > ekv.elitekv_decode_step_workspace_bytes(big, 1, 4096)
-    assert ekv.elitekv_block_step_workspace_bytes(big, 8, 4096) > 0            # eight sequences: the composed form
+    assert ekv.elitekv_block_step_workspace_bytes(big, 8, 4096) > 0            # the composed form
     assert ekv.elitekv_block_step_workspace_bytes(big, 65, 4096) == 0          # more than 64 sequences: not covered
     tiny = ekv.make_dims(128, 4, 32, 2, 64, "fp32")
     assert ekv.elitekv_block_step_workspace_bytes(tiny, 1, 128) == 0           # fp32: not covered

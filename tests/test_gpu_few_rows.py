@@ -75,11 +75,11 @@ def test_separated_decode(dims6, n_splits):
     assert torch.count_nonzero(out[1]) == 0
 
 
-@pytest.mark.parametrize("B", [1, 3, 7])
-def test_hidden_width_outside_the_matrix_core_front(B):
-    sh = shape(1004, 32, 128, 8, 512, "bf16")              # rows of x are not 16-byte aligned
+@pytest.mark.parametrize("B, n_h", [(1, 32), (3, 32), (7, 32), (8, 32), (8, 40)])     # eight: every sequence on one XCD
+def test_hidden_width_outside_the_matrix_core_front(B, n_h):
+    sh = shape(1004, n_h, 128, 8, 512, "bf16")             # rows of x are not 16-byte aligned
     seqs = [5 + 13 * i for i in range(B)]
-    stride, n_h, d_h = max(seqs) + 1, 32, 128
+    stride, d_h = max(seqs) + 1, 128
     rng, idx, W_ke, W_dkv, W_uk, W_uv, x, q = _draw(sh, B, B, 80 + B)
     dims = dims_of(sh)
     ke64, c64 = synth.draw_cache_planes(rng, B * stride, n_h, 8, 512)

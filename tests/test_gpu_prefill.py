@@ -25,7 +25,7 @@ CASES = {
     "7b_full_prefill": (shape(64, 32, 128, 8, 1536, "bf16"), [200], 200, "causal", 10),
     "7b_12pct_chunk_over_context": (shape(64, 32, 128, 4, 768, "bf16"), [130, 257], 70, "causal", 6),
     "13b_full_prefill": (shape(64, 40, 128, 8, 1920, "bf16"), [97], 97, "causal", 6),
-    # more work-groups than compute units, three sequences, five query blocks (an unpaired middle one)
+    # more work-groups than compute units, three sequences, five query blocks
     "many_work_groups": (shape(64, 32, 128, 8, 256, "bf16"), [700, 650, 720], 640, "causal", 5),
     # the sequences lie back to back in the planes (stride == max_seq_len): one rebuild launch for all of them
     "back_to_back": (shape(64, 8, 128, 8, 256, "bf16"), [300, 130, 257], 130, "causal", 8),
