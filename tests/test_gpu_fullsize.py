@@ -206,7 +206,7 @@ def test_slrd_prefill_append_with_wide_tiles():
                                     ("7b_25_b1_s32768", 4500)])
 def test_full_size_prefill_attention(name, T):
     """elitekv_prefill_attn in the configuration bench.py times (one sequence, the T-token prompt attends
-    causally to its own T cache rows; 4500 tokens: two work-groups per compute unit, a ragged last block):
+    causally to its own T cache rows; 4500 tokens: several query blocks per compute unit, a ragged last one):
     the planes come from the library's append of seeded hidden states; sampled (query, head) outputs are
     computed one by one by the float64 oracle from exactly the planes the GPU reads."""
     cfg = synth.CONFIGS[name]
