@@ -48,7 +48,7 @@ struct AttnMfmaParams {
   int n_h, d_c, n_splits, chunk, head_groups;
   int batch, pair_map;    // pair_map: 1-D grid, the two head groups of an item share an XCD (2: one head group, every batch row on one XCD)
                           // 4: 1-D grid, the readers of a split (queries x head groups) follow each other on an XCD
-  int reader_run;         // pair_map 4: work-groups that stay together on an XCD (reader_map.hpp)
+  int reader_run, reader_turns;   // pair_map 4: work-groups that stay together on an XCD, and how often they are dealt out (reader_map.hpp)
   int q_per_seq;          // query rows per sequence (several queries share the cache rows of a sequence)
   int d_q, d_u;           // widths of the absorbed query and of the latent accumulators (d_c when joint)
   int q_slice;            // column slice per wave (DC_W), as the query preparation laid qt out
@@ -200,7 +200,9 @@ __device__ __forceinline__ void store_new_token_row(const AttnMfmaParams& p, int
 // compiled for two work-groups per compute unit, i.e. at most 256 registers per lane: kGroupsPerCu.)
 // SMODE: which loads of cache rows are marked non-temporal (see dma16): 1 = all (nobody else reads the rows),
 // 2 = those of the odd steps only (head-group pairs: at odd steps a work-group is the second and last reader of its tile;
-// several queries: the readers pass a row on half of the time).
+// several queries: the readers pass a row on half of the time), 3 = as 2.  It also says which map of work-groups the code holds
+// (1: none or one head group's, 2: head-group pairs', 3: several queries'): all of them in one kernel cost a step of 16
+// sequences of 8192 tokens at 13B 199.4 us instead of 198.2, one of 32768 tokens at 7B 48.8 instead of 48.55.
 template <int NW, int DC_W, int TWO_R, bool SEP, int SMODE>
 __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsPerCu)) void attn_mfma_kernel(const AttnMfmaParams p) {
   using L = AttnMfmaLayout<NW, DC_W, TWO_R>;
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
   const bool do_v = !SEP || cw >= nwk;                   // this wave's slice is accumulated as values
   const int vwave = SEP ? cw - nwk : cw;                 // position of the slice among the value slices
   int split = blockIdx.x, hg = blockIdx.y, b = blockIdx.z, odd = 0;   // odd: reads every two neighbouring tiles the other way round
-  if (p.pair_map == 2) {
+  if (SMODE == 1 && p.pair_map == 2) {
     // One head group, a multiple of eight batch rows: all splits of batch row b run on XCD b % 8 (work-groups go to
     // the XCDs round-robin by linear index), so an XCD's L2 fetches the absorbed queries of its own rows only
     // instead of every row's (at 64 rows that is 3 MB per XCD, which the streamed cache rows keep evicting:
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     b = (slot / p.n_splits) * 8 + xcd;
     split = slot % p.n_splits;
     if (b >= p.batch) return;
-  } else if (p.pair_map == 4) {
+  } else if (SMODE == 3) {
     // Several queries per sequence: the work-groups that read the same rows (a split of one sequence, every query and head
     // group) follow each other on one XCD in runs, and all but the first of a run find the rows in its L2 (reader_map.hpp);
     // every other one swaps neighbouring tiles, so that not all of them ask for the same lines at once.  Spread over the XCDs
@@ -257,14 +259,14 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     // 4 x 5 queries of 4096 tokens
     // 89.9 / 86.7 / 86.0, 8 x 8 of 8192 297 / 295 / 280, 1 x 5 of 4096 56.0 / 53.7 / 53.4; 13B 4 x 5 of 4096 154 / 160 / 151.
     const int readers = p.q_per_seq * p.head_groups;
-    const int item_wg = reader_place(blockIdx.x, p.n_splits * p.batch * p.head_groups, p.reader_run);
+    const int item_wg = reader_place(blockIdx.x, p.n_splits * p.batch * p.head_groups, p.reader_run, p.reader_turns);
     if (item_wg < 0) return;
     const int item = item_wg / readers, reader = item_wg % readers;
     split = item % p.n_splits;
     hg = reader % p.head_groups;
     b = item / p.n_splits * p.q_per_seq + reader / p.head_groups;
     odd = reader & 1;
-  } else if (p.pair_map) {
+  } else if (SMODE == 2) {
     // Two head groups read the same latent rows.  Work-groups go to the eight XCDs round-robin by
     // linear index, so indices i and i + 8 land on the same XCD back to back: they are given the
     // two head groups of one (split, batch row) item, and the second reader of a row finds it in
@@ -716,8 +718,9 @@ template <int NW, int DC_W, int TWO_R, bool SEP>
 static hipError_t launch_attn(const AttnMfmaParams& prm, int64_t B, hipStream_t stream) {
   if constexpr (AttnMfmaLayout<NW, DC_W, TWO_R>::kFits) {
     // head-group pairs and several queries share their rows through the L2; every other launch reads a row once
-    return (prm.pair_map & 5) ? launch_attn_as<NW, DC_W, TWO_R, SEP, 2>(prm, B, stream)
-                        : launch_attn_as<NW, DC_W, TWO_R, SEP, 1>(prm, B, stream);
+    return prm.pair_map == 4 ? launch_attn_as<NW, DC_W, TWO_R, SEP, 3>(prm, B, stream)
+         : (prm.pair_map & 1) ? launch_attn_as<NW, DC_W, TWO_R, SEP, 2>(prm, B, stream)
+                              : launch_attn_as<NW, DC_W, TWO_R, SEP, 1>(prm, B, stream);
   } else {
     return hipErrorInvalidValue;                            // decode_mfma_supported() keeps such shapes away
   }
@@ -805,11 +808,13 @@ hipError_t launch_decode_mfma(const DecodeArgs& a, const DecodePlan& p, hipStrea
   prm.batch = (int)a.B;
   const bool rows_to_xcds = a.B >= 8 && a.B % 8 == 0 && a.q_per_seq == 1;
   prm.pair_map = p.head_groups == 2 ? (rows_to_xcds ? 3 : 1) : rows_to_xcds ? 2 : 0;
-  prm.reader_run = 0;
+  prm.reader_run = prm.reader_turns = 0;
   // (two readers gain nothing: 1 x 2 queries of 32768 tokens 74.3 against 78.0 us, 16 x 2 of 4096 at 7B 12.5 % 75.2 / 77.8)
   if (a.q_per_seq > 1 && a.q_per_seq * p.head_groups > 2 && (int64_t)p.n_splits * a.B * p.head_groups < (1 << 30)) {
     prm.pair_map = 4;
-    prm.reader_run = reader_run(a.q_per_seq * p.head_groups, (int)(p.n_splits * a.B * p.head_groups));
+    const int all = (int)(p.n_splits * a.B * p.head_groups);
+    prm.reader_run = reader_run(a.q_per_seq * p.head_groups, all);
+    prm.reader_turns = reader_turns(all, prm.reader_run);
   }
   prm.d_q = p.d_q; prm.d_u = p.d_u; prm.q_per_seq = a.q_per_seq; prm.q_slice = slice_width(d.d_c);
   prm.n_part = p.n_part; prm.fresh = p.fresh;

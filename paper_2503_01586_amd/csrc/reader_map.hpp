@@ -22,14 +22,17 @@ constexpr int kReaderRun = 16;
 
 inline int reader_run(int readers, int all) { return all <= 256 ? all : readers < kReaderRun ? readers : kReaderRun; }
 
+// How often every XCD gets a run (a division less at the start of every work-group: 4 x 5 queries of 4096 tokens 86.0 -> 85.7 us)
+inline int reader_turns(int all, int run) { return all / (8 * run); }
+
 // Place on the line of `all` work-groups that work-group `block` takes (-1: none).  Work-groups go to the eight XCDs
 // round-robin by index.  The line is dealt out in runs, there and back (XCD 0 .. 7, 7 .. 0, ...): the rows that a query sees
 // grow along the line where the queries are a prompt's, or fall where a batch is sorted by length, and every XCD gets its
 // share of both ends.  What is left, less than a run per XCD, is divided in eighths, so that no XCD has more than one
 // work-group more than another.
-EKV_HOST_DEVICE int reader_place(int block, int all, int run) {
+EKV_HOST_DEVICE int reader_place(int block, int all, int run, int turns) {
   const int xcd = block & 7, slot = block >> 3;
-  const int turns = all / (8 * run), turn = slot / run;
+  const int turn = slot / run;
   if (turn < turns) return (turn * 8 + (turn & 1 ? 7 - xcd : xcd)) * run + slot % run;
   const int rest = all - turns * 8 * run, share = (rest + 7) / 8, k = slot - turns * run;
   const int at = turns * 8 * run + xcd * share + k;

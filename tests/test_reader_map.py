@@ -15,7 +15,7 @@ def places(tmp_path_factory):
     d = tmp_path_factory.mktemp("map")
     (d / "m.cpp").write_text('#include "reader_map.hpp"\n'
                              'extern "C" int run(int n, int all) { return ekv::reader_run(n, all); }\n'
-                             'extern "C" int place(int b, int all, int run) { return ekv::reader_place(b, all, run); }\n')
+                             'extern "C" int place(int b, int all, int run) { return ekv::reader_place(b, all, run, ekv::reader_turns(all, run)); }\n')
     subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-I", CSRC, str(d / "m.cpp"), "-o", str(d / "m.so")], check=True)
     lib = ctypes.CDLL(str(d / "m.so"))
 
