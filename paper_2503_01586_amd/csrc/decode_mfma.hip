@@ -255,9 +255,9 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     // Several queries per sequence: the work-groups that read the same rows (a split of one sequence, every query and head
     // group) follow each other on one XCD in runs, and all but the first of a run find the rows in its L2 (reader_map.hpp);
     // every other one swaps neighbouring tiles, so that not all of them ask for the same lines at once.  Spread over the XCDs
-    // as they came, each L2 fetched its own copy: us for an append and its queries, before / without the swap / now:
-    // 4 x 5 queries of 4096 tokens
-    // 89.9 / 86.7 / 86.0, 8 x 8 of 8192 297 / 295 / 280, 1 x 5 of 4096 56.0 / 53.7 / 53.4; 13B 4 x 5 of 4096 154 / 160 / 151.
+    // as they came, each L2 fetched its own copy: us for an append and its queries, before / without the swap / now: 4 x 5
+    // queries of 4096 tokens 89.9 / 86.7 / 85.4, 8 x 8 of 8192 297 / 295 / 276, 1 x 5 of 4096 56.0 / 53.7 / 53.4; 13B 4 x 5 of
+    // 4096 154 / 160 / 151.
     const int readers = p.q_per_seq * p.head_groups;
     const int item_wg = reader_place(blockIdx.x, p.n_splits * p.batch * p.head_groups, p.reader_run, p.reader_turns);
     if (item_wg < 0) return;
