@@ -226,8 +226,9 @@ int elitekv_decode_attn_noalloc(const elitekv_dims* dims, const void* q, const i
  * Workspace: elitekv_ropelite_search_min_workspace_bytes is what a search needs (about 32 KiB per head and 16 tokens: 66 MB
  * for 32 heads, 1000 tokens; 270 MB for 4096); it never falls as T grows.  elitekv_ropelite_search_workspace_bytes adds
  * room to keep every causal pair's residual score from round to round (4 bytes a pair and head, T <= 4096, up to 4 GiB:
- * 66 MB and 1.1 GB there), with which 1000 tokens take 1.1 instead of 1.6 ms; with less room it sums them again in every
- * round, to the same distances up to rounding.  EWORKSPACE below the smaller size.
+ * 1.1 GB for 4096 tokens) or, where the sum stays below 280 MiB, also for operands in three bf16 parts (210 MB in all for 1000
+ * tokens), with which 1000 tokens take 0.9 instead of 1.6 ms; with less room it sums the residuals again in every round,
+ * to the same distances up to rounding.  EWORKSPACE below the smaller size.
  * Enqueues r + 1 kernels on hip_stream; no host synchronisation.
  * ------------------------------------------------------------------------------------------- */
 size_t elitekv_ropelite_search_workspace_bytes(int64_t T, int32_t n_heads, int32_t head_dim, int32_t r);

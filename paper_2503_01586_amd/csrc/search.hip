@@ -18,6 +18,8 @@
 //                   16 x 16 tile of pairs is one v_mfma_f32_16x16x4_f32 (fp32 in, fp32 out) with the residual as its third
 //                   operand.  The last work-group of a head to arrive adds up the head's distances in a fixed order and
 //                   takes the arg-min.
+//   search_blocks : the same on products of bf16 parts, eight to a term, whose sum is as exact as the fp32 product: 64 x 64 pairs by
+//                   a work-group whose waves have a quarter of the chunks each; the samples of search_blocks' sizes take it
 // All state (packed copies, residuals, partial distances, elite masks) lives in the caller's workspace; a search is
 // 1 + r launches on the caller's stream with no host synchronisation in between.
 #include <algorithm>
@@ -37,33 +39,50 @@ typedef __attribute__((ext_vector_type(4))) float sr_f32x4;
 // [quad of chunks c4 (16)][lane (64)][4 chunks], lane = 16 * row + token % 16: one 16-byte load per lane and
 // instruction, 1 KiB contiguous per wave instruction, 16 instructions per operand.  Tokens beyond T are zeros.
 
-// Work-group = (tile of 16 tokens, kSrPackHeads heads): the tile's 16 x 64 rotations are formed once for all of its heads;
+// An fp32 value as the exact sum of three bf16 parts, each rounded to the nearest (ties away from zero; cut off where rounding
+// would leave the range): hm = the first (low half) and the second, ll = the third, twice.  Rounded and not cut off: the matrix
+// instruction drops the last bits of every product of a group of eight, and the products of parts of one sign would all lose
+// in the same direction (measured on normal factors: 6.6e-8 of the sum, against 1e-10 with rounded parts).
+struct SrParts { uint32_t hm, ll; };
+__device__ __forceinline__ uint32_t sr_top(float x) {
+  const uint32_t u = __float_as_uint(x), up = u + 0x8000u;
+  return ((u & 0x7f800000u) < 0x7f000000u ? up : u) & 0xffff0000u;
+}
+__device__ __forceinline__ SrParts sr_parts(float x) {
+  const uint32_t h = sr_top(x);
+  const float xm = x - __uint_as_float(h);
+  const uint32_t m = sr_top(xm);
+  const uint32_t l = __float_as_uint(xm - __uint_as_float(m)) & 0xffff0000u;
+  return {(h >> 16) | m, (l >> 16) | l};
+}
+
+// Work-group = (tile of 16 tokens, `heads` heads): the tile's 16 x 64 rotations are formed once for all of its heads;
 // a thread holds four chunks of one token, so every store is 16 bytes and 16 tokens' stores are contiguous.  A thread per
 // (token, head, chunk), with its own rotation and eight 4-byte stores, took 40 us for 1000 tokens of 32 heads; this 25.
-constexpr int kSrPackHeads = 4;
+template <bool SPLIT>
 __global__ __launch_bounds__(256) void search_pack_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                          const int32_t* __restrict__ pos, float* __restrict__ qp,
-                                                          float* __restrict__ kp, uint64_t* __restrict__ emask,
+                                                          const int32_t* __restrict__ pos, void* __restrict__ qp,
+                                                          void* __restrict__ kp, uint64_t* __restrict__ emask,
                                                           int32_t* __restrict__ arrived, int64_t T, int n_h, int d_h,
-                                                          float scale, RopeTable rope) {
+                                                          int heads, float scale, RopeTable rope) {
   __shared__ float2 turn[kSrMaxChunks][kSrTile + 1];
   const int tid = threadIdx.x, half = d_h / 2;
   const int64_t tile = blockIdx.x;
-  const int h0 = blockIdx.y * kSrPackHeads;
+  const int h0 = blockIdx.y * heads;
   for (int e = tid; e < kSrTile * kSrMaxChunks; e += 256) {
     const int t = e % kSrTile, i = e / kSrTile;
     float sn = 0.f, cs = 1.f;
     if (i < half && tile * kSrTile + t < T) rope_sincos(pos[tile * kSrTile + t], rope.theta[i], &sn, &cs);
     turn[i][t] = make_float2(sn, cs);
   }
-  if (tile == 0 && tid < kSrPackHeads && h0 + tid < n_h) {     // the heads' state, before the first round
+  if (tile == 0 && tid < heads && h0 + tid < n_h) {     // the heads' state, before the first round
     emask[h0 + tid] = 0ull;
     arrived[h0 + tid] = 0;
   }
   __syncthreads();
   const int t = tid % kSrTile, c4 = tid / kSrTile;
   const int64_t token = tile * kSrTile + t;
-  for (int h = h0; h < min(h0 + kSrPackHeads, n_h); ++h) {
+  for (int h = h0; h < min(h0 + heads, n_h); ++h) {
     sr_f32x4 qo[4], ko[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -82,6 +101,18 @@ __global__ __launch_bounds__(256) void search_pack_kernel(const float* __restric
       ko[1][e] = ku * r.x + kv * r.y;
       ko[2][e] = ku;
       ko[3][e] = kv;
+    }
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int row = 0; row < 4; ++row) {
+          const int64_t o = (((int64_t)h * kSrMaxChunks + 4 * c4 + e) * gridDim.x + tile) * 64 + 16 * row + t;
+          const SrParts a = sr_parts(qo[row][e]), b = sr_parts(ko[row][e]);
+          reinterpret_cast<uint2*>(qp)[o] = make_uint2(a.hm, a.ll);
+          reinterpret_cast<uint2*>(kp)[o] = make_uint2(b.ll, b.hm);
+        }
+      continue;
     }
     const int64_t o = ((tile * n_h + h) * (kSrMaxChunks / 4) + c4) * 64 + t;      // 16-byte units
 #pragma unroll
@@ -146,6 +177,47 @@ __device__ __forceinline__ void sr_distances(const sr_f32x4 (*A)[64], int lane, 
   }
 }
 
+// The end of a round: the last work-group of the head to arrive (device-scope stores, acknowledged before the count) adds up the
+// head's distances in a fixed order and takes the arg-min.  red: 2 KiB of LDS.
+__device__ __forceinline__ void sr_choose(float* red, int* last, uint64_t* emask, int32_t* arrived, const float* partial,
+                                          int32_t* elite_out, float* dist_out, int h, int n_items, int half, int r, int round,
+                                          uint64_t elite) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    *last = __hip_atomic_fetch_add(arrived + h, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_items - 1;
+    if (*last) __hip_atomic_store(arrived + h, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!*last) return;
+  // in 64 bits: thirty-four sums of a wave, one after the other (136 blocks of 1000 tokens), lost 4e-8 of the distance in 32
+  double sum = 0.0;
+#pragma unroll 16
+  for (int i = wave; i < n_items; i += 4)
+    sum += __hip_atomic_load(partial + ((int64_t)h * n_items + i) * kSrMaxChunks + lane, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+  double* sums = reinterpret_cast<double*>(red);
+  sums[wave * 64 + lane] = sum;
+  __syncthreads();
+  if (wave != 0) return;
+  const float d = (float)((sums[lane] + sums[64 + lane]) + (sums[128 + lane] + sums[192 + lane]));
+  const bool cand = lane < half && !((elite >> lane) & 1ull);
+  float best = cand ? d : INFINITY;
+  int arg = cand ? lane : kSrMaxChunks;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {                 // arg-min, the lowest index wins a tie
+    const float ob = __shfl_xor(best, o, kWave);
+    const int oa = __shfl_xor(arg, o, kWave);
+    if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
+  }
+  if (lane == 0) {
+    elite_out[h * r + round] = arg;
+    if (dist_out) dist_out[h * r + round] = best;
+    emask[h] = elite | (1ull << (arg & 63));
+  }
+}
+
 // grid (heads, items), four waves; item = (32 queries, up to `keys` key tiles), the key tiles dealt to the waves round-robin.
 // A wave holds the key operand B of a tile in registers and uses it for both query tiles (their operands in LDS):
 //   residual  LOAD: what the last round left, less the chunk it chose; else the sum over the chunks outside E
@@ -163,7 +235,7 @@ __global__ __launch_bounds__(256, 2) void search_round_kernel(
     float* __restrict__ dist_out, int n_h, int n_tiles, int keys, int half, int r, int round,
     bool keep) {
   __shared__ sr_f32x4 As[2][kSrMaxChunks / 4][64];
-  __shared__ float red[4][kSrMaxChunks];
+  __shared__ __attribute__((aligned(8))) float red[8][kSrMaxChunks];   // (twice the waves' sums: also the choice's, in 64 bits)
   __shared__ int last;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i16 = lane & 15, kk = lane >> 4;
@@ -261,38 +333,197 @@ __global__ __launch_bounds__(256, 2) void search_round_kernel(
     __hip_atomic_store(partial + ((int64_t)h * n_items + item) * kSrMaxChunks + lane,
                        (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
-  // the last work-group of the head to arrive makes the choice (device-scope stores, acknowledged before the count)
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (tid == 0) {
-    last = __hip_atomic_fetch_add(arrived + h, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_items - 1;
-    if (last) __hip_atomic_store(arrived + h, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __syncthreads();
-  if (!last) return;
-  float d = 0.f;
-#pragma unroll 16
-  for (int i = wave; i < n_items; i += 4)
-    d += __hip_atomic_load(partial + ((int64_t)h * n_items + i) * kSrMaxChunks + lane, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-  red[wave][lane] = d;
-  __syncthreads();
-  if (wave != 0) return;
-  d = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-  const bool cand = lane < half && !((elite >> lane) & 1ull);
-  float best = cand ? d : INFINITY;
-  int arg = cand ? lane : kSrMaxChunks;
+  sr_choose(&red[0][0], &last, emask, arrived, partial, elite_out, dist_out, h, n_items, half, r, round, elite);
+}
+
+// ---- the round on products of bf16 parts -------------------------------------------------------------------------------
+//
+// A factor of the 4-term product is the exact sum of three bf16 parts (SrParts), and v_mfma_f32_16x16x32_bf16 has room for
+// eight products of every term: all pairs of parts but the two last ones' (2^-32 of the term).  A lane holds one term (row) of
+// one token: query side {hm, ll, hm, hm}, key side {ll, hm, hm, mh}, of which {hm, ll} and {ll, hm} lie in memory as
+// [head][chunk][tile of 16 tokens][lane] (tiles padded to whole blocks, zeros beyond T).
+
+typedef __attribute__((ext_vector_type(8))) __bf16 sr_bf16x8;
+typedef __attribute__((ext_vector_type(4))) uint32_t sr_u32x4;
+
+constexpr int kSbTiles = 4;                                 // tiles of queries (and of keys) in a block: 64 x 64 pairs
+constexpr int kSbChunks = kSrMaxChunks / 4;                 // chunks of a wave
+constexpr int kSbLag = 3;                                   // products between a product and the sums of its values
+
+struct SbOperands {
+  sr_u32x4 a[kSbTiles], b[kSbTiles];
+  __device__ __forceinline__ void load(const uint2* q, const uint2* k) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {                 // arg-min, the lowest index wins a tie
-    const float ob = __shfl_xor(best, o, kWave);
-    const int oa = __shfl_xor(arg, o, kWave);
-    if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
+    for (int i = 0; i < kSbTiles; ++i) {
+      const uint2 x = q[i * 64], y = k[i * 64];
+      a[i].x = x.x; a[i].y = x.y;
+      b[i].x = y.x; b[i].y = y.y;
+    }
   }
-  if (lane == 0) {
-    elite_out[h * r + round] = arg;
-    if (dist_out) dist_out[h * r + round] = best;
-    emask[h] = elite | (1ull << (arg & 63));
+  __device__ __forceinline__ void expand() {
+#pragma unroll
+    for (int i = 0; i < kSbTiles; ++i) {
+      a[i].z = a[i].x; a[i].w = a[i].x;
+      b[i].z = b[i].y; b[i].w = __builtin_amdgcn_alignbit(b[i].y, b[i].y, 16);
+    }
   }
+  __device__ __forceinline__ sr_f32x4 product(int qi, int ki, const sr_f32x4& c) const {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(sr_bf16x8, a[qi]), __builtin_bit_cast(sr_bf16x8, b[ki]),
+                                                   c, 0, 0, 0);
+  }
+};
+
+// red[c][lane] = the lane's sum over the block's pairs of |R - D_c|, for the wave's chunks c.  DIAG: the block on the
+// diagonal: tiles above it are left out, those on it weighted by w (0 above the diagonal).
+template <bool DIAG, bool FUSED>
+__device__ __forceinline__ void sb_distances(const uint2* q, const uint2* k, int64_t step, const sr_f32x4 (&R)[kSbTiles][kSbTiles],
+                                             const float (&w)[4], float* red) {
+  constexpr int kPairs = kSbTiles * kSbTiles;
+  SbOperands op[2];
+  op[0].load(q, k);
+  op[0].expand();
+#pragma unroll 2
+  for (int c = 0; c < kSbChunks; ++c) {
+    SbOperands& now = op[c & 1];
+    SbOperands& next = op[(c + 1) & 1];
+    const int64_t ahead = (c + 1 < kSbChunks ? c + 1 : c) * step;
+    next.load(q + ahead, k + ahead);
+    float a[4] = {0.f, 0.f, 0.f, 0.f};
+    sr_f32x4 D[kSbLag + 1];
+#pragma unroll
+    for (int i = 0; i < kPairs + kSbLag; ++i) {
+      if (i < kPairs) {
+        const int qi = i / kSbTiles, ki = i % kSbTiles;
+        if (!DIAG || ki <= qi) D[i % (kSbLag + 1)] = now.product(qi, ki, FUSED ? R[qi][ki] : (sr_f32x4)(0.f));
+      }
+      if (i >= kSbLag) {
+        const int j = i - kSbLag, qi = j / kSbTiles, ki = j % kSbTiles;
+        if (!DIAG || ki <= qi) {
+          const sr_f32x4& d = D[j % (kSbLag + 1)];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float e = fabsf(FUSED ? d[v] : R[qi][ki][v] + d[v]);
+            a[v] = DIAG && ki == qi ? fmaf(w[v], e, a[v]) : a[v] + e;
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    next.expand();
+    red[c * 64] = (a[0] + a[1]) + (a[2] + a[3]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// What bounds it: the chip's power.  With every SIMD at work a product of 16 x 16 x 32 bf16 takes 12 ns (16 cycles at the 1.35 GHz
+// that are left of 2.4), 18 with its four additions and the operands' copies; the fp32 instruction takes 14, and 25 with the additions,
+// for the two do not overlap.  1000 tokens of 32 heads: 75 us of products in a round of 95 (search_round_kernel: 119).  Block size and
+// split: a block of 64 x 64 needs half an operand per product and twelve waves of it fit a compute unit; the chunks and not the
+// pairs divided among its waves, so that 128 tokens already make 96 work-groups.  Not kept: the queries' operands of all chunks in LDS (1030
+// against 900 us a search), both sides through a ring of LDS for 128 x 128 pairs (1325), the work-group's next blocks one after
+// the other (two: 940).
+// grid n_h x blocks, four waves: a work-group has a block of 64 queries x 64 keys, its waves sixteen chunks each; every wave
+// holds the block's residuals in registers:
+//   LOAD  what the last round left, less the chunk it chose; else the sum over the chunks outside E, a quarter by each wave
+template <bool LOAD, bool FUSED>
+__global__ __launch_bounds__(256, 2) void search_blocks_kernel(
+    const uint2* __restrict__ qp, const uint2* __restrict__ kp, float* __restrict__ res, uint64_t* __restrict__ emask,
+    int32_t* __restrict__ arrived, float* __restrict__ partial, int32_t* __restrict__ elite_out,
+    float* __restrict__ dist_out, int n_h, int n_blocks, int half, int r, int round, bool keep) {
+  __shared__ __attribute__((aligned(8))) float red[kSrMaxChunks * 64];
+  __shared__ sr_f32x4 part[LOAD ? 1 : 4][LOAD ? 1 : 2 * kSbTiles][64];
+  __shared__ int last;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, kk = lane >> 4;
+  // the blocks of a head on one XCD where the heads can be dealt evenly (their operands in its L2); the lighter ones on the
+  // diagonal last
+  const int n_items = n_blocks * (n_blocks + 1) / 2, n_full = n_items - n_blocks;
+  const int h = n_h % 8 == 0 ? blockIdx.x % 8 + 8 * (blockIdx.x / 8 / n_items) : blockIdx.x % n_h;
+  const int item = n_h % 8 == 0 ? blockIdx.x / 8 % n_items : blockIdx.x / n_h;
+  int qb = item - n_full, kb = qb;
+  if (item < n_full) {
+    qb = 1;
+    while (qb * (qb + 1) / 2 <= item) ++qb;
+    kb = item - qb * (qb - 1) / 2;
+  }
+
+  const int64_t step = (int64_t)n_blocks * kSbTiles * 64;        // from chunk to chunk
+  const int c0 = wave * kSbChunks;
+  const uint2* qt = qp + (int64_t)h * kSrMaxChunks * step + qb * kSbTiles * 64 + lane;
+  const uint2* kt = kp + (int64_t)h * kSrMaxChunks * step + kb * kSbTiles * 64 + lane;
+  float* mine = red + c0 * 64 + lane;
+  float w[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) w[v] = i16 <= 4 * kk + v ? 1.f : 0.f;
+  const uint64_t elite = emask[h];
+  const int chosen = LOAD ? elite_out[h * r + round - 1] : kSrMaxChunks;
+
+  sr_f32x4* mem = reinterpret_cast<sr_f32x4*>(res) + ((int64_t)h * n_items + item) * kSbTiles * kSbTiles * 64 + lane;
+  sr_f32x4 R[kSbTiles][kSbTiles];
+  if constexpr (LOAD) {
+#pragma unroll
+    for (int e = 0; e < kSbTiles * kSbTiles; ++e) R[e / kSbTiles][e % kSbTiles] = mem[e * 64];
+    if (chosen >= 0 && chosen < kSrMaxChunks) {
+      SbOperands op;
+      op.load(qt + chosen * step, kt + chosen * step);
+      op.expand();
+#pragma unroll
+      for (int i = 0; i < kSbTiles; ++i)
+#pragma unroll
+        for (int j = 0; j < kSbTiles; ++j) R[i][j] = op.product(i, j, R[i][j]);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < kSbTiles * kSbTiles; ++e) R[e / kSbTiles][e % kSbTiles] = (sr_f32x4)(0.f);
+    SbOperands op[2];
+    op[0].load(qt + c0 * step, kt + c0 * step);
+#pragma unroll 2
+    for (int c = c0; c < c0 + kSbChunks; ++c) {
+      SbOperands& now = op[c & 1];
+      const int64_t ahead = (c + 1 < c0 + kSbChunks ? c + 1 : c) * step;
+      op[(c + 1) & 1].load(qt + ahead, kt + ahead);
+      if ((elite >> c) & 1ull) continue;
+      now.expand();
+#pragma unroll
+      for (int i = 0; i < kSbTiles; ++i)
+#pragma unroll
+        for (int j = 0; j < kSbTiles; ++j) R[i][j] = now.product(i, j, R[i][j]);
+    }
+    // the waves' sums through LDS, half a block at a time
+#pragma unroll
+    for (int i0 = 0; i0 < kSbTiles; i0 += 2) {
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 2 * kSbTiles; ++e) part[wave][e][lane] = R[i0 + e / kSbTiles][e % kSbTiles];
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 2 * kSbTiles; ++e)
+        R[i0 + e / kSbTiles][e % kSbTiles] = -((part[0][e][lane] + part[1][e][lane]) + (part[2][e][lane] + part[3][e][lane]));
+    }
+  }
+  // waited for here, not wherever they are used below
+#pragma unroll
+  for (int e = 0; e < kSbTiles * kSbTiles; ++e) asm volatile("" : "+v"(R[e / kSbTiles][e % kSbTiles]));
+  if (keep) {
+    if constexpr (LOAD) __syncthreads();                         // every wave has read the last round's residuals
+#pragma unroll
+    for (int e = 0; e < kSbTiles * kSbTiles; ++e)
+      if (e / kSbTiles == wave) mem[e * 64] = R[e / kSbTiles][e % kSbTiles];
+  }
+  if (kb == qb) sb_distances<true, FUSED>(qt + c0 * step, kt + c0 * step, step, R, w, mine);
+  else sb_distances<false, FUSED>(qt + c0 * step, kt + c0 * step, step, R, w, mine);
+
+  // four threads to a chunk, sixteen lanes' sums each
+  __syncthreads();
+  float d = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) d += red[(tid >> 2) * 64 + (tid & 3) * 16 + ((i + (tid >> 2)) & 15)];
+  d += __shfl_xor(d, 1, kWave);
+  d += __shfl_xor(d, 2, kWave);
+  if ((tid & 3) == 0)
+    __hip_atomic_store(partial + ((int64_t)h * n_items + item) * kSrMaxChunks + (tid >> 2), d, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  sr_choose(red, &last, emask, arrived, partial, elite_out, dist_out, h, n_items, half, r, round, elite);
 }
 
 // Samples of up to this many tokens keep the residuals where the caller's workspace has room for them (n_h (T / 16)^2 / 2
@@ -302,57 +533,93 @@ __global__ __launch_bounds__(256, 2) void search_round_kernel(
 constexpr int64_t kSrKeepTokens = 4096;
 constexpr size_t kSrKeepBytes = (size_t)4 << 30;
 
+// search_blocks_kernel takes samples of seven tiles and more (shorter ones leave most of a 64 x 64 block empty: 32 heads x 96 tokens
+// 100 against 96 us, 128: 102 and 102) whose operands and residuals the 256 MB cache behind the L2s holds but for a little (64 heads
+// x 640 tokens, 224 MB: 790 against 879 us; 32 x 1280, 275 MB: 1468 against 1555; 64 x 768, 283 MB: 1177 against 1163; 64 x 900,
+// 340 MB: 1843 against 1655), other than those of 13 and 14 tiles (a fourth row of blocks, a quarter or half of it tokens: 32 x 200
+// 145 against 139; 15 and 16 tiles 144 against 198).
+constexpr size_t kSbBytes = (size_t)280 << 20;
+
 // least: bytes a search needs, which never falls as T grows (the pieces per head do, wherever a piece gets longer: the
-// partial distances are laid out for the most that a shorter sample has); total: with the residuals, if they are kept
-struct SearchLayout { size_t kp, partial, emask, arrived, res, least, total; int n_tiles, keys, n_items; };
-static SearchLayout search_layout(int64_t T, int n_h) {
+// partial distances are laid out for the most that a shorter sample has); total: with what it is faster with, for every
+// shorter sample too.  room: what a caller has; decides what the search keeps
+struct SearchLayout { size_t kp, partial, emask, arrived, res, least, total; int n_tiles, keys, n_items; bool blocks, keep; };
+static SearchLayout search_layout(int64_t T, int n_h, size_t room) {
   SearchLayout L;
-  L.n_tiles = (int)((T + kSrTile - 1) / kSrTile);
-  const int n_q32 = (L.n_tiles + 1) / 2;
+  auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+  auto lay = [&](size_t vec, int64_t items) {                    // one packed operand, partial distances: returns the bytes
+    L.kp = up(vec);
+    L.partial = 2 * L.kp;
+    L.emask = L.partial + up((size_t)n_h * items * kSrMaxChunks * sizeof(float));
+    L.arrived = L.emask + up((size_t)n_h * sizeof(uint64_t));
+    return L.res = L.arrived + up((size_t)n_h * sizeof(int32_t));
+  };
+  auto lay_blocks = [&](int64_t n_blocks) {
+    const int64_t items = n_blocks * (n_blocks + 1) / 2;
+    L.n_tiles = (int)n_blocks * kSbTiles;
+    L.n_items = (int)items;
+    return lay((size_t)L.n_tiles * kSrTile * n_h * kSrRow * 8, items) + (size_t)items * n_h * kSbTiles * kSbTiles * 1024;
+  };
+  const int64_t tiles = (T + kSrTile - 1) / kSrTile, n_q32 = (tiles + 1) / 2, blocks = (tiles + kSbTiles - 1) / kSbTiles;
+  int64_t fast_blocks = std::min<int64_t>(blocks, kSrKeepTokens / (kSbTiles * kSrTile));
+  while (fast_blocks > 0 && lay_blocks(fast_blocks) > kSbBytes) --fast_blocks;
+  const size_t fast = lay_blocks(fast_blocks);
+  L.n_tiles = (int)tiles;
   L.keys = sr_keys_per_item(n_q32, n_h);
   L.n_items = (int)sr_items_before(n_q32, L.keys);
-  auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-  const size_t vec = up((size_t)L.n_tiles * kSrTile * n_h * kSrRow * sizeof(float));      // one packed operand (whole tiles)
-  L.kp = vec;
-  L.partial = L.kp + vec;
   const int64_t most_items = std::min<int64_t>(sr_items_before(n_q32, 4), 1024 + n_q32);
-  L.emask = L.partial + up((size_t)n_h * most_items * kSrMaxChunks * sizeof(float));
-  L.arrived = L.emask + up((size_t)n_h * sizeof(uint64_t));
-  L.res = L.arrived + up((size_t)n_h * sizeof(int32_t));
-  L.least = L.total = L.res;
-  const size_t kept = (size_t)L.n_tiles * (L.n_tiles + 1) / 2 * n_h * 1024;
+  L.least = L.total = lay((size_t)tiles * kSrTile * n_h * kSrRow * sizeof(float), most_items);
+  const size_t kept = (size_t)tiles * (tiles + 1) / 2 * n_h * 1024;
   if (T <= kSrKeepTokens && kept <= kSrKeepBytes) L.total += kept;
+  L.keep = L.total > L.least && room >= L.total;
+  L.blocks = blocks == fast_blocks && tiles >= 7 && tiles != 13 && tiles != 14 && room >= fast;
+  if (tiles >= 7) L.total = std::max(L.total, fast);
+  if (L.blocks) lay_blocks(blocks);
   return L;
 }
 
-size_t search_workspace_bytes(int64_t T, int n_h) { return search_layout(T, n_h).total; }
-size_t search_min_workspace_bytes(int64_t T, int n_h) { return search_layout(T, n_h).least; }
+size_t search_workspace_bytes(int64_t T, int n_h) { return search_layout(T, n_h, 0).total; }
+size_t search_min_workspace_bytes(int64_t T, int n_h) { return search_layout(T, n_h, 0).least; }
 
 hipError_t launch_ropelite_search(const float* q, const float* k, const int32_t* pos, int64_t T, int n_h, int d_h,
                                   int r, double rope_base, int32_t* elite_out, float* dist_out, char* ws,
                                   size_t ws_bytes, hipStream_t stream) {
-  const SearchLayout L = search_layout(T, n_h);
-  float* qp = (float*)ws;
-  float* kp = (float*)(ws + L.kp);
+  const SearchLayout L = search_layout(T, n_h, ws_bytes);
+  char *qp = ws, *kp = ws + L.kp;
   float* partial = (float*)(ws + L.partial);
   uint64_t* emask = (uint64_t*)(ws + L.emask);
   int32_t* arrived = (int32_t*)(ws + L.arrived);
-  float* res = L.total > L.least && ws_bytes >= L.total ? (float*)(ws + L.res) : nullptr;
+  float* res = L.blocks || L.keep ? (float*)(ws + L.res) : nullptr;
   const int half = d_h / 2;
   const float scale = 1.f / sqrtf((float)d_h);
-  search_pack_kernel<<<dim3(L.n_tiles, (n_h + kSrPackHeads - 1) / kSrPackHeads), 256, 0, stream>>>(
-      q, k, pos, qp, kp, emask, arrived, T, n_h, d_h, scale, rope_table(rope_base, d_h));
-  const dim3 grid(n_h, L.n_items);
+  // heads of a work-group: as many as leave a few hundred work-groups, for they share the rotations
+  const int heads = std::max<int64_t>(1, std::min<int64_t>(4, (int64_t)L.n_tiles * n_h / 512));
+  const dim3 pack_grid(L.n_tiles, (n_h + heads - 1) / heads);
+  if (L.blocks)
+    search_pack_kernel<true><<<pack_grid, 256, 0, stream>>>(q, k, pos, qp, kp, emask, arrived, T, n_h, d_h, heads, scale,
+                                                            rope_table(rope_base, d_h));
+  else
+    search_pack_kernel<false><<<pack_grid, 256, 0, stream>>>(q, k, pos, qp, kp, emask, arrived, T, n_h, d_h, heads, scale,
+                                                             rope_table(rope_base, d_h));
   // A residual carries the rounding errors of the full sum along, while it shrinks as chunks leave it: once more than a
   // quarter of the chunks are chosen it is summed afresh and the products are rounded before they are taken off it, so
   // that the last chunk's distance vanishes exactly.
   for (int round = 0; round < r; ++round) {
     const bool early = 4 * round <= half, keep = res && 4 * (round + 1) <= half && round + 1 < r;
-    auto kernel = !early           ? search_round_kernel<false, false>
-                  : round && res   ? search_round_kernel<true, true>
-                                   : search_round_kernel<false, true>;
-    kernel<<<grid, 256, 0, stream>>>(qp, kp, res, emask, arrived, partial, elite_out, dist_out, n_h, L.n_tiles, L.keys, half,
-                                     r, round, keep);
+    if (L.blocks) {
+      auto kernel = !early  ? search_blocks_kernel<false, false>
+                    : round ? search_blocks_kernel<true, true>
+                            : search_blocks_kernel<false, true>;
+      kernel<<<(unsigned)(n_h * L.n_items), 256, 0, stream>>>((const uint2*)qp, (const uint2*)kp, res, emask, arrived, partial,
+                                                              elite_out, dist_out, n_h, L.n_tiles / kSbTiles, half, r, round,
+                                                              keep);
+    } else {
+      auto kernel = !early           ? search_round_kernel<false, false>
+                    : round && res   ? search_round_kernel<true, true>
+                                     : search_round_kernel<false, true>;
+      kernel<<<dim3(n_h, L.n_items), 256, 0, stream>>>((const float*)qp, (const float*)kp, res, emask, arrived, partial, elite_out,
+                                                       dist_out, n_h, L.n_tiles, L.keys, half, r, round, keep);
+    }
   }
   return hipGetLastError();
 }
