@@ -99,7 +99,9 @@ struct AttnMfmaLayout {
   static constexpr int X1_ROW = 33;                         // floats per token row (padded)
   static constexpr int X1 = NW * kTile * X1_ROW * 4;        // stage 1: every wave's partial scores
   static constexpr int X2_ROW = 20;                         // floats per head row (16 tokens, padded)
-  static constexpr int X2 = 32 * X2_ROW * 4;                // stage 2: the final scores
+  static constexpr int X2 = 32 * X2_ROW * 4;                // stage 2: the final scores; or, in the same place,
+  static constexpr int P_ROW = 48;                          // bytes per head row (16 probabilities, padded)
+  static_assert(32 * P_ROW + 4 <= X2, "the probabilities, and the tile that raised a maximum");
   // elite keys of a tile: per wave the TPW tokens it finalises x the 32 heads of the group
   static constexpr int KE_ROW = 32 * TWO_R * 2;             // bytes of one token's group row
   static constexpr int KE_CPT = KE_ROW / 16;                // 16-byte chunks per token
@@ -133,24 +135,41 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// One direct global->LDS load: every lane fetches 16 bytes from its own global address; lane l's
-// data lands at lds_base + l*16.  Issued through inline assembly so that the waits on these loads
+// One direct global->LDS load: lane l fetches 16 bytes from base + voff + OFF, its data lands at lds_base + l*16.  The
+// instruction's offset counts on both sides (M0 is set to as much less), so that loads of neighbouring columns share one
+// register of lane offsets and the rows' base stays in scalar registers: with an address per load and lane they took two vector
+// instructions each (13B 16 x 8192 186.9 -> 184.6 us a step, 4 x 5 drafted over 4096 tokens 81.2 -> 80.1).  Issued through inline assembly so that the waits on these loads
 // stay entirely under the kernel's control (vmcnt counting, see the tile loop).
 // STREAM marks the load non-temporal: cache rows that are read once per step stream from HBM
 // about 15 % faster that way (a plain read of 1 GiB through these loads: 6.0 TB/s, marked: 6.9 TB/s).
 // Rows that a second work-group is about to re-read from the L2 (head-group pairs) are loaded unmarked.
 template <int OFF, bool STREAM>
-__device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_base) {
+__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_base) {
+  static_assert(OFF >= 0 && OFF < 4096, "outside the instruction's offset");
   if constexpr (STREAM)
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off offset:%2 nt"
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt"
                  :
-                 : "s"(lds_base), "v"(gptr), "n"(OFF)
+                 : "s"(lds_base - OFF), "v"(voff), "s"(base), "n"(OFF)
                  : "memory", "m0");
   else
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off offset:%2"
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
                  :
-                 : "s"(lds_base), "v"(gptr), "n"(OFF)
+                 : "s"(lds_base - OFF), "v"(voff), "s"(base), "n"(OFF)
                  : "memory", "m0");
+}
+// dma16 of COUNT neighbouring 128-byte column blocks, 1 KiB of LDS apart
+template <int COUNT, bool STREAM, int CB = 0>
+__device__ __forceinline__ void dma16_blocks(const void* base, uint32_t voff, uint32_t lds_base) {
+  if constexpr (CB < COUNT) {
+    dma16<CB * 128, STREAM>(base, voff, lds_base + CB * 1024);
+    dma16_blocks<COUNT, STREAM, CB + 1>(base, voff, lds_base);
+  }
+}
+// an address that is the same in every lane, in scalar registers (64-bit comparisons leave it in vector registers)
+__device__ __forceinline__ const char* uniform(const char* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
 }
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
@@ -207,6 +226,15 @@ template <int NW, int DC_W, int TWO_R, bool SEP, int SMODE>
 __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsPerCu)) void attn_mfma_kernel(const AttnMfmaParams p) {
   using L = AttnMfmaLayout<NW, DC_W, TWO_R>;
   constexpr int KS = L::KS, CT = L::CT, NCB = L::NCB, EPL = L::EPL, TPW = L::TPW;
+  // Who forms the probabilities: the lane that finalised the score, once, against the maximum so far (OWNER_P), or every wave from
+  // the scores, eight a lane, behind the second barrier.  In the first form a lane has one or two exponentials of a tile instead of
+  // eight on the chain between the matrix products, which bounds a launch whose rows come from the L2 or that has one wave per SIMD:
+  // without loads in the loop a tile took 1.73 us at 13B (now 1.3), 1.55 for drafted tokens at 7B (1.1).  us a step: 13B 16 x 8192
+  // 197.7 -> 188.0 (with the addresses of dma16 183, with the operands below read ahead 180.5), 4 x 5 drafted over 4096 85.5 ->
+  // 81.0 (80.3), 7B 12.5 % 64 x 2048 80.7 -> 79.2 (78.8), 1 x 30000 36.7 -> 35.4.  Where the memory is the bound, eight waves a
+  // work-group that share rows with nobody, the loads then come in shorter bursts and the launch is longer (7B 1 x 32768
+  // 48.6 -> 49.8, 16 x 8192 114.2 -> 115.4): those keep the second form, unless its registers do not suffice.
+  constexpr bool OWNER_P = !(SMODE == 1 && NW == 8 && KS * 8 + CT * 16 + TWO_R <= 160);
   constexpr int KCH = TWO_R / 8;                 // 16-byte chunks of one head's elite key
   // One wave per SIMD (512 registers per lane, half of them accumulation registers): the accumulators are pinned to
   // the AGPRs by hand.  Left to the compiler, such a kernel keeps the accumulators in VGPRs and parks the absorbed
@@ -286,6 +314,9 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
       b = item / per_row;
     }
   }
+  // (divisions leave them in vector registers: the same in every lane)
+  split = __builtin_amdgcn_readfirstlane(split); hg = __builtin_amdgcn_readfirstlane(hg);
+  b = __builtin_amdgcn_readfirstlane(b); odd = __builtin_amdgcn_readfirstlane(odd);
   if (split == 0 && hg == 0)
     for (int i = tid; i < p.n_h; i += NW * 64) p.chunk_counters[(int64_t)b * p.n_h + i] = 0;
   // ---- the query
@@ -337,12 +368,13 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
       for (int j = 0; j < TWO_R / 4; ++j) asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(qv[j]) : "v"(qer + 4 * j) : "memory");
     }
   };
-  const int64_t row0 = (int64_t)(b / p.q_per_seq) * p.batch_stride_rows;
+  const int64_t row0 = (int64_t)__builtin_amdgcn_readfirstlane(b / p.q_per_seq) * p.batch_stride_rows;
 
   char* ctile0 = smem + wave * L::WTILE;                 // buffer 0; buffer 1 is TILE_BYTES further
   char* ketile0 = smem + L::KE_OFF + wave * L::KE_W;     // buffer 0; buffer 1 (if any) is KE_BYTES further
   float* x1 = reinterpret_cast<float*>(smem + L::X1_OFF);
-  float* x2 = reinterpret_cast<float*>(smem + L::X2_OFF);
+  char* x2 = smem + L::X2_OFF;
+  int* raised = reinterpret_cast<int*>(x2 + 32 * L::P_ROW);
 
   // Split s takes the 16-token tiles s, s + n_splits, s + 2 n_splits, ...: at any moment the
   // work-groups of a batch row read one contiguous window of the planes that moves through the
@@ -363,14 +395,18 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
   const int64_t crow_bytes = (int64_t)p.d_c * 2;
   const int64_t krow_bytes = (int64_t)p.n_h * TWO_R * 2;
   // loader: lane l fills slot (row l/8, position l%8) of every block; it fetches the logical
-  // chunk that the swizzle puts there
+  // chunk that the swizzle puts there (bytes inside a cache row)
   const int ld_row = lane >> 3;
-  const char* cbase = reinterpret_cast<const char*>(p.c_plane) + (int64_t)cw * DC_W * 2 +
-                      (((lane & 7) ^ tile_swz(ld_row)) << 4);
-  const char* hbase = reinterpret_cast<const char*>(p.c_plane) + ((int64_t)cw * DC_W + NCB * 64) * 2 +
-                      (((lane & 3) ^ half_swz(lane >> 2)) << 4);
+  const uint32_t c_col = cw * DC_W * 2 + (((lane & 7) ^ tile_swz(ld_row)) << 4);
+  const uint32_t h_col = (cw * DC_W + NCB * 64) * 2 + (((lane & 3) ^ half_swz(lane >> 2)) << 4);
   // elite-key loader: slot c = i*64 + lane of the wave's slice is (token c / KE_CPT, chunk c % KE_CPT)
-  const char* kbase = reinterpret_cast<const char*>(p.ke_plane);
+  constexpr int KEQ = TWO_R > 0 ? (L::KE_CPT > 64 ? L::KE_CPT / 64 : 1) : 1;   // loads per token
+  uint32_t ke_col[KEQ];
+#pragma unroll
+  for (int i = 0; i < KEQ; ++i) {
+    const int ch = (i * 64 + lane) % (TWO_R > 0 ? L::KE_CPT : 1), kch = TWO_R > 0 ? KCH : 1;
+    ke_col[i] = (min(hg * 32 + ch / kch, p.n_h - 1) * kch + ch % kch) * 16;
+  }
 
   // LDS read offsets (inside a wave's tile slice) that do not change from tile to tile.
   // score A operand: token row i16, logical chunk 4*ks + q16 -> block (i16/8, ks/2)
@@ -398,36 +434,32 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     const int row = 8 * (q16 >> 1) + 4 * e + (i16 >> 2);
     trh_off[e] = L::HALF_OFF + row * 64 + ((tr_lo ^ half_swz(row)) << 4) + ((i16 & 1) << 3);
   }
+  if (OWNER_P && tid == 0) *raised = 0;                  // the first tile has no maximum yet
   // stage-2 ownership: this wave finalises tokens wave*TPW + g + 2*e (e < EPL) for head n
   const int own_t0 = wave * TPW + g;
 
+  // (rows past the sequence's end repeat its last one)
   auto issue_c = [&](int64_t tile_t0, char* ctile, auto nt) {
     constexpr bool STREAM = decltype(nt)::value;
     const uint32_t cl = __builtin_amdgcn_readfirstlane(lds_addr(ctile));
+    const char* base = uniform(reinterpret_cast<const char*>(p.c_plane) + (row0 + tile_t0) * crow_bytes);
+    const int last = (int)min(t_end - 1 - tile_t0, (int64_t)(kTile - 1));
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      const int64_t t = min(tile_t0 + rb * 8 + ld_row, t_end - 1);
-      const char* gp = cbase + (row0 + t) * crow_bytes;
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) dma16<0, STREAM>(gp + cb * 128, cl + (rb * NCB + cb) * 1024);
-    }
-    if (L::HALF) {   // lane l fills slot (row l/4, position l%4) of the half-width block
-      const int hr = lane >> 2;
-      const int64_t t = min(tile_t0 + hr, t_end - 1);
-      dma16<0, STREAM>(hbase + (row0 + t) * crow_bytes, cl + L::HALF_OFF);
-    }
+    for (int rb = 0; rb < 2; ++rb)
+      dma16_blocks<NCB, STREAM>(base, __umul24(min(rb * 8 + ld_row, last), (uint32_t)crow_bytes) + c_col, cl + rb * NCB * 1024);
+    // lane l fills slot (row l/4, position l%4) of the half-width block
+    if (L::HALF) dma16<0, STREAM>(base, __umul24(min(lane >> 2, last), (uint32_t)crow_bytes) + h_col, cl + L::HALF_OFF);
   };
   auto issue_ke = [&](int64_t tile_t0, char* ketile, auto nt) {
     constexpr bool STREAM = decltype(nt)::value;
-    if (TWO_R > 0) {
+    if constexpr (TWO_R > 0) {
       const uint32_t kl = __builtin_amdgcn_readfirstlane(lds_addr(ketile));
+      const char* base = uniform(reinterpret_cast<const char*>(p.ke_plane) + (row0 + tile_t0) * krow_bytes);
+      const int last = (int)min(t_end - 1 - tile_t0, (int64_t)(kTile - 1));
 #pragma unroll
       for (int i = 0; i < L::NKE; ++i) {
-        const int c = i * 64 + lane;
-        const int tl = min(c / L::KE_CPT, TPW - 1), ch = c % L::KE_CPT;
-        const int hd = min(hg * 32 + ch / KCH, p.n_h - 1);
-        const int64_t t = min(tile_t0 + wave * TPW + tl, t_end - 1);
-        dma16<0, STREAM>(kbase + (row0 + t) * krow_bytes + ((int64_t)hd * KCH + ch % KCH) * 16, kl + i * 1024);
+        const int tl = min((i * 64 + lane) / L::KE_CPT, TPW - 1);
+        dma16<0, STREAM>(base, __umul24(min(wave * TPW + tl, last), (uint32_t)krow_bytes) + ke_col[i % KEQ], kl + i * 1024);
       }
     }
   };
@@ -438,18 +470,41 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
   using NtEven = std::integral_constant<bool, SMODE == 1>;   // even steps (buffer 0)
   using NtOdd = std::integral_constant<bool, SMODE != 0>;    // odd steps (buffer 1)
 
-  auto compute = [&](int64_t tile, const char* ctile, char* ketile, int64_t next_tile, auto nt_next) {
+  auto compute = [&](int i_tile, int64_t tile, const char* ctile, char* ketile, int64_t next_tile, auto nt_next) {
+    // The elite query takes its value here, behind the wait for its loads: rearranged for the sums below ahead of the loop (two
+    // waves of 64 columns, whose lanes finalise four tokens), its registers were read before the data was in them.
+    if constexpr (TWO_R > 0) {
+#pragma unroll
+      for (int j = 0; j < TWO_R / 4; ++j) asm volatile("" : "+v"(qv[j]));
+    }
     // ---- partial scores over this wave's latent slice, two head halves
     f32x4 sd[2] = {(f32x4)(0.f), (f32x4)(0.f)};
     if (do_s) {
+      auto row_operand = [&](int ks) {
+        const int aoff = (L::HALF && ks == 2 * NCB) ? ah_off : (ks >> 1) * 1024 + ((ks & 1) ? a_c1 : a_c0);
+        return *reinterpret_cast<const bf16x8*>(ctile + aoff);
+      };
+      auto score = [&](int ks, const bf16x8& a) {
+        sd[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, Qb[ks][0]), sd[0], 0, 0, 0);
+        sd[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, Qb[ks][1]), sd[1], 0, 0, 0);
+      };
+      if constexpr (KS > 8) {
+        // wide slices, one wave per SIMD: the operands LOOK steps ahead, in this order, here and for the values (reads bounded to
+        // four at a time and the products behind them left the matrix cores idle in between: 13B 16 x 8192 183.0 -> 180.0)
+        constexpr int LOOK = 4;
+        bf16x8 a[LOOK];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (KS > 8 && ks % 4 == 0) asm volatile("" ::: "memory");   // wide slices: bound the operand look-ahead
-      const int aoff = (L::HALF && ks == 2 * NCB) ? ah_off : (ks >> 1) * 1024 + ((ks & 1) ? a_c1 : a_c0);
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(ctile + aoff);
-      sd[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, Qb[ks][0]), sd[0], 0, 0, 0);
-      sd[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, Qb[ks][1]), sd[1], 0, 0, 0);
-    }
+        for (int ks = 0; ks < LOOK; ++ks) a[ks] = row_operand(ks);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          score(ks, a[ks % LOOK]);
+          if (ks + LOOK < KS) a[ks % LOOK] = row_operand(ks + LOOK);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) score(ks, row_operand(ks));
+      }
     }
     // ---- stage 1: publish them as x1[slice][token][head]; lane holds tokens 4*q16 + v, head hh*16 + i16
     if (do_s) {
@@ -483,79 +538,153 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       issue_ke(next_tile, ketile, nt_next);
     }
-    // ---- stage 2: sum the NW partials in a fixed order, publish as x2[head][token]
+    auto rescale = [&](float alpha) {
+      if (__any(alpha != 1.f)) {
+        if (ACC_AGPR) {
+          // One wave per SIMD: the accumulator tiles are kept in the accumulation registers (AGPRs).
+          // Rescaling them as ordinary vector arithmetic would make the compiler hold every tile in
+          // VGPRs across the whole loop; the explicit moves pin them to AGPRs instead.
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const int tok = own_t0 + 2 * e;
+          for (int ct = 0; ct < CT; ++ct) {
 #pragma unroll
-      for (int w2 = 0; w2 < NW; ++w2)
-        if (!SEP || w2 < nwk) fin[e] += x1[(w2 * kTile + tok) * L::X1_ROW + n];
-      x2[n * L::X2_ROW + tok] = fin[e];
-    }
-    __syncthreads();
-    // ---- online softmax; lane = head n, tokens 8*g + j
-    float s[8];
-    {
-      const f32x4 lo = *reinterpret_cast<const f32x4*>(x2 + n * L::X2_ROW + 8 * g);
-      const f32x4 hi = *reinterpret_cast<const f32x4*>(x2 + n * L::X2_ROW + 8 * g + 4);
-      s[0] = lo[0]; s[1] = lo[1]; s[2] = lo[2]; s[3] = lo[3];
-      s[4] = hi[0]; s[5] = hi[1]; s[6] = hi[2]; s[7] = hi[3];
-    }
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      s[j] = (tile + 8 * g + j < t_end) ? s[j] : -INFINITY;
-      tmax = fmaxf(tmax, s[j]);
-    }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
-    // the reference maximum is raised only when a score exceeds it by more than the slack
-    const float m_new = (tmax > m_run + kRescaleSlack || m_run == -INFINITY) ? tmax : m_run;
-    const float alpha = exp2f(m_run - m_new);
-    float psum = 0.f;
-    bf16x8 P;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float pv = exp2f(s[j] - m_new);
-      psum += pv;
-      P[j] = (__bf16)pv;
-    }
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
-    if (__any(alpha != 1.f)) {
-      if (ACC_AGPR) {
-        // One wave per SIMD: the accumulator tiles are kept in the accumulation registers (AGPRs).
-        // Rescaling them as ordinary vector arithmetic would make the compiler hold every tile in
-        // VGPRs across the whole loop; the explicit moves pin them to AGPRs instead.
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-#pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            float y, z;
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(y) : "a"(uacc[ct][j]));
-            y *= alpha;
-            asm volatile("v_accvgpr_write_b32 %0, %1\n\ts_nop 2" : "=a"(z) : "v"(y));   // + wait states before an MFMA reads it
-            uacc[ct][j] = z;
+            for (int j = 0; j < 16; ++j) {
+              float y, z;
+              asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(y) : "a"(uacc[ct][j]));
+              y *= alpha;
+              asm volatile("v_accvgpr_write_b32 %0, %1\n\ts_nop 2" : "=a"(z) : "v"(y));   // + wait states before an MFMA reads it
+              uacc[ct][j] = z;
+            }
           }
-        }
-      } else {
+        } else {
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) uacc[ct] *= alpha;
+          for (int ct = 0; ct < CT; ++ct) uacc[ct] *= alpha;
+        }
       }
+    };
+    bf16x8 P;                                              // lane = head n, tokens 8*g + j
+    if constexpr (OWNER_P) {
+      // ---- stage 2: sum the NW partials in a fixed order: the scores of head n and this lane's tokens; their probabilities
+      //      against the maximum so far, published as P[head][token].  A score that exceeds that maximum by more than the slack
+      //      (and the first tile, which has none) leaves the tile's number in `raised`.
+      float s[EPL];
+      auto publish = [&]() {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+          const float pv = __builtin_amdgcn_exp2f(s[e] - m_run);
+          l_run += pv;
+          *reinterpret_cast<uint16_t*>(x2 + n * L::P_ROW + (own_t0 + 2 * e) * 2) = f32_to_bf16_bits(pv);
+        }
+      };
+      bool over = false;
+      const int rows = (int)min(t_end - tile, (int64_t)kTile);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        const int tok = own_t0 + 2 * e;
+#pragma unroll
+        for (int w2 = 0; w2 < NW; ++w2)
+          if (!SEP || w2 < nwk) fin[e] += x1[(w2 * kTile + tok) * L::X1_ROW + n];
+        s[e] = tok < rows ? fin[e] : -INFINITY;
+        over |= s[e] > m_run + kRescaleSlack;
+      }
+      const float l_old = l_run;
+      // (for the maxima below: where this lane alone has read)
+      auto show = [&]() {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) x1[(own_t0 + 2 * e) * L::X1_ROW + n] = s[e];
+      };
+      if (i_tile > 0) {
+        publish();
+        if (over) *raised = i_tile;
+      } else {
+        show();
+      }
+      __syncthreads();
+      P = *reinterpret_cast<const bf16x8*>(x2 + n * L::P_ROW + 16 * g);         // lane = head n, tokens 8*g + j
+      if (__builtin_amdgcn_readfirstlane(*raised) == i_tile) {
+        // the maximum of every head over the tile
+        if (i_tile > 0) {
+          show();
+          __syncthreads();
+        }
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < kTile; ++j) tmax = fmaxf(tmax, x1[j * L::X1_ROW + n]);
+        const float m_new = (tmax > m_run + kRescaleSlack || m_run == -INFINITY) ? tmax : m_run;
+        const float alpha = exp2f(m_run - m_new);
+        l_run = l_old * alpha;
+        m_run = m_new;
+        publish();
+        rescale(alpha);
+        __syncthreads();
+        P = *reinterpret_cast<const bf16x8*>(x2 + n * L::P_ROW + 16 * g);
+      }
+    } else {
+      float* xs = reinterpret_cast<float*>(x2);
+      // ---- stage 2: sum the NW partials in a fixed order, publish as x2[head][token]
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        const int tok = own_t0 + 2 * e;
+#pragma unroll
+        for (int w2 = 0; w2 < NW; ++w2)
+          if (!SEP || w2 < nwk) fin[e] += x1[(w2 * kTile + tok) * L::X1_ROW + n];
+        xs[n * L::X2_ROW + tok] = fin[e];
+      }
+      __syncthreads();
+      // ---- online softmax; lane = head n, tokens 8*g + j
+      float s[8];
+      {
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(xs + n * L::X2_ROW + 8 * g);
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(xs + n * L::X2_ROW + 8 * g + 4);
+        s[0] = lo[0]; s[1] = lo[1]; s[2] = lo[2]; s[3] = lo[3];
+        s[4] = hi[0]; s[5] = hi[1]; s[6] = hi[2]; s[7] = hi[3];
+      }
+      float tmax = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        s[j] = (tile + 8 * g + j < t_end) ? s[j] : -INFINITY;
+        tmax = fmaxf(tmax, s[j]);
+      }
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+      // the reference maximum is raised only when a score exceeds it by more than the slack
+      const float m_new = (tmax > m_run + kRescaleSlack || m_run == -INFINITY) ? tmax : m_run;
+      const float alpha = exp2f(m_run - m_new);
+      float psum = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float pv = exp2f(s[j] - m_new);
+        psum += pv;
+        P[j] = (__bf16)pv;
+      }
+      l_run = l_run * alpha + psum;
+      m_run = m_new;
+      rescale(alpha);
     }
     // ---- latent accumulation: U^T += C^T P^T, the tile read transposed from LDS
     if (do_v) {
+      auto col_operand = [&](int ct) {
+        const bool in_half = L::HALF && ct == 2 * NCB;
+        const char* trp = ctile + (in_half ? 0 : (ct >> 1) * 1024);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_s16x4_t*)(trp + (in_half ? trh_off[0] : tr_off[0][ct & 1])));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_s16x4_t*)(trp + (in_half ? trh_off[1] : tr_off[1][ct & 1])));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      };
+      if constexpr (CT > 8) {
+        constexpr int LOOK = 3;
+        bf16x8 a[LOOK];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      if (CT > 8 && ct % 4 == 0) asm volatile("" ::: "memory");
-      const bool in_half = L::HALF && ct == 2 * NCB;
-      const char* trp = ctile + (in_half ? 0 : (ct >> 1) * 1024);
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (lds_s16x4_t*)(trp + (in_half ? trh_off[0] : tr_off[0][ct & 1])));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (lds_s16x4_t*)(trp + (in_half ? trh_off[1] : tr_off[1][ct & 1])));
-      const s16x8 a16 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      uacc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a16), P, uacc[ct], 0, 0, 0);
-    }
+        for (int ct = 0; ct < LOOK; ++ct) a[ct] = col_operand(ct);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          uacc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ct % LOOK], P, uacc[ct], 0, 0, 0);
+          if (ct + LOOK < CT) a[ct % LOOK] = col_operand(ct + LOOK);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) uacc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_operand(ct), P, uacc[ct], 0, 0, 0);
+      }
     }
   };
 
@@ -643,7 +772,7 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     const int64_t ta = tile_at(i), tb = tile_at(i + 1), tc = tile_at(i + 2), td = tile_at(i + 3);
     if (tb < t_end) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IN_FLIGHT) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    compute(ta, ctile0, ketile0, tb, NtOdd{});
+    compute(i, ta, ctile0, ketile0, tb, NtOdd{});
     if (tb >= t_end) break;
     if (tc < t_end) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // buffer 0 was last read one tile ago
@@ -652,7 +781,7 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    compute(tb, ctile1, ketile1, tc, NtEven{});
+    compute(i + 1, tb, ctile1, ketile1, tc, NtEven{});
     if (td < t_end) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       issue(td, ctile1, ketile1, NtOdd{});
@@ -660,16 +789,20 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
   }
 
   // ---- write this split's partial (m, l, U)
-  const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
-  if (wave == 0 && g == 0) {
-    p.part_m[pidx + n] = m_run;
-    p.part_l[pidx + n] = head_ok ? l_tot : 0.f;
-  }
+  l_run += __shfl_xor(l_run, 32, kWave);
+  if (OWNER_P && g == 0) x1[wave * 32 + n] = l_run;         // a wave has the sums of the tokens it finalised
   // U goes out head-major in bf16.  The accumulators hold, per lane, one head and scattered
   // columns; they are transposed through LDS (free now) so that global stores are row-contiguous.
   constexpr int TSTR = DC_W * 2 + 16;                       // bytes per head row in LDS
-  static_assert(NW * 32 * TSTR <= L::LDS_BYTES, "transpose staging exceeds the LDS allocation");
+  static_assert(NW * 32 * TSTR <= L::X1_OFF, "transpose staging reaches the sums");
   __syncthreads();                                          // every wave is done with its tile slices
+  if (wave == 0 && g == 0) {
+    float l_tot = OWNER_P ? 0.f : l_run;
+#pragma unroll
+    for (int w2 = 0; OWNER_P && w2 < NW; ++w2) l_tot += x1[w2 * 32 + n];
+    p.part_m[pidx + n] = m_run;
+    p.part_l[pidx + n] = head_ok ? l_tot : 0.f;
+  }
   char* tt = smem + wave * (32 * TSTR);
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
