@@ -53,13 +53,16 @@ def scan(path: str):
     for name, lines in kernels.items():
         first_mfma = next((i for i, ln in enumerate(lines) if ln.strip().startswith("v_mfma")), len(lines))
         live = set()
+        by_hand = False
         for ln in lines[:first_mfma]:
             s = ln.strip()
+            if s.startswith((";;#ASMSTART", ";;#ASMEND")):
+                by_hand = s.startswith(";;#ASMSTART")
             if not s or s[0] in ";.":
                 continue
             op = s.split()[0]
             ops = s[len(op):].split(",")
-            if op == "global_load_dwordx4":          # the hand-issued query loads (tile loads are global_load_lds_*)
+            if op == "global_load_dwordx4" and by_hand:   # the query's (tile loads are global_load_lds_*; the compiler waits for its own)
                 live |= _regs(ops[0])
             elif op.startswith(HARD) or op.startswith(SOFT):
                 src = set().union(*[_regs(t) for t in (ops if op.startswith("scratch_store") else ops[1:])])

@@ -185,30 +185,34 @@ constexpr float kRescaleSlack = 8.f;
 // before they request anything from the planes: the tile loads then bring the row in like any other.
 template <int NT, int TWO_R>
 __device__ __forceinline__ void store_new_token_row(const AttnMfmaParams& p, int b, int64_t slot) {
-  const int tid = threadIdx.x;
+  constexpr int V = 4;                                     // elements of a thread at a time: one pass of the work-group at 2048 of them
+  typedef __attribute__((ext_vector_type(V))) float fv;    // (two: a step of 256 tokens 28.7 instead of 28.2 us, of 64 x 2048 at 7B
+  typedef __attribute__((ext_vector_type(V))) __bf16 bv;   // 12.5 % 78.0 instead of 77.1, of 3 x 5001 39.4 instead of 38.9)
   const int NE = p.n_h * TWO_R, N = NE + p.d_c;
   if (slot < 0 || slot >= p.plane_rows) return;            // a token without a row is not stored
-  for (int pr = tid; pr < N / 2; pr += NT) {
-    const int n = 2 * pr;
-    float a0 = 0.f, a1 = 0.f;
+  for (int n = V * (int)threadIdx.x; n < N; n += V * NT) {
+    fv a = (fv)(0.f);
     for (int s0 = 0; s0 < p.fr_ks; s0 += 8) {              // eight independent loads in flight; split order kept
-      float2 v[8];
+      fv v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         v[u] = (s0 + u < p.fr_ks)
-                   ? *reinterpret_cast<const float2*>(p.fr_partial + ((int64_t)(s0 + u) * p.batch + b) * p.fr_stride + n)
-                   : make_float2(0.f, 0.f);
+                   ? *reinterpret_cast<const fv*>(p.fr_partial + ((int64_t)(s0 + u) * p.batch + b) * p.fr_stride + n)
+                   : (fv)(0.f);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) { a0 += v[u].x; a1 += v[u].y; }
+      for (int u = 0; u < 8; ++u) a += v[u];
     }
-    if (n < NE) {                                          // pair index pr = h * r + j
-      const float2 sc = p.fr_sincos[(int64_t)b * (NE / 2) + pr];
-      const float o0 = a0 * sc.y - a1 * sc.x, o1 = a1 * sc.y + a0 * sc.x;
-      a0 = o0; a1 = o1;
+    if (n < NE) {                                          // pairs n / 2 .. of index h * r + j
+      const fv sc = *reinterpret_cast<const fv*>(p.fr_sincos + (int64_t)b * (NE / 2) + n / 2);
+#pragma unroll
+      for (int e = 0; e < V; e += 2) {
+        const float o0 = a[e] * sc[e + 1] - a[e + 1] * sc[e], o1 = a[e + 1] * sc[e + 1] + a[e] * sc[e];
+        a[e] = o0; a[e + 1] = o1;
+      }
     }
-    const uint32_t pk = pack_bf16x2(a0, a1);
-    if (n < NE) *reinterpret_cast<uint32_t*>(p.fr_ke_out + slot * NE + n) = pk;
-    else *reinterpret_cast<uint32_t*>(p.fr_c_out + slot * (int64_t)p.d_c + (n - NE)) = pk;
+    const bv row = __builtin_convertvector(a, bv);
+    if (n < NE) *reinterpret_cast<bv*>(p.fr_ke_out + slot * NE + n) = row;
+    else *reinterpret_cast<bv*>(p.fr_c_out + slot * (int64_t)p.d_c + (n - NE)) = row;
   }
 }
 
