@@ -421,8 +421,15 @@ __global__ __launch_bounds__(kTtWaves * 64) void attn_tiled_kernel(
 
 // ---- merge of the splits ----
 // Work-group = (256 latent columns, head, query row): four groups of 64 lanes take every fourth split, 16 bytes per lane.
-// Bound by the split accumulators' bytes.  
-// 63 splits of two rows, 7B 25 %: 9.3 us for 25 MB; with the up-projection below 18.5 (merge_upproj_generic_kernel 291).
+// Bound by the split accumulators' bytes where there are many rows, by the trips to memory where there are few: with up to two
+// work-groups a compute unit (kTmFewGroups) AHEAD accumulators of every lane are requested before the weights of the splits
+// are formed, and one for every one that is used from then on.  A decode step, us, without / with: 1 x 1000 tokens (192
+// work-groups, 63 splits) 50.2 / 47.5, 1 x 8000 (128 splits) 81.2 / 75.3, 2 x 1000 (384) 56.1 / 55.3, 2 x 3000 at 12.5 % 43.6 /
+// 40.5.  With more work-groups the registers cost more than the trips: 4 x 300 (768) 53.4 / 55.0, 64 x 1000 389 / 410.
+// 63 splits of two rows, 7B 25 %: 8.1 us for 25 MB (9.3 without AHEAD; merge_upproj_generic_kernel, with the up-projection below, 291).
+constexpr int kTmAhead = 16, kTmFewGroups = 2 * kTtComputeUnits;
+
+template <int AHEAD>
 __global__ __launch_bounds__(256) void merge_tiled_kernel(const float* __restrict__ part_m,
                                                           const float* __restrict__ part_l, const float* part_u,
                                                           float* ubar, int ubar_rows, int n_h, int d_u, int n_splits) {
@@ -430,18 +437,31 @@ __global__ __launch_bounds__(256) void merge_tiled_kernel(const float* __restric
   tf_f32x4* sums = reinterpret_cast<tf_f32x4*>(smem);      // [4][64]
   float* red = smem + 1024;                                // [8]
   float* w = red + 8;                                      // [n_splits]
-  const int h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t base = (int64_t)b * n_splits * n_h + h;
-  float m = -INFINITY;
-  for (int s = tid; s < n_splits; s += 256) m = fmaxf(m, part_m[base + (int64_t)s * n_h]);
+  const int k = blockIdx.x * 256 + lane * 4;
+  // the first 256 maxima and sums, then the first accumulators (what lies in the place of an empty split's is not used)
+  float m = -INFINITY, l0 = 0.f;
+  if (tid < n_splits) {
+    m = part_m[base + (int64_t)tid * n_h];
+    l0 = part_l[base + (int64_t)tid * n_h];
+  }
+  const float m0 = m;
+  tf_f32x4 u[AHEAD > 0 ? AHEAD : 1];
+  const float* pu = part_u + base * d_u + min(k, d_u - 4);
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i)
+    if (wave + 4 * i < n_splits) u[i] = ld4(pu + (int64_t)(wave + 4 * i) * n_h * d_u);
+  for (int s = tid + 256; s < n_splits; s += 256) m = fmaxf(m, part_m[base + (int64_t)s * n_h]);
   m = wave_max(m);
   if (lane == 0) red[wave] = m;
   __syncthreads();
   m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   float lsum = 0.f;
   for (int s = tid; s < n_splits; s += 256) {
-    const float ls = part_l[base + (int64_t)s * n_h];
-    const float ws = ls > 0.f ? exp2f(part_m[base + (int64_t)s * n_h] - m) : 0.f;
+    const float ls = s == tid ? l0 : part_l[base + (int64_t)s * n_h];
+    const float ws = ls > 0.f ? exp2f((s == tid ? m0 : part_m[base + (int64_t)s * n_h]) - m) : 0.f;
     w[s] = ws;
     lsum += ws * ls;
   }
@@ -449,16 +469,30 @@ __global__ __launch_bounds__(256) void merge_tiled_kernel(const float* __restric
   if (lane == 0) red[4 + wave] = lsum;
   __syncthreads();
   const float L = (red[4] + red[5]) + (red[6] + red[7]);
-  const int k = blockIdx.x * 256 + lane * 4;
   tf_f32x4 a = (tf_f32x4)(0.f);
-  if (k < d_u) {
+  if constexpr (AHEAD > 0) {
+    for (int s0 = wave; s0 < n_splits; s0 += 4 * AHEAD) {
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+        const int s = s0 + 4 * i, next = s + 4 * AHEAD;
+        if (s < n_splits) {
+          const float ws = w[s];
+          if (ws != 0.f) {                                 // wave-uniform; an empty split has left no accumulators
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = fmaf(ws, u[i][e], a[e]);
+          }
+        }
+        if (next < n_splits) u[i] = ld4(pu + (int64_t)next * n_h * d_u);
+      }
+    }
+  } else if (k < d_u) {
 #pragma unroll 8
     for (int s = wave; s < n_splits; s += 4) {
       const float ws = w[s];
-      if (ws != 0.f) {                                     // wave-uniform; an empty split has left no accumulators
-        const tf_f32x4 u = ld4(part_u + (base + (int64_t)s * n_h) * d_u + k);
+      if (ws != 0.f) {
+        const tf_f32x4 us = ld4(pu + (int64_t)s * n_h * d_u);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a[e] = fmaf(ws, u[e], a[e]);
+        for (int e = 0; e < 4; ++e) a[e] = fmaf(ws, us[e], a[e]);
       }
     }
   }
@@ -588,8 +622,10 @@ static hipError_t launch_decode_tiled_t(const DecodeArgs& a, const DecodePlan& p
     if (e != hipSuccess) return e;
   }
   if (a.stages & 4) {
-    merge_tiled_kernel<<<dim3((p.d_u + 255) / 256, n_h, B), 256, sizeof(float) * (size_t)(1024 + 8 + p.n_splits), stream>>>(
-        pm, pl, pu, ubar, p.ubar_rows, n_h, p.d_u, p.n_splits);
+    const dim3 grid((p.d_u + 255) / 256, n_h, B);
+    const auto merge = (int64_t)grid.x * n_h * B <= kTmFewGroups ? merge_tiled_kernel<kTmAhead> : merge_tiled_kernel<0>;
+    merge<<<grid, 256, sizeof(float) * (size_t)(1024 + 8 + p.n_splits), stream>>>(pm, pl, pu, ubar, p.ubar_rows, n_h, p.d_u,
+                                                                                 p.n_splits);
 #define EKV_UP(BT)                                                                                              \
   {                                                                                                             \
     static LdsLimit limit;                                                                                      \

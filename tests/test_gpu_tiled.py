@@ -72,6 +72,29 @@ def test_tiled_decode_matches_oracle(name):
         assert orc.max_abs_rel(host64(out), ref) <= TOL[dt], ns
 
 
+# the merge reads ahead in batches of 64 splits for up to 512 work-groups (272 columns: two a head), and not for more; empty
+# splits leave the workspace as it was (filled with NaN)
+@pytest.mark.parametrize("B", [1, 64, 65])
+@pytest.mark.parametrize("ns", [3, 63, 64, 65, 300])
+def test_merge_of_few_and_many_rows(B, ns):
+    n_h, d_h, r, d_c, S = 4, 32, 2, 272, 90
+    dims = ekv.make_dims(64, n_h, d_h, r, d_c, "fp32")
+    rng = np.random.default_rng(synth.SEED_BASE + 760 + ns)
+    idx = synth.draw_elite_idx(rng, n_h, d_h, r)
+    n = lambda *s, std=1.0: dev(rng.standard_normal(s) * std, "fp32")
+    q, W_uk, W_uv = n(B, n_h, d_h), n(d_c, n_h, d_h - 2 * r, std=d_c ** -0.5), n(d_c, n_h, d_h, std=d_c ** -0.5)
+    ke, c = n(B * S, n_h, 2 * r), n(B * S, d_c)
+    lens = np.array([S] + [int(v) for v in rng.integers(0, S + 1, B - 1)])
+    q_pos = np.maximum(lens - 1, 0)
+    out = torch.full((B, n_h, d_h), float("nan"), device=DEV)
+    ws = torch.full((ekv.elitekv_decode_workspace_bytes(dims, B, S, ns),), 0xFF, dtype=torch.uint8, device=DEV)
+    ekv.elitekv_decode_attn(dims, q, i32(q_pos), i32(lens), S, S, W_uk, W_uv, i32(idx), ke, c, out, ws, n_splits=ns)
+    torch.cuda.synchronize()
+    ref = orc.decode_attn(host64(q), q_pos, host64(ke).reshape(B, S, n_h, 2 * r), host64(c).reshape(B, S, d_c), lens,
+                          host64(W_uk), host64(W_uv), idx, d_h, 10000.0)
+    assert orc.max_abs_rel(host64(out), ref) <= TOL["fp32"]
+
+
 @pytest.mark.parametrize("name", ["one_block", "seventeen_blocks_17_heads", "all_elite", "7b", "separated",
                                   "separated_wide_values"])
 @pytest.mark.parametrize("T", [1, 2, 3, 5, 9, 257])     # token tiles of 1, 2, 4 and 8; the serial kernel beyond 256
