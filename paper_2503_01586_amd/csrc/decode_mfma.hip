@@ -165,11 +165,15 @@ __device__ __forceinline__ void dma16_blocks(const void* base, uint32_t voff, ui
     dma16_blocks<COUNT, STREAM, CB + 1>(base, voff, lds_base);
   }
 }
-// an address that is the same in every lane, in scalar registers (64-bit comparisons leave it in vector registers)
+// An address that is the same in every lane, in scalar registers (64-bit comparisons leave it in vector registers), ready to be a
+// base of dma16: a vector-memory instruction may read a scalar register five wait states after a vector instruction (the
+// readfirstlanes here) wrote it, not before, and for one in inline assembly the compiler does not see to that.
 __device__ __forceinline__ const char* uniform(const char* p) {
   const uint64_t v = reinterpret_cast<uint64_t>(p);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+  const char* base = reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+  asm volatile("s_nop 4" : "+s"(base));
+  return base;
 }
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;

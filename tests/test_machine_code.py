@@ -1,0 +1,54 @@
+"""The built library's machine code keeps the rules that the compiler does not see to in inline assembly
+(paper_2503_01586_amd/check_machine_code.py), and the scan finds what breaks them."""
+import pytest
+
+from paper_2503_01586_amd import check_machine_code as mc
+
+
+def code(*lines):
+    """Instructions 4 bytes apart; a branch is written with the number of the line it goes to."""
+    out = []
+    for i, line in enumerate(lines):
+        op, _, text = line.partition(" ")
+        word = 0
+        if op.startswith(("s_branch", "s_cbranch")):
+            word = (int(text) - i - 1) & 0xffff
+        out.append(mc.Instruction(op, text, 4 * i, "%08X" % word))
+    return out
+
+
+def findings(scan, *lines):
+    return [f.address // 4 for f in scan.run("k", *mc.blocks_of(code(*lines)))]
+
+
+def test_scalar_registers_that_a_vector_instruction_wrote():
+    scan = mc.VectorWrittenScalars()
+    write, load, other = "v_readfirstlane_b32 s3, v1", "global_load_lds_dwordx4 v5, s[2:3]", "v_mov_b32_e32 v9, v8"
+    assert findings(scan, write, load, "s_endpgm ") == [1]
+    assert findings(scan, write, "s_nop 3", load, "s_endpgm ") == [2]
+    assert findings(scan, write, "s_nop 4", load, "s_endpgm ") == []
+    assert findings(scan, write, "s_nop 3", other, load, "s_endpgm ") == []
+    assert findings(scan, write, "s_cmp_eq_u32 s3, 0", load, "s_endpgm ") == [2]        # read, not written anew
+    assert findings(scan, write, "s_mov_b32 s3, s9", load, "s_endpgm ") == []
+    assert findings(scan, write, "s_nop 4", "global_load_dword v1, v2, s[4:5]", load, "s_endpgm ") == []
+    assert findings(scan, "v_cmp_lt_u32_e64 s[2:3], v1, v2", load, "s_endpgm ") == [1]
+    assert findings(scan, "v_add_co_u32_e32 v1, vcc, v1, v2", "buffer_load_dword v1, v2, s[4:7], vcc_lo offen", "s_endpgm ") == [1]
+    # the shorter of two ways to the load, and the way around a loop
+    assert findings(scan, write, "s_cbranch_scc1 3", "s_nop 4", load, "s_endpgm ") == [3]
+    assert findings(scan, "s_nop 0", load, other, write, "s_cbranch_scc1 1", "s_endpgm ") == [1]
+
+
+@pytest.fixture(scope="module")
+def library():
+    return mc.check()
+
+
+def test_library_is_scanned(library):
+    kernels, _ = library
+    assert kernels >= 300
+
+
+@pytest.mark.parametrize("rule", [s.rule for s in mc.SCANS])
+def test_no_findings(library, rule):
+    found = [f for f in library[1] if f.rule == rule]
+    assert not found, "%d findings, the first: %s" % (len(found), found[0])
