@@ -7,6 +7,8 @@ whatever the compiler made of the sources, whoever wrote the instruction:
 
   sgpr   a vector-memory instruction that reads a scalar register (an address, a buffer descriptor, an offset) fewer than five wait
          states after a vector instruction wrote it (v_readfirstlane and the like) may use the register's old value
+  m0     a direct-to-LDS load right behind the write of M0, which holds its place in the LDS, may go to the place before it; one
+         wait state must lie between
 
     python -m paper_2503_01586_amd.check_machine_code [libelitekv.so]
 
@@ -27,10 +29,12 @@ LIB_PATH = os.path.join(PKG_DIR, "libelitekv.so")
 OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
 
 SGPR_WAIT = 5
+M0_WAIT = 1
 MEMORY = ("global_", "buffer_", "flat_", "scratch_")
 # registers as integers: v0.. from 0, a0.. from 1000, s0.. from 2000, then the named ones
 BASE = {"v": 0, "a": 1000, "s": 2000}
 NAMED = {"vcc": (3000, 3001), "vcc_lo": (3000,), "vcc_hi": (3001,), "m0": (3002,)}
+M0 = NAMED["m0"][0]
 _REG = re.compile(r"\b(?:([vas])(?:(\d+)|\[(\d+):(\d+)\])|(vcc_lo|vcc_hi|vcc|m0))(?![\w\[])")
 _CODE = re.compile(r"^\t(\S+)\s*(.*?)\s*// ([0-9A-F]+): ([0-9A-F ]+)")
 _LABEL = re.compile(r"^[0-9a-f]+ <([^>]+)>:")
@@ -192,7 +196,21 @@ class VectorWrittenScalars(Scan):
         return ins.operands[0] if ins.op.startswith("s_") and not ins.op.startswith(("s_cmp", "s_bitcmp", "s_cbranch")) else ()
 
 
-SCANS = (VectorWrittenScalars(),)
+class LdsLoadsBehindM0(Scan):
+    def __init__(self):
+        super().__init__("m0", M0_WAIT, "reads M0 %%d wait states after it was written (%d needed)" % M0_WAIT)
+
+    def reads(self, ins):
+        return (M0,) if ins.memory and ("_load_lds_" in ins.op or ins.text.endswith(" lds")) else ()
+
+    def writes(self, ins):
+        return (M0,) if M0 in ins.operands[0] and not ins.op.startswith(("s_cmp", "s_bitcmp")) else ()
+
+    def settled(self, ins):
+        return ()
+
+
+SCANS = (VectorWrittenScalars(), LdsLoadsBehindM0())
 
 
 def check(lib: str = LIB_PATH, scans=SCANS):

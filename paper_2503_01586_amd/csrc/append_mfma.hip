@@ -309,8 +309,9 @@ __device__ __forceinline__ int gd_swz8(int row) { return ((row & 3) << 1) | ((ro
 // rows r, r+4, r+8, r+12 that share a 64-byte bank window take four different pieces
 __device__ __forceinline__ int gd_swz4(int row) { return (row >> 2) & 3; }
 
+// (M0 is read one wait state after its write: the s_nop, which the compiler does not put into inline assembly)
 __device__ __forceinline__ void gd_dma16(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
 }
 
 // WN = 32-token tiles per wave, WNW = waves along the tokens, CM = waves along the columns (64 columns each)

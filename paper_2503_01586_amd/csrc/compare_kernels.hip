@@ -237,11 +237,13 @@ __global__ __launch_bounds__(kStreamThreads) void stream_read_lds_kernel(const c
   for (size_t g = 0; g < groups; ++g) {
     const uint32_t b = base + (uint32_t)(g & 1) * 8192;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < 8; ++u) {                            // (M0 is read one wait state after its write: the s_nop)
       if (NT)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(b + u * 1024), "v"(p + u * 1024) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                     : : "s"(b + u * 1024), "v"(p + u * 1024) : "memory", "m0");
       else
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(b + u * 1024), "v"(p + u * 1024) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                     : : "s"(b + u * 1024), "v"(p + u * 1024) : "memory", "m0");
     }
     asm volatile("s_waitcnt vmcnt(8)" ::: "memory");         // the group before this one has landed
     p += 8192;

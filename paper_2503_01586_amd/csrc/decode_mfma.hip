@@ -139,7 +139,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // instruction's offset counts on both sides (M0 is set to as much less), so that loads of neighbouring columns share one
 // register of lane offsets and the rows' base stays in scalar registers: with an address per load and lane they took two vector
 // instructions each (13B 16 x 8192 186.9 -> 184.6 us a step, 4 x 5 drafted over 4096 tokens 81.2 -> 80.1).  Issued through inline assembly so that the waits on these loads
-// stay entirely under the kernel's control (vmcnt counting, see the tile loop).
+// stay entirely under the kernel's control (vmcnt counting, see the tile loop).  M0 is read one wait state after its write, not
+// before: the s_nop, which the compiler does not put into inline assembly.
 // STREAM marks the load non-temporal: cache rows that are read once per step stream from HBM
 // about 15 % faster that way (a plain read of 1 GiB through these loads: 6.0 TB/s, marked: 6.9 TB/s).
 // Rows that a second work-group is about to re-read from the L2 (head-group pairs) are loaded unmarked.
@@ -147,12 +148,12 @@ template <int OFF, bool STREAM>
 __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_base) {
   static_assert(OFF >= 0 && OFF < 4096, "outside the instruction's offset");
   if constexpr (STREAM)
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt"
                  :
                  : "s"(lds_base - OFF), "v"(voff), "s"(base), "n"(OFF)
                  : "memory", "m0");
   else
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
                  :
                  : "s"(lds_base - OFF), "v"(voff), "s"(base), "n"(OFF)
                  : "memory", "m0");

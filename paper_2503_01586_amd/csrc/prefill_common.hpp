@@ -57,8 +57,9 @@ __host__ __device__ inline int pf_block_tiles(int64_t S, int64_t T, int i, int b
 // 64-byte windows
 __device__ __forceinline__ int pf_swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
 
+// (M0 is read one wait state after its write: the s_nop, which the compiler does not put into inline assembly)
 __device__ __forceinline__ void pf_dma16(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
 }
 
 __device__ __forceinline__ uint32_t pf_pack2(float lo, float hi) {

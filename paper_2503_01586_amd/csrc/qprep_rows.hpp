@@ -114,7 +114,8 @@ __device__ __forceinline__ void qprep_rows_body(const QprepRowsParams& P, const 
     for (int j = wave; j * 64 < total; j += 4) {
       const bool real = cc < nchunk && r0 + rr < rows_total && m < total;
       const bf16_t* src = W_uk + (real ? (r0 + rr) * nd + cc * 8 : 0);        // padding pieces fetch piece 0
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+      // (M0 is read one wait state after its write: the s_nop, which the compiler does not put into inline assembly)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                    :
                    : "s"(__builtin_amdgcn_readfirstlane(lbase + j * 1024)), "v"(src)
                    : "memory", "m0");

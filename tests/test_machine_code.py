@@ -38,6 +38,16 @@ def test_scalar_registers_that_a_vector_instruction_wrote():
     assert findings(scan, "s_nop 0", load, other, write, "s_cbranch_scc1 1", "s_endpgm ") == [1]
 
 
+def test_direct_loads_behind_a_write_of_m0():
+    scan = mc.LdsLoadsBehindM0()
+    write, load = "s_mov_b32 m0, s29", "global_load_lds_dwordx4 v1, s[50:51]"
+    assert findings(scan, write, load, "s_endpgm ") == [1]
+    assert findings(scan, write, "buffer_load_dword v1, s[4:7], 0 offen lds", "s_endpgm ") == [1]
+    assert findings(scan, write, "s_nop 0", load, "s_endpgm ") == []
+    assert findings(scan, write, "s_mov_b32 s4, s29", load, "s_endpgm ") == []
+    assert findings(scan, write, "global_load_dword v1, v2, s[4:5]", load, load, "s_endpgm ") == []
+
+
 @pytest.fixture(scope="module")
 def library():
     return mc.check()
