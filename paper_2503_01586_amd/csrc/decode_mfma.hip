@@ -414,7 +414,7 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
 #pragma unroll
   for (int i = 0; i < KEQ; ++i) {
     const int ch = (i * 64 + lane) % (TWO_R > 0 ? L::KE_CPT : 1), kch = TWO_R > 0 ? KCH : 1;
-    ke_col[i] = (min(hg * 32 + ch / kch, p.n_h - 1) * kch + ch % kch) * 16;
+    ke_col[i] = (uint32_t)(min(hg * 32 + ch / kch, p.n_h - 1) * kch + ch % kch) * 16;
   }
 
   // LDS read offsets (inside a wave's tile slice) that do not change from tile to tile.
@@ -453,6 +453,7 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     const uint32_t cl = __builtin_amdgcn_readfirstlane(lds_addr(ctile));
     const char* base = uniform(reinterpret_cast<const char*>(p.c_plane) + (row0 + tile_t0) * crow_bytes);
     const int last = (int)min(t_end - 1 - tile_t0, (int64_t)(kTile - 1));
+    static_assert(NW * DC_W * 2 < (1 << 24), "a latent row passes __umul24");
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
       dma16_blocks<NCB, STREAM>(base, __umul24(min(rb * 8 + ld_row, last), (uint32_t)crow_bytes) + c_col, cl + rb * NCB * 1024);
@@ -465,10 +466,12 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
       const uint32_t kl = __builtin_amdgcn_readfirstlane(lds_addr(ketile));
       const char* base = uniform(reinterpret_cast<const char*>(p.ke_plane) + (row0 + tile_t0) * krow_bytes);
       const int last = (int)min(t_end - 1 - tile_t0, (int64_t)(kTile - 1));
+      // (32-bit products: rows of 131072 heads with 64 values each pass 2^24 bytes; the grid has room for 65535 head groups)
+      static_assert((uint64_t)kTile * 65535 * 32 * TWO_R * 2 <= UINT32_MAX, "a tile's elite keys pass a lane's offset");
 #pragma unroll
       for (int i = 0; i < L::NKE; ++i) {
         const int tl = min((i * 64 + lane) / L::KE_CPT, TPW - 1);
-        dma16<0, STREAM>(base, __umul24(min(wave * TPW + tl, last), (uint32_t)krow_bytes) + ke_col[i % KEQ], kl + i * 1024);
+        dma16<0, STREAM>(base, (uint32_t)min(wave * TPW + tl, last) * (uint32_t)krow_bytes + ke_col[i % KEQ], kl + i * 1024);
       }
     }
   };
