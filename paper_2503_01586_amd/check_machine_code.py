@@ -9,6 +9,7 @@ whatever the compiler made of the sources, whoever wrote the instruction:
          states after a vector instruction wrote it (v_readfirstlane and the like) may use the register's old value
   m0     a direct-to-LDS load right behind the write of M0, which holds its place in the LDS, may go to the place before it; one
          wait state must lie between
+  query  a register of the split attention's query is read, or given to something else, before the load that fills it has landed
 
     python -m paper_2503_01586_amd.check_machine_code [libelitekv.so]
 
@@ -30,6 +31,7 @@ OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", 
 
 SGPR_WAIT = 5
 M0_WAIT = 1
+MOST_BEHIND = 63                                           # a wave has no more than 63 vector-memory operations under way
 MEMORY = ("global_", "buffer_", "flat_", "scratch_")
 # registers as integers: v0.. from 0, a0.. from 1000, s0.. from 2000, then the named ones
 BASE = {"v": 0, "a": 1000, "s": 2000}
@@ -37,6 +39,7 @@ NAMED = {"vcc": (3000, 3001), "vcc_lo": (3000,), "vcc_hi": (3001,), "m0": (3002,
 M0 = NAMED["m0"][0]
 _REG = re.compile(r"\b(?:([vas])(?:(\d+)|\[(\d+):(\d+)\])|(vcc_lo|vcc_hi|vcc|m0))(?![\w\[])")
 _CODE = re.compile(r"^\t(\S+)\s*(.*?)\s*// ([0-9A-F]+): ([0-9A-F ]+)")
+_VMCNT = re.compile(r"vmcnt\((\d+)\)")
 _LABEL = re.compile(r"^[0-9a-f]+ <([^>]+)>:")
 
 Finding = collections.namedtuple("Finding", "rule kernel address text what")
@@ -138,6 +141,14 @@ class Scan:
     def __init__(self, rule, wait, what):
         self.rule, self.wait, self.what = rule, wait, what
 
+    def merge(self, old, state):
+        """Takes `state` into the entry state `old` of a block; whether that changed it."""
+        changed = False
+        for r, n in state.items():
+            if old.get(r, self.wait) > n:
+                old[r], changed = n, True
+        return changed
+
     def run(self, kernel, blocks, follow):
         entry = [None] * len(blocks)
         entry[0] = {}
@@ -151,12 +162,7 @@ class Scan:
                 if entry[j] is None:
                     entry[j] = dict(state)
                     work.append(j)
-                    continue
-                old, changed = entry[j], False
-                for r, n in state.items():
-                    if old.get(r, self.wait) > n:
-                        old[r], changed = n, True
-                if changed and j not in work:
+                elif self.merge(entry[j], state) and j not in work:
                     work.append(j)
         findings = []
         for i, b in enumerate(blocks):
@@ -210,7 +216,72 @@ class LdsLoadsBehindM0(Scan):
         return ()
 
 
-SCANS = (VectorWrittenScalars(), LdsLoadsBehindM0())
+class QueryInFlight:
+    """The split attention issues its query loads ahead of the first tile's wait; until then nothing may touch their registers:
+    a read finds the old value, and what is written there (the registers are free wherever the query is not used, in
+    an empty split) is overwritten when the load lands.  Followed from the blocks that load the query to the first matrix
+    product or to the wait that covers a load: vmcnt(n) does where n other operations were issued behind it, for they complete in
+    order (the most of all the ways that lead there: which tiles were requested is not followed).  A way that leads from one
+    such block to another is left out: a launch loads the query once."""
+    rule, what = "query", "uses a register that a load of the query has yet to fill"
+
+    def run(self, kernel, blocks, follow):
+        if "attn_mfma_kernel" not in kernel:
+            return []
+        product = next(ins for b in blocks for ins in b if ins.op.startswith("v_mfma"))
+        loads = [[k for k, ins in enumerate(b) if self.loads(ins) and set(product.operands[2]) & set(ins.operands[0])]
+                 for b in blocks]
+        before = collections.defaultdict(list)
+        for i, nxt in enumerate(follow):
+            for j in nxt:
+                before[j].append(i)
+        once, work = set(), [i for i, b in enumerate(blocks) if b[-1].op == "s_endpgm"]
+        while work:                                        # blocks from which the end is reached without loading (again)
+            i = work.pop()
+            if i not in once and not loads[i]:
+                once.add(i)
+                work += before[i]
+        findings = {}
+        for i, at in enumerate(loads):
+            if at:
+                self.follow(kernel, blocks, follow, once, i, findings)
+        assert any(loads), kernel
+        return [findings[a] for a in sorted(findings)]
+
+    @staticmethod
+    def loads(ins):
+        return ins.op == "global_load_dwordx4" and ins.text.endswith(", off")
+
+    def follow(self, kernel, blocks, follow, once, start, findings):
+        entry, work = {start: {}}, [start]                 # register -> operations issued behind its load
+        while work:
+            i = work.pop()
+            live = dict(entry[i])
+            for ins in blocks[i]:
+                if ins.op.startswith("v_mfma"):
+                    live.clear()
+                    break
+                if ins.op == "s_waitcnt":
+                    n = _VMCNT.search(ins.text)
+                    live = {r: behind for r, behind in live.items() if n is None or behind < int(n.group(1))}
+                    continue
+                load = i == start and self.loads(ins)
+                if any(r in live for t in ins.operands[1 if load else 0:] for r in t):
+                    findings[ins.address] = Finding(self.rule, kernel, ins.address, ins.text, self.what)
+                if ins.memory:
+                    live = {r: min(behind + 1, MOST_BEHIND) for r, behind in live.items()}
+                if load:
+                    live.update((r, 0) for r in ins.operands[0])
+            for j in follow[i]:
+                if live and j in once:
+                    old = entry.setdefault(j, {})
+                    more = {r: behind for r, behind in live.items() if behind > old.get(r, -1)}
+                    if more:
+                        old.update(more)
+                        work.append(j)
+
+
+SCANS = (VectorWrittenScalars(), LdsLoadsBehindM0(), QueryInFlight())
 
 
 def check(lib: str = LIB_PATH, scans=SCANS):

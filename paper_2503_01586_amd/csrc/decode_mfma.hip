@@ -760,6 +760,7 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
   // tile its partner fetched one step earlier in the XCD's L2 (twice as many independent streams
   // as when both ask for the same rows at the same time).
   const int n_my = (int)((t_end - t0 + t_step - 1) / t_step);
+  __builtin_assume(n_my > 0);                            // (t0 < t_end: no way past the loop, on which the query's registers would be free)
   auto tile_at = [&](int i) -> int64_t {     // t_end stands for "no such tile"
     if (i >= n_my) return t_end;
     const int j = i ^ swp;
@@ -782,8 +783,9 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
   }
   for (int i = 0; i < n_my; i += 2) {
     const int64_t ta = tile_at(i), tb = tile_at(i + 1), tc = tile_at(i + 2), td = tile_at(i + 3);
-    if (tb < t_end) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IN_FLIGHT) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // (one wait that every way passes, and not one of two: seen from the machine code alone, both could be skipped)
+    if (tb >= t_end) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(IN_FLIGHT) : "memory");
     compute(i, ta, ctile0, ketile0, tb, NtOdd{});
     if (tb >= t_end) break;
     if (tc < t_end) {

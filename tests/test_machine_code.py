@@ -17,8 +17,8 @@ def code(*lines):
     return out
 
 
-def findings(scan, *lines):
-    return [f.address // 4 for f in scan.run("k", *mc.blocks_of(code(*lines)))]
+def findings(scan, *lines, kernel="k"):
+    return [f.address // 4 for f in scan.run(kernel, *mc.blocks_of(code(*lines)))]
 
 
 def test_scalar_registers_that_a_vector_instruction_wrote():
@@ -46,6 +46,25 @@ def test_direct_loads_behind_a_write_of_m0():
     assert findings(scan, write, "s_nop 0", load, "s_endpgm ") == []
     assert findings(scan, write, "s_mov_b32 s4, s29", load, "s_endpgm ") == []
     assert findings(scan, write, "global_load_dword v1, v2, s[4:5]", load, load, "s_endpgm ") == []
+
+
+def test_registers_of_the_query_in_flight():
+    q, q2 = "global_load_dwordx4 v[8:11], v[2:3], off", "global_load_dwordx4 v[12:15], v[4:5], off"
+    tile, product = "global_load_lds_dwordx4 v1, s[2:3]", "v_mfma_f32_16x16x32_bf16 v[20:23], v[16:19], v[8:11], 0"
+    found = lambda *lines: findings(mc.QueryInFlight(), *lines, kernel="attn_mfma_kernel")
+    assert found(q, q2, "s_waitcnt vmcnt(0)", product, "s_endpgm ") == []
+    assert found(q, q2, tile, "s_waitcnt vmcnt(1)", product, "v_mov_b32_e32 v8, v9", "s_endpgm ") == []
+    # a copy, arithmetic, or another use of the register, ahead of the wait
+    assert found(q, q2, "v_accvgpr_write_b32 a1, v15", "s_waitcnt vmcnt(0)", product, "s_endpgm ") == [2]
+    assert found(q, q2, "v_pk_mul_f16 v30, v31, v9", "s_waitcnt vmcnt(0)", product, "s_endpgm ") == [2]
+    assert found(q, q2, "v_mov_b32_e32 v12, 0", "s_waitcnt vmcnt(0)", product, "s_endpgm ") == [2]
+    # a wait that leaves them under way, the address of a later load, the way out of an empty split
+    assert found(q, q2, tile, "s_waitcnt vmcnt(2)", "v_mov_b32_e32 v12, 0", product, "s_endpgm ") == [4]
+    assert found(q, "global_load_dwordx4 v[12:15], v[8:9], off", "s_waitcnt vmcnt(0)", product, "s_endpgm ") == [1]
+    assert found(q, q2, "s_cbranch_scc1 6", "s_waitcnt vmcnt(0)", product, "s_endpgm ", "v_mov_b32_e32 v8, 0",
+                 "s_waitcnt vmcnt(0)", "s_endpgm ") == [6]
+    # loaded in one of two places: what stands ahead of the second is not on the first one's way
+    assert found("s_cbranch_scc1 3", q, q2, "s_cbranch_scc0 6", "v_mov_b32_e32 v8, 0", q, "s_waitcnt vmcnt(0)", product, "s_endpgm ") == []
 
 
 @pytest.fixture(scope="module")
