@@ -18,16 +18,18 @@ pytestmark = pytest.mark.gpu
 LEAN = np.array([0.0, 9.0, 2.0, 16.0, 16.0, 5.0, 20.0, 1.0, 11.0])   # natural logits, tile by tile
 
 
-def leaning_latents(rng, c, q, W_uk, idx):
-    """c [rows, d_c] leaned towards the absorbed query of every head (q [n_h, d_h])."""
+def leaning_latents(rng, c, q, W_uk, idx, thirds=False):
+    """c [rows, d_c] leaned towards the absorbed query of every head (q [n_h, d_h]), or of another third of the heads in every tile."""
     n_h, d_h = q.shape
     qt = np.zeros((n_h, c.shape[1]))
     for h in range(n_h):
         chunks = set(idx[h].tolist())
         others = [i for i in range(d_h) if i // 2 not in chunks]
         qt[h] = W_uk[:, h] @ q[h, others] / np.sqrt(d_h)
-    u = (qt / np.sum(qt * qt, axis=1, keepdims=True)).sum(axis=0)
-    return c + LEAN[np.arange(c.shape[0]) // 16 % len(LEAN)][:, None] * u[None]
+    u = qt / np.sum(qt * qt, axis=1, keepdims=True)
+    tile = np.arange(c.shape[0]) // 16
+    heads = np.arange(n_h)[None] % 3 == tile[:, None] % 3 if thirds else np.ones((c.shape[0], n_h))
+    return c + LEAN[tile % len(LEAN)][:, None] * (heads @ u)
 
 
 @pytest.mark.parametrize("n_h,r,d_c,T", [
@@ -66,3 +68,47 @@ def test_scores_that_rise_and_fall(n_h, r, d_c, T, n_splits):
         ref = orc.multiquery_attn(host64(qd), pos, ke_h, c_h, seen, host64(Wukd), host64(Wuvd), idx, d_h, 10000.0)
     assert np.all(np.isfinite(out))
     assert orc.max_abs_rel(out, ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("n_h,r,d_c,d_ck,T", [
+    (32, 8, 128, 0, 1), (40, 8, 1920, 0, 1), (32, 4, 768, 0, 1), (32, 8, 1536, 0, 1),
+    (32, 8, 1536, 0, 3), (40, 8, 1920, 0, 3),
+    # separated latents: the waves of the values finalise scores too, from the partial scores of the others alone
+    (32, 8, 128, 64, 1), (32, 8, 768, 384, 1), (32, 16, 1536, 576, 1), (32, 8, 1536, 576, 1),
+    (32, 8, 1536, 576, 3), (32, 4, 768, 192, 4),
+])
+@pytest.mark.parametrize("n_splits", [1, 2])
+def test_heads_that_rise_in_different_tiles(n_h, r, d_c, d_ck, T, n_splits):
+    """In every tile some heads raise their maximum and the others keep theirs, over the accumulators of both."""
+    rng = np.random.default_rng(d_c + d_ck + n_h + T)
+    d_h, lens = 128, [145, 17, 112, 33]
+    B, stride, dk = len(lens), max(lens) + 3, d_ck or d_c
+    idx = synth.draw_elite_idx(rng, n_h, d_h, r)
+    _, _, W_uk, _ = synth.draw_weights(rng, 64, n_h, d_h, r, dk)
+    _, _, _, W_uv = synth.draw_weights(rng, 64, n_h, d_h, r, d_c - d_ck)
+    ke64, c64 = synth.draw_cache_planes(rng, B * stride, n_h, r, d_c)
+    q = np.repeat(synth.draw_query(rng, B, n_h, d_h)[:, None], T, axis=1)
+    for b in range(B):
+        rows = slice(b * stride, (b + 1) * stride)
+        c64[rows, :dk] = leaning_latents(rng, c64[rows, :dk], q[b, 0], W_uk, idx, thirds=True)
+    dims = ekv.make_dims(64, n_h, d_h, r, d_c, "bf16", 10000.0)
+    assert ekv.elitekv_decode_path(dims, d_ck) == 1
+    ked, cd, qd, Wukd, Wuvd = (dev(a, "bf16") for a in (ke64, c64, q, W_uk, W_uv))
+    seen = np.array([[n - (T - 1 - t) for t in range(T)] for n in lens])
+    pos = seen - 1
+    ke_h, c_h = host64(ked).reshape(B, stride, n_h, -1), host64(cd).reshape(B, stride, -1)
+    o = torch.full((B, T, n_h, d_h), float("nan"), dtype=torch.bfloat16, device=DEV)
+    sep = (d_ck,) if d_ck else ()
+    size = ekv.elitekv_slrd_multiquery_workspace_bytes if d_ck else ekv.elitekv_multiquery_workspace_bytes
+    attend = ekv.elitekv_slrd_multiquery_attn if d_ck else ekv.elitekv_multiquery_attn
+    ws = torch.full((size(dims, *sep, B, T, max(lens), n_splits),), 0xFF, dtype=torch.uint8, device=DEV)
+    attend(dims, *sep, qd, i32(pos.reshape(-1)), i32(seen.reshape(-1)), max(lens), stride, Wukd, Wuvd, i32(idx), ked, cd, o, ws,
+           n_splits=n_splits)
+    torch.cuda.synchronize()
+    if d_ck:
+        ref = orc.slrd_multiquery_attn(host64(qd), pos, ke_h, c_h[..., :dk], c_h[..., dk:], seen, host64(Wukd), host64(Wuvd), idx, d_h,
+                                       10000.0)
+    else:
+        ref = orc.multiquery_attn(host64(qd), pos, ke_h, c_h, seen, host64(Wukd), host64(Wuvd), idx, d_h, 10000.0)
+    assert np.all(np.isfinite(host64(o)))
+    assert orc.max_abs_rel(host64(o), ref) <= TOL["bf16"]
