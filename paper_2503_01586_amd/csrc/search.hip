@@ -19,19 +19,16 @@
 //                   operand.  The last work-group of a head to arrive adds up the head's distances in a fixed order and
 //                   takes the arg-min.
 //   search_blocks : the same on products of bf16 parts, eight to a term, whose sum is as exact as the fp32 product: 64 x 64 pairs by
-//                   a work-group whose waves have a quarter of the chunks each; the samples of search_blocks' sizes take it
+//                   a work-group whose waves have a quarter of the chunks each; sb_faster (search_plan.hpp) says which samples take it
 // All state (packed copies, residuals, partial distances, elite masks) lives in the caller's workspace; a search is
 // 1 + r launches on the caller's stream with no host synchronisation in between.
 #include <algorithm>
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "search_plan.hpp"
 
 namespace ekv {
-
-constexpr int kSrTile = 16;      // queries (and keys) per tile
-constexpr int kSrMaxChunks = 64; // head_dim <= 128; the packed rows always hold 64 chunks (zeros beyond d_h / 2)
-constexpr int kSrRow = 4 * kSrMaxChunks;   // floats per (token, head) of a packed operand
 
 typedef __attribute__((ext_vector_type(4))) float sr_f32x4;
 
@@ -123,21 +120,6 @@ __global__ __launch_bounds__(256) void search_pack_kernel(const float* __restric
   }
 }
 
-// Key tiles per work-group (a power of two, at least one per wave) and the work-groups ("items") per head: 32-query block Q
-// has 2 Q + 2 key tiles, cut into pieces of that many.  A search's launches have about a thousand work-groups (two to four
-// rounds of the chip: 512 / 1024 / 2048 / 4096 wanted: 1103 / 1060 / 1145 / 1233 us (before the products were grouped) at 1000 tokens of 32 heads, 205 / 235 /
-// 235 / 235 at 300), and a head at most about a thousand or one per 32-query block, since one work-group adds up their
-// distances (a piece of 2 n_q32 tiles is a whole block: nothing is gained by longer ones).
-inline int sr_keys_per_item(int64_t n_q32, int64_t n_h) {
-  int k = 4;
-  while (k < 2 * n_q32 && (n_q32 * n_q32 / k > 1024 || n_h * n_q32 * n_q32 / k > 1024)) k *= 2;
-  return k;
-}
-inline int64_t sr_items_before(int q32, int keys) {      // items of the 32-query blocks below q32
-  const int64_t per = keys / 2, g = q32 / per;
-  return per * g * (g + 1) / 2 + (q32 % per) * (g + 1);
-}
-
 // acc[c] += sum over the lane's pairs of w |R - D_c| for all chunks: a product per chunk, its absolute sums taken while the
 // next four products are on the matrix cores.  PREFETCH: a group's key operand is replaced by the next tile's as soon as
 // this (the last) query tile has used it.  FUSED: the residual is the product's third operand; else it is added afterwards.
@@ -225,7 +207,8 @@ __device__ __forceinline__ void sr_choose(float* red, int* last, uint64_t* emask
 // (lane l of a result tile holds queries 4 (l / 16) + v, v < 4, against key l % 16).  Chunks in E are computed like the
 // others and ignored by the choice.  Bound by the fp32 matrix cores: 64 instructions of 32 cycles per tile of 256 pairs.
 // Before (the residual summed again in every round, subtraction and weights on the vector units, 16 queries per
-// work-group) a round of 1000 tokens, 32 heads took 302 us and a launch of 6 us for the choice; now 127.
+// work-group) a round of 1000 tokens, 32 heads took 302 us and a launch of 6 us for the choice; now 119 to 130
+// (less on a cool chip).
 // The product and the additions of its four absolute values do not overlap on a SIMD (measured apart: 13.9 ns a product,
 // 2 ns an addition, 25 ns for one product and four additions), which leaves 60 % of the measured time for the instructions.
 template <bool LOAD, bool FUSED>
@@ -346,7 +329,6 @@ __global__ __launch_bounds__(256, 2) void search_round_kernel(
 typedef __attribute__((ext_vector_type(8))) __bf16 sr_bf16x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t sr_u32x4;
 
-constexpr int kSbTiles = 4;                                 // tiles of queries (and of keys) in a block: 64 x 64 pairs
 constexpr int kSbChunks = kSrMaxChunks / 4;                 // chunks of a wave
 constexpr int kSbLag = 3;                                   // products between a product and the sums of its values
 
@@ -417,7 +399,8 @@ __device__ __forceinline__ void sb_distances(const uint2* q, const uint2* k, int
 
 // What bounds it: the chip's power.  With every SIMD at work a product of 16 x 16 x 32 bf16 takes 12 ns (16 cycles at the 1.35 GHz
 // that are left of 2.4), 18 with its four additions and the operands' copies; the fp32 instruction takes 14, and 25 with the additions,
-// for the two do not overlap.  1000 tokens of 32 heads: 75 us of products in a round of 95 (search_round_kernel: 119).  Block size and
+// for the two do not overlap.  1000 tokens of 32 heads: 75 us of products in a round of 95 to 113
+// (search_round_kernel: 119 to 130; both the slower the longer the chip has been at work).  Block size and
 // split: a block of 64 x 64 needs half an operand per product and twelve waves of it fit a compute unit; the chunks and not the
 // pairs divided among its waves, so that 128 tokens already make 96 work-groups.  Not kept: the queries' operands of all chunks in LDS (1030
 // against 900 us a search), both sides through a ring of LDS for 128 x 128 pairs (1325), the work-group's next blocks one after
@@ -524,58 +507,6 @@ __global__ __launch_bounds__(256, 2) void search_blocks_kernel(
     __hip_atomic_store(partial + ((int64_t)h * n_items + item) * kSrMaxChunks + (tid >> 2), d, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
   sr_choose(red, &last, emask, arrived, partial, elite_out, dist_out, h, n_items, half, r, round, elite);
-}
-
-// Samples of up to this many tokens keep the residuals where the caller's workspace has room for them (n_h (T / 16)^2 / 2
-// KiB: 66 MB for 1000 tokens of 32 heads, 1.1 GB for 4096) and the size function asks for that room up to this many bytes.
-// The other searches sum the residuals again in every round, at twice the matrix instructions (32 heads, r = 8, 128 / 1000 / 4096
-// tokens: 0.128 / 1.56 / 20.9 ms instead of 0.108 / 1.07 / 14.3).
-constexpr int64_t kSrKeepTokens = 4096;
-constexpr size_t kSrKeepBytes = (size_t)4 << 30;
-
-// search_blocks_kernel takes samples of seven tiles and more (shorter ones leave most of a 64 x 64 block empty: 32 heads x 96 tokens
-// 100 against 96 us, 128: 102 and 102) whose operands and residuals the 256 MB cache behind the L2s holds but for a little (64 heads
-// x 640 tokens, 224 MB: 790 against 879 us; 32 x 1280, 275 MB: 1468 against 1555; 64 x 768, 283 MB: 1177 against 1163; 64 x 900,
-// 340 MB: 1843 against 1655), other than those of 13 and 14 tiles (a fourth row of blocks, a quarter or half of it tokens: 32 x 200
-// 145 against 139; 15 and 16 tiles 144 against 198).
-constexpr size_t kSbBytes = (size_t)280 << 20;
-
-// least: bytes a search needs, which never falls as T grows (the pieces per head do, wherever a piece gets longer: the
-// partial distances are laid out for the most that a shorter sample has); total: with what it is faster with, for every
-// shorter sample too.  room: what a caller has; decides what the search keeps
-struct SearchLayout { size_t kp, partial, emask, arrived, res, least, total; int n_tiles, keys, n_items; bool blocks, keep; };
-static SearchLayout search_layout(int64_t T, int n_h, size_t room) {
-  SearchLayout L;
-  auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-  auto lay = [&](size_t vec, int64_t items) {                    // one packed operand, partial distances: returns the bytes
-    L.kp = up(vec);
-    L.partial = 2 * L.kp;
-    L.emask = L.partial + up((size_t)n_h * items * kSrMaxChunks * sizeof(float));
-    L.arrived = L.emask + up((size_t)n_h * sizeof(uint64_t));
-    return L.res = L.arrived + up((size_t)n_h * sizeof(int32_t));
-  };
-  auto lay_blocks = [&](int64_t n_blocks) {
-    const int64_t items = n_blocks * (n_blocks + 1) / 2;
-    L.n_tiles = (int)n_blocks * kSbTiles;
-    L.n_items = (int)items;
-    return lay((size_t)L.n_tiles * kSrTile * n_h * kSrRow * 8, items) + (size_t)items * n_h * kSbTiles * kSbTiles * 1024;
-  };
-  const int64_t tiles = (T + kSrTile - 1) / kSrTile, n_q32 = (tiles + 1) / 2, blocks = (tiles + kSbTiles - 1) / kSbTiles;
-  int64_t fast_blocks = std::min<int64_t>(blocks, kSrKeepTokens / (kSbTiles * kSrTile));
-  while (fast_blocks > 0 && lay_blocks(fast_blocks) > kSbBytes) --fast_blocks;
-  const size_t fast = lay_blocks(fast_blocks);
-  L.n_tiles = (int)tiles;
-  L.keys = sr_keys_per_item(n_q32, n_h);
-  L.n_items = (int)sr_items_before(n_q32, L.keys);
-  const int64_t most_items = std::min<int64_t>(sr_items_before(n_q32, 4), 1024 + n_q32);
-  L.least = L.total = lay((size_t)tiles * kSrTile * n_h * kSrRow * sizeof(float), most_items);
-  const size_t kept = (size_t)tiles * (tiles + 1) / 2 * n_h * 1024;
-  if (T <= kSrKeepTokens && kept <= kSrKeepBytes) L.total += kept;
-  L.keep = L.total > L.least && room >= L.total;
-  L.blocks = blocks == fast_blocks && tiles >= 7 && tiles != 13 && tiles != 14 && room >= fast;
-  if (tiles >= 7) L.total = std::max(L.total, fast);
-  if (L.blocks) lay_blocks(blocks);
-  return L;
 }
 
 size_t search_workspace_bytes(int64_t T, int n_h) { return search_layout(T, n_h, 0).total; }

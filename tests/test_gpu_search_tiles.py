@@ -24,7 +24,8 @@ def residual_rounding(q, k, h):
 @pytest.mark.parametrize("T,n_h,d_h,r", [
     (1, 3, 16, 2), (16, 5, 8, 4), (17, 1, 128, 3), (33, 2, 66, 5), (48, 7, 16, 8), (129, 1, 64, 32), (530, 1, 16, 3),
     (395, 64, 16, 3),        # pieces of sixteen key tiles, residuals kept over three rounds
-    (97, 2, 32, 8), (128, 8, 16, 4), (208, 3, 16, 2),        # blocks of 64 x 64: the fewest tiles, whole blocks, thirteen tiles
+    (97, 2, 32, 8), (128, 8, 16, 4), (208, 3, 16, 2),        # few work-groups
+    (97, 64, 8, 3), (128, 64, 6, 2), (208, 40, 8, 2),        # blocks of 64 x 64: the fewest tiles, whole blocks, thirteen tiles
     (225, 1, 128, 20), (257, 8, 16, 8),                      # ... residuals summed afresh in late rounds, one tile in the last row
     (1281, 2, 8, 2), (1408, 36, 4, 2),                       # ... many blocks, more than the cache holds (one work-group per item)
     (4097, 1, 4, 2),         # longer than what keeps the residuals; one token in the last tile
