@@ -582,7 +582,7 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
       auto publish = [&]() {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) {
-          const float pv = __builtin_amdgcn_exp2f(s[e] - m_run);
+          const float pv = exp2f(s[e] - m_run);            // (not the instruction alone: it drops probabilities below 2^-126)
           l_run += pv;
           *reinterpret_cast<uint16_t*>(x2 + n * L::P_ROW + (own_t0 + 2 * e) * 2) = f32_to_bf16_bits(pv);
         }

@@ -12,6 +12,7 @@ import paper_2503_01586_amd as ekv
 from oracle import elitekv_oracle as orc
 
 from gpu_util import DEV, TOL, dev, gpu_decode, host64, i32
+from test_gpu_slrd import gpu_slrd_decode
 
 pytestmark = pytest.mark.gpu
 
@@ -112,3 +113,32 @@ def test_heads_that_rise_in_different_tiles(n_h, r, d_c, d_ck, T, n_splits):
         ref = orc.multiquery_attn(host64(qd), pos, ke_h, c_h, seen, host64(Wukd), host64(Wuvd), idx, d_h, 10000.0)
     assert np.all(np.isfinite(host64(o)))
     assert orc.max_abs_rel(host64(o), ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("r,d_c,d_ck", [(8, 128, 64), (8, 768, 384), (16, 1536, 576), (8, 1536, 576)])
+@pytest.mark.parametrize("exponent", [-120, -127])
+def test_probability_below_the_normal_range(r, d_c, d_ck, exponent):
+    """A row whose probability is 2^exponent and whose values are 2^(-1 - exponent) adds a half to every column of the merged latent,
+    also where the probability is a subnormal number.  Its logit lies 88 below the largest: the rounding of the absorbed query (2^-9
+    of every one of d_ck terms, of independent signs) moves it by 88 * 2^-9 / sqrt(d_ck / 3) < 0.04, and its half by that share."""
+    rng = np.random.default_rng(d_c)
+    n_h, d_h, S = 32, 128, 20
+    idx = np.repeat(synth.draw_elite_idx(rng, 1, d_h, r), n_h, axis=0)
+    W_uk = np.repeat(synth.draw_weights(rng, 64, 1, d_h, r, d_ck)[2], n_h, axis=1)
+    W_uv = synth.draw_weights(rng, 64, n_h, d_h, r, d_c - d_ck)[3]
+    q = np.repeat(synth.draw_query(rng, 1, 1, d_h), n_h, axis=1)
+    others = [i for i in range(d_h) if i // 2 not in set(idx[0].tolist())]
+    qt = W_uk[:, 0] @ q[0, 0, others] / np.sqrt(d_h)
+    logit = np.full(S, -300.0)
+    logit[0], logit[1] = 0.0, exponent * np.log(2.0)
+    ke, c = np.zeros((S, n_h, 2 * r)), np.empty((S, d_c))
+    c[:, :d_ck] = logit[:, None] * (qt / np.sum(qt * qt))[None]
+    c[:, d_ck:] = rng.standard_normal((S, d_c - d_ck))
+    c[1, d_ck:] = 2.0 ** (-1 - exponent)
+    dims = ekv.make_dims(64, n_h, d_h, r, d_c, "bf16", 10000.0)
+    ked, cd, qd, Wukd, Wuvd = (dev(a, "bf16") for a in (ke, c, q, W_uk, W_uv))
+    out = host64(gpu_slrd_decode(dims, d_ck, qd, i32([S - 1]), i32([S]), S, S, Wukd, Wuvd, i32(idx), ked, cd, 1))
+    ch = host64(cd).reshape(1, S, -1)
+    ref = orc.slrd_decode_attn(host64(qd), [S - 1], host64(ked).reshape(1, S, n_h, -1), ch[..., :d_ck], ch[..., d_ck:], [S], host64(Wukd),
+                               host64(Wuvd), idx, d_h, 10000.0)
+    assert orc.max_abs_rel(out, ref) <= TOL["bf16"] + 0.04
