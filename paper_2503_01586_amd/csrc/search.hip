@@ -36,8 +36,9 @@ typedef __attribute__((ext_vector_type(4))) float sr_f32x4;
 // [quad of chunks c4 (16)][lane (64)][4 chunks], lane = 16 * row + token % 16: one 16-byte load per lane and
 // instruction, 1 KiB contiguous per wave instruction, 16 instructions per operand.  Tokens beyond T are zeros.
 
-// An fp32 value as the exact sum of three bf16 parts, each rounded to the nearest (ties away from zero; cut off where rounding
-// would leave the range): hm = the first (low half) and the second, ll = the third, twice.  Rounded and not cut off: the matrix
+// An fp32 value as the exact sum (from 2^-103 on; of smaller values the last part may be denormal or fall away) of three bf16 parts,
+// each rounded to the nearest (ties away from zero; cut off where rounding would leave the range): hm = the first (low half) and
+// the second, ll = the third, twice.  Rounded and not cut off: the matrix
 // instruction drops the last bits of every product of a group of eight, and the products of parts of one sign would all lose
 // in the same direction (measured on normal factors: 6.6e-8 of the sum, against 1e-10 with rounded parts).
 struct SrParts { uint32_t hm, ll; };

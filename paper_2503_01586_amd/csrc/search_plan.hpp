@@ -40,21 +40,28 @@ constexpr size_t kSrKeepBytes = (size_t)4 << 30;
 // 267 MiB, 1493 / 1572; 64 x 768, 271 MiB, 1194 / 1171; 32 x 1536, 344 MiB, 2281 / 2132; 64 x 1000, 394 MiB, 2090 / 1943).
 constexpr size_t kSbBytes = (size_t)280 << 20;
 
-// Which of them: 15 tiles and more (32 heads x 240 tokens 144 against 191 us, 512 332 / 419, 1000 949 / 1052; one head x 240
-// 94.0 / 97.7, 1000 112 / 136; a step below 10 % the other way only for one to five heads of 512 tokens, 106 / 97).  Of the
-// shorter ones, whose blocks of 64 x 64 are partly empty and whose operands take more to pack, those whose round launch has
-// more work-groups than the chip holds at once (two a compute unit: 64 x 144 150 / 173; 40 heads of 64 dims x 200, r = 4, 88.6
-// / 105), or two a compute unit where the same pairs are at most half as many blocks, one each (32 x 176 107 / 124, 64 x 128
-// 118 / 125).  The others lose by it or gain nothing: 32 x 128 102 / 98, of 64 dims 61 / 53; 32 x 200 144 / 137; 20 heads of
-// 64 dims x 200 77 / 69; 8 x 128 91 / 89; 16 x 192 (100 / 107) and 32 x 160 (106 / 116; of 64 dims 63 / 64) are given up for
-// the rule.  Below seven tiles no sample gains but by what two runs differ.
+// Which of them (us a search of 128 dims, r = 8, blocks / search_round_kernel): 15 tiles and more (32 heads x 240 tokens 143 / 190, 512
+// 332 / 419, 1000 949 / 1052; one head x 240 94.0 / 97.7, 1000 112 / 136; a step below 10 % the other way only for one to five
+// heads of 512 tokens, 106 / 97).  Of the shorter ones, whose blocks of 64 x 64 are partly empty and whose operands take more to
+// pack, those
+//   whose round launch has more work-groups than the chip holds at once (two a compute unit: 64 x 144 150 / 173, 40 x 200 154 / 195),
+//   or more than compute units where the same pairs are at most half as many blocks (32 x 176 106 / 123, 48 x 112 103 / 114,
+//   28 x 176 117 / 125, 64 x 128 118 / 124),
+//   or more than compute units where there is a block for each of them at most and the heads are dealt to the XCDs evenly, a
+//   head's operands to one L2 (32 x 160 106 / 115, x 144 105 / 105, 24 x 200 112 / 125, 40 x 144 120 / 121; not so 20 x 200 135 /
+//   125, 28 x 160 117 / 107, 36 x 144 125 / 119).  A search of fewer rounds gains less, for the packing is the same: r = 4, 64
+//   dims, 24 x 200 64.4 / 68.0, 32 x 160 63.0 / 63.2, 40 x 160 70.1 / 68.0; r = 2, 16 dims, 32 x 160 39.5 / 37.5.
+// The others lose by it or gain nothing: 32 x 128 102 / 97, x 200 144 / 135; 48 x 144 139 / 124; 44 x 144 142 / 127; 28 x 200 150 / 136; 8 x 128 91 / 89; 24 x 160
+// 103 / 103; 16 x 192 (100 / 107) has the work-groups of 32 x 128 and is given up for the rule.  Below seven tiles no sample gains but
+// by what two runs differ.
 constexpr int kSrComputeUnits = 256;
 inline bool sb_faster(int64_t tiles, int64_t n_h) {
   if (tiles < 7 || tiles >= 15) return tiles >= 15;
   const int64_t n_q32 = (tiles + 1) / 2, n_blocks = (tiles + kSbTiles - 1) / kSbTiles;
   const int64_t round_groups = n_h * sr_items_before((int)n_q32, sr_keys_per_item(n_q32, n_h));
   const int64_t block_groups = n_h * (n_blocks * (n_blocks + 1) / 2);
-  return round_groups > 2 * kSrComputeUnits || (round_groups > kSrComputeUnits && round_groups >= 2 * block_groups);
+  if (round_groups <= kSrComputeUnits) return false;
+  return round_groups > 2 * kSrComputeUnits || round_groups >= 2 * block_groups || (n_h % 8 == 0 && block_groups <= kSrComputeUnits);
 }
 
 // least: bytes a search needs, which never falls as T grows (the pieces per head do, wherever a piece gets longer: the

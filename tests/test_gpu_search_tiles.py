@@ -26,6 +26,7 @@ def residual_rounding(q, k, h):
     (395, 64, 16, 3),        # pieces of sixteen key tiles, residuals kept over three rounds
     (97, 2, 32, 8), (128, 8, 16, 4), (208, 3, 16, 2),        # few work-groups
     (97, 64, 8, 3), (128, 64, 6, 2), (208, 40, 8, 2),        # blocks of 64 x 64: the fewest tiles, whole blocks, thirteen tiles
+    (145, 32, 6, 2),                                         # ... a block for each compute unit at most
     (225, 1, 128, 20), (257, 8, 16, 8),                      # ... residuals summed afresh in late rounds, one tile in the last row
     (1281, 2, 8, 2), (1408, 36, 4, 2),                       # ... many blocks, more than the cache holds (one work-group per item)
     (4097, 1, 4, 2),         # longer than what keeps the residuals; one token in the last tile

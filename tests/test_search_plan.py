@@ -34,13 +34,14 @@ def layout(tmp_path_factory):
 
 # measured at 128 or 64 dims: the one faster than the other by four per cent and more
 @pytest.mark.parametrize("n_h,T", [(32, 176), (32, 192), (64, 128), (64, 144), (64, 192), (40, 200), (40, 224), (16, 240), (1, 1000),
+                                   (32, 160), (24, 176), (24, 200), (48, 112), (28, 176), (52, 128),
                                    (8, 320), (32, 240), (32, 512), (32, 1000), (64, 640), (32, 1280)])
 def test_samples_that_take_the_blocks(layout, n_h, T):
     assert layout(T, n_h).blocks
 
 
 @pytest.mark.parametrize("n_h,T", [(32, 96), (64, 96), (32, 112), (32, 128), (40, 128), (20, 160), (12, 160), (20, 200), (32, 200), (32, 224),
-                                   (20, 224), (32, 1536), (64, 1000)])
+                                   (20, 224), (32, 1536), (64, 1000), (48, 144), (28, 160), (36, 144)])
 def test_samples_that_take_the_rounds(layout, n_h, T):
     assert not layout(T, n_h).blocks
 
