@@ -135,35 +135,45 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// One direct global->LDS load: lane l fetches 16 bytes from base + voff + OFF, its data lands at lds_base + l*16.  The
+// One direct global->LDS load: lane l fetches 16 bytes from base + voff + OFF, its data lands at lds_base + ADD + l*16.  The
 // instruction's offset counts on both sides (M0 is set to as much less), so that loads of neighbouring columns share one
 // register of lane offsets and the rows' base stays in scalar registers: with an address per load and lane they took two vector
 // instructions each (13B 16 x 8192 186.9 -> 184.6 us a step, 4 x 5 drafted over 4096 tokens 81.2 -> 80.1).  Issued through inline assembly so that the waits on these loads
 // stay entirely under the kernel's control (vmcnt counting, see the tile loop).  M0 is read one wait state after its write, not
-// before: the s_nop, which the compiler does not put into inline assembly.
+// before: the s_nop, which the compiler does not put into inline assembly.  ADD is added by the write of M0 itself, where
+// an addition of its own ahead of the s_nop had made a tile's loads longer (with the offsets of elite keys as minima: 13B 16 x 8192
+// 182.6 -> 181.1 us a step).
 // STREAM marks the load non-temporal: cache rows that are read once per step stream from HBM
 // about 15 % faster that way (a plain read of 1 GiB through these loads: 6.0 TB/s, marked: 6.9 TB/s).
 // Rows that a second work-group is about to re-read from the L2 (head-group pairs) are loaded unmarked.
-template <int OFF, bool STREAM>
+template <int OFF, int ADD, bool STREAM>
 __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_base) {
   static_assert(OFF >= 0 && OFF < 4096, "outside the instruction's offset");
   if constexpr (STREAM)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt"
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4 nt"
                  :
-                 : "s"(lds_base - OFF), "v"(voff), "s"(base), "n"(OFF)
-                 : "memory", "m0");
+                 : "s"(lds_base), "n"(ADD - OFF), "v"(voff), "s"(base), "n"(OFF)
+                 : "memory", "m0", "scc");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4"
                  :
-                 : "s"(lds_base - OFF), "v"(voff), "s"(base), "n"(OFF)
-                 : "memory", "m0");
+                 : "s"(lds_base), "n"(ADD - OFF), "v"(voff), "s"(base), "n"(OFF)
+                 : "memory", "m0", "scc");
 }
-// dma16 of COUNT neighbouring 128-byte column blocks, 1 KiB of LDS apart
-template <int COUNT, bool STREAM, int CB = 0>
+// dma16 of COUNT neighbouring 128-byte column blocks, 1 KiB of LDS apart from ADD on
+template <int COUNT, int ADD, bool STREAM, int CB = 0>
 __device__ __forceinline__ void dma16_blocks(const void* base, uint32_t voff, uint32_t lds_base) {
   if constexpr (CB < COUNT) {
-    dma16<CB * 128, STREAM>(base, voff, lds_base + CB * 1024);
-    dma16_blocks<COUNT, STREAM, CB + 1>(base, voff, lds_base);
+    dma16<CB * 128, ADD + CB * 1024, STREAM>(base, voff, lds_base);
+    dma16_blocks<COUNT, ADD, STREAM, CB + 1>(base, voff, lds_base);
+  }
+}
+// dma16 of COUNT kilobytes of LDS, the i-th from base + voff(i)
+template <int COUNT, bool STREAM, int I = 0, class F>
+__device__ __forceinline__ void dma16_each(const void* base, uint32_t lds_base, const F& voff) {
+  if constexpr (I < COUNT) {
+    dma16<0, I * 1024, STREAM>(base, voff(I), lds_base);
+    dma16_each<COUNT, STREAM, I + 1>(base, lds_base, voff);
   }
 }
 // An address that is the same in every lane, in scalar registers (64-bit comparisons leave it in vector registers), ready to be a
@@ -242,7 +252,9 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
   // 197.7 -> 188.0 (with the addresses of dma16 183, with the operands below read ahead 180.5), 4 x 5 drafted over 4096 85.5 ->
   // 81.0 (80.3), 7B 12.5 % 64 x 2048 80.7 -> 79.2 (78.8), 1 x 30000 36.7 -> 35.4.  Where the memory is the bound, eight waves a
   // work-group that share rows with nobody, the loads then come in shorter bursts and the launch is longer (7B 1 x 32768
-  // 48.6 -> 49.8, 16 x 8192 114.2 -> 115.4): those keep the second form, unless its registers do not suffice.
+  // 48.6 -> 49.8, 16 x 8192 114.2 -> 115.4): those keep the second form, unless its registers do not suffice (an estimate, which
+  // leaves out 1536 columns with 32 elite values a head).  It loses nothing where a work-group has few tiles: 1 x 256 (one tile) 27.8
+  // in both forms, 3 x 5001 separated 39.0 in both, 8 x 4096 ragged 54.9 / 55.2 with the first, a block of 1 x 4096 60.7 / 60.6.
   constexpr bool OWNER_P = !(SMODE == 1 && NW == 8 && KS * 8 + CT * 16 + TWO_R <= 160);
   constexpr int KCH = TWO_R / 8;                 // 16-byte chunks of one head's elite key
   // One wave per SIMD (512 registers per lane, half of them accumulation registers): the accumulators are pinned to
@@ -454,11 +466,11 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
     const char* base = uniform(reinterpret_cast<const char*>(p.c_plane) + (row0 + tile_t0) * crow_bytes);
     const int last = (int)min(t_end - 1 - tile_t0, (int64_t)(kTile - 1));
     static_assert(NW * DC_W * 2 < (1 << 24), "a latent row passes __umul24");
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-      dma16_blocks<NCB, STREAM>(base, __umul24(min(rb * 8 + ld_row, last), (uint32_t)crow_bytes) + c_col, cl + rb * NCB * 1024);
+    const uint32_t row8 = __umul24(min(ld_row, last), (uint32_t)crow_bytes), row16 = __umul24(min(8 + ld_row, last), (uint32_t)crow_bytes);
+    dma16_blocks<NCB, 0, STREAM>(base, row8 + c_col, cl);
+    dma16_blocks<NCB, NCB * 1024, STREAM>(base, row16 + c_col, cl);
     // lane l fills slot (row l/4, position l%4) of the half-width block
-    if (L::HALF) dma16<0, STREAM>(base, __umul24(min(lane >> 2, last), (uint32_t)crow_bytes) + h_col, cl + L::HALF_OFF);
+    if (L::HALF) dma16<0, L::HALF_OFF, STREAM>(base, __umul24(min(lane >> 2, last), (uint32_t)crow_bytes) + h_col, cl);
   };
   auto issue_ke = [&](int64_t tile_t0, char* ketile, auto nt) {
     constexpr bool STREAM = decltype(nt)::value;
@@ -468,11 +480,11 @@ __global__ __launch_bounds__(NW * 64, (AttnMfmaLayout<NW, DC_W, TWO_R>::kGroupsP
       const int last = (int)min(t_end - 1 - tile_t0, (int64_t)(kTile - 1));
       // (32-bit products: rows of 131072 heads with 64 values each pass 2^24 bytes; the grid has room for 65535 head groups)
       static_assert((uint64_t)kTile * 65535 * 32 * TWO_R * 2 <= UINT32_MAX, "a tile's elite keys pass a lane's offset");
-#pragma unroll
-      for (int i = 0; i < L::NKE; ++i) {
-        const int tl = min((i * 64 + lane) / L::KE_CPT, TPW - 1);
-        dma16<0, STREAM>(base, (uint32_t)min(wave * TPW + tl, last) * (uint32_t)krow_bytes + ke_col[i % KEQ], kl + i * 1024);
-      }
+      // (the smaller of two products, one the same in every tile, one in every lane: a product in each load is a 64-bit one)
+      const uint32_t krow = (uint32_t)krow_bytes, last_row = (uint32_t)last * krow;
+      dma16_each<L::NKE, STREAM>(base, kl, [&](int i) {
+        return min((uint32_t)(wave * TPW + min((i * 64 + lane) / L::KE_CPT, TPW - 1)) * krow, last_row) + ke_col[i % KEQ];
+      });
     }
   };
   auto issue = [&](int64_t tile_t0, char* ctile, char* ketile, auto nt) {
