@@ -424,7 +424,7 @@ __global__ __launch_bounds__(kTtWaves * 64) void attn_tiled_kernel(
 // Bound by the split accumulators' bytes where there are many rows, by the trips to memory where there are few: with up to two
 // work-groups a compute unit (kTmFewGroups) AHEAD accumulators of every lane are requested before the weights of the splits
 // are formed, and one for every one that is used from then on.  A decode step, us, without / with: 1 x 1000 tokens (192
-// work-groups, 63 splits) 50.2 / 47.5, 1 x 8000 (128 splits) 81.2 / 75.3, 2 x 1000 (384) 56.1 / 55.3, 2 x 3000 at 12.5 % 43.6 /
+// work-groups, 63 splits) 50.2 / 47.5, 1 x 8000 (128 splits) 81.2 / 75.3, 2 x 1000 (384) 56.1 / 55.3 (little more than two runs differ by), 2 x 3000 at 12.5 % 43.6 /
 // 40.5.  With more work-groups the registers cost more than the trips: 4 x 300 (768) 53.4 / 55.0, 64 x 1000 389 / 410.
 // 63 splits of two rows, 7B 25 %: 8.1 us for 25 MB (9.3 without AHEAD; merge_upproj_generic_kernel, with the up-projection below, 291).
 constexpr int kTmAhead = 16, kTmFewGroups = 2 * kTtComputeUnits;
