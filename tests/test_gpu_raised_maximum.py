@@ -19,18 +19,16 @@ pytestmark = pytest.mark.gpu
 LEAN = np.array([0.0, 9.0, 2.0, 16.0, 16.0, 5.0, 20.0, 1.0, 11.0])   # natural logits, tile by tile
 
 
-def leaning_latents(rng, c, q, W_uk, idx, thirds=False):
-    """c [rows, d_c] leaned towards the absorbed query of every head (q [n_h, d_h]), or of another third of the heads in every tile."""
+def leaning_latents(rng, c, q, W_uk, idx):
+    """c [rows, d_c] leaned towards the absorbed query of every head (q [n_h, d_h])."""
     n_h, d_h = q.shape
     qt = np.zeros((n_h, c.shape[1]))
     for h in range(n_h):
         chunks = set(idx[h].tolist())
         others = [i for i in range(d_h) if i // 2 not in chunks]
         qt[h] = W_uk[:, h] @ q[h, others] / np.sqrt(d_h)
-    u = qt / np.sum(qt * qt, axis=1, keepdims=True)
-    tile = np.arange(c.shape[0]) // 16
-    heads = np.arange(n_h)[None] % 3 == tile[:, None] % 3 if thirds else np.ones((c.shape[0], n_h))
-    return c + LEAN[tile % len(LEAN)][:, None] * (heads @ u)
+    u = (qt / np.sum(qt * qt, axis=1, keepdims=True)).sum(axis=0)
+    return c + LEAN[np.arange(c.shape[0]) // 16 % len(LEAN)][:, None] * u[None]
 
 
 @pytest.mark.parametrize("n_h,r,d_c,T", [
@@ -71,6 +69,15 @@ def test_scores_that_rise_and_fall(n_h, r, d_c, T, n_splits):
     assert orc.max_abs_rel(out, ref) <= TOL["bf16"]
 
 
+def latents_leaning_to_thirds(rng, c, q, W_uk, idx):
+    """The same towards another third of the heads in every tile."""
+    tile = np.arange(c.shape[0]) // 16
+    out = c.copy()
+    for k in range(3):
+        out[tile % 3 == k] = leaning_latents(rng, c, q[k::3], W_uk[:, k::3], idx[k::3])[tile % 3 == k]
+    return out
+
+
 @pytest.mark.parametrize("n_h,r,d_c,d_ck,T", [
     (32, 8, 128, 0, 1), (40, 8, 1920, 0, 1), (32, 4, 768, 0, 1), (32, 8, 1536, 0, 1),
     (32, 8, 1536, 0, 3), (40, 8, 1920, 0, 3),
@@ -91,7 +98,7 @@ def test_heads_that_rise_in_different_tiles(n_h, r, d_c, d_ck, T, n_splits):
     q = np.repeat(synth.draw_query(rng, B, n_h, d_h)[:, None], T, axis=1)
     for b in range(B):
         rows = slice(b * stride, (b + 1) * stride)
-        c64[rows, :dk] = leaning_latents(rng, c64[rows, :dk], q[b, 0], W_uk, idx, thirds=True)
+        c64[rows, :dk] = latents_leaning_to_thirds(rng, c64[rows, :dk], q[b, 0], W_uk, idx)
     dims = ekv.make_dims(64, n_h, d_h, r, d_c, "bf16", 10000.0)
     assert ekv.elitekv_decode_path(dims, d_ck) == 1
     ked, cd, qd, Wukd, Wuvd = (dev(a, "bf16") for a in (ke64, c64, q, W_uk, W_uv))
